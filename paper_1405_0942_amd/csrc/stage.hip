@@ -86,16 +86,18 @@ __device__ __forceinline__ double wave_min(double v) {
 // diagnostics sweep of x[diag_buf]: no step gating and no k_1; writes u (optionally scaled by
 // det F), B, J, alpha* and the convexity where the caller asked for them.  REC (FP64 stages
 // 4 and 6): also store the stage input at the node, for the reverse sweeps.
-template <int S, bool MIXED, bool XYP, bool DIAG = false, bool REC = false, bool NNN = false>
+template <int S, bool MIXED, bool DIAG = false, bool REC = false, bool NNN = false>
 __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) void stage_kernel(SweepArgs a) {
   using T = typename std::conditional<MIXED, float, double>::type;
-  // NNN: the current from the next-nearest-neighbour octilateral loops (Sec. 2.3), which reach
-  // positions and B on the planes q - 1 and q + 1 with an x-y offset: the stage-input ring
-  // keeps five planes and the B ring three
-  constexpr int RYS = NNN ? 5 : 3;
+  // The stage-input ring holds the planes p - 1 .. p + 1 that the field of plane p reads and the
+  // plane p + 2 committed meanwhile; B is written on plane p while the current of plane p - 1
+  // reads its own, so one barrier per plane step is enough.  NNN: the octilateral loops (Sec. 2.3)
+  // of plane p - 1 read positions and B on the planes p - 2 .. p, B of plane p included: a barrier
+  // before them, five planes of stage input and three of B.
+  constexpr int RYS = NNN ? 5 : 4;
   constexpr int RBS = NNN ? 3 : 2;
-  auto yslot = [](int p) { return (int)((unsigned)(p + 1024 * RYS) % (unsigned)RYS); };
-  auto bslot = [](int p) { return (int)((unsigned)(p + 1024 * RBS) % (unsigned)RBS); };
+  auto yslot = [](int p) { return NNN ? (int)((unsigned)(p + 1024 * 5) % 5u) : (p & 3); };
+  auto bslot = [](int p) { return NNN ? mod3(p) : (p & 1); };
   constexpr bool STAGE1 = (S == 1);
   constexpr bool LAST = (S == 6);
   // the window is a base vector (x_n; y_3 in stage 3, y_5 in stage 5) plus at most one vector
@@ -104,7 +106,7 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
   // own-node values carried from the window to the output node (3 planes later): x_n in
   // stages 2, 4, 6 (and k_1 in stage 2)
   constexpr bool CX = WV;
-  constexpr bool CK1 = (S == 2);
+  constexpr bool CV = (S == 2);
   constexpr int NPK = (S == 3) ? 2 : (S == 4 ? 3 : 0);  // k_j read at the output node
   constexpr int NPKA = NPK > 0 ? NPK : 1;
   constexpr bool PS = (S == 5 || LAST);  // two partial sums read at the output node
@@ -143,9 +145,7 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
   const Geometry& g = a.g;
   const int nx = g.n[0], ny = g.n[1], nz = g.n[2];
   const long long N = g.N;
-  const int bcx = XYP ? BC_PERIODIC : g.bc[0];
-  const int bcy = XYP ? BC_PERIODIC : g.bc[1];
-  const int bcz = g.bc[2];
+  const int bcx = g.bc[0], bcy = g.bc[1], bcz = g.bc[2];
   const double inv8h3 = g.inv8h3;
   const unsigned nxy = (unsigned)nx * (unsigned)ny;
 
@@ -176,9 +176,8 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
   };
 
   // ---- per-thread index tables: the (x, y) part of every address is the same on all planes.
-  // Window point e, row-major over the window; in the stages that carry own-node values,
-  // e < NTHREADS is the tile node of thread e instead (each thread loads its own node), then
-  // the two rows below and the two above the tile, then the two columns on either side.
+  // Window point e < NTHREADS is the tile node of thread e (each thread loads its own node), then
+  // come the two rows below and the two above the tile, then the two columns on either side.
   unsigned w2e[NP2];  // stage-input window point -> flat (x, y) index, IE off the grid
   int w2w[NP2];       // its periodic wraps: x in the low 16 bits, y in the high 16 bits (signed)
   int w2o[NP2];       // its LDS offset, -1 past the window
@@ -186,10 +185,7 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
   for (int r = 0; r < NP2; r++) {
     const int e = tid + r * NTHREADS;
     int row, col;
-    if (!CX) {
-      row = e / RX2;
-      col = e - row * RX2;
-    } else if (e < NTHREADS) {
+    if (e < NTHREADS) {
       row = e / TX + 2;
       col = e % TX + 2;
     } else {
@@ -212,8 +208,9 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
     w2o[r] = in_win ? row * RX2 + col : -1;
   }
   // field point e: e < NTHREADS is the tile node of thread e; the rest is the halo ring
-  unsigned f1e[NP1];
-  int f1r[NP1], f1c[NP1];
+  unsigned f1e[NP1];  // flat (x, y) index, IE off the grid
+  int f1o[NP1];       // offset in the B window, -1 past it
+  int f1y[NP1];       // offset in the stage-input window
 #pragma unroll
   for (int r = 0; r < NP1; r++) {
     const int e = tid + r * NTHREADS;
@@ -235,84 +232,177 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
         c1 = (e3 & 1) ? RX1 - 1 : 0;
       }
     }
+    const bool in_win = e < RY1 * RX1;
     const AxisIdx rx = resolve(i0 + c1 - 1, nx, bcx), ry = resolve(j0 + r1 - 1, ny, bcy);
-    f1e[r] = (e < RY1 * RX1 && rx.ok && ry.ok) ? (unsigned)(ry.i * nx + rx.i) : IE;
-    f1r[r] = (e < RY1 * RX1) ? r1 : -1;
-    f1c[r] = c1;
+    f1e[r] = (in_win && rx.ok && ry.ok) ? (unsigned)(ry.i * nx + rx.i) : IE;
+    f1o[r] = in_win ? r1 * RX1 + c1 : -1;
+    f1y[r] = (r1 + 1) * RX2 + c1 + 1;
+  }
+  // Ghost nodes just beyond a line-tied face: y(-1) = 3 (y(0) - y(1)) + y(2), and likewise at the
+  // other end, so that the central difference at the face node is the one-sided second-order row
+  // -3 y(0) + 4 y(1) - y(2) and every node takes the same path.  Beyond faces across x and y a
+  // thread fills one ghost component of a plane; beyond faces across z see commit_window.
+  constexpr int NGC = 3 * RY2, NGR = 3 * RX2;  // ghosts of one column, of one row
+  constexpr int NPG = (2 * NGC + 2 * NGR + NTHREADS - 1) / NTHREADS;
+  int gh_o[NPG], gh_s[NPG];  // offset in the plane's three components (-1: none), step into the grid
+#pragma unroll
+  for (int r = 0; r < NPG; r++) {
+    gh_o[r] = -1;
+    gh_s[r] = 0;
+    const int t = tid + r * NTHREADS;
+    if (t < 2 * NGC) {
+      const int side = t / NGC, t1 = t - side * NGC, m = t1 / RY2, row = t1 - m * RY2;
+      const int col = side == 0 ? 1 - i0 : nx - i0 + 2;
+      if (bcx == BC_LINE_TIED && col >= 0 && col < RX2) {
+        gh_o[r] = m * (RY2 * RX2) + row * RX2 + col;
+        gh_s[r] = side == 0 ? 1 : -1;
+      }
+    } else if (t < 2 * NGC + 2 * NGR) {
+      const int t0 = t - 2 * NGC, side = t0 / NGR, t1 = t0 - side * NGR, m = t1 / RX2, col = t1 - m * RX2;
+      const int row = side == 0 ? 1 - j0 : ny - j0 + 2;
+      if (bcy == BC_LINE_TIED && row >= 0 && row < RY2) {
+        gh_o[r] = m * (RY2 * RX2) + row * RX2 + col;
+        gh_s[r] = side == 0 ? RX2 : -RX2;
+      }
+    }
   }
 
   // tile node owned by this thread
   const int gi_t = i0 + tx, gj_t = j0 + ty;
   const bool tile_ok = (gi_t < nx) && (gj_t < ny);
   const unsigned out_e = tile_ok ? (unsigned)(gj_t * nx + gi_t) : IE;
-  const bool face_xy = !XYP && ((bcx == BC_LINE_TIED && (gi_t == 0 || gi_t == nx - 1)) ||
-                                (bcy == BC_LINE_TIED && (gj_t == 0 || gj_t == ny - 1)));
+  const bool face_x = bcx == BC_LINE_TIED && (gi_t == 0 || gi_t == nx - 1);
+  const bool face_y = bcy == BC_LINE_TIED && (gj_t == 0 || gj_t == ny - 1);
 
   // ---- loads of one plane, issued one plane step ahead of their use -------------------------
-  double wx[NP2][3];      // window base (x_n, y_3 or y_5)
-  T wk[WV ? NP2 : 1][3];  // the window vector v
-  T b0r[NP1][3];          // B0'' at the field points
-  T pk[NPKA][3];          // k_j at the output node (stages 3, 4)
-  T ps[PS ? 2 : 1][3];    // stage 5: (P6, E); stage 6: (X, E) at the output node
-  // own-node values of the three committed planes hi - 2, hi - 1, hi (oldest first)
-  double cx[CX ? 3 : 1][3] = {};
-  T ck[CK1 ? 3 : 1][3] = {};
-  auto load_window = [&](int pz) {
+  T b0r[NP1][3];        // B0'' at the field points
+  T pk[NPKA][3];        // k_j at the output node (stages 3, 4)
+  T ps[PS ? 2 : 1][3];  // stage 5: (P6, E); stage 6: (X, E) at the output node
+  struct Window {
+    double x[NP2][3];      // window base (x_n, y_3 or y_5)
+    T v[WV ? NP2 : 1][3];  // the window vector
+  };
+  auto load_window = [&](Window& w, int pz, bool on) {
     const long long zo = (long long)zload(pz) * nxy;
+    unsigned e[NP2];
+#pragma unroll
+    for (int r = 0; r < NP2; r++) e[r] = on ? w2e[r] : IE;
 #pragma unroll
     for (int m = 0; m < 3; m++) {
       const auto rs = plane_rsrc(wbase + m * N + zo, nxy);
 #pragma unroll
-      for (int r = 0; r < NP2; r++) wx[r][m] = bload<double>(rs, w2e[r]);
+      for (int r = 0; r < NP2; r++) w.x[r][m] = bload<double>(rs, e[r]);
     }
     if constexpr (WV) {
 #pragma unroll
       for (int m = 0; m < 3; m++) {
         const auto rs = plane_rsrc(wvec + m * N + zo, nxy);
 #pragma unroll
-        for (int r = 0; r < NP2; r++) wk[r][m] = bload<T>(rs, w2e[r]);
+        for (int r = 0; r < NP2; r++) w.v[r][m] = bload<T>(rs, e[r]);
       }
     }
   };
   // y = base + cv v, rounded once, plus the periodic shift of a wrapped neighbour
-  auto commit_window = [&](int pz) {
-    const AxisIdx rz = resolve_near(pz, nz, bcz);
+  auto window_value = [&](const Window& w, int r, double shz, double v[3]) {
+#pragma unroll
+    for (int m = 0; m < 3; m++) {
+      double y = w.x[r][m];
+      if constexpr (S == 2) {
+        y = y + cv * (double)w.v[r][m];
+      } else if constexpr (WV) {
+        y = y + (double)w.v[r][m];
+      }
+      v[m] = y;
+    }
+    v[0] += (double)(short)(w2w[r] & 0xffff) * g.period[0];
+    v[1] += (double)(w2w[r] >> 16) * g.period[1];
+    v[2] += shz;
+  };
+  auto commit_window = [&](const Window& w, int pz) {
+    const double shz = resolve_near(pz, nz, bcz).w * g.period[2];
     const int slot = yslot(pz);
-    const double shz = rz.w * g.period[2];
 #pragma unroll
     for (int r = 0; r < NP2; r++) {
-      const bool ok = (w2e[r] != IE);
       double v[3];
-#pragma unroll
-      for (int m = 0; m < 3; m++) {
-        double y = wx[r][m];
-        if constexpr (S == 2) {
-          y = y + cv * (double)wk[r][m];
-        } else if constexpr (WV) {
-          y = y + (double)wk[r][m];
-        }
-        v[m] = y;
-      }
-      v[0] += (double)(short)(w2w[r] & 0xffff) * g.period[0];
-      v[1] += (double)(w2w[r] >> 16) * g.period[1];
-      v[2] += shz;
+      window_value(w, r, shz, v);
       if (w2o[r] >= 0) {
 #pragma unroll
-        for (int m = 0; m < 3; m++) ys[slot][m][w2o[r]] = ok ? v[m] : 0.0;
+        for (int m = 0; m < 3; m++) ys[slot][m][w2o[r]] = (w2e[r] != IE) ? v[m] : 0.0;
       }
     }
-    // the own node (window point 0) enters the carry
+  };
+  // the ghost plane beyond a line-tied z face from the three planes pa, pb, pc inside it (pa the
+  // face): each thread reads back the points it committed itself
+  auto commit_ghost_plane = [&](int pz, int pa, int pb, int pc) {
+    const int slot = yslot(pz), sa = yslot(pa), sb = yslot(pb), sc = yslot(pc);
+#pragma unroll
+    for (int r = 0; r < NP2; r++) {
+      if (w2o[r] >= 0) {
+#pragma unroll
+        for (int m = 0; m < 3; m++)
+          ys[slot][m][w2o[r]] = fma(3.0, ys[sa][m][w2o[r]] - ys[sb][m][w2o[r]], ys[sc][m][w2o[r]]);
+      }
+    }
+  };
+  // NNN: the one-sided rows themselves.  (The octilateral runs that break down amplify the rounding
+  // of the face rows, so these keep the order of operations they have always had.)
+  auto jacobian_rows = [&](int o, unsigned e, int p, double F[3][3]) {
+    const int gj = (int)(e / (unsigned)nx), gi = (int)(e - (unsigned)gj * nx);
+    const int sp = yslot(p);
+#pragma unroll
+    for (int m = 0; m < 3; m++) {
+      const double* yc = ys[sp][m];
+      if (bcx == BC_PERIODIC || (gi > 0 && gi < nx - 1))
+        F[m][0] = yc[o + 1] - yc[o - 1];
+      else if (gi == 0)
+        F[m][0] = -3.0 * yc[o] + 4.0 * yc[o + 1] - yc[o + 2];
+      else
+        F[m][0] = 3.0 * yc[o] - 4.0 * yc[o - 1] + yc[o - 2];
+      if (bcy == BC_PERIODIC || (gj > 0 && gj < ny - 1))
+        F[m][1] = yc[o + RX2] - yc[o - RX2];
+      else if (gj == 0)
+        F[m][1] = -3.0 * yc[o] + 4.0 * yc[o + RX2] - yc[o + 2 * RX2];
+      else
+        F[m][1] = 3.0 * yc[o] - 4.0 * yc[o - RX2] + yc[o - 2 * RX2];
+    }
+    if (bcz == BC_PERIODIC || (p > 0 && p < nz - 1)) {
+      const int sa = yslot(p + 1), sb = yslot(p - 1);
+#pragma unroll
+      for (int m = 0; m < 3; m++) F[m][2] = ys[sa][m][o] - ys[sb][m][o];
+    } else if (p == 0) {
+#pragma unroll
+      for (int m = 0; m < 3; m++) F[m][2] = -3.0 * ys[yslot(0)][m][o] + 4.0 * ys[yslot(1)][m][o] - ys[yslot(2)][m][o];
+    } else {
+      const int s0 = yslot(p), s1 = yslot(p - 1), s2 = yslot(p - 2);
+#pragma unroll
+      for (int m = 0; m < 3; m++) F[m][2] = 3.0 * ys[s0][m][o] - 4.0 * ys[s1][m][o] + ys[s2][m][o];
+    }
+  };
+  auto fill_ghosts = [&](int pz) {
+    if constexpr (NNN) return;
+#pragma unroll
+    for (int r = 0; r < NPG; r++) {
+      if (gh_o[r] >= 0) {
+        double* y = &ys[yslot(pz)][0][gh_o[r]];
+        *y = fma(3.0, y[gh_s[r]] - y[2 * gh_s[r]], y[3 * gh_s[r]]);
+      }
+    }
+  };
+  // own-node values (window point 0) of the planes p - 1, p, p + 1, oldest first
+  double cx[CX ? 3 : 1][3] = {};
+  T cvv[CV ? 3 : 1][3] = {};
+  auto carry = [&](const Window& w) {
 #pragma unroll
     for (int m = 0; m < 3; m++) {
       if constexpr (CX) {
         cx[0][m] = cx[1][m];
         cx[1][m] = cx[2][m];
-        cx[2][m] = wx[0][m];
+        cx[2][m] = w.x[0][m];
       }
-      if constexpr (CK1) {
-        ck[0][m] = ck[1][m];
-        ck[1][m] = ck[2][m];
-        ck[2][m] = wk[0][m];
+      if constexpr (CV) {
+        cvv[0][m] = cvv[1][m];
+        cvv[1][m] = cvv[2][m];
+        cvv[2][m] = w.v[0][m];
       }
     }
   };
@@ -327,68 +417,29 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
   };
   auto load_point = [&](int pz) {
     const long long zo = (long long)zload(pz) * nxy;
+    const unsigned eo = (pz >= z0 && pz < z1) ? out_e : IE;
     if constexpr (NPK > 0) {
 #pragma unroll
       for (int j = 0; j < NPK; j++) {
         const T* kj = static_cast<const T*>(a.k[j]);
 #pragma unroll
-        for (int m = 0; m < 3; m++) pk[j][m] = bload<T, CPOL_STREAM>(plane_rsrc(kj + m * N + zo, nxy), out_e);
+        for (int m = 0; m < 3; m++) pk[j][m] = bload<T, CPOL_STREAM>(plane_rsrc(kj + m * N + zo, nxy), eo);
       }
     }
     if constexpr (PS) {
       const T* s0 = static_cast<const T*>(S == 5 ? a.sum[0] : a.sum[1]);
       const T* s1 = static_cast<const T*>(a.sum[2]);
 #pragma unroll
-      for (int m = 0; m < 3; m++) ps[0][m] = bload<T, CPOL_STREAM>(plane_rsrc(s0 + m * N + zo, nxy), out_e);
+      for (int m = 0; m < 3; m++) ps[0][m] = bload<T, CPOL_STREAM>(plane_rsrc(s0 + m * N + zo, nxy), eo);
 #pragma unroll
-      for (int m = 0; m < 3; m++) ps[1][m] = bload<T, CPOL_STREAM>(plane_rsrc(s1 + m * N + zo, nxy), out_e);
+      for (int m = 0; m < 3; m++) ps[1][m] = bload<T, CPOL_STREAM>(plane_rsrc(s1 + m * N + zo, nxy), eo);
     }
   };
 
-  // ---- unscaled Jacobian at a window point (r, c in stage-input window coordinates) -----
-  auto jac_xy = [&](int r, int c, int p, int gi, int gj, double F[3][3]) {
-    const int o = r * RX2 + c;
-    const int sp = yslot(p);
-#pragma unroll
-    for (int m = 0; m < 3; m++) {
-      const double* yc = ys[sp][m];
-      if (XYP || bcx == BC_PERIODIC || (gi > 0 && gi < nx - 1))
-        F[m][0] = yc[o + 1] - yc[o - 1];
-      else if (gi == 0)
-        F[m][0] = -3.0 * yc[o] + 4.0 * yc[o + 1] - yc[o + 2];
-      else
-        F[m][0] = 3.0 * yc[o] - 4.0 * yc[o - 1] + yc[o - 2];
-      if (XYP || bcy == BC_PERIODIC || (gj > 0 && gj < ny - 1))
-        F[m][1] = yc[o + RX2] - yc[o - RX2];
-      else if (gj == 0)
-        F[m][1] = -3.0 * yc[o] + 4.0 * yc[o + RX2] - yc[o + 2 * RX2];
-      else
-        F[m][1] = 3.0 * yc[o] - 4.0 * yc[o - RX2] + yc[o - 2 * RX2];
-    }
-  };
-  auto jacobian = [&](int r, int c, int p, int gi, int gj, double F[3][3]) {
-    jac_xy(r, c, p, gi, gj, F);
-    const int o = r * RX2 + c;
-    if (bcz == BC_PERIODIC || (p > 0 && p < nz - 1)) {
-      const int sa = yslot(p + 1), sb = yslot(p - 1);
-#pragma unroll
-      for (int m = 0; m < 3; m++) F[m][2] = ys[sa][m][o] - ys[sb][m][o];
-    } else if (p == 0) {
-#pragma unroll
-      for (int m = 0; m < 3; m++) F[m][2] = -3.0 * ys[yslot(0)][m][o] + 4.0 * ys[yslot(1)][m][o] - ys[yslot(2)][m][o];
-    } else {
-      const int s0 = yslot(p), s1 = yslot(p - 1), s2 = yslot(p - 2);
-#pragma unroll
-      for (int m = 0; m < 3; m++) F[m][2] = 3.0 * ys[s0][m][o] - 4.0 * ys[s1][m][o] + ys[s2][m][o];
-    }
-  };
-
-  // B planes this chunk needs, and the stage-input window [lo(p), hi(p)] behind each
+  // planes of B this chunk needs
   const bool perz = (bcz == BC_PERIODIC);
   const int pb0 = perz ? z0 - 1 : max(z0 - 1, 0);
   const int pb1 = perz ? z1 : min(z1, nz - 1);
-  auto need_hi = [&](int p) { return perz ? p + 1 : (p == 0 ? 2 : (p == nz - 1 ? p : p + 1)); };
-  auto need_lo = [&](int p) { return perz ? p - 1 : (p == 0 ? 0 : (p == nz - 1 ? p - 2 : p - 1)); };
 
   // reductions
   double acc_E = 0.0, acc_R2 = 0.0, acc_min = INFINITY, acc_null = 0.0, acc_lam = 0.0;
@@ -396,15 +447,16 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
   // xi: the node of largest |f|^2 / B^4 so far, kept as (|f|^2, B^4, B^2) and compared by
   // cross-multiplication, so that the square root and the division are taken once at the end
   double xi_F2 = 0.0, xi_B4 = 1.0, xi_B2 = 1.0;
-  int kap_q = 1;  // DIAG: convexity of the own node of the output plane q
 
   // ---- stores of one output plane (every lane issues them; masked-off lanes are dropped) ----
-  T so_k[3] = {T(0), T(0), T(0)};    // k_s (stages 1..3), u (DIAG)
-  double so_y[3] = {0.0, 0.0, 0.0};  // x_n copy (stage 1), y_3 (stage 2), y_5 (stage 4), x_{n+1}
-  T so_s[SUMS_OUT ? 3 : 1][3] = {};  // stage 3: d_4; stage 4: P6, X, E; stage 5: P6, -, E
-  double so_p[DIAG ? 3 : 1][3] = {}; // DIAG: B, J, alpha*
-  double ycq[3] = {0.0, 0.0, 0.0};   // the stage input at the tile node of plane q
-  auto store_plane = [&](int qz, bool on) {
+  struct Outputs {
+    T k[3];                      // k_s (stages 1..3), u (DIAG)
+    double y[3];                 // x_n copy (stage 1), y_3 (stage 2), y_5 (stage 4), x_{n+1}
+    T s[SUMS_OUT ? 3 : 1][3];    // stage 3: d_4; stage 4: P6, X, E; stage 5: P6, -, E
+    double p[DIAG ? 3 : 1][3];   // DIAG: B, J, alpha*
+    double yc[REC ? 3 : 1];      // REC: the stage input at the node
+  };
+  auto store_plane = [&](const Outputs& so, int qz, bool on, int kap = 1) {
     const long long zo = (long long)zload(qz) * nxy;
     const unsigned eo = on ? out_e : IE;
     if constexpr (DIAG) {
@@ -419,89 +471,118 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
       int* dK = a.kappa_out ? a.kappa_out : reinterpret_cast<int*>(fb);
       const unsigned eA = (on && a.alpha_out) ? out_e : IE, eK = (on && a.kappa_out) ? out_e : IE;
 #pragma unroll
-      for (int m = 0; m < 3; m++) bstore<double>(plane_rsrc(du + m * N + zo, nxy), eu, (double)so_k[m]);
+      for (int m = 0; m < 3; m++) bstore<double>(plane_rsrc(du + m * N + zo, nxy), eu, (double)so.k[m]);
 #pragma unroll
-      for (int m = 0; m < 3; m++) bstore<double>(plane_rsrc(dB + m * N + zo, nxy), eB, so_p[0][m]);
+      for (int m = 0; m < 3; m++) bstore<double>(plane_rsrc(dB + m * N + zo, nxy), eB, so.p[0][m]);
 #pragma unroll
-      for (int m = 0; m < 3; m++) bstore<double>(plane_rsrc(dJ + m * N + zo, nxy), eJ, so_p[1][m]);
-      bstore<double>(plane_rsrc(dA + zo, nxy), eA, so_p[2][0]);
-      bstore<int>(plane_rsrc(dK + zo, nxy), eK, kap_q);
+      for (int m = 0; m < 3; m++) bstore<double>(plane_rsrc(dJ + m * N + zo, nxy), eJ, so.p[1][m]);
+      bstore<double>(plane_rsrc(dA + zo, nxy), eA, so.p[2][0]);
+      bstore<int>(plane_rsrc(dK + zo, nxy), eK, kap);
     } else if constexpr (STAGE1) {
       const unsigned ec = (on && record_ck) ? out_e : IE;
       T* dk = static_cast<T*>(a.k[0]);
       double* dc = record_ck ? a.ckpt + ck_slot * 3 * N : a.xout[0];
 #pragma unroll
-      for (int m = 0; m < 3; m++) bstore<T>(plane_rsrc(dk + m * N + zo, nxy), eo, so_k[m]);
+      for (int m = 0; m < 3; m++) bstore<T>(plane_rsrc(dk + m * N + zo, nxy), eo, so.k[m]);
 #pragma unroll
-      for (int m = 0; m < 3; m++) bstore<double>(plane_rsrc(dc + m * N + zo, nxy), ec, so_y[m]);
+      for (int m = 0; m < 3; m++) bstore<double>(plane_rsrc(dc + m * N + zo, nxy), ec, so.y[m]);
     } else if constexpr (S == 2) {
       T* dk = static_cast<T*>(a.k[1]);
 #pragma unroll
-      for (int m = 0; m < 3; m++) bstore<T>(plane_rsrc(dk + m * N + zo, nxy), eo, so_k[m]);
+      for (int m = 0; m < 3; m++) bstore<T>(plane_rsrc(dk + m * N + zo, nxy), eo, so.k[m]);
 #pragma unroll
-      for (int m = 0; m < 3; m++) bstore<double>(plane_rsrc(a.y3 + m * N + zo, nxy), eo, so_y[m]);
+      for (int m = 0; m < 3; m++) bstore<double>(plane_rsrc(a.y3 + m * N + zo, nxy), eo, so.y[m]);
     } else if constexpr (S == 3) {
       T* dk = static_cast<T*>(a.k[2]);
       T* dd = static_cast<T*>(a.d4);
 #pragma unroll
-      for (int m = 0; m < 3; m++) bstore<T>(plane_rsrc(dk + m * N + zo, nxy), eo, so_k[m]);
+      for (int m = 0; m < 3; m++) bstore<T>(plane_rsrc(dk + m * N + zo, nxy), eo, so.k[m]);
 #pragma unroll
-      for (int m = 0; m < 3; m++) bstore<T>(plane_rsrc(dd + m * N + zo, nxy), eo, so_s[0][m]);
+      for (int m = 0; m < 3; m++) bstore<T>(plane_rsrc(dd + m * N + zo, nxy), eo, so.s[0][m]);
     } else if constexpr (S == 4) {
 #pragma unroll
-      for (int m = 0; m < 3; m++) bstore<double>(plane_rsrc(a.y5 + m * N + zo, nxy), eo, so_y[m]);
+      for (int m = 0; m < 3; m++) bstore<double>(plane_rsrc(a.y5 + m * N + zo, nxy), eo, so.y[m]);
 #pragma unroll
       for (int i = 0; i < 3; i++) {
         T* ds = static_cast<T*>(a.sum[i]);
 #pragma unroll
-        for (int m = 0; m < 3; m++) bstore<T>(plane_rsrc(ds + m * N + zo, nxy), eo, so_s[i][m]);
+        for (int m = 0; m < 3; m++) bstore<T>(plane_rsrc(ds + m * N + zo, nxy), eo, so.s[i][m]);
       }
     } else if constexpr (S == 5) {
 #pragma unroll
       for (int i = 0; i < 3; i += 2) {
         T* ds = static_cast<T*>(a.sum[i]);
 #pragma unroll
-        for (int m = 0; m < 3; m++) bstore<T>(plane_rsrc(ds + m * N + zo, nxy), eo, so_s[i][m]);
+        for (int m = 0; m < 3; m++) bstore<T>(plane_rsrc(ds + m * N + zo, nxy), eo, so.s[i][m]);
       }
     } else {
       double* xo = a.xout[1 - cur];
 #pragma unroll
-      for (int m = 0; m < 3; m++) bstore<double>(plane_rsrc(xo + m * N + zo, nxy), eo, so_y[m]);
+      for (int m = 0; m < 3; m++) bstore<double>(plane_rsrc(xo + m * N + zo, nxy), eo, so.y[m]);
     }
     if constexpr (REC) {
       double* dy = a.yrec[S == 4 ? 0 : 1];
 #pragma unroll
-      for (int m = 0; m < 3; m++) bstore<double>(plane_rsrc(dy + m * N + zo, nxy), eo, ycq[m]);
+      for (int m = 0; m < 3; m++) bstore<double>(plane_rsrc(dy + m * N + zo, nxy), eo, so.yc[m]);
     }
   };
 
-  // ---- prologue: the first stage-input window, synchronously ---------------------------------
-  int hi = need_hi(pb0);
-  for (int pz = need_lo(pb0); pz <= hi; pz++) {
-    load_window(pz);
-    commit_window(pz);
+  Window win;
+  auto commit_next = [&](int p) {
+    if (p + 2 <= pb1 + 1) {
+      if (!perz && p + 2 == nz)
+        commit_ghost_plane(nz, nz - 1, nz - 2, nz - 3);
+      else
+        commit_window(win, p + 2);
+    }
+    carry(win);
+  };
+
+  // ---- prologue: the stage input on the planes pb0 - 1 .. pb0 + 1, loaded together
+  {
+    const bool low = !perz && pb0 == 0;  // the plane below is a ghost plane
+    const int lo = low ? 0 : pb0 - 1;
+    Window w1, w2;
+    load_window(win, lo, true);
+    load_window(w1, lo + 1, true);
+    load_window(w2, lo + 2, true);
+    commit_window(win, lo);
+    commit_window(w1, lo + 1);
+    commit_window(w2, lo + 2);
+    if (low) {  // plane 2 stays in the ring and is committed again by the first plane step
+      commit_ghost_plane(-1, 0, 1, 2);
+      carry(win);
+      carry(win);
+      carry(w1);
+    } else {
+      carry(win);
+      carry(w1);
+      carry(w2);
+    }
   }
   __syncthreads();
+  fill_ghosts(pb0);
   // leave the same loads and (dropped) stores in flight, in the same order, as a plane step
   load_b0(pb0);
-  if constexpr (!NNN) load_window(hi + 1);
   load_point(pb0 - 1);
-  if constexpr (NNN) load_window(hi + 1);
-  store_plane(pb0 - 1, false);
+  store_plane(Outputs{}, pb0 - 1, false);
+  load_window(win, pb0 + 2, true);
+  __syncthreads();
 
-  // own-node values carried between plane steps: B at q - 1 and q; at q: F' z column,
-  // 1 / det F', det F
+  // own-node values carried between plane steps: B at q - 1 and q; at q: F', 1 / det F', det F
   T Bqm[3] = {T(0), T(0), T(0)}, Bq[3] = {T(0), T(0), T(0)};
-  T Fzq[3] = {T(0), T(0), T(0)};
+  T Fq[3][3] = {};
   T rDq = T(0);
   double Dq = 0.0;
+  int kap_q = 1;  // DIAG: convexity
 
   for (int p = pb0; p <= z1; p++) {
     const int q = p - 1;
     const bool qout = (q >= z0 && q < z1);
+    fill_ghosts(p + 1);
     // 1. F', det F' and B on the tile + 1-node halo of plane p
     T Bp[3] = {T(0), T(0), T(0)};
-    T Fzp[3] = {T(0), T(0), T(0)};
+    T Fp[3][3] = {};
     T rDp = T(0);
     double Dp = 0.0;
     int kap_p = 1;
@@ -510,13 +591,21 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
 #pragma unroll
       for (int r = 0; r < NP1; r++) {
         __builtin_amdgcn_sched_barrier(0);  // one field point at a time: bounds live temporaries
-        if (f1r[r] >= 0) {
-          const int r1 = f1r[r], c1 = f1c[r];
-          const int gi = i0 + c1 - 1, gj = j0 + r1 - 1;
+        if (f1o[r] >= 0) {
           T B[3] = {T(0), T(0), T(0)};
           if (f1e[r] != IE) {
+            const int o = f1y[r];
+            const int sc = yslot(p), sl = yslot(p - 1), sh = yslot(p + 1);
             double F[3][3];
-            jacobian(r1 + 1, c1 + 1, p, gi, gj, F);
+            if constexpr (NNN)
+              jacobian_rows(o, f1e[r], p, F);
+            else
+#pragma unroll
+            for (int m = 0; m < 3; m++) {
+              F[m][0] = ys[sc][m][o + 1] - ys[sc][m][o - 1];
+              F[m][1] = ys[sc][m][o + RX2] - ys[sc][m][o - RX2];
+              F[m][2] = ys[sh][m][o] - ys[sl][m][o];
+            }
             const double D = det3(F);
             const double rD = rcp_nr(D);
             T q0 = b0r[r][0], q1 = b0r[r][1], q2 = b0r[r][2];
@@ -537,16 +626,17 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
             if (r == 0) {  // this thread's own tile node
 #pragma unroll
               for (int m = 0; m < 3; m++) {
-                Fzp[m] = (T)F[m][2];
+#pragma unroll
+                for (int c = 0; c < 3; c++) Fp[m][c] = (T)F[m][c];
                 Bp[m] = B[m];
               }
               rDp = (T)rD;
               Dp = D * inv8h3;
-              if (STAGE1 && p >= z0 && p < z1 && gi < nx && gj < ny) {
+              if (STAGE1 && p >= z0 && p < z1 && tile_ok) {
                 // energy in FP64 from the FP64 Jacobian and B0'', weights zeta on line-tied faces
                 double zeta = 1.0;
-                if (bcx == BC_LINE_TIED && (gi == 0 || gi == nx - 1)) zeta *= 0.5;
-                if (bcy == BC_LINE_TIED && (gj == 0 || gj == ny - 1)) zeta *= 0.5;
+                if (face_x) zeta *= 0.5;
+                if (face_y) zeta *= 0.5;
                 if (bcz == BC_LINE_TIED && (p == 0 || p == nz - 1)) zeta *= 0.5;
                 double Bd[3];
 #pragma unroll
@@ -558,20 +648,19 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
                   // convexity (Sec. 3.2.3, eq. "convexity"): every trihedron of edge vectors to
                   // the neighbours p + di e_x, p + dj e_y, p + dk e_z must have a determinant of
                   // sign di dj dk; trihedra beyond a line-tied face are not formed
-                  const int oc = (r1 + 1) * RX2 + (c1 + 1), sc = yslot(p);
-                  const bool lox = XYP || bcx == BC_PERIODIC || gi > 0, hix = XYP || bcx == BC_PERIODIC || gi < nx - 1;
-                  const bool loy = XYP || bcy == BC_PERIODIC || gj > 0, hiy = XYP || bcy == BC_PERIODIC || gj < ny - 1;
+                  const bool lox = bcx == BC_PERIODIC || gi_t > 0, hix = bcx == BC_PERIODIC || gi_t < nx - 1;
+                  const bool loy = bcy == BC_PERIODIC || gj_t > 0, hiy = bcy == BC_PERIODIC || gj_t < ny - 1;
                   const bool loz = bcz == BC_PERIODIC || p > 0, hiz = bcz == BC_PERIODIC || p < nz - 1;
                   double ex[2][3], ey[2][3], ez[2][3];  // [0]: toward -, [1]: toward +
 #pragma unroll
                   for (int m = 0; m < 3; m++) {
-                    const double c0 = ys[sc][m][oc];
-                    ex[0][m] = ys[sc][m][oc - 1] - c0;
-                    ex[1][m] = ys[sc][m][oc + 1] - c0;
-                    ey[0][m] = ys[sc][m][oc - RX2] - c0;
-                    ey[1][m] = ys[sc][m][oc + RX2] - c0;
-                    ez[0][m] = loz ? ys[yslot(p - 1)][m][oc] - c0 : 0.0;
-                    ez[1][m] = hiz ? ys[yslot(p + 1)][m][oc] - c0 : 0.0;
+                    const double c0 = ys[sc][m][o];
+                    ex[0][m] = ys[sc][m][o - 1] - c0;
+                    ex[1][m] = ys[sc][m][o + 1] - c0;
+                    ey[0][m] = ys[sc][m][o - RX2] - c0;
+                    ey[1][m] = ys[sc][m][o + RX2] - c0;
+                    ez[0][m] = ys[sl][m][o] - c0;
+                    ez[1][m] = ys[sh][m][o] - c0;
                   }
                   bool convex = true;
 #pragma unroll
@@ -593,60 +682,43 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
             }
           }
 #pragma unroll
-          for (int m = 0; m < 3; m++) bs[sb][m][r1 * RX1 + c1] = B[m];
+          for (int m = 0; m < 3; m++) bs[sb][m][f1o[r]] = B[m];
         }
       }
     }
     load_b0(p + 1 <= pb1 ? p + 1 : pb1);
-    // x and y columns of F' and the stage input at the tile node of plane q, read before
-    // the barrier: the commit below reuses plane q's ring slot
-    T Fxy[3][2];
-    if (qout) {
-      double Ft[3][3];
-      jac_xy(ty + 2, tx + 2, q, gi_t, gj_t, Ft);
-      const int o = (ty + 2) * RX2 + tx + 2, sq = yslot(q);
-#pragma unroll
-      for (int m = 0; m < 3; m++) {
-        Fxy[m][0] = (T)Ft[m][0];
-        Fxy[m][1] = (T)Ft[m][1];
-        ycq[m] = ys[sq][m][o];
-      }
-    }
-    __syncthreads();
-
-    // carried own-node values of plane q (the carry holds planes hi - 2, hi - 1, hi), taken
-    // before the commit below moves it on
+    // own-node values of plane q
     double xq[3] = {0.0, 0.0, 0.0};
-    T kq[3] = {T(0), T(0), T(0)};
-    if constexpr (CX) {
-      const int cidx = q - (hi - 2);
+    T vq[3] = {T(0), T(0), T(0)};
 #pragma unroll
-      for (int m = 0; m < 3; m++) {
-        xq[m] = cidx == 0 ? cx[0][m] : (cidx == 1 ? cx[1][m] : cx[2][m]);
-        if constexpr (CK1) kq[m] = cidx == 0 ? ck[0][m] : (cidx == 1 ? ck[1][m] : ck[2][m]);
-      }
+    for (int m = 0; m < 3; m++) {
+      if constexpr (CX) xq[m] = cx[0][m];
+      if constexpr (CV) vq[m] = cvv[0][m];
+    }
+    // the octilateral walk needs many registers: the window is committed before it and loaded
+    // after it, so that no window value is live across it
+    if constexpr (NNN) {
+      __syncthreads();
+      commit_next(p);
     }
 
-    // 2. commit the stage-input plane that field(p + 1) needs; issue the next one
-    if (p + 1 <= pb1 && need_hi(p + 1) > hi) {
-      hi++;
-      commit_window(hi);
-    }
-    // the octilateral walk below needs many registers: its sweeps load the next window only
-    // after it, so that the window buffers are not live across it
-    if constexpr (!NNN) load_window(hi + 1);
-
-    // 3. current, force and velocity on the tile of plane q = p - 1
+    // 2. current, force and velocity on the tile of plane q = p - 1
+    Outputs so = {};
     if (qout) {
-      const bool face = face_xy || (bcz == BC_LINE_TIED && (q == 0 || q == nz - 1));
+      const int oy = (ty + 2) * RX2 + tx + 2;  // the tile node in the window
+      if constexpr (REC) {
+#pragma unroll
+        for (int m = 0; m < 3; m++) so.yc[m] = ys[yslot(q)][m][oy];
+      }
+      const bool face = face_x || face_y || (bcz == BC_LINE_TIED && (q == 0 || q == nz - 1));
       T u[3] = {T(0), T(0), T(0)};
       if constexpr (DIAG) {
 #pragma unroll
         for (int m = 0; m < 3; m++) {
-          so_p[0][m] = Bq[m];
-          so_p[1][m] = 0.0;  // J: zero on line-tied faces
+          so.p[0][m] = Bq[m];
+          so.p[1][m] = 0.0;  // J: zero on line-tied faces
         }
-        so_p[2][0] = 0.0;
+        so.p[2][0] = 0.0;
       }
       if (!face) {
         const int o = (ty + 1) * RX1 + (tx + 1);
@@ -658,7 +730,6 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
           // circulation sum (B_r + B_r+1)/2 . dx_r; area vector = the triangles at the edge
           // points (V2 V3 V4, V4 V5 V6, V6 V7 V8, V8 V1 V2) plus the quadrilateral through the
           // diagonal points V2 V4 V6 V8; then J . N_q = C_q by Cramer's rule
-          const int oy = (ty + 2) * RX2 + tx + 2;
           constexpr int RD[9][2] = {{1, 0}, {1, 1}, {0, 1}, {-1, 1}, {-1, 0}, {-1, -1}, {0, -1}, {1, -1}, {1, 0}};
           double Mq[3][3], Cq[3];
 #pragma unroll 1
@@ -764,13 +835,6 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
             G[1][m] = bs[sq][m][o + RX1] - bs[sq][m][o - RX1];
             G[2][m] = Bp[m] - Bqm[m];
           }
-          T Fq[3][3];
-#pragma unroll
-          for (int m = 0; m < 3; m++) {
-            Fq[m][0] = Fxy[m][0];
-            Fq[m][1] = Fxy[m][1];
-            Fq[m][2] = Fzq[m];
-          }
           // c'_q = (F' e_b) . G'_a - (F' e_a) . G'_b, (a, b, q) = (y, z, x), (z, x, y), (x, y, z)
           T cq[3];
           cq[0] = Fq[0][2] * G[1][0] + Fq[1][2] * G[1][1] + Fq[2][2] * G[1][2] -
@@ -784,11 +848,11 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
         }
         if constexpr (DIAG) {
 #pragma unroll
-          for (int m = 0; m < 3; m++) so_p[1][m] = J[m];
+          for (int m = 0; m < 3; m++) so.p[1][m] = J[m];
           // alpha* = J.B / B^2 (Sec. 3.2.1); 0 where B vanishes
           const double B2 = (double)Bq[0] * Bq[0] + (double)Bq[1] * Bq[1] + (double)Bq[2] * Bq[2];
           const double JB = (double)J[0] * Bq[0] + (double)J[1] * Bq[1] + (double)J[2] * Bq[2];
-          so_p[2][0] = B2 > 0.0 ? JB / B2 : 0.0;
+          so.p[2][0] = B2 > 0.0 ? JB / B2 : 0.0;
         }
         const T f0 = J[1] * Bq[2] - J[2] * Bq[1];
         const T f1 = J[2] * Bq[0] - J[0] * Bq[2];
@@ -817,16 +881,16 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
         const double sc = (diag_only && a.u_det_scale != 0.0) ? Dq * a.u_det_scale : 1.0;
 #pragma unroll
         for (int m = 0; m < 3; m++) {
-          so_k[m] = diag_only ? (T)((double)u[m] * sc) : u[m];
-          so_y[m] = ycq[m];
+          so.k[m] = diag_only ? (T)((double)u[m] * sc) : u[m];
+          if constexpr (!DIAG) so.y[m] = ys[yslot(q)][m][oy];
         }
       } else if constexpr (S == 2) {
         // y_3 = x_n + dt (a_31 k_1 + a_32 k_2), from the own node's x_n and k_1 of plane q
 #pragma unroll
         for (int m = 0; m < 3; m++) {
-          const double d3 = fma(dt * CK::a[2][1], (double)u[m], (dt * CK::a[2][0]) * (double)kq[m]);
-          so_y[m] = xq[m] + d3;
-          so_k[m] = u[m];
+          const double d3 = fma(dt * CK::a[2][1], (double)u[m], (dt * CK::a[2][0]) * (double)vq[m]);
+          so.y[m] = xq[m] + d3;
+          so.k[m] = u[m];
         }
       } else if constexpr (S == 3) {
         // d_4 = dt (a_41 k_1 + a_42 k_2 + a_43 k_3)
@@ -835,8 +899,8 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
           double d4 = (dt * CK::a[3][0]) * (double)pk[0][m];
           d4 = fma(dt * CK::a[3][1], (double)pk[1][m], d4);
           d4 = fma(dt * CK::a[3][2], (double)u[m], d4);
-          so_k[m] = u[m];
-          so_s[0][m] = (T)d4;
+          so.k[m] = u[m];
+          so.s[0][m] = (T)d4;
         }
       } else if constexpr (S == 4) {
         // y_5 = x_n + d_5, and the partial sums of k_1..k_4 the last two stages need
@@ -858,22 +922,22 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
           double es = (dt * (CK::b5[0] - CK::b4[0])) * k1;
           es = fma(dt * (CK::b5[2] - CK::b4[2]), k3, es);
           es = fma(dt * (CK::b5[3] - CK::b4[3]), k4, es);
-          so_y[m] = xq[m] + d5;
-          so_s[0][m] = (T)p6;
-          so_s[1][m] = (T)xs;
-          so_s[2][m] = (T)es;
+          so.y[m] = xq[m] + d5;
+          so.s[0][m] = (T)p6;
+          so.s[1][m] = (T)xs;
+          so.s[2][m] = (T)es;
         }
       } else if constexpr (S == 5) {
 #pragma unroll
         for (int m = 0; m < 3; m++) {
-          so_s[0][m] = (T)fma(dt * CK::a[5][4], (double)u[m], (double)ps[0][m]);
-          so_s[2][m] = (T)fma(dt * (CK::b5[4] - CK::b4[4]), (double)u[m], (double)ps[1][m]);
+          so.s[0][m] = (T)fma(dt * CK::a[5][4], (double)u[m], (double)ps[0][m]);
+          so.s[2][m] = (T)fma(dt * (CK::b5[4] - CK::b4[4]), (double)u[m], (double)ps[1][m]);
         }
       } else {
         // x_{n+1} = x_n + (X + dt b5_6 k_6);  error E + dt (b5_6 - b4_6) k_6
 #pragma unroll
         for (int m = 0; m < 3; m++) {
-          so_y[m] = xq[m] + fma(dt * CK::b5[5], (double)u[m], (double)ps[0][m]);
+          so.y[m] = xq[m] + fma(dt * CK::b5[5], (double)u[m], (double)ps[0][m]);
           const double e = fma(dt * (CK::b5[5] - CK::b4[5]), (double)u[m], (double)ps[1][m]);
           const double err = tile_ok ? fabs(e) : 0.0;
           acc_lam = (err > acc_lam || err != err) ? err : acc_lam;
@@ -881,15 +945,19 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
       }
     }
     load_point(p);  // output node of the next plane step
-    if constexpr (NNN) load_window(hi + 1);
-    store_plane(q, qout);
+    store_plane(so, q, qout, kap_q);
+
+    // 3. commit the stage-input plane of the next field; load the one after it
+    if constexpr (!NNN) commit_next(p);
+    load_window(win, p + 3, p + 3 <= pb1 + 1);
     __syncthreads();
 
 #pragma unroll
     for (int m = 0; m < 3; m++) {
       Bqm[m] = Bq[m];
       Bq[m] = Bp[m];
-      Fzq[m] = Fzp[m];
+#pragma unroll
+      for (int c = 0; c < 3; c++) Fq[m][c] = Fp[m][c];
     }
     rDq = rDp;
     Dq = Dp;
@@ -942,62 +1010,48 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
   }
 }
 
-template <bool MIXED, bool XYP, bool NNN = false>
+template <bool MIXED, bool NNN = false>
 hipError_t launch_stage_t(int s, const SweepArgs& a, hipStream_t st) {
   const dim3 grid(a.g.nblocks), block(NTHREADS);
   switch (s) {
-    case 1: hipLaunchKernelGGL((stage_kernel<1, MIXED, XYP, false, false, NNN>), grid, block, 0, st, a); break;
-    case 2: hipLaunchKernelGGL((stage_kernel<2, MIXED, XYP, false, false, NNN>), grid, block, 0, st, a); break;
-    case 3: hipLaunchKernelGGL((stage_kernel<3, MIXED, XYP, false, false, NNN>), grid, block, 0, st, a); break;
-    case 4: hipLaunchKernelGGL((stage_kernel<4, MIXED, XYP, false, false, NNN>), grid, block, 0, st, a); break;
-    case 5: hipLaunchKernelGGL((stage_kernel<5, MIXED, XYP, false, false, NNN>), grid, block, 0, st, a); break;
-    case 6: hipLaunchKernelGGL((stage_kernel<6, MIXED, XYP, false, false, NNN>), grid, block, 0, st, a); break;
+    case 1: hipLaunchKernelGGL((stage_kernel<1, MIXED, false, false, NNN>), grid, block, 0, st, a); break;
+    case 2: hipLaunchKernelGGL((stage_kernel<2, MIXED, false, false, NNN>), grid, block, 0, st, a); break;
+    case 3: hipLaunchKernelGGL((stage_kernel<3, MIXED, false, false, NNN>), grid, block, 0, st, a); break;
+    case 4: hipLaunchKernelGGL((stage_kernel<4, MIXED, false, false, NNN>), grid, block, 0, st, a); break;
+    case 5: hipLaunchKernelGGL((stage_kernel<5, MIXED, false, false, NNN>), grid, block, 0, st, a); break;
+    case 6: hipLaunchKernelGGL((stage_kernel<6, MIXED, false, false, NNN>), grid, block, 0, st, a); break;
     default: return hipErrorInvalidValue;
   }
-  return hipGetLastError();
-}
-
-// the forward replay of the reverse pass (FP64): stages 4 and 6 also store their input
-template <bool XYP>
-hipError_t launch_stage_rec_t(int s, const SweepArgs& a, hipStream_t st) {
-  const dim3 grid(a.g.nblocks), block(NTHREADS);
-  switch (s) {
-    case 4: hipLaunchKernelGGL((stage_kernel<4, false, XYP, false, true>), grid, block, 0, st, a); break;
-    case 6: hipLaunchKernelGGL((stage_kernel<6, false, XYP, false, true>), grid, block, 0, st, a); break;
-    default: return launch_stage_t<false, XYP>(s, a, st);
-  }
-  return hipGetLastError();
-}
-
-template <bool XYP, bool NNN>
-hipError_t launch_diagnostics_t(const SweepArgs& a, hipStream_t st) {
-  hipLaunchKernelGGL((stage_kernel<1, false, XYP, true, false, NNN>), dim3(a.g.nblocks), dim3(NTHREADS), 0, st, a);
   return hipGetLastError();
 }
 
 }  // namespace
 
 hipError_t launch_stage(int s, bool mixed, const SweepArgs& a, hipStream_t st) {
-  const bool xyp = (a.g.bc[0] == BC_PERIODIC && a.g.bc[1] == BC_PERIODIC);
-  if (a.g.curl == CURL_NNN) {
-    if (mixed) return hipErrorInvalidValue;
-    return xyp ? launch_stage_t<false, true, true>(s, a, st) : launch_stage_t<false, false, true>(s, a, st);
-  }
-  if (mixed) return xyp ? launch_stage_t<true, true>(s, a, st) : launch_stage_t<true, false>(s, a, st);
-  return xyp ? launch_stage_t<false, true>(s, a, st) : launch_stage_t<false, false>(s, a, st);
+  if (a.g.curl == CURL_NNN) return mixed ? hipErrorInvalidValue : launch_stage_t<false, true>(s, a, st);
+  return mixed ? launch_stage_t<true>(s, a, st) : launch_stage_t<false>(s, a, st);
 }
 
+// the forward replay of the reverse pass (FP64): stages 4 and 6 also store their input
 hipError_t launch_stage_rec(int s, const SweepArgs& a, hipStream_t st) {
   if (a.g.curl == CURL_NNN) return hipErrorInvalidValue;
-  const bool xyp = (a.g.bc[0] == BC_PERIODIC && a.g.bc[1] == BC_PERIODIC);
-  return xyp ? launch_stage_rec_t<true>(s, a, st) : launch_stage_rec_t<false>(s, a, st);
+  const dim3 grid(a.g.nblocks), block(NTHREADS);
+  if (s == 4)
+    hipLaunchKernelGGL((stage_kernel<4, false, false, true>), grid, block, 0, st, a);
+  else if (s == 6)
+    hipLaunchKernelGGL((stage_kernel<6, false, false, true>), grid, block, 0, st, a);
+  else
+    return launch_stage_t<false>(s, a, st);
+  return hipGetLastError();
 }
 
 hipError_t launch_diagnostics(const SweepArgs& a, hipStream_t st) {
-  const bool xyp = (a.g.bc[0] == BC_PERIODIC && a.g.bc[1] == BC_PERIODIC);
+  const dim3 grid(a.g.nblocks), block(NTHREADS);
   if (a.g.curl == CURL_NNN)
-    return xyp ? launch_diagnostics_t<true, true>(a, st) : launch_diagnostics_t<false, true>(a, st);
-  return xyp ? launch_diagnostics_t<true, false>(a, st) : launch_diagnostics_t<false, false>(a, st);
+    hipLaunchKernelGGL((stage_kernel<1, false, true, false, true>), grid, block, 0, st, a);
+  else
+    hipLaunchKernelGGL((stage_kernel<1, false, true, false, false>), grid, block, 0, st, a);
+  return hipGetLastError();
 }
 
 }  // namespace relax

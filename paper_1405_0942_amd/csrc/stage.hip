@@ -211,6 +211,7 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
   unsigned f1e[NP1];  // flat (x, y) index, IE off the grid
   int f1o[NP1];       // offset in the B window, -1 past it
   int f1y[NP1];       // offset in the stage-input window
+  int f1k[NP1];       // NNN: line-tied ends it lies on: 1, 2 along x, 4, 8 along y
 #pragma unroll
   for (int r = 0; r < NP1; r++) {
     const int e = tid + r * NTHREADS;
@@ -237,6 +238,9 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
     f1e[r] = (in_win && rx.ok && ry.ok) ? (unsigned)(ry.i * nx + rx.i) : IE;
     f1o[r] = in_win ? r1 * RX1 + c1 : -1;
     f1y[r] = (r1 + 1) * RX2 + c1 + 1;
+    f1k[r] = 0;
+    if (bcx == BC_LINE_TIED) f1k[r] |= rx.i == 0 ? 1 : (rx.i == nx - 1 ? 2 : 0);
+    if (bcy == BC_LINE_TIED) f1k[r] |= ry.i == 0 ? 4 : (ry.i == ny - 1 ? 8 : 0);
   }
   // Ghost nodes just beyond a line-tied face: y(-1) = 3 (y(0) - y(1)) + y(2), and likewise at the
   // other end, so that the central difference at the face node is the one-sided second-order row
@@ -346,21 +350,20 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
   };
   // NNN: the one-sided rows themselves.  (The octilateral runs that break down amplify the rounding
   // of the face rows, so these keep the order of operations they have always had.)
-  auto jacobian_rows = [&](int o, unsigned e, int p, double F[3][3]) {
-    const int gj = (int)(e / (unsigned)nx), gi = (int)(e - (unsigned)gj * nx);
+  auto jacobian_rows = [&](int o, int ends, int p, double F[3][3]) {
     const int sp = yslot(p);
 #pragma unroll
     for (int m = 0; m < 3; m++) {
       const double* yc = ys[sp][m];
-      if (bcx == BC_PERIODIC || (gi > 0 && gi < nx - 1))
+      if (!(ends & 3))
         F[m][0] = yc[o + 1] - yc[o - 1];
-      else if (gi == 0)
+      else if (ends & 1)
         F[m][0] = -3.0 * yc[o] + 4.0 * yc[o + 1] - yc[o + 2];
       else
         F[m][0] = 3.0 * yc[o] - 4.0 * yc[o - 1] + yc[o - 2];
-      if (bcy == BC_PERIODIC || (gj > 0 && gj < ny - 1))
+      if (!(ends & 12))
         F[m][1] = yc[o + RX2] - yc[o - RX2];
-      else if (gj == 0)
+      else if (ends & 4)
         F[m][1] = -3.0 * yc[o] + 4.0 * yc[o + RX2] - yc[o + 2 * RX2];
       else
         F[m][1] = 3.0 * yc[o] - 4.0 * yc[o - RX2] + yc[o - 2 * RX2];
@@ -398,11 +401,13 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
         cx[0][m] = cx[1][m];
         cx[1][m] = cx[2][m];
         cx[2][m] = w.x[0][m];
+        pin(cx[2][m]);
       }
       if constexpr (CV) {
         cvv[0][m] = cvv[1][m];
         cvv[1][m] = cvv[2][m];
         cvv[2][m] = w.v[0][m];
+        pin(cvv[2][m]);
       }
     }
   };
@@ -529,12 +534,8 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
 
   Window win;
   auto commit_next = [&](int p) {
-    if (p + 2 <= pb1 + 1) {
-      if (!perz && p + 2 == nz)
-        commit_ghost_plane(nz, nz - 1, nz - 2, nz - 3);
-      else
-        commit_window(win, p + 2);
-    }
+    commit_window(win, p + 2);  // past the chunk's last plane: zeros that nothing reads
+    if (!perz && p + 2 == nz) commit_ghost_plane(nz, nz - 1, nz - 2, nz - 3);
     carry(win);
   };
 
@@ -580,111 +581,118 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
     const int q = p - 1;
     const bool qout = (q >= z0 && q < z1);
     fill_ghosts(p + 1);
-    // 1. F', det F' and B on the tile + 1-node halo of plane p
-    T Bp[3] = {T(0), T(0), T(0)};
-    T Fp[3][3] = {};
-    T rDp = T(0);
-    double Dp = 0.0;
+    // 1. F', det F' and B of field point R of plane p; off the grid B = 0
+    T Bp[3], Fp[3][3], rDp;
+    double Dp;
     int kap_p = 1;
-    if (p <= pb1) {
+    auto field = [&](auto point) {
+      constexpr int R = decltype(point)::value;
       const int sb = bslot(p);
-#pragma unroll
-      for (int r = 0; r < NP1; r++) {
-        __builtin_amdgcn_sched_barrier(0);  // one field point at a time: bounds live temporaries
-        if (f1o[r] >= 0) {
-          T B[3] = {T(0), T(0), T(0)};
-          if (f1e[r] != IE) {
-            const int o = f1y[r];
-            const int sc = yslot(p), sl = yslot(p - 1), sh = yslot(p + 1);
-            double F[3][3];
-            if constexpr (NNN)
-              jacobian_rows(o, f1e[r], p, F);
-            else
-#pragma unroll
-            for (int m = 0; m < 3; m++) {
-              F[m][0] = ys[sc][m][o + 1] - ys[sc][m][o - 1];
-              F[m][1] = ys[sc][m][o + RX2] - ys[sc][m][o - RX2];
-              F[m][2] = ys[sh][m][o] - ys[sl][m][o];
-            }
-            const double D = det3(F);
-            const double rD = rcp_nr(D);
-            T q0 = b0r[r][0], q1 = b0r[r][1], q2 = b0r[r][2];
-            if constexpr (DIAG) {
-              q0 *= a.b0_mul[0];
-              q1 *= a.b0_mul[1];
-              q2 *= a.b0_mul[2];
-            }
-            if constexpr (MIXED) {
-              const float fi = (float)rD;
-#pragma unroll
-              for (int m = 0; m < 3; m++)
-                B[m] = ((float)F[m][0] * q0 + (float)F[m][1] * q1 + (float)F[m][2] * q2) * fi;
-            } else {
-#pragma unroll
-              for (int m = 0; m < 3; m++) B[m] = (F[m][0] * q0 + F[m][1] * q1 + F[m][2] * q2) * rD;
-            }
-            if (r == 0) {  // this thread's own tile node
-#pragma unroll
-              for (int m = 0; m < 3; m++) {
-#pragma unroll
-                for (int c = 0; c < 3; c++) Fp[m][c] = (T)F[m][c];
-                Bp[m] = B[m];
-              }
-              rDp = (T)rD;
-              Dp = D * inv8h3;
-              if (STAGE1 && p >= z0 && p < z1 && tile_ok) {
-                // energy in FP64 from the FP64 Jacobian and B0'', weights zeta on line-tied faces
-                double zeta = 1.0;
-                if (face_x) zeta *= 0.5;
-                if (face_y) zeta *= 0.5;
-                if (bcz == BC_LINE_TIED && (p == 0 || p == nz - 1)) zeta *= 0.5;
-                double Bd[3];
-#pragma unroll
-                for (int m = 0; m < 3; m++)
-                  Bd[m] = (F[m][0] * (double)q0 + F[m][1] * (double)q1 + F[m][2] * (double)q2) * rD;
-                acc_E += zeta * (Bd[0] * Bd[0] + Bd[1] * Bd[1] + Bd[2] * Bd[2]) * Dp;
-                acc_min = (Dp < acc_min || Dp != Dp) ? Dp : acc_min;
-                if constexpr (DIAG) {
-                  // convexity (Sec. 3.2.3, eq. "convexity"): every trihedron of edge vectors to
-                  // the neighbours p + di e_x, p + dj e_y, p + dk e_z must have a determinant of
-                  // sign di dj dk; trihedra beyond a line-tied face are not formed
-                  const bool lox = bcx == BC_PERIODIC || gi_t > 0, hix = bcx == BC_PERIODIC || gi_t < nx - 1;
-                  const bool loy = bcy == BC_PERIODIC || gj_t > 0, hiy = bcy == BC_PERIODIC || gj_t < ny - 1;
-                  const bool loz = bcz == BC_PERIODIC || p > 0, hiz = bcz == BC_PERIODIC || p < nz - 1;
-                  double ex[2][3], ey[2][3], ez[2][3];  // [0]: toward -, [1]: toward +
+      const bool ok = (f1e[R] != IE);
+      T B[3];
+                  const int o = f1y[R];
+                  const int sc = yslot(p), sl = yslot(p - 1), sh = yslot(p + 1);
+                  double F[3][3];
+                  if constexpr (NNN)
+                    jacobian_rows(o, f1k[R], p, F);
+                  else
 #pragma unroll
                   for (int m = 0; m < 3; m++) {
-                    const double c0 = ys[sc][m][o];
-                    ex[0][m] = ys[sc][m][o - 1] - c0;
-                    ex[1][m] = ys[sc][m][o + 1] - c0;
-                    ey[0][m] = ys[sc][m][o - RX2] - c0;
-                    ey[1][m] = ys[sc][m][o + RX2] - c0;
-                    ez[0][m] = ys[sl][m][o] - c0;
-                    ez[1][m] = ys[sh][m][o] - c0;
+                    F[m][0] = ys[sc][m][o + 1] - ys[sc][m][o - 1];
+                    F[m][1] = ys[sc][m][o + RX2] - ys[sc][m][o - RX2];
+                    F[m][2] = ys[sh][m][o] - ys[sl][m][o];
                   }
-                  bool convex = true;
-#pragma unroll
-                  for (int t = 0; t < 8; t++) {
-                    const int a = t & 1, b = (t >> 1) & 1, c = (t >> 2) & 1;
-                    const bool formed = (a ? hix : lox) && (b ? hiy : loy) && (c ? hiz : loz);
-                    const double* u1 = ex[a];
-                    const double* u2 = ey[b];
-                    const double* u3 = ez[c];
-                    const double det = u1[0] * (u2[1] * u3[2] - u2[2] * u3[1]) - u1[1] * (u2[0] * u3[2] - u2[2] * u3[0]) +
-                                       u1[2] * (u2[0] * u3[1] - u2[1] * u3[0]);
-                    const double want = ((a + b + c) & 1) ? 1.0 : -1.0;  // (2a-1)(2b-1)(2c-1)
-                    if (formed && !(det * want > 0.0)) convex = false;
+                  const double D = det3(F);
+                  const double rD = ok ? rcp_nr(D) : 0.0;
+                  T q0 = b0r[R][0], q1 = b0r[R][1], q2 = b0r[R][2];
+                  if constexpr (DIAG) {
+                    q0 *= a.b0_mul[0];
+                    q1 *= a.b0_mul[1];
+                    q2 *= a.b0_mul[2];
                   }
-                  acc_conc += convex ? 0.0 : 1.0;
-                  kap_p = convex ? 1 : -1;
-                }
-              }
-            }
-          }
+                  if constexpr (MIXED) {
+                    const float fi = (float)rD;
 #pragma unroll
-          for (int m = 0; m < 3; m++) bs[sb][m][f1o[r]] = B[m];
-        }
+                    for (int m = 0; m < 3; m++)
+                      B[m] = ((float)F[m][0] * q0 + (float)F[m][1] * q1 + (float)F[m][2] * q2) * fi;
+                  } else {
+#pragma unroll
+                    for (int m = 0; m < 3; m++) B[m] = (F[m][0] * q0 + F[m][1] * q1 + F[m][2] * q2) * rD;
+                  }
+                  if constexpr (R == 0) {  // this thread's own tile node
+#pragma unroll
+                    for (int m = 0; m < 3; m++) {
+#pragma unroll
+                      for (int c = 0; c < 3; c++) Fp[m][c] = (T)F[m][c];
+                      Bp[m] = B[m];
+                    }
+                    rDp = (T)rD;
+                    Dp = D * inv8h3;
+                    if (STAGE1 && p >= z0 && p < z1 && tile_ok) {
+                      // energy in FP64 from the FP64 Jacobian and B0'', weights zeta on line-tied faces
+                      double zeta = 1.0;
+                      if (face_x) zeta *= 0.5;
+                      if (face_y) zeta *= 0.5;
+                      if (bcz == BC_LINE_TIED && (p == 0 || p == nz - 1)) zeta *= 0.5;
+                      double Bd[3];
+#pragma unroll
+                      for (int m = 0; m < 3; m++)
+                        Bd[m] = (F[m][0] * (double)q0 + F[m][1] * (double)q1 + F[m][2] * (double)q2) * rD;
+                      acc_E += zeta * (Bd[0] * Bd[0] + Bd[1] * Bd[1] + Bd[2] * Bd[2]) * Dp;
+                      acc_min = (Dp < acc_min || Dp != Dp) ? Dp : acc_min;
+                      if constexpr (DIAG) {
+                        // convexity (Sec. 3.2.3, eq. "convexity"): every trihedron of edge vectors to
+                        // the neighbours p + di e_x, p + dj e_y, p + dk e_z must have a determinant of
+                        // sign di dj dk; trihedra beyond a line-tied face are not formed
+                        const bool lox = bcx == BC_PERIODIC || gi_t > 0, hix = bcx == BC_PERIODIC || gi_t < nx - 1;
+                        const bool loy = bcy == BC_PERIODIC || gj_t > 0, hiy = bcy == BC_PERIODIC || gj_t < ny - 1;
+                        const bool loz = bcz == BC_PERIODIC || p > 0, hiz = bcz == BC_PERIODIC || p < nz - 1;
+                        double ex[2][3], ey[2][3], ez[2][3];  // [0]: toward -, [1]: toward +
+#pragma unroll
+                        for (int m = 0; m < 3; m++) {
+                          const double c0 = ys[sc][m][o];
+                          ex[0][m] = ys[sc][m][o - 1] - c0;
+                          ex[1][m] = ys[sc][m][o + 1] - c0;
+                          ey[0][m] = ys[sc][m][o - RX2] - c0;
+                          ey[1][m] = ys[sc][m][o + RX2] - c0;
+                          ez[0][m] = ys[sl][m][o] - c0;
+                          ez[1][m] = ys[sh][m][o] - c0;
+                        }
+                        bool convex = true;
+#pragma unroll
+                        for (int t = 0; t < 8; t++) {
+                          const int a = t & 1, b = (t >> 1) & 1, c = (t >> 2) & 1;
+                          const bool formed = (a ? hix : lox) && (b ? hiy : loy) && (c ? hiz : loz);
+                          const double* u1 = ex[a];
+                          const double* u2 = ey[b];
+                          const double* u3 = ez[c];
+                          const double det = u1[0] * (u2[1] * u3[2] - u2[2] * u3[1]) - u1[1] * (u2[0] * u3[2] - u2[2] * u3[0]) +
+                                             u1[2] * (u2[0] * u3[1] - u2[1] * u3[0]);
+                          const double want = ((a + b + c) & 1) ? 1.0 : -1.0;  // (2a-1)(2b-1)(2c-1)
+                          if (formed && !(det * want > 0.0)) convex = false;
+                        }
+                        acc_conc += convex ? 0.0 : 1.0;
+                        kap_p = convex ? 1 : -1;
+                      }
+                    }
+                  }
+#pragma unroll
+      for (int m = 0; m < 3; m++) bs[sb][m][f1o[R]] = B[m];
+    };
+    static_assert(NP1 == 2 && RY1 * RX1 >= NTHREADS, "one tile node and at most one halo point per thread");
+    using OwnNode = std::integral_constant<int, 0>;
+    using HaloPoint = std::integral_constant<int, 1>;
+    if constexpr (NNN) {
+      if (p <= pb1) {
+        field(OwnNode{});
+        __builtin_amdgcn_sched_barrier(0);  // one field point at a time: bounds live temporaries
+        if (f1o[1] >= 0) field(HaloPoint{});
       }
+    } else {
+      // the halo points first (three of the eight waves); past the chunk's last plane the field is
+      // computed too and not read
+      if (f1o[1] >= 0) field(HaloPoint{});
+      field(OwnNode{});
     }
     load_b0(p + 1 <= pb1 ? p + 1 : pb1);
     // own-node values of plane q
@@ -703,7 +711,7 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
     }
 
     // 2. current, force and velocity on the tile of plane q = p - 1
-    Outputs so = {};
+    Outputs so;
     if (qout) {
       const int oy = (ty + 2) * RX2 + tx + 2;  // the tile node in the window
       if constexpr (REC) {
@@ -720,7 +728,7 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
         }
         so.p[2][0] = 0.0;
       }
-      if (!face) {
+      if (!NNN || !face) {
         const int o = (ty + 1) * RX1 + (tx + 1);
         const int sq = bslot(q);
         T J[3];
@@ -848,20 +856,20 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
         }
         if constexpr (DIAG) {
 #pragma unroll
-          for (int m = 0; m < 3; m++) so.p[1][m] = J[m];
+          for (int m = 0; m < 3; m++) so.p[1][m] = face ? 0.0 : (double)J[m];
           // alpha* = J.B / B^2 (Sec. 3.2.1); 0 where B vanishes
           const double B2 = (double)Bq[0] * Bq[0] + (double)Bq[1] * Bq[1] + (double)Bq[2] * Bq[2];
           const double JB = (double)J[0] * Bq[0] + (double)J[1] * Bq[1] + (double)J[2] * Bq[2];
-          so.p[2][0] = B2 > 0.0 ? JB / B2 : 0.0;
+          so.p[2][0] = (B2 > 0.0 && !face) ? JB / B2 : 0.0;
         }
         const T f0 = J[1] * Bq[2] - J[2] * Bq[1];
         const T f1 = J[2] * Bq[0] - J[0] * Bq[2];
         const T f2 = J[0] * Bq[1] - J[1] * Bq[0];
         const T gm = (T)gamma;
-        u[0] = gm * f0;
-        u[1] = gm * f1;
-        u[2] = gm * f2;
-        if (STAGE1 && tile_ok) {
+        u[0] = face ? T(0) : gm * f0;
+        u[1] = face ? T(0) : gm * f1;
+        u[2] = face ? T(0) : gm * f2;
+        if (STAGE1 && tile_ok && !face) {
           const double F2 = (double)f0 * f0 + (double)f1 * f1 + (double)f2 * f2;
           const double B2 = (double)Bq[0] * Bq[0] + (double)Bq[1] * Bq[1] + (double)Bq[2] * Bq[2];
           acc_R2 += Dq * F2;

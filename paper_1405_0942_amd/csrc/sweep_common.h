@@ -76,6 +76,14 @@ __device__ __forceinline__ void bstore(__amdgpu_buffer_rsrc_t r, unsigned e, V v
     __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), r, (int)(e * 4u), 0, CPOL_STREAM);
 }
 
+// Gives v a register of its own here.  Without it a value carried over a load into the variable
+// it came from may keep that variable's register: the load then goes elsewhere and is copied at
+// the end of the loop, which waits for it at once.
+template <typename V>
+__device__ __forceinline__ void pin(V& v) {
+  asm volatile("" : "+v"(v));
+}
+
 // logical tile of this workgroup; consecutive logical tiles share an XCD (the hardware
 // hands workgroup b to XCD b mod 8), so neighbouring tiles reuse each other's halos in L2
 __device__ __forceinline__ int logical_block(int bid, int nb) {

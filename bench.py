@@ -44,15 +44,19 @@ ALGO_STEP = {"fp64": sum(ALGO_FP64), "fp32-mixed": sum(ALGO_MIXED)}
 
 # What this library's sweeps move per node (its own design, used only for the "design" keys).
 # Every stage input is x_n plus one increment rounded once; a window holds at most two vectors:
+# FP64:
 #   stage 1: x_n, B0 -> k_1
-#   stage 2: x_n, k_1, B0 -> k_2, y_3
-#   stage 3: y_3, B0, k_1, k_2 at the node -> k_3, d_4
-#   stage 4: x_n, d_4, B0, k_1..k_3 at the node -> y_5, P6, X, E
-#   stage 5: y_5, B0, P6, E -> P6 (now d_6), E
+#   stage 2: x_n, k_1, B0 -> C4 (the part of d_4 from k_1 and k_2), y_3
+#   stage 3: y_3, B0, C4 at the node -> k_3, d_4
+#   stage 4: x_n, d_4, B0, k_1 and k_3 at the node -> y_5, P6, X, E
+#   stage 5: y_5, B0, P6 -> P6 (now d_6)
 #   stage 6: x_n, d_6, B0, X, E -> x_{n+1}
-# FP64: every vector 24 B (864 B per attempt); FP32-mixed: x_n, y_3, y_5 and x_{n+1} 24 B, the
-# k_j, d_4, the partial sums and B0 12 B (540 B per attempt).
-DESIGN_FP64 = [72, 120, 144, 240, 144, 144]
+# Every vector 24 B (768 B per attempt).  FP32-mixed and the octilateral current store k_2 instead of
+# C4, read k_1, k_2 (stage 3) and k_1..k_3 (stage 4) at the node, and read and write E in stage 5;
+# FP32-mixed: x_n, y_3, y_5 and x_{n+1} 24 B, the k_j, d_4, the partial sums and B0 12 B (540 B per
+# attempt); octilateral: 864 B per attempt.
+DESIGN_FP64 = [72, 120, 120, 216, 96, 144]
+DESIGN_NNN = [72, 120, 144, 240, 144, 144]
 DESIGN_MIXED = [48, 84, 84, 144, 84, 96]
 
 
@@ -89,7 +93,7 @@ def run_precision(R, torch, w, precision, steps, warmup, tol, dt0, curl=0):
         r.step(steps, diag=False)
         prof = r.profile(False)
     algo = ALGO_FP64 if precision == R.RELAX_FP64 else ALGO_MIXED
-    design = DESIGN_FP64 if precision == R.RELAX_FP64 else DESIGN_MIXED
+    design = DESIGN_MIXED if precision != R.RELAX_FP64 else (DESIGN_NNN if curl else DESIGN_FP64)
     kernels = {}
     for s in range(1, 7):
         ms, n = prof[f"stage{s}"]

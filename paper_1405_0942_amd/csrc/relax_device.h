@@ -73,7 +73,8 @@ struct SweepArgs {
   Geometry g;
   const double* x[2];  // position buffers (x_n is x[ctl->cur])
   double* xout[2];     // same buffers, writable (stage 6 writes x[1 - cur])
-  void* k[3];          // stage vectors k_1..k_3 (double, or float in mixed mode)
+  void* k[3];          // stage vectors k_1..k_3 (double, or float in mixed mode); k[1] holds C4 in
+                       // the sweeps that do not store k_2 (stage.hip)
   double* y3;          // stage input y_3, written by stage 2
   void* d4;            // stage-4 increment d_4 (element type of k), written by stage 3
   double* y5;          // stage input y_5, written by stage 4
@@ -129,6 +130,9 @@ struct CK {
   static constexpr double b5[6] = {37.0 / 378.0, 0.0, 250.0 / 621.0, 125.0 / 594.0, 0.0, 512.0 / 1771.0};
   static constexpr double b4[6] = {2825.0 / 27648.0, 0.0, 18575.0 / 48384.0, 13525.0 / 55296.0,
                                    277.0 / 14336.0, 1.0 / 4.0};
+  // error weights b5 - b4
+  static constexpr double e[6] = {37.0 / 378.0 - 2825.0 / 27648.0, 0.0, 250.0 / 621.0 - 18575.0 / 48384.0,
+                                  125.0 / 594.0 - 13525.0 / 55296.0, -277.0 / 14336.0, 512.0 / 1771.0 - 1.0 / 4.0};
 };
 
 // ------------------------------------------------------------------------------------------

@@ -29,25 +29,39 @@
 // grid a rounding of y_s is amplified by about 1/h^2 in u, so the inputs are rounded once from
 // x_n (as the plain definition does) and never accumulated stage by stage.  A stencilled
 // window holds at most two vectors (more overflow each XCD's L2 with halo lines); what a
-// stage needs at its output node from its own window (x_n, and k_1 in stage 2) is carried in
+// stage needs at its output node from its own window (x_n with k_1, d_4 or d_6) is carried in
 // registers from the window load, three plane steps earlier, instead of being read again.
+// FP64 with the nearest-neighbour current (LEAN; C4 = dt (a_41 k_1 + a_42 k_2)):
 //   stage 1: window x_n                    -> k_1
-//   stage 2: window x_n + dt a_21 k_1      -> k_2, y_3 = x_n + dt (a_31 k_1 + a_32 k_2)
-//   stage 3: window y_3; k_1, k_2 at node  -> k_3, d_4 = dt (a_41 k_1 + a_42 k_2 + a_43 k_3)
-//   stage 4: window x_n + d_4; k_1..k_3    -> y_5 = x_n + d_5 and the partial sums of k_1..k_4
-//            P6 = dt sum a_6j k_j, X = dt sum b5_j k_j, E = dt sum (b5_j - b4_j) k_j
-//   stage 5: window y_5; P6, E at node     -> P6 += dt a_65 k_5 (now d_6), E += dt (b5_5 - b4_5) k_5
+//   stage 2: window x_n + dt a_21 k_1      -> C4, y_3 = x_n + dt (a_31 k_1 + a_32 k_2)
+//   stage 3: window y_3; C4 at node        -> k_3, d_4 = C4 + dt a_43 k_3
+//   stage 4: window x_n + d_4; k_1, k_3    -> y_5 = x_n + d_5 and the partial sums of k_1..k_4
+//            P6 = dt sum a_6j k_j, X = dt sum b5_j k_j, E = dt sum e_j k_j - mu P6
+//            (e_j = b5_j - b4_j, mu = e_5 / a_65; k_2 from the own node's d_4, which is in the window)
+//   stage 5: window y_5; P6 at node        -> P6 += dt a_65 k_5 (now d_6)
 //   stage 6: window x_n + d_6; X, E        -> x_{n+1} = x_n + (X + dt b5_6 k_6),
-//                                             Lambda = max |E + dt (b5_6 - b4_6) k_6|
-// k_4, k_5 and k_6 are never stored.  HBM bytes per node and attempt: 864 (FP64), 540
-// (FP32-mixed: the k_j, d_4 and the partial sums in FP32; x_n, y_3 and y_5 in FP64).  x_{n+1}
-// is x_n plus an increment built from the k_j alone, so the step keeps full relative precision
-// however small it is.  A retried step (smaller dt, same x_n and k_1) starts again at stage 2,
-// and every stored vector is rewritten before it is read again.  REC (the forward replay of
-// the reverse pass) also stores y_4 and y_6 at the node for the reverse sweeps.
+//                                             Lambda = max |E + mu d_6 + dt e_6 k_6|
+// k_2, k_4, k_5 and k_6 are never stored: 768 HBM bytes per node and attempt, where storing k_2
+// and adding e_5 k_5 to E in stage 5 took 864 (256^3: 2.83 -> 2.52 ms per attempt).  Against
+// 80-bit arithmetic the error of Lambda is the same (1e-17 to 5e-15 of dt |k|, from the k_j
+// themselves).  FP32-mixed keeps k_2 and accumulates E in stage 5, since there mu d_6 would add its
+// FP32 rounding to E: Lambda off by 1.1e-8 instead of 5e-9 of dt |k| in the worst case measured.
+// So does the octilateral current, whose runs that break down amplify every rounding.  Their
+// stages 2..6:
+//   stage 2: as above                      -> k_2, y_3
+//   stage 3: window y_3; k_1, k_2          -> k_3, d_4
+//   stage 4: window x_n + d_4; k_1..k_3    -> y_5, P6, X, E = dt sum e_j k_j
+//   stage 5: window y_5; P6, E             -> P6 (now d_6), E += dt e_5 k_5
+//   stage 6: as above                      -> x_{n+1}, Lambda = max |E + dt e_6 k_6|
+// HBM bytes per node and attempt: 540 FP32-mixed (the k_j, d_4 and the partial sums in FP32; x_n,
+// y_3 and y_5 in FP64), 864 with the octilateral.  x_{n+1} is x_n plus an increment built from the
+// k_j alone, so the step keeps full relative precision however small it is.  A retried step
+// (smaller dt, same x_n and k_1) starts again at stage 2, and every stored vector is rewritten
+// before it is read again.  REC (the forward replay of the reverse pass) also stores y_4 and y_6 at
+// the node for the reverse sweeps.
 //
 // Data flow: a workgroup owns a 64 x 8 (x, y) tile and marches up a z-chunk.  Each plane
-// of the stage input (tile + 2-node halo, FP64) goes into an LDS ring of three planes;
+// of the stage input (tile + 2-node halo, FP64) goes into an LDS ring of four planes;
 // F', det F' and B are formed on the tile + 1-node halo into an LDS ring of two B planes
 // (the z difference of B at the tile node uses the node's own B of the neighbouring
 // planes, kept in registers); the current, force and velocity are formed on the tile one
@@ -55,6 +69,11 @@
 // an offset past the record count (loads return 0, stores are dropped), so the march has
 // no divergent branch around a memory instruction: each load is issued one plane step
 // before its use, in the same order on every step, and waited for by exact counts.
+//
+// What bounds it: at 256^3 a stage moves its bytes at 5.5 to 6.0 TB/s, against 6.1 of a streaming
+// kernel with the same accesses; without any global access in the march the same sweep takes a
+// third of the time (0.15 of 0.44 ms, stage 3).  Small grids are bound by latency: about 1.2 us of
+// dependent FP64 and LDS work per plane step, 5 us before the first plane.
 #include <type_traits>
 
 #include "sweep_common.h"
@@ -100,16 +119,20 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
   auto bslot = [](int p) { return NNN ? mod3(p) : (p & 1); };
   constexpr bool STAGE1 = (S == 1);
   constexpr bool LAST = (S == 6);
+  constexpr bool LEAN = !MIXED && !NNN;  // the lean set of stored vectors (above)
   // the window is a base vector (x_n; y_3 in stage 3, y_5 in stage 5) plus at most one vector
   // v with coefficient cv: k_1 (cv = dt a_21) in stage 2, d_4 and d_6 (cv = 1) in stages 4, 6
   constexpr bool WV = (S == 2 || S == 4 || LAST);
   // own-node values carried from the window to the output node (3 planes later): x_n in
   // stages 2, 4, 6 (and k_1 in stage 2)
   constexpr bool CX = WV;
-  constexpr bool CV = (S == 2);
-  constexpr int NPK = (S == 3) ? 2 : (S == 4 ? 3 : 0);  // k_j read at the output node
+  constexpr bool CV = LEAN ? WV : (S == 2);
+  // vectors read at the output node: lean, c_4 in stage 3 and k_1, k_3 in stage 4; else k_1, k_2
+  // and k_1..k_3
+  constexpr int NPK = (S == 3) ? (LEAN ? 1 : 2) : (S == 4 ? (LEAN ? 2 : 3) : 0);
   constexpr int NPKA = NPK > 0 ? NPK : 1;
-  constexpr bool PS = (S == 5 || LAST);  // two partial sums read at the output node
+  constexpr bool PS = (S == 5 || LAST);             // partial sums read at the output node
+  constexpr int NPS = PS ? (LEAN && S == 5 ? 1 : 2) : 1;
   constexpr bool SUMS_OUT = (S == 3 || S == 4 || S == 5);
   constexpr int NP2 = (RY2 * RX2 + NTHREADS - 1) / NTHREADS;  // stage-input points per thread
   constexpr int NP1 = (RY1 * RX1 + NTHREADS - 1) / NTHREADS;  // field points per thread
@@ -281,7 +304,7 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
   // ---- loads of one plane, issued one plane step ahead of their use -------------------------
   T b0r[NP1][3];        // B0'' at the field points
   T pk[NPKA][3];        // k_j at the output node (stages 3, 4)
-  T ps[PS ? 2 : 1][3];  // stage 5: (P6, E); stage 6: (X, E) at the output node
+  T ps[NPS][3];         // stage 5: P6 (and E, not lean); stage 6: X, E at the output node
   struct Window {
     double x[NP2][3];      // window base (x_n, y_3 or y_5)
     T v[WV ? NP2 : 1][3];  // the window vector
@@ -426,7 +449,7 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
     if constexpr (NPK > 0) {
 #pragma unroll
       for (int j = 0; j < NPK; j++) {
-        const T* kj = static_cast<const T*>(a.k[j]);
+        const T* kj = static_cast<const T*>(a.k[LEAN ? (S == 3 ? 1 : 2 * j) : j]);
 #pragma unroll
         for (int m = 0; m < 3; m++) pk[j][m] = bload<T, CPOL_STREAM>(plane_rsrc(kj + m * N + zo, nxy), eo);
       }
@@ -437,7 +460,7 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
 #pragma unroll
       for (int m = 0; m < 3; m++) ps[0][m] = bload<T, CPOL_STREAM>(plane_rsrc(s0 + m * N + zo, nxy), eo);
 #pragma unroll
-      for (int m = 0; m < 3; m++) ps[1][m] = bload<T, CPOL_STREAM>(plane_rsrc(s1 + m * N + zo, nxy), eo);
+      for (int m = 0; m < 3 && NPS == 2; m++) ps[NPS - 1][m] = bload<T, CPOL_STREAM>(plane_rsrc(s1 + m * N + zo, nxy), eo);
     }
   };
 
@@ -515,7 +538,7 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
       }
     } else if constexpr (S == 5) {
 #pragma unroll
-      for (int i = 0; i < 3; i += 2) {
+      for (int i = 0; i < (LEAN ? 1 : 3); i += 2) {
         T* ds = static_cast<T*>(a.sum[i]);
 #pragma unroll
         for (int m = 0; m < 3; m++) bstore<T>(plane_rsrc(ds + m * N + zo, nxy), eo, so.s[i][m]);
@@ -898,14 +921,20 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
         for (int m = 0; m < 3; m++) {
           const double d3 = fma(dt * CK::a[2][1], (double)u[m], (dt * CK::a[2][0]) * (double)vq[m]);
           so.y[m] = xq[m] + d3;
-          so.k[m] = u[m];
+          if constexpr (LEAN)
+            so.k[m] = fma(dt * CK::a[3][1], u[m], (dt * CK::a[3][0]) * vq[m]);
+          else
+            so.k[m] = u[m];
         }
       } else if constexpr (S == 3) {
         // d_4 = dt (a_41 k_1 + a_42 k_2 + a_43 k_3)
 #pragma unroll
         for (int m = 0; m < 3; m++) {
-          double d4 = (dt * CK::a[3][0]) * (double)pk[0][m];
-          d4 = fma(dt * CK::a[3][1], (double)pk[1][m], d4);
+          double d4 = (double)pk[0][m];
+          if constexpr (!LEAN) {
+            d4 = (dt * CK::a[3][0]) * (double)pk[0][m];
+            d4 = fma(dt * CK::a[3][1], (double)pk[NPKA - 1][m], d4);
+          }
           d4 = fma(dt * CK::a[3][2], (double)u[m], d4);
           so.k[m] = u[m];
           so.s[0][m] = (T)d4;
@@ -913,40 +942,72 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
       } else if constexpr (S == 4) {
         // y_5 = x_n + d_5, and the partial sums of k_1..k_4 the last two stages need
         // (b5_2 = b4_2 = 0: k_2 enters neither X nor E)
+        if constexpr (LEAN) {
+          // dt a_42 k_2 = d_4 - dt a_41 k_1 - dt a_43 k_3, from the own node's d_4
+          constexpr double r5 = CK::a[4][1] / CK::a[3][1], r6 = CK::a[5][1] / CK::a[3][1];
+          // E is stored less the multiple of P6 that stage 6 adds back as d_6 = P6 + dt a_65 k_5
+          constexpr double mu = CK::e[4] / CK::a[5][4];
 #pragma unroll
-        for (int m = 0; m < 3; m++) {
-          const double k1 = pk[0][m], k2 = pk[1][m], k3 = pk[2][m], k4 = u[m];
-          double d5 = (dt * CK::a[4][0]) * k1;
-          d5 = fma(dt * CK::a[4][1], k2, d5);
-          d5 = fma(dt * CK::a[4][2], k3, d5);
-          d5 = fma(dt * CK::a[4][3], k4, d5);
-          double p6 = (dt * CK::a[5][0]) * k1;
-          p6 = fma(dt * CK::a[5][1], k2, p6);
-          p6 = fma(dt * CK::a[5][2], k3, p6);
-          p6 = fma(dt * CK::a[5][3], k4, p6);
-          double xs = (dt * CK::b5[0]) * k1;
-          xs = fma(dt * CK::b5[2], k3, xs);
-          xs = fma(dt * CK::b5[3], k4, xs);
-          double es = (dt * (CK::b5[0] - CK::b4[0])) * k1;
-          es = fma(dt * (CK::b5[2] - CK::b4[2]), k3, es);
-          es = fma(dt * (CK::b5[3] - CK::b4[3]), k4, es);
-          so.y[m] = xq[m] + d5;
-          so.s[0][m] = (T)p6;
-          so.s[1][m] = (T)xs;
-          so.s[2][m] = (T)es;
+          for (int m = 0; m < 3; m++) {
+            const double k1 = pk[0][m], k3 = pk[1][m], k4 = u[m], d4 = vq[m];
+            double d5 = r5 * d4;
+            d5 = fma(dt * (CK::a[4][0] - r5 * CK::a[3][0]), k1, d5);
+            d5 = fma(dt * (CK::a[4][2] - r5 * CK::a[3][2]), k3, d5);
+            d5 = fma(dt * CK::a[4][3], k4, d5);
+            double p6 = r6 * d4;
+            p6 = fma(dt * (CK::a[5][0] - r6 * CK::a[3][0]), k1, p6);
+            p6 = fma(dt * (CK::a[5][2] - r6 * CK::a[3][2]), k3, p6);
+            p6 = fma(dt * CK::a[5][3], k4, p6);
+            double xs = (dt * CK::b5[0]) * k1;
+            xs = fma(dt * CK::b5[2], k3, xs);
+            xs = fma(dt * CK::b5[3], k4, xs);
+            double es = -mu * p6;
+            es = fma(dt * CK::e[0], k1, es);
+            es = fma(dt * CK::e[2], k3, es);
+            es = fma(dt * CK::e[3], k4, es);
+            so.y[m] = xq[m] + d5;
+            so.s[0][m] = p6;
+            so.s[1][m] = xs;
+            so.s[2][m] = es;
+          }
+        } else {
+#pragma unroll
+          for (int m = 0; m < 3; m++) {
+            const double k1 = pk[0][m], k2 = pk[1][m], k3 = pk[NPKA - 1][m], k4 = u[m];
+            double d5 = (dt * CK::a[4][0]) * k1;
+            d5 = fma(dt * CK::a[4][1], k2, d5);
+            d5 = fma(dt * CK::a[4][2], k3, d5);
+            d5 = fma(dt * CK::a[4][3], k4, d5);
+            double p6 = (dt * CK::a[5][0]) * k1;
+            p6 = fma(dt * CK::a[5][1], k2, p6);
+            p6 = fma(dt * CK::a[5][2], k3, p6);
+            p6 = fma(dt * CK::a[5][3], k4, p6);
+            double xs = (dt * CK::b5[0]) * k1;
+            xs = fma(dt * CK::b5[2], k3, xs);
+            xs = fma(dt * CK::b5[3], k4, xs);
+            double es = (dt * (CK::b5[0] - CK::b4[0])) * k1;
+            es = fma(dt * (CK::b5[2] - CK::b4[2]), k3, es);
+            es = fma(dt * (CK::b5[3] - CK::b4[3]), k4, es);
+            so.y[m] = xq[m] + d5;
+            so.s[0][m] = (T)p6;
+            so.s[1][m] = (T)xs;
+            so.s[2][m] = (T)es;
+          }
         }
       } else if constexpr (S == 5) {
 #pragma unroll
         for (int m = 0; m < 3; m++) {
           so.s[0][m] = (T)fma(dt * CK::a[5][4], (double)u[m], (double)ps[0][m]);
-          so.s[2][m] = (T)fma(dt * (CK::b5[4] - CK::b4[4]), (double)u[m], (double)ps[1][m]);
+          if constexpr (!LEAN) so.s[2][m] = (T)fma(dt * (CK::b5[4] - CK::b4[4]), (double)u[m], (double)ps[NPS - 1][m]);
         }
       } else {
         // x_{n+1} = x_n + (X + dt b5_6 k_6);  error E + dt (b5_6 - b4_6) k_6
 #pragma unroll
         for (int m = 0; m < 3; m++) {
           so.y[m] = xq[m] + fma(dt * CK::b5[5], (double)u[m], (double)ps[0][m]);
-          const double e = fma(dt * (CK::b5[5] - CK::b4[5]), (double)u[m], (double)ps[1][m]);
+          double es = (double)ps[NPS - 1][m];
+          if constexpr (LEAN) es = fma(CK::e[4] / CK::a[5][4], vq[m], es);
+          const double e = fma(dt * (CK::b5[5] - CK::b4[5]), (double)u[m], es);
           const double err = tile_ok ? fabs(e) : 0.0;
           acc_lam = (err > acc_lam || err != err) ? err : acc_lam;
         }

@@ -1,0 +1,449 @@
+// brick.hip -- the stage sweep for small grids: one workgroup per brick of nodes, all planes at once.
+//
+// The z-marching sweep of stage.hip pays one plane step after another: about 1.2 us of dependent FP64
+// and LDS work each, with at least 12 steps per chunk, on a grid that has too few tiles to fill the
+// CUs.  Here a workgroup of 512 threads loads the stage input of a whole brick with its 2-node halo
+// into LDS at once, forms F', det F' and B on the brick and its 1-node halo (the own node first, then
+// the shell), and the current, force and update of one node per thread: two barriers in all (three at
+// line-tied faces), so that a sweep takes one round of global latency instead of a dozen.  The price is
+// the halo: a brick of 8 x 8 x 8 loads 3.4 window points and evaluates 2 fields per node where the
+// march of a tall chunk takes 1.6 and 1.3, so that bricks are used only where latency decides
+// (choose_brick in relax.cpp).  The arithmetic of a node is that of stage.hip (stage_math.h).
+#include "stage_math.h"
+
+namespace relax {
+namespace {
+
+constexpr int NPW = (BRICK_WINDOW + BRICK_THREADS - 1) / BRICK_THREADS;  // window points per thread
+constexpr int NPF = 1 + (BRICK_SHELL + BRICK_THREADS - 1) / BRICK_THREADS;  // field points per thread
+
+// e / d for 0 <= e < 4096, 1 <= d < 4096: (e + 1/2) / d is at least 1 / (2 d) away from an integer,
+// far more than the rounding of the reciprocal
+__device__ __forceinline__ int small_div(int e, int d) {
+  return (int)(((float)e + 0.5f) * __builtin_amdgcn_rcpf((float)d));
+}
+
+template <int S, bool MIXED, bool NNN, bool DIAG = false, bool REC = false>
+__global__ __launch_bounds__(BRICK_THREADS) __attribute__((amdgpu_waves_per_eu(NNN ? 2 : 4))) void brick_kernel(SweepArgs a) {
+  using St = Stage<S, MIXED, NNN>;
+  using T = typename St::T;
+  constexpr bool STAGE1 = St::STAGE1, LAST = St::LAST, LEAN = St::LEAN, WV = St::WV, CX = St::CX, CV = St::CV;
+  constexpr bool PS = St::PS;
+  constexpr int NPK = St::NPK, NPKA = St::NPKA, NPS = St::NPS;
+  static_assert(!DIAG || (S == 1 && !MIXED), "the diagnostics sweep is the FP64 stage-1 sweep");
+
+  Control* ctl = a.ctl;
+  int cur;
+  double dt = 0.0;
+  bool record_ck = false;
+  long long ck_slot = 0;
+  if (!DIAG) {
+    if (ctl->status != 0 || ctl->accepted >= ctl->target) return;
+    if (STAGE1 && ctl->need_k1 == 0) return;
+    cur = ctl->cur;
+    dt = ctl->dt;
+    if (STAGE1 && ctl->record) {
+      const long long st = ctl->steps_total;
+      if (st % ctl->ck_every == 0 && st / ctl->ck_every < a.ckpt_slots) {
+        record_ck = true;
+        ck_slot = st / ctl->ck_every;
+      }
+    }
+  } else {
+    cur = a.diag_buf;
+  }
+  const double gamma = ctl->gamma;
+  const double tau_B2 = ctl->tau_B2;
+  const double cv = (S == 2) ? dt * CK::a[1][0] : 1.0;
+
+  const Geometry& g = a.g;
+  const int nx = g.n[0], ny = g.n[1], nz = g.n[2];
+  const int nxy = nx * ny;
+  const long long N = g.N;
+  const int bcx = g.bc[0], bcy = g.bc[1], bcz = g.bc[2];
+  const int bx = g.brick[0], by = g.brick[1], bz = g.brick[2];
+  const int sx = bx + 4, sy = by + 4, sxy = sx * sy;   // window strides
+  const int fx = bx + 2, fy = by + 2, fxy = fx * fy;   // B strides
+  const int nwin = sxy * (bz + 4), nown = bx * by * bz;
+
+  const int lb = logical_block(blockIdx.x, g.nblocks);
+  const int i0 = (lb % g.tiles[0]) * bx;
+  const int j0 = ((lb / g.tiles[0]) % g.tiles[1]) * by;
+  const int k0 = (lb / (g.tiles[0] * g.tiles[1])) * bz;
+  const int tid = threadIdx.x;
+
+  __shared__ double ys[3][BRICK_WINDOW];
+  __shared__ T bs[3][BRICK_FIELD];
+  __shared__ double red[BRICK_THREADS / 64][NPART];
+
+  const double* __restrict__ xn = a.x[cur];
+  const double* __restrict__ wbase = (S == 3) ? a.y3 : ((S == 5) ? a.y5 : xn);
+  const T* __restrict__ wvec = static_cast<const T*>(S == 2 ? a.k[0] : (S == 4 ? a.d4 : a.sum[0]));
+  const T* __restrict__ b0p = static_cast<const T*>(a.B0);
+
+  // ---- all loads first ---------------------------------------------------------------------
+  double wx[NPW][3];
+  T wk[WV ? NPW : 1][3];
+  int we[NPW], wg[NPW];  // grid index (-1 off the grid), step into the grid of a ghost point (0: none)
+  int ww[NPW];           // periodic wraps of x, y, z, each + 1, in bits 0-1, 2-3, 4-5
+#pragma unroll
+  for (int r = 0; r < NPW; r++) {
+    const int e = tid + r * BRICK_THREADS;
+    const int lz = small_div(e, sxy), e2 = e - lz * sxy, ly = small_div(e2, sx), lx = e2 - ly * sx;
+    const int gi = i0 + lx - 2, gj = j0 + ly - 2, gk = k0 + lz - 2;
+    const AxisIdx rx = resolve_near(gi, nx, bcx), ry = resolve_near(gj, ny, bcy), rz = resolve_near(gk, nz, bcz);
+    const bool in = e < nwin;
+    we[r] = (in && rx.ok && ry.ok && rz.ok) ? rz.i * nxy + ry.i * nx + rx.i : -1;
+    ww[r] = (rx.w + 1) | (ry.w + 1) << 2 | (rz.w + 1) << 4;
+    wg[r] = 0;
+    if constexpr (!NNN) {
+      if (in) {
+        if (ry.ok && rz.ok && !rx.ok) wg[r] = gi == -1 ? 1 : (gi == nx ? -1 : 0);
+        if (rx.ok && rz.ok && !ry.ok) wg[r] = gj == -1 ? sx : (gj == ny ? -sx : 0);
+        if (rx.ok && ry.ok && !rz.ok) wg[r] = gk == -1 ? sxy : (gk == nz ? -sxy : 0);
+      }
+    }
+    const int i = max(we[r], 0);
+#pragma unroll
+    for (int m = 0; m < 3; m++) wx[r][m] = wbase[m * N + i];
+    if constexpr (WV) {
+#pragma unroll
+      for (int m = 0; m < 3; m++) wk[r][m] = wvec[m * N + i];
+    }
+  }
+  // field point 0 is the own node; then the shell: the planes below and above the brick, then a ring
+  // around each of its planes
+  T b0r[NPF][3];
+  int fo[NPF], fw[NPF], fend[NPF];  // offsets in the B window (-1: none) and the stage-input window, ends
+  bool fok[NPF];
+  int tx = 0, ty = 0, tz = 0;
+#pragma unroll
+  for (int r = 0; r < NPF; r++) {
+    int cx, cy, cz;  // B window coordinates
+    bool in;
+    if (r == 0) {
+      in = tid < nown;
+      const int e = in ? tid : 0;
+      tz = small_div(e, bx * by);
+      ty = small_div(e - tz * bx * by, bx);
+      tx = e - (tz * by + ty) * bx;
+      cx = tx + 1;
+      cy = ty + 1;
+      cz = tz + 1;
+    } else {
+      const int e = tid + (r - 1) * BRICK_THREADS, ring = 2 * (fx + by);
+      if (e < 2 * fxy) {
+        const int top = e >= fxy ? 1 : 0, e2 = e - top * fxy;
+        cz = top * (bz + 1);
+        cy = small_div(e2, fx);
+        cx = e2 - cy * fx;
+        in = true;
+      } else {
+        const int e2 = e - 2 * fxy, layer = small_div(e2, ring), e3 = e2 - layer * ring;
+        in = layer < bz;
+        cz = in ? layer + 1 : 0;
+        if (e3 < 2 * fx) {
+          cy = e3 < fx ? 0 : by + 1;
+          cx = e3 < fx ? e3 : e3 - fx;
+        } else {
+          cy = 1 + ((e3 - 2 * fx) >> 1);
+          cx = (e3 & 1) ? bx + 1 : 0;
+        }
+      }
+    }
+    const AxisIdx rx = resolve_near(i0 + cx - 1, nx, bcx), ry = resolve_near(j0 + cy - 1, ny, bcy);
+    const AxisIdx rz = resolve_near(k0 + cz - 1, nz, bcz);
+    fok[r] = in && rx.ok && ry.ok && rz.ok;
+    fo[r] = in ? cz * fxy + cy * fx + cx : -1;
+    fw[r] = (cz + 1) * sxy + (cy + 1) * sx + cx + 1;
+    fend[r] = 0;
+    if (bcx == BC_LINE_TIED) fend[r] |= rx.i == 0 ? 1 : (rx.i == nx - 1 ? 2 : 0);
+    if (bcy == BC_LINE_TIED) fend[r] |= ry.i == 0 ? 4 : (ry.i == ny - 1 ? 8 : 0);
+    if (bcz == BC_LINE_TIED) fend[r] |= rz.i == 0 ? 16 : (rz.i == nz - 1 ? 32 : 0);
+    const int i = fok[r] ? rz.i * nxy + ry.i * nx + rx.i : 0;
+#pragma unroll
+    for (int m = 0; m < 3; m++) b0r[r][m] = b0p[m * N + i];
+  }
+  const int gi_t = i0 + tx, gj_t = j0 + ty, gk_t = k0 + tz;
+  const bool node = tid < nown && gi_t < nx && gj_t < ny && gk_t < nz;
+  const int own = node ? gk_t * nxy + gj_t * nx + gi_t : 0;
+  const bool face = node && fend[0] != 0;
+  T pk[NPKA][3], ps[NPS][3], vq[3];
+  double xq[3];
+#pragma unroll
+  for (int m = 0; m < 3; m++) {
+#pragma unroll
+    for (int j = 0; j < NPK; j++) pk[j][m] = static_cast<const T*>(a.k[LEAN ? (S == 3 ? 1 : 2 * j) : j])[m * N + own];
+    if constexpr (PS) ps[0][m] = static_cast<const T*>(S == 5 ? a.sum[0] : a.sum[1])[m * N + own];
+    if constexpr (PS && NPS == 2) ps[NPS - 1][m] = static_cast<const T*>(a.sum[2])[m * N + own];
+    if constexpr (CX) xq[m] = xn[m * N + own];
+    if constexpr (CV) vq[m] = wvec[m * N + own];
+  }
+
+  // ---- stage input on the brick and its 2-node halo ------------------------------------------
+#pragma unroll
+  for (int r = 0; r < NPW; r++) {
+    const int e = tid + r * BRICK_THREADS;
+    double v[3];
+#pragma unroll
+    for (int m = 0; m < 3; m++) {
+      double y = wx[r][m];
+      if constexpr (S == 2) {
+        y = y + cv * (double)wk[r][m];
+      } else if constexpr (WV) {
+        y = y + (double)wk[r][m];
+      }
+      v[m] = y + (double)(((ww[r] >> (2 * m)) & 3) - 1) * g.period[m];
+    }
+    if (e < nwin) {
+#pragma unroll
+      for (int m = 0; m < 3; m++) ys[m][e] = we[r] >= 0 ? v[m] : 0.0;
+    }
+  }
+  __syncthreads();
+  if constexpr (!NNN) {
+    // ghost nodes beyond line-tied faces (see stage.hip)
+    const bool faces = (bcx == BC_LINE_TIED && (i0 <= 1 || i0 + bx >= nx - 1)) ||
+                       (bcy == BC_LINE_TIED && (j0 <= 1 || j0 + by >= ny - 1)) ||
+                       (bcz == BC_LINE_TIED && (k0 <= 1 || k0 + bz >= nz - 1));
+    if (faces) {
+#pragma unroll
+      for (int r = 0; r < NPW; r++) {
+        const int e = tid + r * BRICK_THREADS, s = wg[r];
+        if (s != 0) {
+#pragma unroll
+          for (int m = 0; m < 3; m++) ys[m][e] = fma(3.0, ys[m][e + s] - ys[m][e + 2 * s], ys[m][e + 3 * s]);
+        }
+      }
+      __syncthreads();
+    }
+  }
+
+  // ---- F', det F' and B on the brick and its 1-node halo ---------------------------------------
+  Sums acc;
+  T Fq[3][3], Bq[3], rDq;
+  double Dq;
+  int kap = 1;
+#pragma unroll
+  for (int r = 0; r < NPF; r++) {
+    if (r == 0 || fo[r] >= 0) {
+      const int o = fw[r];
+      double F[3][3];
+      if constexpr (NNN) {
+        // the one-sided rows themselves (see stage.hip)
+        auto row = [&](const double* yc, int s, int end) {
+          return end == 0   ? yc[o + s] - yc[o - s]
+                 : end == 1 ? -3.0 * yc[o] + 4.0 * yc[o + s] - yc[o + 2 * s]
+                            : 3.0 * yc[o] - 4.0 * yc[o - s] + yc[o - 2 * s];
+        };
+#pragma unroll
+        for (int m = 0; m < 3; m++) {
+          F[m][0] = row(ys[m], 1, fend[r] & 3);
+          F[m][1] = row(ys[m], sx, (fend[r] >> 2) & 3);
+          F[m][2] = row(ys[m], sxy, (fend[r] >> 4) & 3);
+        }
+      } else {
+#pragma unroll
+        for (int m = 0; m < 3; m++) {
+          F[m][0] = ys[m][o + 1] - ys[m][o - 1];
+          F[m][1] = ys[m][o + sx] - ys[m][o - sx];
+          F[m][2] = ys[m][o + sxy] - ys[m][o - sxy];
+        }
+      }
+      const double D = det3(F);
+      const double rD = fok[r] ? rcp_nr(D) : 0.0;
+      T q0 = b0r[r][0], q1 = b0r[r][1], q2 = b0r[r][2];
+      if constexpr (DIAG) {
+        q0 *= a.b0_mul[0];
+        q1 *= a.b0_mul[1];
+        q2 *= a.b0_mul[2];
+      }
+      T B[3];
+      pull_back(F, q0, q1, q2, rD, B);
+      if (r == 0) {
+#pragma unroll
+        for (int m = 0; m < 3; m++) {
+#pragma unroll
+          for (int c = 0; c < 3; c++) Fq[m][c] = (T)F[m][c];
+          Bq[m] = B[m];
+        }
+        rDq = (T)rD;
+        Dq = D * g.inv8h3;
+        if (STAGE1 && node) {
+          double zeta = 1.0;
+          if (fend[0] & 3) zeta *= 0.5;
+          if (fend[0] & 12) zeta *= 0.5;
+          if (fend[0] & 48) zeta *= 0.5;
+          double Bd[3];
+#pragma unroll
+          for (int m = 0; m < 3; m++)
+            Bd[m] = (F[m][0] * (double)q0 + F[m][1] * (double)q1 + F[m][2] * (double)q2) * rD;
+          acc.E += zeta * (Bd[0] * Bd[0] + Bd[1] * Bd[1] + Bd[2] * Bd[2]) * Dq;
+          acc.min_det = (Dq < acc.min_det || Dq != Dq) ? Dq : acc.min_det;
+          if constexpr (DIAG) {
+            double ex[2][3], ey[2][3], ez[2][3];
+#pragma unroll
+            for (int m = 0; m < 3; m++) {
+              const double c0 = ys[m][o];
+              ex[0][m] = ys[m][o - 1] - c0;
+              ex[1][m] = ys[m][o + 1] - c0;
+              ey[0][m] = ys[m][o - sx] - c0;
+              ey[1][m] = ys[m][o + sx] - c0;
+              ez[0][m] = ys[m][o - sxy] - c0;
+              ez[1][m] = ys[m][o + sxy] - c0;
+            }
+            const bool convex = is_convex(ex, ey, ez, !(fend[0] & 1), !(fend[0] & 2), !(fend[0] & 4), !(fend[0] & 8),
+                                          !(fend[0] & 16), !(fend[0] & 32));
+            acc.concave += convex ? 0.0 : 1.0;
+            kap = convex ? 1 : -1;
+          }
+        }
+      }
+      if (fo[r] >= 0) {
+#pragma unroll
+        for (int m = 0; m < 3; m++) bs[m][fo[r]] = B[m];
+      }
+    }
+  }
+  __syncthreads();
+
+  // ---- current, force, velocity and the stage's outputs at the own node --------------------------
+  if (node) {
+    StageOut<S, MIXED, NNN, DIAG, REC> so;
+    const int oy = fw[0], o = fo[0];
+    T u[3] = {T(0), T(0), T(0)};
+    if constexpr (DIAG) {
+#pragma unroll
+      for (int m = 0; m < 3; m++) {
+        so.p[0][m] = Bq[m];
+        so.p[1][m] = 0.0;
+      }
+      so.p[2][0] = 0.0;
+    }
+    if (!face) {
+      T J[3];
+      if constexpr (NNN) {
+        octilateral([&](int dx, int dy, int dz, int m) { return ys[m][oy + dz * sxy + dy * sx + dx]; },
+                    [&](int dx, int dy, int dz, int m) { return (double)bs[m][o + dz * fxy + dy * fx + dx]; }, J);
+      } else {
+        T G[3][3];
+#pragma unroll
+        for (int m = 0; m < 3; m++) {
+          G[0][m] = bs[m][o + 1] - bs[m][o - 1];
+          G[1][m] = bs[m][o + fx] - bs[m][o - fx];
+          G[2][m] = bs[m][o + fxy] - bs[m][o - fxy];
+        }
+        current(Fq, G, rDq, J);
+      }
+      if constexpr (DIAG) {
+#pragma unroll
+        for (int m = 0; m < 3; m++) so.p[1][m] = J[m];
+        const double B2 = (double)Bq[0] * Bq[0] + (double)Bq[1] * Bq[1] + (double)Bq[2] * Bq[2];
+        const double JB = (double)J[0] * Bq[0] + (double)J[1] * Bq[1] + (double)J[2] * Bq[2];
+        so.p[2][0] = B2 > 0.0 ? JB / B2 : 0.0;
+      }
+      const T f0 = J[1] * Bq[2] - J[2] * Bq[1];
+      const T f1 = J[2] * Bq[0] - J[0] * Bq[2];
+      const T f2 = J[0] * Bq[1] - J[1] * Bq[0];
+      const T gm = (T)gamma;
+      u[0] = gm * f0;
+      u[1] = gm * f1;
+      u[2] = gm * f2;
+      if constexpr (STAGE1) {
+        const double F2 = (double)f0 * f0 + (double)f1 * f1 + (double)f2 * f2;
+        const double B2 = (double)Bq[0] * Bq[0] + (double)Bq[1] * Bq[1] + (double)Bq[2] * Bq[2];
+        acc.force(F2, B2, Dq, tau_B2);
+      }
+    }
+    auto put = [&](auto* to, const auto (&v)[3]) {
+#pragma unroll
+      for (int m = 0; m < 3; m++) to[m * N + own] = v[m];
+    };
+    if constexpr (DIAG) {
+      const double sc = a.u_det_scale != 0.0 ? Dq * a.u_det_scale : 1.0;
+      const double us[3] = {(double)u[0] * sc, (double)u[1] * sc, (double)u[2] * sc};
+      if (a.u_out) put(a.u_out, us);
+      if (a.B_out) put(a.B_out, so.p[0]);
+      if (a.J_out) put(a.J_out, so.p[1]);
+      if (a.alpha_out) a.alpha_out[own] = so.p[2][0];
+      if (a.kappa_out) a.kappa_out[own] = kap;
+    } else if constexpr (STAGE1) {
+      put(static_cast<T*>(a.k[0]), u);
+      if (record_ck) {
+        const double xo[3] = {ys[0][oy], ys[1][oy], ys[2][oy]};
+        put(a.ckpt + ck_slot * 3 * N, xo);
+      }
+    } else {
+      double err[3];
+      advance<S, MIXED, NNN, REC>(u, xq, vq, pk, ps, dt, so, err);
+      if constexpr (S == 2) {
+        put(static_cast<T*>(a.k[1]), so.k);
+        put(a.y3, so.y);
+      } else if constexpr (S == 3) {
+        put(static_cast<T*>(a.k[2]), so.k);
+        put(static_cast<T*>(a.d4), so.s[0]);
+      } else if constexpr (S == 4) {
+        put(a.y5, so.y);
+#pragma unroll
+        for (int i = 0; i < 3; i++) put(static_cast<T*>(a.sum[i]), so.s[i]);
+      } else if constexpr (S == 5) {
+        put(static_cast<T*>(a.sum[0]), so.s[0]);
+        if constexpr (!LEAN) put(static_cast<T*>(a.sum[2]), so.s[2]);
+      } else {
+        put(a.xout[1 - cur], so.y);
+#pragma unroll
+        for (int m = 0; m < 3; m++) acc.error(err[m]);
+      }
+    }
+    if constexpr (REC) {
+      const double yo[3] = {ys[0][oy], ys[1][oy], ys[2][oy]};
+      put(a.yrec[S == 4 ? 0 : 1], yo);
+    }
+  }
+  if (STAGE1) store_sums<BRICK_THREADS>(acc, red, a.part + (long long)blockIdx.x * NPART);
+  if (LAST) store_lambda<BRICK_THREADS>(acc, red, a.lam_part + blockIdx.x);
+}
+
+template <bool MIXED, bool NNN>
+hipError_t launch_brick_t(int s, const SweepArgs& a, hipStream_t st) {
+  const dim3 grid(a.g.nblocks), block(BRICK_THREADS);
+  switch (s) {
+    case 1: hipLaunchKernelGGL((brick_kernel<1, MIXED, NNN>), grid, block, 0, st, a); break;
+    case 2: hipLaunchKernelGGL((brick_kernel<2, MIXED, NNN>), grid, block, 0, st, a); break;
+    case 3: hipLaunchKernelGGL((brick_kernel<3, MIXED, NNN>), grid, block, 0, st, a); break;
+    case 4: hipLaunchKernelGGL((brick_kernel<4, MIXED, NNN>), grid, block, 0, st, a); break;
+    case 5: hipLaunchKernelGGL((brick_kernel<5, MIXED, NNN>), grid, block, 0, st, a); break;
+    case 6: hipLaunchKernelGGL((brick_kernel<6, MIXED, NNN>), grid, block, 0, st, a); break;
+    default: return hipErrorInvalidValue;
+  }
+  return hipGetLastError();
+}
+
+}  // namespace
+
+hipError_t launch_brick(int s, bool mixed, const SweepArgs& a, hipStream_t st) {
+  if (a.g.curl == CURL_NNN) return mixed ? hipErrorInvalidValue : launch_brick_t<false, true>(s, a, st);
+  return mixed ? launch_brick_t<true, false>(s, a, st) : launch_brick_t<false, false>(s, a, st);
+}
+
+hipError_t launch_brick_rec(int s, const SweepArgs& a, hipStream_t st) {
+  const dim3 grid(a.g.nblocks), block(BRICK_THREADS);
+  if (s == 4)
+    hipLaunchKernelGGL((brick_kernel<4, false, false, false, true>), grid, block, 0, st, a);
+  else if (s == 6)
+    hipLaunchKernelGGL((brick_kernel<6, false, false, false, true>), grid, block, 0, st, a);
+  else
+    return launch_brick_t<false, false>(s, a, st);
+  return hipGetLastError();
+}
+
+hipError_t launch_brick_diagnostics(const SweepArgs& a, hipStream_t st) {
+  const dim3 grid(a.g.nblocks), block(BRICK_THREADS);
+  if (a.g.curl == CURL_NNN)
+    hipLaunchKernelGGL((brick_kernel<1, false, true, true>), grid, block, 0, st, a);
+  else
+    hipLaunchKernelGGL((brick_kernel<1, false, false, true>), grid, block, 0, st, a);
+  return hipGetLastError();
+}
+
+}  // namespace relax

@@ -147,7 +147,52 @@ int choose_tz(const relax_config* c, int tiles_xy) {
   return best_tz;
 }
 
-Geometry make_geometry(const relax_config* c) {
+// Bricks (brick.hip) or z-marching tiles, and which bricks.  A brick sweep takes its time from the
+// points it loads and evaluates, a march from the plane steps of a chunk, which a small grid cannot
+// shorten.  Measured us per step, march / bricks, FP64: 16^3 line-tied 161 / 49, 33^3 line-tied 175 /
+// 56, 64^3 periodic 185 / 95, 65^3 line-tied 200 / 117, 81^3 line-tied 215 / 194, 96^3 periodic 234 /
+// 237, 64 x 64 x 192 205 / 207, 128^3 359 / 653; FP32-mixed 142 / 47, 156 / 54, 159 / 85, 171 / 108,
+// 181 / 178, 197 / 210, 169 / 183, 294 / 492.  The octilateral current, whose march holds one plane
+// more and two barriers: 400 / 72 at 16^3, 499 / 190 at 65^3, 503 / 413 at 96^3, 774 / 1017 at 128^3.
+bool choose_brick(const relax_config* c, int brick[3]) {
+  if (std::getenv("RELAX_TZ")) return false;  // a chosen chunk length is a choice of the march
+  const long long N = (long long)c->n[0] * c->n[1] * c->n[2];
+  if (N > (c->curl == RELAX_CURL_NNN ? 1000000 : 600000)) return false;
+  // edges that split an axis evenly (every ceil(n / k) up to 64), shortest first
+  int edge[3][64], ne[3];
+  for (int a = 0; a < 3; a++) {
+    ne[a] = 0;
+    for (int b = 1; b <= std::min(c->n[a], 64); b++) {
+      const int k = (c->n[a] + b - 1) / b;
+      if ((c->n[a] + k - 1) / k == b) edge[a][ne[a]++] = b;
+    }
+  }
+  double best = -1.0;
+  for (int iz = 0; iz < ne[2]; iz++)
+    for (int iy = 0; iy < ne[1] && edge[1][iy] * edge[2][iz] <= BRICK_THREADS; iy++)
+      for (int ix = 0; ix < ne[0]; ix++) {
+        const int bx = edge[0][ix], by = edge[1][iy], bz = edge[2][iz];
+        if (bx * by * bz > BRICK_THREADS) break;
+        const int win = (bx + 4) * (by + 4) * (bz + 4), fld = (bx + 2) * (by + 2) * (bz + 2);
+        const int shell = fld - bx * by * bz;
+        if (win > BRICK_WINDOW || fld > BRICK_FIELD || shell > BRICK_SHELL) break;
+        const long long blocks = (long long)((c->n[0] + bx - 1) / bx) * ((c->n[1] + by - 1) / by) * ((c->n[2] + bz - 1) / bz);
+        // rounds of the 512 resident workgroups x the passes of a workgroup over its points (4: its
+        // fixed part); on a tie the fewer points loaded
+        const int t = BRICK_THREADS;
+        const double passes = 4.0 + (win + t - 1) / t + 1.5 * (1 + (shell + t - 1) / t);
+        const double cost = (double)((blocks + 511) / 512) * passes + 1e-9 * (double)(blocks * win);
+        if (best < 0.0 || cost < best) {
+          best = cost;
+          brick[0] = bx;
+          brick[1] = by;
+          brick[2] = bz;
+        }
+      }
+  return best >= 0.0;
+}
+
+Geometry make_tiles(const relax_config* c) {
   Geometry g{};
   for (int a = 0; a < 3; a++) {
     g.n[a] = c->n[a];
@@ -167,6 +212,15 @@ Geometry make_geometry(const relax_config* c) {
   g.tiles[2] = (c->n[2] + g.tz - 1) / g.tz;
   g.nblocks = g.tiles[0] * g.tiles[1] * g.tiles[2];
   g.curl = c->curl;
+  return g;
+}
+
+Geometry make_geometry(const relax_config* c) {
+  Geometry g = make_tiles(c);
+  if (choose_brick(c, g.brick)) {
+    for (int a = 0; a < 3; a++) g.tiles[a] = (c->n[a] + g.brick[a] - 1) / g.brick[a];
+    g.nblocks = g.tiles[0] * g.tiles[1] * g.tiles[2];
+  }
   return g;
 }
 
@@ -568,7 +622,7 @@ int relax_backward(void* ctx, double seed_EM, double seed_R2, double* d_grad_x0,
   hipStream_t st = c->stream;
 
   AdjArgs a{};
-  a.g = c->g;
+  a.g = make_tiles(&c->cfg);
   a.B0 = c->d_B0_64;
   a.Fbar = c->d_Fbar;
   a.B0bar = c->d_B0bar;

@@ -26,6 +26,14 @@ constexpr int RX1 = TX + 2, RY1 = TY + 2;  // pulled-back field window (1-node h
 constexpr int NPART = 8;                   // doubles per workgroup partial record
 constexpr int RING_CAP = 4096;             // per-call diagnostics ring entries
 
+// Bricks of the small-grid sweeps (brick.hip): at most BRICK_THREADS nodes, BRICK_WINDOW points with the
+// 2-node halo, BRICK_FIELD points with the 1-node halo, BRICK_SHELL of them around the brick.  FP64: 77
+// KB of LDS, two workgroups per CU.
+constexpr int BRICK_THREADS = 512;
+constexpr int BRICK_WINDOW = 2048;
+constexpr int BRICK_FIELD = 1152;
+constexpr int BRICK_SHELL = 1024;
+
 enum { BC_LINE_TIED = 0, BC_PERIODIC = 1 };
 enum { CURL_NN = 0, CURL_NNN = 1 };  // the values of RELAX_CURL_NN / RELAX_CURL_NNN
 
@@ -40,6 +48,7 @@ struct Geometry {
   double b0scale[3]; // 4 h_b h_c: B0'' = B0 * b0scale (component-wise), see stage.hip
   int tiles[3];      // tiles along x, along y, z-chunks
   int tz;            // z-chunk length
+  int brick[3];      // nodes of a brick (brick.hip), or 0: z-marching tiles (stage.hip)
   int nblocks;       // tiles[0] * tiles[1] * tiles[2]
   int curl;          // CURL_NN: loops over the four nearest neighbours (Sec. 2.2); CURL_NNN:
                      // the octilateral over the eight ring neighbours (Sec. 2.3)
@@ -140,7 +149,9 @@ struct CK {
 // ------------------------------------------------------------------------------------------
 bool valid_config(const relax_config* c);          // every field in range
 int choose_tz(const relax_config* c, int tiles_xy);  // z-chunk length
-Geometry make_geometry(const relax_config* c);     // tiles, chunks and scale factors
+bool choose_brick(const relax_config* c, int brick[3]);  // whether, and which, bricks
+Geometry make_tiles(const relax_config* c);        // scale factors, z-marching tiles and chunks
+Geometry make_geometry(const relax_config* c);     // the same with bricks where they are used
 
 // ------------------------------------------------------------------------------------------
 // Launchers implemented in the kernel translation units
@@ -151,6 +162,10 @@ hipError_t launch_stage(int s, bool mixed, const SweepArgs& a, hipStream_t st);
 // stage input at the node into a.yrec
 hipError_t launch_stage_rec(int s, const SweepArgs& a, hipStream_t st);
 hipError_t launch_diagnostics(const SweepArgs& a, hipStream_t st);  // FP64 sweep of x[diag_buf]
+// the same sweeps over bricks (a.g.brick set)
+hipError_t launch_brick(int s, bool mixed, const SweepArgs& a, hipStream_t st);
+hipError_t launch_brick_rec(int s, const SweepArgs& a, hipStream_t st);
+hipError_t launch_brick_diagnostics(const SweepArgs& a, hipStream_t st);
 hipError_t launch_control(Control* ctl, const double* part, const double* lam_part, int nblocks,
                           double* ring, double* dt_record, hipStream_t st);
 // out6 = {E_M, R2, xi, min det F, null-guard skips, concave nodes} of a diagnostics sweep

@@ -74,38 +74,16 @@
 // kernel with the same accesses; without any global access in the march the same sweep takes a
 // third of the time (0.15 of 0.44 ms, stage 3).  Small grids are bound by latency: about 1.2 us of
 // dependent FP64 and LDS work per plane step, 5 us before the first plane.
-#include <type_traits>
-
-#include "sweep_common.h"
+#include "stage_math.h"
 
 namespace relax {
 namespace {
 
-__device__ __forceinline__ double wave_sum(double v) {
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-  return v;
-}
-__device__ __forceinline__ double wave_max(double v) {
-  for (int o = 32; o > 0; o >>= 1) {
-    double w = __shfl_xor(v, o, 64);
-    v = (w > v || w != w) ? w : v;
-  }
-  return v;
-}
-__device__ __forceinline__ double wave_min(double v) {
-  for (int o = 32; o > 0; o >>= 1) {
-    double w = __shfl_xor(v, o, 64);
-    v = (w < v || w != w) ? w : v;
-  }
-  return v;
-}
-
 // S: stage 1..6.  MIXED: the k_j, the partial sums and B0 in FP32, and the stencil past F' in
-// FP32.  XYP: x and y both periodic (no line-tied rows in x and y).  DIAG (stage 1, FP64): the
-// diagnostics sweep of x[diag_buf]: no step gating and no k_1; writes u (optionally scaled by
+// FP32.  NNN: the octilateral current.  DIAG (stage 1, FP64): the diagnostics sweep of x[diag_buf]: no step gating and no k_1; writes u (optionally scaled by
 // det F), B, J, alpha* and the convexity where the caller asked for them.  REC (FP64 stages
 // 4 and 6): also store the stage input at the node, for the reverse sweeps.
-template <int S, bool MIXED, bool DIAG = false, bool REC = false, bool NNN = false>
+template <int S, bool MIXED, bool NNN, bool DIAG = false, bool REC = false>
 __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) void stage_kernel(SweepArgs a) {
   using T = typename std::conditional<MIXED, float, double>::type;
   // The stage-input ring holds the planes p - 1 .. p + 1 that the field of plane p reads and the
@@ -119,21 +97,9 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
   auto bslot = [](int p) { return NNN ? mod3(p) : (p & 1); };
   constexpr bool STAGE1 = (S == 1);
   constexpr bool LAST = (S == 6);
-  constexpr bool LEAN = !MIXED && !NNN;  // the lean set of stored vectors (above)
-  // the window is a base vector (x_n; y_3 in stage 3, y_5 in stage 5) plus at most one vector
-  // v with coefficient cv: k_1 (cv = dt a_21) in stage 2, d_4 and d_6 (cv = 1) in stages 4, 6
-  constexpr bool WV = (S == 2 || S == 4 || LAST);
-  // own-node values carried from the window to the output node (3 planes later): x_n in
-  // stages 2, 4, 6 (and k_1 in stage 2)
-  constexpr bool CX = WV;
-  constexpr bool CV = LEAN ? WV : (S == 2);
-  // vectors read at the output node: lean, c_4 in stage 3 and k_1, k_3 in stage 4; else k_1, k_2
-  // and k_1..k_3
-  constexpr int NPK = (S == 3) ? (LEAN ? 1 : 2) : (S == 4 ? (LEAN ? 2 : 3) : 0);
-  constexpr int NPKA = NPK > 0 ? NPK : 1;
-  constexpr bool PS = (S == 5 || LAST);             // partial sums read at the output node
-  constexpr int NPS = PS ? (LEAN && S == 5 ? 1 : 2) : 1;
-  constexpr bool SUMS_OUT = (S == 3 || S == 4 || S == 5);
+  using St = Stage<S, MIXED, NNN>;
+  constexpr bool LEAN = St::LEAN, WV = St::WV, CX = St::CX, CV = St::CV, PS = St::PS;
+  constexpr int NPK = St::NPK, NPKA = St::NPKA, NPS = St::NPS;
   constexpr int NP2 = (RY2 * RX2 + NTHREADS - 1) / NTHREADS;  // stage-input points per thread
   constexpr int NP1 = (RY1 * RX1 + NTHREADS - 1) / NTHREADS;  // field points per thread
   static_assert(!DIAG || (S == 1 && !MIXED), "the diagnostics sweep is the FP64 stage-1 sweep");
@@ -371,6 +337,9 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
       }
     }
   };
+  // no field point of the tile lies on a line-tied face across x or y
+  const bool inner_xy = (bcx == BC_PERIODIC || (i0 > 0 && i0 + TX + 1 < nx)) &&
+                        (bcy == BC_PERIODIC || (j0 > 0 && j0 + TY + 1 < ny));
   // NNN: the one-sided rows themselves.  (The octilateral runs that break down amplify the rounding
   // of the face rows, so these keep the order of operations they have always had.)
   auto jacobian_rows = [&](int o, int ends, int p, double F[3][3]) {
@@ -469,21 +438,10 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
   const int pb0 = perz ? z0 - 1 : max(z0 - 1, 0);
   const int pb1 = perz ? z1 : min(z1, nz - 1);
 
-  // reductions
-  double acc_E = 0.0, acc_R2 = 0.0, acc_min = INFINITY, acc_null = 0.0, acc_lam = 0.0;
-  double acc_conc = 0.0;  // DIAG: concave nodes
-  // xi: the node of largest |f|^2 / B^4 so far, kept as (|f|^2, B^4, B^2) and compared by
-  // cross-multiplication, so that the square root and the division are taken once at the end
-  double xi_F2 = 0.0, xi_B4 = 1.0, xi_B2 = 1.0;
+  Sums acc;
 
   // ---- stores of one output plane (every lane issues them; masked-off lanes are dropped) ----
-  struct Outputs {
-    T k[3];                      // k_s (stages 1..3), u (DIAG)
-    double y[3];                 // x_n copy (stage 1), y_3 (stage 2), y_5 (stage 4), x_{n+1}
-    T s[SUMS_OUT ? 3 : 1][3];    // stage 3: d_4; stage 4: P6, X, E; stage 5: P6, -, E
-    double p[DIAG ? 3 : 1][3];   // DIAG: B, J, alpha*
-    double yc[REC ? 3 : 1];      // REC: the stage input at the node
-  };
+  using Outputs = StageOut<S, MIXED, NNN, DIAG, REC>;
   auto store_plane = [&](const Outputs& so, int qz, bool on, int kap = 1) {
     const long long zo = (long long)zload(qz) * nxy;
     const unsigned eo = on ? out_e : IE;
@@ -608,97 +566,76 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
     T Bp[3], Fp[3][3], rDp;
     double Dp;
     int kap_p = 1;
+    const bool central = inner_xy && (perz || (p > 0 && p < nz - 1));
     auto field = [&](auto point) {
       constexpr int R = decltype(point)::value;
       const int sb = bslot(p);
       const bool ok = (f1e[R] != IE);
       T B[3];
-                  const int o = f1y[R];
-                  const int sc = yslot(p), sl = yslot(p - 1), sh = yslot(p + 1);
-                  double F[3][3];
-                  if constexpr (NNN)
-                    jacobian_rows(o, f1k[R], p, F);
-                  else
+      const int o = f1y[R];
+      const int sc = yslot(p), sl = yslot(p - 1), sh = yslot(p + 1);
+      double F[3][3];
+      if (NNN && !central) {
+        jacobian_rows(o, f1k[R], p, F);
+      } else {
 #pragma unroll
-                  for (int m = 0; m < 3; m++) {
-                    F[m][0] = ys[sc][m][o + 1] - ys[sc][m][o - 1];
-                    F[m][1] = ys[sc][m][o + RX2] - ys[sc][m][o - RX2];
-                    F[m][2] = ys[sh][m][o] - ys[sl][m][o];
-                  }
-                  const double D = det3(F);
-                  const double rD = ok ? rcp_nr(D) : 0.0;
-                  T q0 = b0r[R][0], q1 = b0r[R][1], q2 = b0r[R][2];
-                  if constexpr (DIAG) {
-                    q0 *= a.b0_mul[0];
-                    q1 *= a.b0_mul[1];
-                    q2 *= a.b0_mul[2];
-                  }
-                  if constexpr (MIXED) {
-                    const float fi = (float)rD;
+        for (int m = 0; m < 3; m++) {
+          F[m][0] = ys[sc][m][o + 1] - ys[sc][m][o - 1];
+          F[m][1] = ys[sc][m][o + RX2] - ys[sc][m][o - RX2];
+          F[m][2] = ys[sh][m][o] - ys[sl][m][o];
+        }
+      }
+      const double D = det3(F);
+      const double rD = ok ? rcp_nr(D) : 0.0;
+      T q0 = b0r[R][0], q1 = b0r[R][1], q2 = b0r[R][2];
+      if constexpr (DIAG) {
+        q0 *= a.b0_mul[0];
+        q1 *= a.b0_mul[1];
+        q2 *= a.b0_mul[2];
+      }
+      pull_back(F, q0, q1, q2, rD, B);
+      if constexpr (R == 0) {  // this thread's own tile node
 #pragma unroll
-                    for (int m = 0; m < 3; m++)
-                      B[m] = ((float)F[m][0] * q0 + (float)F[m][1] * q1 + (float)F[m][2] * q2) * fi;
-                  } else {
+        for (int m = 0; m < 3; m++) {
 #pragma unroll
-                    for (int m = 0; m < 3; m++) B[m] = (F[m][0] * q0 + F[m][1] * q1 + F[m][2] * q2) * rD;
-                  }
-                  if constexpr (R == 0) {  // this thread's own tile node
+          for (int c = 0; c < 3; c++) Fp[m][c] = (T)F[m][c];
+          Bp[m] = B[m];
+        }
+        rDp = (T)rD;
+        Dp = D * inv8h3;
+        if (STAGE1 && p >= z0 && p < z1 && tile_ok) {
+          // energy in FP64 from the FP64 Jacobian and B0'', weights zeta on line-tied faces
+          double zeta = 1.0;
+          if (face_x) zeta *= 0.5;
+          if (face_y) zeta *= 0.5;
+          if (bcz == BC_LINE_TIED && (p == 0 || p == nz - 1)) zeta *= 0.5;
+          double Bd[3];
 #pragma unroll
-                    for (int m = 0; m < 3; m++) {
+          for (int m = 0; m < 3; m++)
+            Bd[m] = (F[m][0] * (double)q0 + F[m][1] * (double)q1 + F[m][2] * (double)q2) * rD;
+          acc.E += zeta * (Bd[0] * Bd[0] + Bd[1] * Bd[1] + Bd[2] * Bd[2]) * Dp;
+          acc.min_det = (Dp < acc.min_det || Dp != Dp) ? Dp : acc.min_det;
+          if constexpr (DIAG) {
+            const bool lox = bcx == BC_PERIODIC || gi_t > 0, hix = bcx == BC_PERIODIC || gi_t < nx - 1;
+            const bool loy = bcy == BC_PERIODIC || gj_t > 0, hiy = bcy == BC_PERIODIC || gj_t < ny - 1;
+            const bool loz = bcz == BC_PERIODIC || p > 0, hiz = bcz == BC_PERIODIC || p < nz - 1;
+            double ex[2][3], ey[2][3], ez[2][3];  // [0]: toward -, [1]: toward +
 #pragma unroll
-                      for (int c = 0; c < 3; c++) Fp[m][c] = (T)F[m][c];
-                      Bp[m] = B[m];
-                    }
-                    rDp = (T)rD;
-                    Dp = D * inv8h3;
-                    if (STAGE1 && p >= z0 && p < z1 && tile_ok) {
-                      // energy in FP64 from the FP64 Jacobian and B0'', weights zeta on line-tied faces
-                      double zeta = 1.0;
-                      if (face_x) zeta *= 0.5;
-                      if (face_y) zeta *= 0.5;
-                      if (bcz == BC_LINE_TIED && (p == 0 || p == nz - 1)) zeta *= 0.5;
-                      double Bd[3];
-#pragma unroll
-                      for (int m = 0; m < 3; m++)
-                        Bd[m] = (F[m][0] * (double)q0 + F[m][1] * (double)q1 + F[m][2] * (double)q2) * rD;
-                      acc_E += zeta * (Bd[0] * Bd[0] + Bd[1] * Bd[1] + Bd[2] * Bd[2]) * Dp;
-                      acc_min = (Dp < acc_min || Dp != Dp) ? Dp : acc_min;
-                      if constexpr (DIAG) {
-                        // convexity (Sec. 3.2.3, eq. "convexity"): every trihedron of edge vectors to
-                        // the neighbours p + di e_x, p + dj e_y, p + dk e_z must have a determinant of
-                        // sign di dj dk; trihedra beyond a line-tied face are not formed
-                        const bool lox = bcx == BC_PERIODIC || gi_t > 0, hix = bcx == BC_PERIODIC || gi_t < nx - 1;
-                        const bool loy = bcy == BC_PERIODIC || gj_t > 0, hiy = bcy == BC_PERIODIC || gj_t < ny - 1;
-                        const bool loz = bcz == BC_PERIODIC || p > 0, hiz = bcz == BC_PERIODIC || p < nz - 1;
-                        double ex[2][3], ey[2][3], ez[2][3];  // [0]: toward -, [1]: toward +
-#pragma unroll
-                        for (int m = 0; m < 3; m++) {
-                          const double c0 = ys[sc][m][o];
-                          ex[0][m] = ys[sc][m][o - 1] - c0;
-                          ex[1][m] = ys[sc][m][o + 1] - c0;
-                          ey[0][m] = ys[sc][m][o - RX2] - c0;
-                          ey[1][m] = ys[sc][m][o + RX2] - c0;
-                          ez[0][m] = ys[sl][m][o] - c0;
-                          ez[1][m] = ys[sh][m][o] - c0;
-                        }
-                        bool convex = true;
-#pragma unroll
-                        for (int t = 0; t < 8; t++) {
-                          const int a = t & 1, b = (t >> 1) & 1, c = (t >> 2) & 1;
-                          const bool formed = (a ? hix : lox) && (b ? hiy : loy) && (c ? hiz : loz);
-                          const double* u1 = ex[a];
-                          const double* u2 = ey[b];
-                          const double* u3 = ez[c];
-                          const double det = u1[0] * (u2[1] * u3[2] - u2[2] * u3[1]) - u1[1] * (u2[0] * u3[2] - u2[2] * u3[0]) +
-                                             u1[2] * (u2[0] * u3[1] - u2[1] * u3[0]);
-                          const double want = ((a + b + c) & 1) ? 1.0 : -1.0;  // (2a-1)(2b-1)(2c-1)
-                          if (formed && !(det * want > 0.0)) convex = false;
-                        }
-                        acc_conc += convex ? 0.0 : 1.0;
-                        kap_p = convex ? 1 : -1;
-                      }
-                    }
-                  }
+            for (int m = 0; m < 3; m++) {
+              const double c0 = ys[sc][m][o];
+              ex[0][m] = ys[sc][m][o - 1] - c0;
+              ex[1][m] = ys[sc][m][o + 1] - c0;
+              ey[0][m] = ys[sc][m][o - RX2] - c0;
+              ey[1][m] = ys[sc][m][o + RX2] - c0;
+              ez[0][m] = ys[sl][m][o] - c0;
+              ez[1][m] = ys[sh][m][o] - c0;
+            }
+            const bool convex = is_convex(ex, ey, ez, lox, hix, loy, hiy, loz, hiz);
+            acc.concave += convex ? 0.0 : 1.0;
+            kap_p = convex ? 1 : -1;
+          }
+        }
+      }
 #pragma unroll
       for (int m = 0; m < 3; m++) bs[sb][m][f1o[R]] = B[m];
     };
@@ -756,108 +693,8 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
         const int sq = bslot(q);
         T J[3];
         if constexpr (NNN) {
-          // the octilateral loops of Sec. 2.3 through the eight ring neighbours of each grid
-          // plane, taken literally: vertices V1..V8 = +a, +a+b, +b, -a+b, -a, -a-b, -b, +a-b;
-          // circulation sum (B_r + B_r+1)/2 . dx_r; area vector = the triangles at the edge
-          // points (V2 V3 V4, V4 V5 V6, V6 V7 V8, V8 V1 V2) plus the quadrilateral through the
-          // diagonal points V2 V4 V6 V8; then J . N_q = C_q by Cramer's rule
-          constexpr int RD[9][2] = {{1, 0}, {1, 1}, {0, 1}, {-1, 1}, {-1, 0}, {-1, -1}, {0, -1}, {1, -1}, {1, 0}};
-          double Mq[3][3], Cq[3];
-#pragma unroll 1
-          for (int qa = 0; qa < 3; qa++) {
-            // (a, b) = (y, z), (z, x), (x, y); walk V1..V8 and back to V1, keeping only the
-            // previous vertex, the previous edge and the diagonal points met so far
-            double Vp[3], Bvp[3], ep[3], e1[3], D1[3], Dp[3], q1[3], qp[3];
-            double circ = 0.0, nA[3] = {0.0, 0.0, 0.0};
-#pragma unroll
-            for (int r = 0; r <= 8; r++) {
-              const int da = RD[r][0], db = RD[r][1];
-              const int dx = qa == 2 ? da : (qa == 1 ? db : 0);
-              const int dy = qa == 0 ? da : (qa == 2 ? db : 0);
-              const int dz = qa == 0 ? db : (qa == 1 ? da : 0);
-              const int sy = yslot(q + dz), sbv = bslot(q + dz);
-              double V[3], Bv[3];
-#pragma unroll
-              for (int m = 0; m < 3; m++) {
-                V[m] = ys[sy][m][oy + dy * RX2 + dx];
-                Bv[m] = (double)bs[sbv][m][o + dy * RX1 + dx];
-              }
-              if (r > 0) {
-                double e[3];
-#pragma unroll
-                for (int m = 0; m < 3; m++) {
-                  e[m] = V[m] - Vp[m];  // dx_r (1-based r), from V_r to V_r+1
-                  circ += 0.5 * (Bvp[m] + Bv[m]) * e[m];
-                }
-                // triangles at the edge points: dx2 x dx3, dx4 x dx5, dx6 x dx7 and dx8 x dx1
-                if (r == 3 || r == 5 || r == 7) {
-                  nA[0] += 0.5 * (ep[1] * e[2] - ep[2] * e[1]);
-                  nA[1] += 0.5 * (ep[2] * e[0] - ep[0] * e[2]);
-                  nA[2] += 0.5 * (ep[0] * e[1] - ep[1] * e[0]);
-                }
-                if (r == 8) {
-                  nA[0] += 0.5 * (e[1] * e1[2] - e[2] * e1[1]);
-                  nA[1] += 0.5 * (e[2] * e1[0] - e[0] * e1[2]);
-                  nA[2] += 0.5 * (e[0] * e1[1] - e[1] * e1[0]);
-                }
-#pragma unroll
-                for (int m = 0; m < 3; m++) {
-                  if (r == 1) e1[m] = e[m];
-                  ep[m] = e[m];
-                }
-              }
-              // the quadrilateral through the diagonal points V2, V4, V6, V8 (r = 1, 3, 5, 7):
-              // edges dx_A..dx_D and the sum of their consecutive cross products over 4
-              if (r == 1 || r == 3 || r == 5 || r == 7) {
-                if (r == 1) {
-#pragma unroll
-                  for (int m = 0; m < 3; m++) D1[m] = V[m];
-                } else {
-                  double qe[3];
-#pragma unroll
-                  for (int m = 0; m < 3; m++) qe[m] = V[m] - Dp[m];
-                  if (r == 3) {
-#pragma unroll
-                    for (int m = 0; m < 3; m++) q1[m] = qe[m];
-                  } else {
-                    nA[0] += 0.25 * (qp[1] * qe[2] - qp[2] * qe[1]);
-                    nA[1] += 0.25 * (qp[2] * qe[0] - qp[0] * qe[2]);
-                    nA[2] += 0.25 * (qp[0] * qe[1] - qp[1] * qe[0]);
-                  }
-#pragma unroll
-                  for (int m = 0; m < 3; m++) qp[m] = qe[m];
-                  if (r == 7) {  // the closing edge V8 -> V2, then its products with dx_C and dx_A
-                    double qd[3];
-#pragma unroll
-                    for (int m = 0; m < 3; m++) qd[m] = D1[m] - V[m];
-                    nA[0] += 0.25 * (qe[1] * qd[2] - qe[2] * qd[1]) + 0.25 * (qd[1] * q1[2] - qd[2] * q1[1]);
-                    nA[1] += 0.25 * (qe[2] * qd[0] - qe[0] * qd[2]) + 0.25 * (qd[2] * q1[0] - qd[0] * q1[2]);
-                    nA[2] += 0.25 * (qe[0] * qd[1] - qe[1] * qd[0]) + 0.25 * (qd[0] * q1[1] - qd[1] * q1[0]);
-                  }
-                }
-#pragma unroll
-                for (int m = 0; m < 3; m++) Dp[m] = V[m];
-              }
-#pragma unroll
-              for (int m = 0; m < 3; m++) {
-                Vp[m] = V[m];
-                Bvp[m] = Bv[m];
-              }
-            }
-#pragma unroll
-            for (int m = 0; m < 3; m++) Mq[qa][m] = nA[m];
-            Cq[qa] = circ;
-          }
-          const double iM = 1.0 / det3(Mq);
-#pragma unroll
-          for (int c = 0; c < 3; c++) {
-            double Mc[3][3];
-#pragma unroll
-            for (int r = 0; r < 3; r++)
-#pragma unroll
-              for (int k = 0; k < 3; k++) Mc[r][k] = (k == c) ? Cq[r] : Mq[r][k];
-            J[c] = (T)(det3(Mc) * iM);
-          }
+          octilateral([&](int dx, int dy, int dz, int m) { return ys[yslot(q + dz)][m][oy + dy * RX2 + dx]; },
+                      [&](int dx, int dy, int dz, int m) { return (double)bs[bslot(q + dz)][m][o + dy * RX1 + dx]; }, J);
         } else {
           T G[3][3];  // G'[a][m] = B_m(n + e_a) - B_m(n - e_a)
 #pragma unroll
@@ -866,16 +703,7 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
             G[1][m] = bs[sq][m][o + RX1] - bs[sq][m][o - RX1];
             G[2][m] = Bp[m] - Bqm[m];
           }
-          // c'_q = (F' e_b) . G'_a - (F' e_a) . G'_b, (a, b, q) = (y, z, x), (z, x, y), (x, y, z)
-          T cq[3];
-          cq[0] = Fq[0][2] * G[1][0] + Fq[1][2] * G[1][1] + Fq[2][2] * G[1][2] -
-                  (Fq[0][1] * G[2][0] + Fq[1][1] * G[2][1] + Fq[2][1] * G[2][2]);
-          cq[1] = Fq[0][0] * G[2][0] + Fq[1][0] * G[2][1] + Fq[2][0] * G[2][2] -
-                  (Fq[0][2] * G[0][0] + Fq[1][2] * G[0][1] + Fq[2][2] * G[0][2]);
-          cq[2] = Fq[0][1] * G[0][0] + Fq[1][1] * G[0][1] + Fq[2][1] * G[0][2] -
-                  (Fq[0][0] * G[1][0] + Fq[1][0] * G[1][1] + Fq[2][0] * G[1][2]);
-#pragma unroll
-          for (int m = 0; m < 3; m++) J[m] = (Fq[m][0] * cq[0] + Fq[m][1] * cq[1] + Fq[m][2] * cq[2]) * rDq;
+          current(Fq, G, rDq, J);
         }
         if constexpr (DIAG) {
 #pragma unroll
@@ -895,17 +723,7 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
         if (STAGE1 && tile_ok && !face) {
           const double F2 = (double)f0 * f0 + (double)f1 * f1 + (double)f2 * f2;
           const double B2 = (double)Bq[0] * Bq[0] + (double)Bq[1] * Bq[1] + (double)Bq[2] * Bq[2];
-          acc_R2 += Dq * F2;
-          if (B2 > tau_B2) {
-            const double B4 = B2 * B2;
-            if (F2 * xi_B4 > xi_F2 * B4 || F2 != F2) {
-              xi_F2 = F2;
-              xi_B4 = B4;
-              xi_B2 = B2;
-            }
-          } else {
-            acc_null += 1.0;
-          }
+          acc.force(F2, B2, Dq, tau_B2);
         }
       }
       if constexpr (STAGE1) {
@@ -915,102 +733,12 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
           so.k[m] = diag_only ? (T)((double)u[m] * sc) : u[m];
           if constexpr (!DIAG) so.y[m] = ys[yslot(q)][m][oy];
         }
-      } else if constexpr (S == 2) {
-        // y_3 = x_n + dt (a_31 k_1 + a_32 k_2), from the own node's x_n and k_1 of plane q
-#pragma unroll
-        for (int m = 0; m < 3; m++) {
-          const double d3 = fma(dt * CK::a[2][1], (double)u[m], (dt * CK::a[2][0]) * (double)vq[m]);
-          so.y[m] = xq[m] + d3;
-          if constexpr (LEAN)
-            so.k[m] = fma(dt * CK::a[3][1], u[m], (dt * CK::a[3][0]) * vq[m]);
-          else
-            so.k[m] = u[m];
-        }
-      } else if constexpr (S == 3) {
-        // d_4 = dt (a_41 k_1 + a_42 k_2 + a_43 k_3)
-#pragma unroll
-        for (int m = 0; m < 3; m++) {
-          double d4 = (double)pk[0][m];
-          if constexpr (!LEAN) {
-            d4 = (dt * CK::a[3][0]) * (double)pk[0][m];
-            d4 = fma(dt * CK::a[3][1], (double)pk[NPKA - 1][m], d4);
-          }
-          d4 = fma(dt * CK::a[3][2], (double)u[m], d4);
-          so.k[m] = u[m];
-          so.s[0][m] = (T)d4;
-        }
-      } else if constexpr (S == 4) {
-        // y_5 = x_n + d_5, and the partial sums of k_1..k_4 the last two stages need
-        // (b5_2 = b4_2 = 0: k_2 enters neither X nor E)
-        if constexpr (LEAN) {
-          // dt a_42 k_2 = d_4 - dt a_41 k_1 - dt a_43 k_3, from the own node's d_4
-          constexpr double r5 = CK::a[4][1] / CK::a[3][1], r6 = CK::a[5][1] / CK::a[3][1];
-          // E is stored less the multiple of P6 that stage 6 adds back as d_6 = P6 + dt a_65 k_5
-          constexpr double mu = CK::e[4] / CK::a[5][4];
-#pragma unroll
-          for (int m = 0; m < 3; m++) {
-            const double k1 = pk[0][m], k3 = pk[1][m], k4 = u[m], d4 = vq[m];
-            double d5 = r5 * d4;
-            d5 = fma(dt * (CK::a[4][0] - r5 * CK::a[3][0]), k1, d5);
-            d5 = fma(dt * (CK::a[4][2] - r5 * CK::a[3][2]), k3, d5);
-            d5 = fma(dt * CK::a[4][3], k4, d5);
-            double p6 = r6 * d4;
-            p6 = fma(dt * (CK::a[5][0] - r6 * CK::a[3][0]), k1, p6);
-            p6 = fma(dt * (CK::a[5][2] - r6 * CK::a[3][2]), k3, p6);
-            p6 = fma(dt * CK::a[5][3], k4, p6);
-            double xs = (dt * CK::b5[0]) * k1;
-            xs = fma(dt * CK::b5[2], k3, xs);
-            xs = fma(dt * CK::b5[3], k4, xs);
-            double es = -mu * p6;
-            es = fma(dt * CK::e[0], k1, es);
-            es = fma(dt * CK::e[2], k3, es);
-            es = fma(dt * CK::e[3], k4, es);
-            so.y[m] = xq[m] + d5;
-            so.s[0][m] = p6;
-            so.s[1][m] = xs;
-            so.s[2][m] = es;
-          }
-        } else {
-#pragma unroll
-          for (int m = 0; m < 3; m++) {
-            const double k1 = pk[0][m], k2 = pk[1][m], k3 = pk[NPKA - 1][m], k4 = u[m];
-            double d5 = (dt * CK::a[4][0]) * k1;
-            d5 = fma(dt * CK::a[4][1], k2, d5);
-            d5 = fma(dt * CK::a[4][2], k3, d5);
-            d5 = fma(dt * CK::a[4][3], k4, d5);
-            double p6 = (dt * CK::a[5][0]) * k1;
-            p6 = fma(dt * CK::a[5][1], k2, p6);
-            p6 = fma(dt * CK::a[5][2], k3, p6);
-            p6 = fma(dt * CK::a[5][3], k4, p6);
-            double xs = (dt * CK::b5[0]) * k1;
-            xs = fma(dt * CK::b5[2], k3, xs);
-            xs = fma(dt * CK::b5[3], k4, xs);
-            double es = (dt * (CK::b5[0] - CK::b4[0])) * k1;
-            es = fma(dt * (CK::b5[2] - CK::b4[2]), k3, es);
-            es = fma(dt * (CK::b5[3] - CK::b4[3]), k4, es);
-            so.y[m] = xq[m] + d5;
-            so.s[0][m] = (T)p6;
-            so.s[1][m] = (T)xs;
-            so.s[2][m] = (T)es;
-          }
-        }
-      } else if constexpr (S == 5) {
-#pragma unroll
-        for (int m = 0; m < 3; m++) {
-          so.s[0][m] = (T)fma(dt * CK::a[5][4], (double)u[m], (double)ps[0][m]);
-          if constexpr (!LEAN) so.s[2][m] = (T)fma(dt * (CK::b5[4] - CK::b4[4]), (double)u[m], (double)ps[NPS - 1][m]);
-        }
       } else {
-        // x_{n+1} = x_n + (X + dt b5_6 k_6);  error E + dt (b5_6 - b4_6) k_6
+        double err[3];
+        advance<S, MIXED, NNN, REC>(u, xq, vq, pk, ps, dt, so, err);
+        if constexpr (LAST)
 #pragma unroll
-        for (int m = 0; m < 3; m++) {
-          so.y[m] = xq[m] + fma(dt * CK::b5[5], (double)u[m], (double)ps[0][m]);
-          double es = (double)ps[NPS - 1][m];
-          if constexpr (LEAN) es = fma(CK::e[4] / CK::a[5][4], vq[m], es);
-          const double e = fma(dt * (CK::b5[5] - CK::b4[5]), (double)u[m], es);
-          const double err = tile_ok ? fabs(e) : 0.0;
-          acc_lam = (err > acc_lam || err != err) ? err : acc_lam;
-        }
+          for (int m = 0; m < 3; m++) acc.error(tile_ok ? err[m] : 0.0);
       }
     }
     load_point(p);  // output node of the next plane step
@@ -1034,61 +762,20 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
   }
 
   // ---- workgroup reductions -> partial records -----------------------------------------
-  const int wave = tid >> 6, lane = tid & 63;
-  if (STAGE1) {
-    const double acc_xi = sqrt(xi_F2) / xi_B2;
-    const double e = wave_sum(acc_E), r2 = wave_sum(acc_R2), xi = wave_max(acc_xi), mn = wave_min(acc_min),
-                 nl = wave_sum(acc_null), cc = wave_sum(acc_conc);
-    if (lane == 0) {
-      red[wave][0] = e;
-      red[wave][1] = r2;
-      red[wave][2] = xi;
-      red[wave][3] = mn;
-      red[wave][4] = nl;
-      red[wave][5] = cc;
-    }
-    __syncthreads();
-    if (tid == 0) {
-      double E = 0, R = 0, X = 0, M = INFINITY, Z = 0, Cc = 0;
-      for (int w = 0; w < NTHREADS / 64; w++) {
-        E += red[w][0];
-        R += red[w][1];
-        X = (red[w][2] > X || red[w][2] != red[w][2]) ? red[w][2] : X;
-        M = (red[w][3] < M || red[w][3] != red[w][3]) ? red[w][3] : M;
-        Z += red[w][4];
-        Cc += red[w][5];
-      }
-      double* pp = a.part + (long long)blockIdx.x * NPART;
-      pp[0] = E;
-      pp[1] = R;
-      pp[2] = X;
-      pp[3] = M;
-      pp[4] = Z;
-      pp[5] = Cc;
-    }
-  }
-  if (LAST) {
-    const double l = wave_max(acc_lam);
-    if (lane == 0) red[wave][5] = l;
-    __syncthreads();
-    if (tid == 0) {
-      double L = 0;
-      for (int w = 0; w < NTHREADS / 64; w++) L = (red[w][5] > L || red[w][5] != red[w][5]) ? red[w][5] : L;
-      a.lam_part[blockIdx.x] = L;
-    }
-  }
+  if (STAGE1) store_sums<NTHREADS>(acc, red, a.part + (long long)blockIdx.x * NPART);
+  if (LAST) store_lambda<NTHREADS>(acc, red, a.lam_part + blockIdx.x);
 }
 
 template <bool MIXED, bool NNN = false>
 hipError_t launch_stage_t(int s, const SweepArgs& a, hipStream_t st) {
   const dim3 grid(a.g.nblocks), block(NTHREADS);
   switch (s) {
-    case 1: hipLaunchKernelGGL((stage_kernel<1, MIXED, false, false, NNN>), grid, block, 0, st, a); break;
-    case 2: hipLaunchKernelGGL((stage_kernel<2, MIXED, false, false, NNN>), grid, block, 0, st, a); break;
-    case 3: hipLaunchKernelGGL((stage_kernel<3, MIXED, false, false, NNN>), grid, block, 0, st, a); break;
-    case 4: hipLaunchKernelGGL((stage_kernel<4, MIXED, false, false, NNN>), grid, block, 0, st, a); break;
-    case 5: hipLaunchKernelGGL((stage_kernel<5, MIXED, false, false, NNN>), grid, block, 0, st, a); break;
-    case 6: hipLaunchKernelGGL((stage_kernel<6, MIXED, false, false, NNN>), grid, block, 0, st, a); break;
+    case 1: hipLaunchKernelGGL((stage_kernel<1, MIXED, NNN>), grid, block, 0, st, a); break;
+    case 2: hipLaunchKernelGGL((stage_kernel<2, MIXED, NNN>), grid, block, 0, st, a); break;
+    case 3: hipLaunchKernelGGL((stage_kernel<3, MIXED, NNN>), grid, block, 0, st, a); break;
+    case 4: hipLaunchKernelGGL((stage_kernel<4, MIXED, NNN>), grid, block, 0, st, a); break;
+    case 5: hipLaunchKernelGGL((stage_kernel<5, MIXED, NNN>), grid, block, 0, st, a); break;
+    case 6: hipLaunchKernelGGL((stage_kernel<6, MIXED, NNN>), grid, block, 0, st, a); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
@@ -1097,6 +784,7 @@ hipError_t launch_stage_t(int s, const SweepArgs& a, hipStream_t st) {
 }  // namespace
 
 hipError_t launch_stage(int s, bool mixed, const SweepArgs& a, hipStream_t st) {
+  if (a.g.brick[0]) return launch_brick(s, mixed, a, st);
   if (a.g.curl == CURL_NNN) return mixed ? hipErrorInvalidValue : launch_stage_t<false, true>(s, a, st);
   return mixed ? launch_stage_t<true>(s, a, st) : launch_stage_t<false>(s, a, st);
 }
@@ -1104,22 +792,24 @@ hipError_t launch_stage(int s, bool mixed, const SweepArgs& a, hipStream_t st) {
 // the forward replay of the reverse pass (FP64): stages 4 and 6 also store their input
 hipError_t launch_stage_rec(int s, const SweepArgs& a, hipStream_t st) {
   if (a.g.curl == CURL_NNN) return hipErrorInvalidValue;
+  if (a.g.brick[0]) return launch_brick_rec(s, a, st);
   const dim3 grid(a.g.nblocks), block(NTHREADS);
   if (s == 4)
-    hipLaunchKernelGGL((stage_kernel<4, false, false, true>), grid, block, 0, st, a);
+    hipLaunchKernelGGL((stage_kernel<4, false, false, false, true>), grid, block, 0, st, a);
   else if (s == 6)
-    hipLaunchKernelGGL((stage_kernel<6, false, false, true>), grid, block, 0, st, a);
+    hipLaunchKernelGGL((stage_kernel<6, false, false, false, true>), grid, block, 0, st, a);
   else
     return launch_stage_t<false>(s, a, st);
   return hipGetLastError();
 }
 
 hipError_t launch_diagnostics(const SweepArgs& a, hipStream_t st) {
+  if (a.g.brick[0]) return launch_brick_diagnostics(a, st);
   const dim3 grid(a.g.nblocks), block(NTHREADS);
   if (a.g.curl == CURL_NNN)
-    hipLaunchKernelGGL((stage_kernel<1, false, true, false, true>), grid, block, 0, st, a);
+    hipLaunchKernelGGL((stage_kernel<1, false, true, true>), grid, block, 0, st, a);
   else
-    hipLaunchKernelGGL((stage_kernel<1, false, true, false, false>), grid, block, 0, st, a);
+    hipLaunchKernelGGL((stage_kernel<1, false, false, true>), grid, block, 0, st, a);
   return hipGetLastError();
 }
 

@@ -250,7 +250,7 @@ __global__ __launch_bounds__(BRICK_THREADS) __attribute__((amdgpu_waves_per_eu(N
           F[m][2] = ys[m][o + sxy] - ys[m][o - sxy];
         }
       }
-      const double D = det3(F);
+      const double D = (NNN || MIXED) ? det3(F) : det3_fused(F);
       const double rD = fok[r] ? rcp_nr(D) : 0.0;
       T q0 = b0r[r][0], q1 = b0r[r][1], q2 = b0r[r][2];
       if constexpr (DIAG) {
@@ -342,15 +342,14 @@ __global__ __launch_bounds__(BRICK_THREADS) __attribute__((amdgpu_waves_per_eu(N
         const double JB = (double)J[0] * Bq[0] + (double)J[1] * Bq[1] + (double)J[2] * Bq[2];
         so.p[2][0] = B2 > 0.0 ? JB / B2 : 0.0;
       }
-      const T f0 = J[1] * Bq[2] - J[2] * Bq[1];
-      const T f1 = J[2] * Bq[0] - J[0] * Bq[2];
-      const T f2 = J[0] * Bq[1] - J[1] * Bq[0];
+      T f[3];
+      force<NNN>(J, Bq, f);
       const T gm = (T)gamma;
-      u[0] = gm * f0;
-      u[1] = gm * f1;
-      u[2] = gm * f2;
+      u[0] = gm * f[0];
+      u[1] = gm * f[1];
+      u[2] = gm * f[2];
       if constexpr (STAGE1) {
-        const double F2 = (double)f0 * f0 + (double)f1 * f1 + (double)f2 * f2;
+        const double F2 = (double)f[0] * f[0] + (double)f[1] * f[1] + (double)f[2] * f[2];
         const double B2 = (double)Bq[0] * Bq[0] + (double)Bq[1] * Bq[1] + (double)Bq[2] * Bq[2];
         acc.force(F2, B2, Dq, tau_B2);
       }

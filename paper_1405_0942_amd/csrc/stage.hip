@@ -100,6 +100,10 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
   using St = Stage<S, MIXED, NNN>;
   constexpr bool LEAN = St::LEAN, WV = St::WV, CX = St::CX, CV = St::CV, PS = St::PS;
   constexpr int NPK = St::NPK, NPKA = St::NPKA, NPS = St::NPS;
+  // Plane steps between a load and its use.  Stage 1 has the registers for two sets: 256^3 270 -> 260
+  // us (FP64), 250 -> 236 us (mixed).  The other stages gain at most 1 % from a second set at 256^3 and
+  // lose 2 to 5 % on grids with short chunks (an extra step and a longer prologue).
+  constexpr int PD = (S == 1 && !NNN && !DIAG) ? 2 : 1;
   constexpr int NP2 = (RY2 * RX2 + NTHREADS - 1) / NTHREADS;  // stage-input points per thread
   constexpr int NP1 = (RY1 * RX1 + NTHREADS - 1) / NTHREADS;  // field points per thread
   static_assert(!DIAG || (S == 1 && !MIXED), "the diagnostics sweep is the FP64 stage-1 sweep");
@@ -268,9 +272,11 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
   const bool face_y = bcy == BC_LINE_TIED && (gj_t == 0 || gj_t == ny - 1);
 
   // ---- loads of one plane, issued one plane step ahead of their use -------------------------
-  T b0r[NP1][3];        // B0'' at the field points
-  T pk[NPKA][3];        // k_j at the output node (stages 3, 4)
-  T ps[NPS][3];         // stage 5: P6 (and E, not lean); stage 6: X, E at the output node
+  struct Nodes {
+    T b0[NP1][3];   // B0'' at the field points
+    T pk[NPKA][3];  // k_j (or C4) at the output node (stages 3, 4)
+    T ps[NPS][3];   // stage 5: P6 (and E, not lean); stage 6: X, E at the output node
+  };
   struct Window {
     double x[NP2][3];      // window base (x_n, y_3 or y_5)
     T v[WV ? NP2 : 1][3];  // the window vector
@@ -403,16 +409,16 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
       }
     }
   };
-  auto load_b0 = [&](int pz) {
+  auto load_b0 = [&](Nodes& nd, int pz) {
     const long long zo = (long long)zload(pz) * nxy;
 #pragma unroll
     for (int m = 0; m < 3; m++) {
       const auto rs = plane_rsrc(b0p + m * N + zo, nxy);
 #pragma unroll
-      for (int r = 0; r < NP1; r++) b0r[r][m] = bload<T>(rs, f1e[r]);
+      for (int r = 0; r < NP1; r++) nd.b0[r][m] = bload<T>(rs, f1e[r]);
     }
   };
-  auto load_point = [&](int pz) {
+  auto load_point = [&](Nodes& nd, int pz) {
     const long long zo = (long long)zload(pz) * nxy;
     const unsigned eo = (pz >= z0 && pz < z1) ? out_e : IE;
     if constexpr (NPK > 0) {
@@ -420,16 +426,16 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
       for (int j = 0; j < NPK; j++) {
         const T* kj = static_cast<const T*>(a.k[LEAN ? (S == 3 ? 1 : 2 * j) : j]);
 #pragma unroll
-        for (int m = 0; m < 3; m++) pk[j][m] = bload<T, CPOL_STREAM>(plane_rsrc(kj + m * N + zo, nxy), eo);
+        for (int m = 0; m < 3; m++) nd.pk[j][m] = bload<T, CPOL_STREAM>(plane_rsrc(kj + m * N + zo, nxy), eo);
       }
     }
     if constexpr (PS) {
       const T* s0 = static_cast<const T*>(S == 5 ? a.sum[0] : a.sum[1]);
       const T* s1 = static_cast<const T*>(a.sum[2]);
 #pragma unroll
-      for (int m = 0; m < 3; m++) ps[0][m] = bload<T, CPOL_STREAM>(plane_rsrc(s0 + m * N + zo, nxy), eo);
+      for (int m = 0; m < 3; m++) nd.ps[0][m] = bload<T, CPOL_STREAM>(plane_rsrc(s0 + m * N + zo, nxy), eo);
 #pragma unroll
-      for (int m = 0; m < 3 && NPS == 2; m++) ps[NPS - 1][m] = bload<T, CPOL_STREAM>(plane_rsrc(s1 + m * N + zo, nxy), eo);
+      for (int m = 0; m < 3 && NPS == 2; m++) nd.ps[NPS - 1][m] = bload<T, CPOL_STREAM>(plane_rsrc(s1 + m * N + zo, nxy), eo);
     }
   };
 
@@ -513,8 +519,9 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
     }
   };
 
-  Window win;
-  auto commit_next = [&](int p) {
+  Window win[PD];
+  Nodes nodes[PD];
+  auto commit_next = [&](const Window& win, int p) {
     commit_window(win, p + 2);  // past the chunk's last plane: zeros that nothing reads
     if (!perz && p + 2 == nz) commit_ghost_plane(nz, nz - 1, nz - 2, nz - 3);
     carry(win);
@@ -524,20 +531,20 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
   {
     const bool low = !perz && pb0 == 0;  // the plane below is a ghost plane
     const int lo = low ? 0 : pb0 - 1;
-    Window w1, w2;
-    load_window(win, lo, true);
+    Window w0, w1, w2;
+    load_window(w0, lo, true);
     load_window(w1, lo + 1, true);
     load_window(w2, lo + 2, true);
-    commit_window(win, lo);
+    commit_window(w0, lo);
     commit_window(w1, lo + 1);
     commit_window(w2, lo + 2);
     if (low) {  // plane 2 stays in the ring and is committed again by the first plane step
       commit_ghost_plane(-1, 0, 1, 2);
-      carry(win);
-      carry(win);
+      carry(w0);
+      carry(w0);
       carry(w1);
     } else {
-      carry(win);
+      carry(w0);
       carry(w1);
       carry(w2);
     }
@@ -545,10 +552,15 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
   __syncthreads();
   fill_ghosts(pb0);
   // leave the same loads and (dropped) stores in flight, in the same order, as a plane step
-  load_b0(pb0);
-  load_point(pb0 - 1);
-  store_plane(Outputs{}, pb0 - 1, false);
-  load_window(win, pb0 + 2, true);
+#pragma unroll
+  for (int d = 0; d < PD; d++) {
+    if constexpr (!NNN) load_window(win[d], pb0 + d + 2, pb0 + d + 2 <= pb1 + 1);
+    load_b0(nodes[d], min(pb0 + d, pb1));
+    load_point(nodes[d], pb0 + d - 1);
+    store_plane(Outputs{}, pb0 + d - 1, false);
+    if constexpr (NNN) load_window(win[d], pb0 + d + 2, pb0 + d + 2 <= pb1 + 1);
+    __builtin_amdgcn_sched_barrier(0);
+  }
   __syncthreads();
 
   // own-node values carried between plane steps: B at q - 1 and q; at q: F', 1 / det F', det F
@@ -558,10 +570,25 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
   double Dq = 0.0;
   int kap_q = 1;  // DIAG: convexity
 
-  for (int p = pb0; p <= z1; p++) {
+  auto step = [&](int p, Nodes& nd, Window& win) {
     const int q = p - 1;
     const bool qout = (q >= z0 && q < z1);
     fill_ghosts(p + 1);
+    // own-node values of plane q
+    double xq[3] = {0.0, 0.0, 0.0};
+    T vq[3] = {T(0), T(0), T(0)};
+#pragma unroll
+    for (int m = 0; m < 3; m++) {
+      if constexpr (CX) xq[m] = cx[0][m];
+      if constexpr (CV) vq[m] = cvv[0][m];
+    }
+    // 0. commit the plane the next field needs and load the one after it.  First, so that the window
+    // loads go out while the field is computed, and not in one burst with the stores at the end of the
+    // step (256^3, stage 3: 375 -> 354 us, stage 5: 312 -> 285)
+    if constexpr (!NNN) {
+      commit_next(win, p);
+      load_window(win, p + PD + 2, p + PD + 2 <= pb1 + 1);
+    }
     // 1. F', det F' and B of field point R of plane p; off the grid B = 0
     T Bp[3], Fp[3][3], rDp;
     double Dp;
@@ -585,9 +612,9 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
           F[m][2] = ys[sh][m][o] - ys[sl][m][o];
         }
       }
-      const double D = det3(F);
+      const double D = (NNN || MIXED) ? det3(F) : det3_fused(F);
       const double rD = ok ? rcp_nr(D) : 0.0;
-      T q0 = b0r[R][0], q1 = b0r[R][1], q2 = b0r[R][2];
+      T q0 = nd.b0[R][0], q1 = nd.b0[R][1], q2 = nd.b0[R][2];
       if constexpr (DIAG) {
         q0 *= a.b0_mul[0];
         q1 *= a.b0_mul[1];
@@ -654,20 +681,12 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
       if (f1o[1] >= 0) field(HaloPoint{});
       field(OwnNode{});
     }
-    load_b0(p + 1 <= pb1 ? p + 1 : pb1);
-    // own-node values of plane q
-    double xq[3] = {0.0, 0.0, 0.0};
-    T vq[3] = {T(0), T(0), T(0)};
-#pragma unroll
-    for (int m = 0; m < 3; m++) {
-      if constexpr (CX) xq[m] = cx[0][m];
-      if constexpr (CV) vq[m] = cvv[0][m];
-    }
+    load_b0(nd, min(p + PD, pb1));
     // the octilateral walk needs many registers: the window is committed before it and loaded
     // after it, so that no window value is live across it
     if constexpr (NNN) {
       __syncthreads();
-      commit_next(p);
+      commit_next(win, p);
     }
 
     // 2. current, force and velocity on the tile of plane q = p - 1
@@ -713,15 +732,14 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
           const double JB = (double)J[0] * Bq[0] + (double)J[1] * Bq[1] + (double)J[2] * Bq[2];
           so.p[2][0] = (B2 > 0.0 && !face) ? JB / B2 : 0.0;
         }
-        const T f0 = J[1] * Bq[2] - J[2] * Bq[1];
-        const T f1 = J[2] * Bq[0] - J[0] * Bq[2];
-        const T f2 = J[0] * Bq[1] - J[1] * Bq[0];
+        T f[3];
+        force<NNN>(J, Bq, f);
         const T gm = (T)gamma;
-        u[0] = face ? T(0) : gm * f0;
-        u[1] = face ? T(0) : gm * f1;
-        u[2] = face ? T(0) : gm * f2;
+        u[0] = face ? T(0) : gm * f[0];
+        u[1] = face ? T(0) : gm * f[1];
+        u[2] = face ? T(0) : gm * f[2];
         if (STAGE1 && tile_ok && !face) {
-          const double F2 = (double)f0 * f0 + (double)f1 * f1 + (double)f2 * f2;
+          const double F2 = (double)f[0] * f[0] + (double)f[1] * f[1] + (double)f[2] * f[2];
           const double B2 = (double)Bq[0] * Bq[0] + (double)Bq[1] * Bq[1] + (double)Bq[2] * Bq[2];
           acc.force(F2, B2, Dq, tau_B2);
         }
@@ -735,18 +753,16 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
         }
       } else {
         double err[3];
-        advance<S, MIXED, NNN, REC>(u, xq, vq, pk, ps, dt, so, err);
+        advance<S, MIXED, NNN, REC>(u, xq, vq, nd.pk, nd.ps, dt, so, err);
         if constexpr (LAST)
 #pragma unroll
           for (int m = 0; m < 3; m++) acc.error(tile_ok ? err[m] : 0.0);
       }
     }
-    load_point(p);  // output node of the next plane step
+    load_point(nd, p + PD - 1);  // output node of the plane step that uses this set next
     store_plane(so, q, qout, kap_q);
 
-    // 3. commit the stage-input plane of the next field; load the one after it
-    if constexpr (!NNN) commit_next(p);
-    load_window(win, p + 3, p + 3 <= pb1 + 1);
+    if constexpr (NNN) load_window(win, p + PD + 2, p + PD + 2 <= pb1 + 1);
     __syncthreads();
 
 #pragma unroll
@@ -759,6 +775,11 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
     rDq = rDp;
     Dq = Dp;
     kap_q = kap_p;
+  };
+  // with two sets, the last step may be one past z1: it writes nothing
+  for (int p = pb0; p <= z1; p += PD) {
+    step(p, nodes[0], win[0]);
+    if constexpr (PD == 2) step(p + 1, nodes[PD - 1], win[PD - 1]);
   }
 
   // ---- workgroup reductions -> partial records -----------------------------------------

@@ -170,11 +170,38 @@ __device__ __forceinline__ void octilateral(Pos pos, Field field, double J[3]) {
   }
 }
 
-// J = F' c' / det F' from the differences G'[a][m] = B_m(n + e_a) - B_m(n - e_a)
-template <typename T>
-__device__ __forceinline__ void current(const T F[3][3], const T G[3][3], T rD, T J[3]) {
-  // c'_q = (F' e_b) . G'_a - (F' e_a) . G'_b, (a, b, q) = (y, z, x), (z, x, y), (x, y, z)
-  T cq[3];
+// The products of the FP64 nearest-neighbour path with every fused multiply-add written out: left to
+// the compiler, the same expression may be fused in different orders in the march and in the bricks,
+// and a node's result would then depend on the sweep in its last bit.
+__device__ __forceinline__ double dot3(double a0, double b0, double a1, double b1, double a2, double b2) {
+  return fma(a2, b2, fma(a0, b0, a1 * b1));
+}
+__device__ __forceinline__ double minor2(double a, double b, double c, double d) {  // a b - c d
+  const double cd = c * d;
+  return fma(a, b, -cd);
+}
+__device__ __forceinline__ double det3_fused(const double F[3][3]) {
+  const double s = F[0][1] * minor2(F[1][0], F[2][2], F[1][2], F[2][0]);
+  return fma(F[0][2], minor2(F[1][0], F[2][1], F[1][1], F[2][0]),
+             fma(F[0][0], minor2(F[1][1], F[2][2], F[1][2], F[2][1]), -s));
+}
+
+// J = F' c' / det F' from the differences G'[a][m] = B_m(n + e_a) - B_m(n - e_a), with
+// c'_q = (F' e_b) . G'_a - (F' e_a) . G'_b, (a, b, q) = (y, z, x), (z, x, y), (x, y, z)
+__device__ __forceinline__ void current(const double F[3][3], const double G[3][3], double rD, double J[3]) {
+#pragma clang fp contract(off)
+  double cq[3];
+#pragma unroll
+  for (int q = 0; q < 3; q++) {
+    const int a = (q + 1) % 3, b = (q + 2) % 3;
+    cq[q] = dot3(F[0][b], G[a][0], F[1][b], G[a][1], F[2][b], G[a][2]) -
+            dot3(F[0][a], G[b][0], F[1][a], G[b][1], F[2][a], G[b][2]);
+  }
+#pragma unroll
+  for (int m = 0; m < 3; m++) J[m] = dot3(F[m][0], cq[0], F[m][1], cq[1], F[m][2], cq[2]) * rD;
+}
+__device__ __forceinline__ void current(const float F[3][3], const float G[3][3], float rD, float J[3]) {
+  float cq[3];
   cq[0] = F[0][2] * G[1][0] + F[1][2] * G[1][1] + F[2][2] * G[1][2] -
           (F[0][1] * G[2][0] + F[1][1] * G[2][1] + F[2][1] * G[2][2]);
   cq[1] = F[0][0] * G[2][0] + F[1][0] * G[2][1] + F[2][0] * G[2][2] -
@@ -183,6 +210,19 @@ __device__ __forceinline__ void current(const T F[3][3], const T G[3][3], T rD, 
           (F[0][0] * G[1][0] + F[1][0] * G[1][1] + F[2][0] * G[1][2]);
 #pragma unroll
   for (int m = 0; m < 3; m++) J[m] = (F[m][0] * cq[0] + F[m][1] * cq[1] + F[m][2] * cq[2]) * rD;
+}
+
+// f = J x B
+template <bool NNN, typename T>
+__device__ __forceinline__ void force(const T J[3], const T B[3], T f[3]) {
+#pragma unroll
+  for (int m = 0; m < 3; m++) {
+    const int a = (m + 1) % 3, b = (m + 2) % 3;
+    if constexpr (!NNN && sizeof(T) == 8)
+      f[m] = minor2(J[a], B[b], J[b], B[a]);
+    else
+      f[m] = J[a] * B[b] - J[b] * B[a];
+  }
 }
 
 // B = F' B0'' / det F'
@@ -195,7 +235,7 @@ __device__ __forceinline__ void pull_back(const double F[3][3], T q0, T q1, T q2
       B[m] = ((float)F[m][0] * q0 + (float)F[m][1] * q1 + (float)F[m][2] * q2) * fi;
   } else {
 #pragma unroll
-    for (int m = 0; m < 3; m++) B[m] = (F[m][0] * q0 + F[m][1] * q1 + F[m][2] * q2) * rD;
+    for (int m = 0; m < 3; m++) B[m] = dot3(F[m][0], q0, F[m][1], q1, F[m][2], q2) * rD;
   }
 }
 

@@ -36,7 +36,7 @@
 // transposed in-plane as soon as it is formed; buffer loads with masked-off lanes (offsets
 // past the record count) issued one plane step ahead, so no divergent branch surrounds a
 // memory instruction and the waits are exact.
-#include "sweep_common.h"
+#include "brick.h"
 
 namespace relax {
 namespace {
@@ -45,6 +45,111 @@ __device__ __forceinline__ void cross(const double a[3], const double b[3], doub
   o[0] = a[1] * b[2] - a[2] * b[1];
   o[1] = a[2] * b[0] - a[0] * b[2];
   o[2] = a[0] * b[1] - a[1] * b[0];
+}
+
+// B and the cotangents Gbar'_a = cotangent of G'_a (a = x, y, z) at a node from F', 1 / det F', B0'' and
+// the cotangent ub of u (0 on line-tied faces)
+__device__ __forceinline__ void transpose_field(const double F[3][3], double rD, const double b0[3], const double ub[3],
+                                                double gamma, double B[3], double Gx[3], double Gy[3], double Gz[3]) {
+#pragma unroll
+  for (int m = 0; m < 3; m++) B[m] = (F[m][0] * b0[0] + F[m][1] * b0[1] + F[m][2] * b0[2]) * rD;
+  const double fb[3] = {gamma * ub[0], gamma * ub[1], gamma * ub[2]};
+  double Jb[3];
+  cross(B, fb, Jb);
+  double cb[3];  // cbar' = rD F'^T Jbar
+#pragma unroll
+  for (int n = 0; n < 3; n++) cb[n] = rD * (F[0][n] * Jb[0] + F[1][n] * Jb[1] + F[2][n] * Jb[2]);
+#pragma unroll
+  for (int m = 0; m < 3; m++) {
+    Gx[m] = cb[2] * F[m][1] - cb[1] * F[m][2];
+    Gy[m] = cb[0] * F[m][2] - cb[2] * F[m][0];
+    Gz[m] = cb[1] * F[m][0] - cb[0] * F[m][1];
+  }
+}
+
+// The transpose at one node: Fbar' (row-major) and the cotangent of B0'', from F', rD = 1 / det F', B,
+// the cotangent ub of u, B0'', the differences G[a][m] of B (0 on line-tied faces, where J = 0), and
+// Bt = the transpose of G'.  zeta: the energy weight of the node (SEED).
+template <bool SEED>
+__device__ __forceinline__ void transpose_node(const double F[3][3], double rD, const double B[3], const double ub[3],
+                                               const double b0[3], const double G[3][3], const double Bt[3],
+                                               bool interior, double zeta, const AdjArgs& a, double Fbar[9],
+                                               double dB0[3]) {
+  double Bb[3] = {0, 0, 0};
+  double Fb[3][3] = {{0, 0, 0}, {0, 0, 0}, {0, 0, 0}};
+  double rDb = 0.0, Db_direct = 0.0;
+  if (interior) {
+    double cq[3];
+    cq[0] = F[0][2] * G[1][0] + F[1][2] * G[1][1] + F[2][2] * G[1][2] -
+            (F[0][1] * G[2][0] + F[1][1] * G[2][1] + F[2][1] * G[2][2]);
+    cq[1] = F[0][0] * G[2][0] + F[1][0] * G[2][1] + F[2][0] * G[2][2] -
+            (F[0][2] * G[0][0] + F[1][2] * G[0][1] + F[2][2] * G[0][2]);
+    cq[2] = F[0][1] * G[0][0] + F[1][1] * G[0][1] + F[2][1] * G[0][2] -
+            (F[0][0] * G[1][0] + F[1][0] * G[1][1] + F[2][0] * G[1][2]);
+    const double w[3] = {cq[0] * rD, cq[1] * rD, cq[2] * rD};
+    double J[3];
+#pragma unroll
+    for (int m = 0; m < 3; m++) J[m] = F[m][0] * w[0] + F[m][1] * w[1] + F[m][2] * w[2];
+    const double fb[3] = {a.gamma * ub[0], a.gamma * ub[1], a.gamma * ub[2]};
+    double Jb[3], t3[3];
+    cross(B, fb, Jb);
+    cross(fb, J, t3);
+#pragma unroll
+    for (int m = 0; m < 3; m++) Bb[m] += t3[m];
+    double wb[3];
+#pragma unroll
+    for (int n = 0; n < 3; n++) wb[n] = F[0][n] * Jb[0] + F[1][n] * Jb[1] + F[2][n] * Jb[2];
+#pragma unroll
+    for (int m = 0; m < 3; m++)
+#pragma unroll
+      for (int n = 0; n < 3; n++) Fb[m][n] += Jb[m] * w[n];
+    const double cb[3] = {wb[0] * rD, wb[1] * rD, wb[2] * rD};
+    rDb += wb[0] * cq[0] + wb[1] * cq[1] + wb[2] * cq[2];
+    // c'_q = F'_b . G'_a - F'_a . G'_b for (a, b, q) = (1, 2, 0), (2, 0, 1), (0, 1, 2)
+#pragma unroll
+    for (int m = 0; m < 3; m++) {
+      Fb[m][2] += cb[0] * G[1][m];
+      Fb[m][1] -= cb[0] * G[2][m];
+      Fb[m][0] += cb[1] * G[2][m];
+      Fb[m][2] -= cb[1] * G[0][m];
+      Fb[m][1] += cb[2] * G[0][m];
+      Fb[m][0] -= cb[2] * G[1][m];
+    }
+    if constexpr (SEED) {
+      double f[3];
+      cross(J, B, f);
+      Db_direct += a.seed_R2 * 0.5 * a.g.dV * a.g.inv8h3 * (f[0] * f[0] + f[1] * f[1] + f[2] * f[2]);
+    }
+  }
+#pragma unroll
+  for (int m = 0; m < 3; m++) Bb[m] += Bt[m];
+  if constexpr (SEED) {
+    const double kappa = a.seed_EM * zeta * a.g.dV * a.g.inv8h3;
+    const double D = 1.0 / rD;
+#pragma unroll
+    for (int m = 0; m < 3; m++) Bb[m] += kappa * D * B[m];
+    Db_direct += 0.5 * kappa * (B[0] * B[0] + B[1] * B[1] + B[2] * B[2]);
+  }
+  // pull-back B = F' B0'' rD
+  double v[3];
+#pragma unroll
+  for (int m = 0; m < 3; m++) v[m] = F[m][0] * b0[0] + F[m][1] * b0[1] + F[m][2] * b0[2];
+  rDb += Bb[0] * v[0] + Bb[1] * v[1] + Bb[2] * v[2];
+#pragma unroll
+  for (int m = 0; m < 3; m++)
+#pragma unroll
+    for (int n = 0; n < 3; n++) Fb[m][n] += rD * Bb[m] * b0[n];
+#pragma unroll
+  for (int n = 0; n < 3; n++) dB0[n] = rD * (F[0][n] * Bb[0] + F[1][n] * Bb[1] + F[2][n] * Bb[2]);
+  // det: Dbar' cof(F')
+  const double Db = -rD * rD * rDb + Db_direct;
+#pragma unroll
+  for (int m = 0; m < 3; m++)
+#pragma unroll
+    for (int n = 0; n < 3; n++) {
+      const int m1 = (m + 1) % 3, m2 = (m + 2) % 3, n1 = (n + 1) % 3, n2 = (n + 2) % 3;
+      Fbar[3 * m + n] = Fb[m][n] + Db * (F[m1][n1] * F[m2][n2] - F[m1][n2] * F[m2][n1]);
+    }
 }
 
 template <int S, bool XYP, bool SEED>
@@ -300,25 +405,10 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
             double F[3][3];
             jacobian(r1 + 1, c1 + 1, p, gi, gj, F);
             const double rD = rcp_nr(det3(F));
-            const double q0 = b0r[r][0], q1 = b0r[r][1], q2 = b0r[r][2];
+            const bool live = !face_at(gi, gj, p);
 #pragma unroll
-            for (int m = 0; m < 3; m++) B[m] = (F[m][0] * q0 + F[m][1] * q1 + F[m][2] * q2) * rD;
-            if (!face_at(gi, gj, p)) {
-#pragma unroll
-              for (int m = 0; m < 3; m++) ub[m] = cv * vr[r][m];
-              const double fb[3] = {gamma * ub[0], gamma * ub[1], gamma * ub[2]};
-              double Jb[3];
-              cross(B, fb, Jb);
-              double cb[3];  // cbar' = rD F'^T Jbar
-#pragma unroll
-              for (int n2 = 0; n2 < 3; n2++) cb[n2] = rD * (F[0][n2] * Jb[0] + F[1][n2] * Jb[1] + F[2][n2] * Jb[2]);
-#pragma unroll
-              for (int m = 0; m < 3; m++) {
-                Gx[m] = cb[2] * F[m][1] - cb[1] * F[m][2];
-                Gy[m] = cb[0] * F[m][2] - cb[2] * F[m][0];
-                Gz[m] = cb[1] * F[m][0] - cb[0] * F[m][1];
-              }
-            }
+            for (int m = 0; m < 3; m++) ub[m] = live ? cv * vr[r][m] : 0.0;
+            transpose_field(F, rD, b0r[r], ub, gamma, B, Gx, Gy, Gz);
             if (r == 0) {
 #pragma unroll
               for (int m = 0; m < 3; m++) {
@@ -368,101 +458,29 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
     // 4. the transpose at the own node of plane q
     if (qout) {
       const bool interior = !face_at(gi_t, gj_t, q);
-      double Bb[3] = {0, 0, 0};
-      double Fb[3][3] = {{0, 0, 0}, {0, 0, 0}, {0, 0, 0}};
-      double rDb = 0.0, Db_direct = 0.0;
+      double G[3][3] = {};  // G[a][m]
       if (interior) {
         const int sq = q & 1;
-        double G[3][3];  // G[a][m]
 #pragma unroll
         for (int m = 0; m < 3; m++) {
           G[0][m] = bs[sq][m][ot + 1] - bs[sq][m][ot - 1];
           G[1][m] = bs[sq][m][ot + RX1] - bs[sq][m][ot - RX1];
           G[2][m] = Bp[m] - Bqm[m];
         }
-        double cq[3];
-        cq[0] = F[0][2] * G[1][0] + F[1][2] * G[1][1] + F[2][2] * G[1][2] -
-                (F[0][1] * G[2][0] + F[1][1] * G[2][1] + F[2][1] * G[2][2]);
-        cq[1] = F[0][0] * G[2][0] + F[1][0] * G[2][1] + F[2][0] * G[2][2] -
-                (F[0][2] * G[0][0] + F[1][2] * G[0][1] + F[2][2] * G[0][2]);
-        cq[2] = F[0][1] * G[0][0] + F[1][1] * G[0][1] + F[2][1] * G[0][2] -
-                (F[0][0] * G[1][0] + F[1][0] * G[1][1] + F[2][0] * G[1][2]);
-        const double w[3] = {cq[0] * rDq, cq[1] * rDq, cq[2] * rDq};
-        double J[3];
-#pragma unroll
-        for (int m = 0; m < 3; m++) J[m] = F[m][0] * w[0] + F[m][1] * w[1] + F[m][2] * w[2];
-        const double fb[3] = {gamma * ubq[0], gamma * ubq[1], gamma * ubq[2]};
-        double Jb[3], t3[3];
-        cross(Bq, fb, Jb);
-        cross(fb, J, t3);
-#pragma unroll
-        for (int m = 0; m < 3; m++) Bb[m] += t3[m];
-        double wb[3];
-#pragma unroll
-        for (int n2 = 0; n2 < 3; n2++) wb[n2] = F[0][n2] * Jb[0] + F[1][n2] * Jb[1] + F[2][n2] * Jb[2];
-#pragma unroll
-        for (int m = 0; m < 3; m++)
-#pragma unroll
-          for (int n2 = 0; n2 < 3; n2++) Fb[m][n2] += Jb[m] * w[n2];
-        const double cb[3] = {wb[0] * rDq, wb[1] * rDq, wb[2] * rDq};
-        rDb += wb[0] * cq[0] + wb[1] * cq[1] + wb[2] * cq[2];
-        // c'_q = F'_b . G'_a - F'_a . G'_b for (a, b, q) = (1, 2, 0), (2, 0, 1), (0, 1, 2)
-#pragma unroll
-        for (int m = 0; m < 3; m++) {
-          Fb[m][2] += cb[0] * G[1][m];
-          Fb[m][1] -= cb[0] * G[2][m];
-          Fb[m][0] += cb[1] * G[2][m];
-          Fb[m][2] -= cb[1] * G[0][m];
-          Fb[m][1] += cb[2] * G[0][m];
-          Fb[m][0] -= cb[2] * G[1][m];
-        }
-        if constexpr (SEED) {
-          double f[3];
-          cross(J, Bq, f);
-          Db_direct += a.seed_R2 * 0.5 * g.dV * g.inv8h3 * (f[0] * f[0] + f[1] * f[1] + f[2] * f[2]);
-        }
       }
-      // transpose of G': Bbar(m) += sum_a Gbar'_a(m - e_a) - Gbar'_a(m + e_a)
+      double Bt[3];  // transpose of G': sum_a Gbar'_a(m - e_a) - Gbar'_a(m + e_a)
 #pragma unroll
-      for (int m = 0; m < 3; m++) Bb[m] += Bbxyq[m] + (gzqm[m] - gzp[m]);
+      for (int m = 0; m < 3; m++) Bt[m] = Bbxyq[m] + (gzqm[m] - gzp[m]);
+      double zeta = 1.0;
       if constexpr (SEED) {
-        double zeta = 1.0;
         if (bcx == BC_LINE_TIED && (gi_t == 0 || gi_t == nx - 1)) zeta *= 0.5;
         if (bcy == BC_LINE_TIED && (gj_t == 0 || gj_t == ny - 1)) zeta *= 0.5;
         if (bcz == BC_LINE_TIED && (q == 0 || q == nz - 1)) zeta *= 0.5;
-        const double kappa = a.seed_EM * zeta * g.dV * g.inv8h3;
-        const double Dp = 1.0 / rDq;
-#pragma unroll
-        for (int m = 0; m < 3; m++) Bb[m] += kappa * Dp * Bq[m];
-        Db_direct += 0.5 * kappa * (Bq[0] * Bq[0] + Bq[1] * Bq[1] + Bq[2] * Bq[2]);
       }
-      // pull-back B = F' B0'' rD
-      double v[3];
+      double dB[3];
+      transpose_node<SEED>(F, rDq, Bq, ubq, b0q, G, Bt, interior, zeta, a, so_F, dB);
 #pragma unroll
-      for (int m = 0; m < 3; m++) v[m] = F[m][0] * b0q[0] + F[m][1] * b0q[1] + F[m][2] * b0q[2];
-      rDb += Bb[0] * v[0] + Bb[1] * v[1] + Bb[2] * v[2];
-#pragma unroll
-      for (int m = 0; m < 3; m++)
-#pragma unroll
-        for (int n2 = 0; n2 < 3; n2++) Fb[m][n2] += rDq * Bb[m] * b0q[n2];
-#pragma unroll
-      for (int n2 = 0; n2 < 3; n2++) so_B[n2] = bbr[n2] + rDq * (F[0][n2] * Bb[0] + F[1][n2] * Bb[1] + F[2][n2] * Bb[2]);
-      // det: Dbar' cof(F')
-      const double Db = -rDq * rDq * rDb + Db_direct;
-      double cof[3][3];
-      cof[0][0] = F[1][1] * F[2][2] - F[1][2] * F[2][1];
-      cof[0][1] = F[1][2] * F[2][0] - F[1][0] * F[2][2];
-      cof[0][2] = F[1][0] * F[2][1] - F[1][1] * F[2][0];
-      cof[1][0] = F[0][2] * F[2][1] - F[0][1] * F[2][2];
-      cof[1][1] = F[0][0] * F[2][2] - F[0][2] * F[2][0];
-      cof[1][2] = F[0][1] * F[2][0] - F[0][0] * F[2][1];
-      cof[2][0] = F[0][1] * F[1][2] - F[0][2] * F[1][1];
-      cof[2][1] = F[0][2] * F[1][0] - F[0][0] * F[1][2];
-      cof[2][2] = F[0][0] * F[1][1] - F[0][1] * F[1][0];
-#pragma unroll
-      for (int m = 0; m < 3; m++)
-#pragma unroll
-        for (int n2 = 0; n2 < 3; n2++) so_F[3 * m + n2] = Fb[m][n2] + Db * cof[m][n2];
+      for (int m = 0; m < 3; m++) so_B[m] = bbr[m] + dB[m];
     }
     load_point(p);  // B0bar'' at the output node of the next plane step
     store_point(q, qout);
@@ -483,63 +501,219 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
   }
 }
 
+// The same for small grids, a brick of nodes per workgroup (see brick.hip): the stage input with its
+// 2-node halo, B and the three Gbar' on the brick and its 1-node halo, all planes at once, two or three
+// barriers.  LDS: up to 157 KB (Gbar' takes 72 bytes a field point), one workgroup per CU.  Up to
+// 600 000 nodes (make_adj_geometry): us per step of a backward pass, march / bricks: 16^3 714 / 145,
+// 33^3 846 / 173, 64^3 606 / 322, 81^3 line-tied 1034 / 703, 64 x 64 x 192 731 / 797, 128^3 1580 / 2187.
+constexpr int NPW = (ADJ_WINDOW + BRICK_THREADS - 1) / BRICK_THREADS;
+constexpr int NPF = 1 + (BRICK_SHELL + BRICK_THREADS - 1) / BRICK_THREADS;
+
+template <int S, bool SEED>
+__global__ __launch_bounds__(BRICK_THREADS) __attribute__((amdgpu_waves_per_eu(2))) void adj_brick_kernel(AdjArgs a) {
+  constexpr bool WK = (!SEED && S == 2);
+  const Geometry& g = a.g;
+  const long long N = g.N;
+  const Brick br(g);
+  const int lb = logical_block(blockIdx.x, g.nblocks);
+  const int i0 = (lb % g.tiles[0]) * br.bx;
+  const int j0 = ((lb / g.tiles[0]) % g.tiles[1]) * br.by;
+  const int k0 = (lb / (g.tiles[0] * g.tiles[1])) * br.bz;
+  const int tid = threadIdx.x;
+  const double dt = SEED ? 0.0 : *a.dt;
+  const double c21 = dt * CK::a[1][0];
+  const bool v_on = !SEED || a.useed != nullptr;
+  const double* __restrict__ vsrc = SEED ? (a.useed ? a.useed : a.B0) : (S == 6 ? a.xbar : a.ubar);
+  const double cv = v_on ? ((!SEED && S == 6) ? dt * CK::b5[5] : 1.0) : 0.0;
+  const double* __restrict__ wsrc = (SEED || S <= 2) ? a.x : a.y[S > 2 ? S - 3 : 0];
+
+  __shared__ double ys[3][ADJ_WINDOW];
+  __shared__ double bs[3][BRICK_FIELD];
+  __shared__ double gs[9][BRICK_FIELD];
+
+  // ---- all loads first
+  double wx[NPW][3], wk[WK ? NPW : 1][3];
+  BrickPoint wp[NPW];
+#pragma unroll
+  for (int r = 0; r < NPW; r++) {
+    wp[r] = brick_window(br, g, tid + r * BRICK_THREADS, i0, j0, k0);
+    const int i = wp[r].index;
+#pragma unroll
+    for (int m = 0; m < 3; m++) wx[r][m] = wsrc[m * N + i];
+    if constexpr (WK) {
+#pragma unroll
+      for (int m = 0; m < 3; m++) wk[r][m] = a.k[0][m * N + i];
+    }
+  }
+  double b0r[NPF][3], vr[NPF][3];
+  BrickField fp[NPF];
+#pragma unroll
+  for (int r = 0; r < NPF; r++) {
+    fp[r] = brick_field(br, g, r, tid, i0, j0, k0);
+#pragma unroll
+    for (int m = 0; m < 3; m++) {
+      b0r[r][m] = a.B0[m * N + fp[r].index];
+      vr[r][m] = vsrc[m * N + fp[r].index];
+    }
+  }
+  const bool node = fp[0].node();
+  const int own = fp[0].index;
+  double bbr[3];
+#pragma unroll
+  for (int m = 0; m < 3; m++) bbr[m] = a.B0bar[m * N + own];
+
+  // ---- stage input
+#pragma unroll
+  for (int r = 0; r < NPW; r++) {
+    const int e = tid + r * BRICK_THREADS;
+    if (e < br.nwin) {
+#pragma unroll
+      for (int m = 0; m < 3; m++) {
+        double y = wx[r][m];
+        if constexpr (WK) y = fma(c21, wk[r][m], y);
+        ys[m][e] = wp[r].on() ? y + wp[r].wrap(m) * g.period[m] : 0.0;
+      }
+    }
+  }
+  __syncthreads();
+  if (br.at_face(g, i0, j0, k0)) {
+#pragma unroll
+    for (int r = 0; r < NPW; r++) {
+      const int e = tid + r * BRICK_THREADS, s = wp[r].ghost;
+      if (s != 0) {
+#pragma unroll
+        for (int m = 0; m < 3; m++) ys[m][e] = fma(3.0, ys[m][e + s] - ys[m][e + 2 * s], ys[m][e + 3 * s]);
+      }
+    }
+    __syncthreads();
+  }
+
+  // ---- B and Gbar' on the brick and its 1-node halo
+  double Fq[3][3], Bq[3], ubq[3], rDq;
+#pragma unroll
+  for (int r = 0; r < NPF; r++) {
+    if (r == 0 || fp[r].slot >= 0) {
+      const int o = fp[r].window;
+      double F[3][3], B[3], Gx[3], Gy[3], Gz[3], ub[3];
+#pragma unroll
+      for (int m = 0; m < 3; m++) {
+        F[m][0] = ys[m][o + 1] - ys[m][o - 1];
+        F[m][1] = ys[m][o + br.sx] - ys[m][o - br.sx];
+        F[m][2] = ys[m][o + br.sxy] - ys[m][o - br.sxy];
+      }
+      const double rD = fp[r].on() ? rcp_nr(det3(F)) : 0.0;
+      const bool live = fp[r].on() && !fp[r].face();
+#pragma unroll
+      for (int m = 0; m < 3; m++) ub[m] = live ? cv * vr[r][m] : 0.0;
+      transpose_field(F, rD, b0r[r], ub, a.gamma, B, Gx, Gy, Gz);
+      if (r == 0) {
+#pragma unroll
+        for (int m = 0; m < 3; m++) {
+#pragma unroll
+          for (int c = 0; c < 3; c++) Fq[m][c] = F[m][c];
+          Bq[m] = B[m];
+          ubq[m] = ub[m];
+        }
+        rDq = rD;
+      }
+      if (fp[r].slot >= 0) {
+        const int f = fp[r].slot;
+#pragma unroll
+        for (int m = 0; m < 3; m++) {
+          bs[m][f] = B[m];
+          gs[m][f] = Gx[m];
+          gs[3 + m][f] = Gy[m];
+          gs[6 + m][f] = Gz[m];
+        }
+      }
+    }
+  }
+  __syncthreads();
+  if (!node) return;
+
+  // ---- the transpose at the own node
+  const int o = fp[0].slot, fx = br.fx, fxy = br.fxy;
+  const bool interior = !fp[0].face();
+  double G[3][3] = {}, Bt[3];
+#pragma unroll
+  for (int m = 0; m < 3; m++) {
+    if (interior) {
+      G[0][m] = bs[m][o + 1] - bs[m][o - 1];
+      G[1][m] = bs[m][o + fx] - bs[m][o - fx];
+      G[2][m] = bs[m][o + fxy] - bs[m][o - fxy];
+    }
+    Bt[m] = (gs[m][o - 1] - gs[m][o + 1]) + (gs[3 + m][o - fx] - gs[3 + m][o + fx]) +
+            (gs[6 + m][o - fxy] - gs[6 + m][o + fxy]);
+  }
+  double zeta = 1.0;
+  if constexpr (SEED) zeta = (fp[0].ends & 3 ? 0.5 : 1.0) * (fp[0].ends & 12 ? 0.5 : 1.0) * (fp[0].ends & 48 ? 0.5 : 1.0);
+  double Fb[9], dB[3];
+  transpose_node<SEED>(Fq, rDq, Bq, ubq, b0r[0], G, Bt, interior, zeta, a, Fb, dB);
+#pragma unroll
+  for (int i = 0; i < 9; i++) a.Fbar[i * N + own] = Fb[i];
+#pragma unroll
+  for (int m = 0; m < 3; m++) a.B0bar[m * N + own] = bbr[m] + dB[m];
+}
+
 // ybar = D^T Fbar': each column a of Fbar' is pulled back along axis a with the transposed
 // difference rows (central: +1 at n+e_a, -1 at n-e_a; one-sided ends: (-3, 4, -1) and (3, -4, 1)).
-// mode 0 (stage t >= 2): ybar_t = D^T Fbar' -> ybar_out, and the cotangent of k_{t-1},
+// MODE 0 (stage STAGE >= 2): ybar_t = D^T Fbar' -> ybar_out, and the cotangent of k_{t-1},
 //   dt (b5_{t-1} xbar + sum_{t' >= t} a_{t',t-1} ybar_{t'}) -> ubar_out;
-// mode 1 (stage 1): xbar += D^T Fbar' + sum_{t=2..6} ybar_t;  mode 2 (seed): xbar = D^T Fbar'
-__global__ __launch_bounds__(256) void adj_gather_kernel(AdjArgs a, int mode, int stage) {
+// MODE 1 (stage 1): xbar += D^T Fbar' + sum_{t=2..6} ybar_t;  MODE 2 (seed): xbar = D^T Fbar'.
+// Bound by its 190 to 290 bytes a node: one thread a node, rows of 64 along x so that every access is
+// coalesced and no index needs a 64-bit division (64 x 64 x 192: 29 us; 16^3: 8 -> 4 us against a
+// grid-stride loop with 64-bit divisions).
+template <int MODE, int STAGE>
+__global__ __launch_bounds__(256) void adj_gather_kernel(AdjArgs a, int bxs, int bys) {
   const Geometry& g = a.g;
   const long long N = g.N;
   const int nx = g.n[0], ny = g.n[1];
-  const double dt = (mode == 0) ? *a.dt : 0.0;
-  for (long long p = (long long)blockIdx.x * blockDim.x + threadIdx.x; p < N; p += (long long)gridDim.x * blockDim.x) {
-    const int i = (int)(p % nx), j = (int)((p / nx) % ny), k = (int)(p / ((long long)nx * ny));
-    const int id[3] = {i, j, k};
-    double yb[3] = {0.0, 0.0, 0.0};
+  const int lb = logical_block(blockIdx.x, gridDim.x);
+  const int k = lb / (bxs * bys), rem = lb - k * bxs * bys, jb = rem / bxs;
+  const int i = (rem - jb * bxs) * 64 + (threadIdx.x & 63), j = jb * 4 + (threadIdx.x >> 6);
+  if (i >= nx || j >= ny) return;
+  const long long p = ((long long)k * ny + j) * nx + i;
+  const double dt = (MODE == 0) ? *a.dt : 0.0;
+  double yb[3] = {0.0, 0.0, 0.0};
 #pragma unroll
-    for (int ax = 0; ax < 3; ax++) {
-      const int n = g.n[ax];
-      const int v = id[ax];
-      const long long stride = (ax == 0) ? 1 : (ax == 1 ? (long long)nx : (long long)nx * ny);
-      auto col = [&](int vv, double c) {  // yb += c * Fbar'[:, ax] at the node with index vv along ax
-        const long long m = p + (long long)(vv - v) * stride;
+  for (int ax = 0; ax < 3; ax++) {
+    const int n = g.n[ax], v = ax == 0 ? i : (ax == 1 ? j : k);
+    const long long stride = ax == 0 ? 1 : (ax == 1 ? (long long)nx : (long long)nx * ny);
+    auto col = [&](int vv, double c) {  // yb += c * Fbar'[:, ax] at the node with index vv along ax
+      const long long m = p + (long long)(vv - v) * stride;
 #pragma unroll
-        for (int r = 0; r < 3; r++) yb[r] += c * a.Fbar[(3 * r + ax) * N + m];
-      };
-      if (g.bc[ax] == BC_PERIODIC) {
-        col(v == 0 ? n - 1 : v - 1, 1.0);
-        col(v == n - 1 ? 0 : v + 1, -1.0);
-      } else {
-        if (v - 1 >= 1 && v - 1 <= n - 2) col(v - 1, 1.0);
-        if (v + 1 >= 1 && v + 1 <= n - 2) col(v + 1, -1.0);
-        if (v == 0) col(0, -3.0);
-        if (v == 1) col(0, 4.0);
-        if (v == 2) col(0, -1.0);
-        if (v == n - 1) col(n - 1, 3.0);
-        if (v == n - 2) col(n - 1, -4.0);
-        if (v == n - 3) col(n - 1, 1.0);
-      }
-    }
-    if (mode == 0) {
-      const int s = stage - 1;  // the stage whose k's cotangent is assembled
-#pragma unroll
-      for (int r = 0; r < 3; r++) {
-        a.ybar_out[p + r * N] = yb[r];
-        double v = CK::b5[s - 1] * a.xbar[p + r * N] + CK::a[stage - 1][s - 1] * yb[r];
-        for (int t = stage + 1; t <= 6; t++) v += CK::a[t - 1][s - 1] * a.ybar[t][p + r * N];
-        a.ubar_out[p + r * N] = dt * v;
-      }
-    } else if (mode == 1) {
-#pragma unroll
-      for (int r = 0; r < 3; r++) {
-        double s = a.xbar_out[p + r * N] + yb[r];
-        for (int t = 2; t <= 6; t++) s += a.ybar[t][p + r * N];
-        a.xbar_out[p + r * N] = s;
-      }
+      for (int r = 0; r < 3; r++) yb[r] += c * a.Fbar[(3 * r + ax) * N + m];
+    };
+    if (g.bc[ax] == BC_PERIODIC) {
+      col(v == 0 ? n - 1 : v - 1, 1.0);
+      col(v == n - 1 ? 0 : v + 1, -1.0);
     } else {
+      if (v - 1 >= 1 && v - 1 <= n - 2) col(v - 1, 1.0);
+      if (v + 1 >= 1 && v + 1 <= n - 2) col(v + 1, -1.0);
+      if (v == 0) col(0, -3.0);
+      if (v == 1) col(0, 4.0);
+      if (v == 2) col(0, -1.0);
+      if (v == n - 1) col(n - 1, 3.0);
+      if (v == n - 2) col(n - 1, -4.0);
+      if (v == n - 3) col(n - 1, 1.0);
+    }
+  }
 #pragma unroll
-      for (int r = 0; r < 3; r++) a.xbar_out[p + r * N] = yb[r];
+  for (int r = 0; r < 3; r++) {
+    if constexpr (MODE == 0) {
+      constexpr int s = STAGE - 1;  // the stage whose k's cotangent is assembled
+      a.ybar_out[p + r * N] = yb[r];
+      double v = CK::b5[s - 1] * a.xbar[p + r * N] + CK::a[STAGE - 1][s - 1] * yb[r];
+#pragma unroll
+      for (int t = STAGE + 1; t <= 6; t++) v += CK::a[t - 1][s - 1] * a.ybar[t][p + r * N];
+      a.ubar_out[p + r * N] = dt * v;
+    } else if constexpr (MODE == 1) {
+      double s = a.xbar_out[p + r * N] + yb[r];
+#pragma unroll
+      for (int t = 2; t <= 6; t++) s += a.ybar[t][p + r * N];
+      a.xbar_out[p + r * N] = s;
+    } else {
+      a.xbar_out[p + r * N] = yb[r];
     }
   }
 }
@@ -592,12 +766,39 @@ unsigned grid_for(long long n) {
 }  // namespace
 
 hipError_t launch_adj_field(int s, bool seed, const AdjArgs& a, hipStream_t st) {
+  if (a.g.brick[0]) {
+    const dim3 grid(a.g.nblocks), block(BRICK_THREADS);
+    switch (seed ? 0 : s) {
+      case 0: hipLaunchKernelGGL((adj_brick_kernel<1, true>), grid, block, 0, st, a); break;
+      case 1: hipLaunchKernelGGL((adj_brick_kernel<1, false>), grid, block, 0, st, a); break;
+      case 2: hipLaunchKernelGGL((adj_brick_kernel<2, false>), grid, block, 0, st, a); break;
+      case 3: hipLaunchKernelGGL((adj_brick_kernel<3, false>), grid, block, 0, st, a); break;
+      case 4: hipLaunchKernelGGL((adj_brick_kernel<4, false>), grid, block, 0, st, a); break;
+      case 5: hipLaunchKernelGGL((adj_brick_kernel<5, false>), grid, block, 0, st, a); break;
+      case 6: hipLaunchKernelGGL((adj_brick_kernel<6, false>), grid, block, 0, st, a); break;
+      default: return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
+  }
   const bool xyp = (a.g.bc[0] == BC_PERIODIC && a.g.bc[1] == BC_PERIODIC);
   return xyp ? launch_field_x<true>(s, seed, a, st) : launch_field_x<false>(s, seed, a, st);
 }
 
 hipError_t launch_adj_gather(const AdjArgs& a, int mode, int stage, hipStream_t st) {
-  hipLaunchKernelGGL(adj_gather_kernel, dim3(grid_for(a.g.N)), dim3(256), 0, st, a, mode, stage);
+  const int bxs = (a.g.n[0] + 63) / 64, bys = (a.g.n[1] + 3) / 4;
+  const long long blocks = (long long)bxs * bys * a.g.n[2];
+  if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
+  const dim3 grid((unsigned)blocks), block(256);
+  switch (mode == 0 ? stage : 10 + mode) {
+    case 2: hipLaunchKernelGGL((adj_gather_kernel<0, 2>), grid, block, 0, st, a, bxs, bys); break;
+    case 3: hipLaunchKernelGGL((adj_gather_kernel<0, 3>), grid, block, 0, st, a, bxs, bys); break;
+    case 4: hipLaunchKernelGGL((adj_gather_kernel<0, 4>), grid, block, 0, st, a, bxs, bys); break;
+    case 5: hipLaunchKernelGGL((adj_gather_kernel<0, 5>), grid, block, 0, st, a, bxs, bys); break;
+    case 6: hipLaunchKernelGGL((adj_gather_kernel<0, 6>), grid, block, 0, st, a, bxs, bys); break;
+    case 11: hipLaunchKernelGGL((adj_gather_kernel<1, 1>), grid, block, 0, st, a, bxs, bys); break;
+    case 12: hipLaunchKernelGGL((adj_gather_kernel<2, 1>), grid, block, 0, st, a, bxs, bys); break;
+    default: return hipErrorInvalidValue;
+  }
   return hipGetLastError();
 }
 

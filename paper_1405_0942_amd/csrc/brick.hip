@@ -9,6 +9,7 @@
 // the halo: a brick of 8 x 8 x 8 loads 3.4 window points and evaluates 2 fields per node where the
 // march of a tall chunk takes 1.6 and 1.3, so that bricks are used only where latency decides
 // (choose_brick in relax.cpp).  The arithmetic of a node is that of stage.hip (stage_math.h).
+#include "brick.h"
 #include "stage_math.h"
 
 namespace relax {
@@ -17,14 +18,8 @@ namespace {
 constexpr int NPW = (BRICK_WINDOW + BRICK_THREADS - 1) / BRICK_THREADS;  // window points per thread
 constexpr int NPF = 1 + (BRICK_SHELL + BRICK_THREADS - 1) / BRICK_THREADS;  // field points per thread
 
-// e / d for 0 <= e < 4096, 1 <= d < 4096: (e + 1/2) / d is at least 1 / (2 d) away from an integer,
-// far more than the rounding of the reciprocal
-__device__ __forceinline__ int small_div(int e, int d) {
-  return (int)(((float)e + 0.5f) * __builtin_amdgcn_rcpf((float)d));
-}
-
 template <int S, bool MIXED, bool NNN, bool DIAG = false, bool REC = false>
-__global__ __launch_bounds__(BRICK_THREADS) __attribute__((amdgpu_waves_per_eu(NNN ? 2 : 4))) void brick_kernel(SweepArgs a) {
+__global__ __launch_bounds__(BRICK_THREADS) __attribute__((amdgpu_waves_per_eu(4))) void brick_kernel(SweepArgs a) {
   using St = Stage<S, MIXED, NNN>;
   using T = typename St::T;
   constexpr bool STAGE1 = St::STAGE1, LAST = St::LAST, LEAN = St::LEAN, WV = St::WV, CX = St::CX, CV = St::CV;
@@ -57,19 +52,14 @@ __global__ __launch_bounds__(BRICK_THREADS) __attribute__((amdgpu_waves_per_eu(N
   const double cv = (S == 2) ? dt * CK::a[1][0] : 1.0;
 
   const Geometry& g = a.g;
-  const int nx = g.n[0], ny = g.n[1], nz = g.n[2];
-  const int nxy = nx * ny;
   const long long N = g.N;
-  const int bcx = g.bc[0], bcy = g.bc[1], bcz = g.bc[2];
-  const int bx = g.brick[0], by = g.brick[1], bz = g.brick[2];
-  const int sx = bx + 4, sy = by + 4, sxy = sx * sy;   // window strides
-  const int fx = bx + 2, fy = by + 2, fxy = fx * fy;   // B strides
-  const int nwin = sxy * (bz + 4), nown = bx * by * bz;
+  const Brick br(g);
+  const int sx = br.sx, sxy = br.sxy, fx = br.fx, fxy = br.fxy;
 
   const int lb = logical_block(blockIdx.x, g.nblocks);
-  const int i0 = (lb % g.tiles[0]) * bx;
-  const int j0 = ((lb / g.tiles[0]) % g.tiles[1]) * by;
-  const int k0 = (lb / (g.tiles[0] * g.tiles[1])) * bz;
+  const int i0 = (lb % g.tiles[0]) * br.bx;
+  const int j0 = ((lb / g.tiles[0]) % g.tiles[1]) * br.by;
+  const int k0 = (lb / (g.tiles[0] * g.tiles[1])) * br.bz;
   const int tid = threadIdx.x;
 
   __shared__ double ys[3][BRICK_WINDOW];
@@ -81,29 +71,14 @@ __global__ __launch_bounds__(BRICK_THREADS) __attribute__((amdgpu_waves_per_eu(N
   const T* __restrict__ wvec = static_cast<const T*>(S == 2 ? a.k[0] : (S == 4 ? a.d4 : a.sum[0]));
   const T* __restrict__ b0p = static_cast<const T*>(a.B0);
 
-  // ---- all loads first ---------------------------------------------------------------------
+  // ---- the window and B0 first ---------------------------------------------------------------------
   double wx[NPW][3];
   T wk[WV ? NPW : 1][3];
-  int we[NPW], wg[NPW];  // grid index (-1 off the grid), step into the grid of a ghost point (0: none)
-  int ww[NPW];           // periodic wraps of x, y, z, each + 1, in bits 0-1, 2-3, 4-5
+  BrickPoint wp[NPW];
 #pragma unroll
   for (int r = 0; r < NPW; r++) {
-    const int e = tid + r * BRICK_THREADS;
-    const int lz = small_div(e, sxy), e2 = e - lz * sxy, ly = small_div(e2, sx), lx = e2 - ly * sx;
-    const int gi = i0 + lx - 2, gj = j0 + ly - 2, gk = k0 + lz - 2;
-    const AxisIdx rx = resolve_near(gi, nx, bcx), ry = resolve_near(gj, ny, bcy), rz = resolve_near(gk, nz, bcz);
-    const bool in = e < nwin;
-    we[r] = (in && rx.ok && ry.ok && rz.ok) ? rz.i * nxy + ry.i * nx + rx.i : -1;
-    ww[r] = (rx.w + 1) | (ry.w + 1) << 2 | (rz.w + 1) << 4;
-    wg[r] = 0;
-    if constexpr (!NNN) {
-      if (in) {
-        if (ry.ok && rz.ok && !rx.ok) wg[r] = gi == -1 ? 1 : (gi == nx ? -1 : 0);
-        if (rx.ok && rz.ok && !ry.ok) wg[r] = gj == -1 ? sx : (gj == ny ? -sx : 0);
-        if (rx.ok && ry.ok && !rz.ok) wg[r] = gk == -1 ? sxy : (gk == nz ? -sxy : 0);
-      }
-    }
-    const int i = max(we[r], 0);
+    wp[r] = brick_window(br, g, tid + r * BRICK_THREADS, i0, j0, k0);
+    const int i = wp[r].index;
 #pragma unroll
     for (int m = 0; m < 3; m++) wx[r][m] = wbase[m * N + i];
     if constexpr (WV) {
@@ -111,75 +86,17 @@ __global__ __launch_bounds__(BRICK_THREADS) __attribute__((amdgpu_waves_per_eu(N
       for (int m = 0; m < 3; m++) wk[r][m] = wvec[m * N + i];
     }
   }
-  // field point 0 is the own node; then the shell: the planes below and above the brick, then a ring
-  // around each of its planes
   T b0r[NPF][3];
-  int fo[NPF], fw[NPF], fend[NPF];  // offsets in the B window (-1: none) and the stage-input window, ends
-  bool fok[NPF];
-  int tx = 0, ty = 0, tz = 0;
+  BrickField fp[NPF];
 #pragma unroll
   for (int r = 0; r < NPF; r++) {
-    int cx, cy, cz;  // B window coordinates
-    bool in;
-    if (r == 0) {
-      in = tid < nown;
-      const int e = in ? tid : 0;
-      tz = small_div(e, bx * by);
-      ty = small_div(e - tz * bx * by, bx);
-      tx = e - (tz * by + ty) * bx;
-      cx = tx + 1;
-      cy = ty + 1;
-      cz = tz + 1;
-    } else {
-      const int e = tid + (r - 1) * BRICK_THREADS, ring = 2 * (fx + by);
-      if (e < 2 * fxy) {
-        const int top = e >= fxy ? 1 : 0, e2 = e - top * fxy;
-        cz = top * (bz + 1);
-        cy = small_div(e2, fx);
-        cx = e2 - cy * fx;
-        in = true;
-      } else {
-        const int e2 = e - 2 * fxy, layer = small_div(e2, ring), e3 = e2 - layer * ring;
-        in = layer < bz;
-        cz = in ? layer + 1 : 0;
-        if (e3 < 2 * fx) {
-          cy = e3 < fx ? 0 : by + 1;
-          cx = e3 < fx ? e3 : e3 - fx;
-        } else {
-          cy = 1 + ((e3 - 2 * fx) >> 1);
-          cx = (e3 & 1) ? bx + 1 : 0;
-        }
-      }
-    }
-    const AxisIdx rx = resolve_near(i0 + cx - 1, nx, bcx), ry = resolve_near(j0 + cy - 1, ny, bcy);
-    const AxisIdx rz = resolve_near(k0 + cz - 1, nz, bcz);
-    fok[r] = in && rx.ok && ry.ok && rz.ok;
-    fo[r] = in ? cz * fxy + cy * fx + cx : -1;
-    fw[r] = (cz + 1) * sxy + (cy + 1) * sx + cx + 1;
-    fend[r] = 0;
-    if (bcx == BC_LINE_TIED) fend[r] |= rx.i == 0 ? 1 : (rx.i == nx - 1 ? 2 : 0);
-    if (bcy == BC_LINE_TIED) fend[r] |= ry.i == 0 ? 4 : (ry.i == ny - 1 ? 8 : 0);
-    if (bcz == BC_LINE_TIED) fend[r] |= rz.i == 0 ? 16 : (rz.i == nz - 1 ? 32 : 0);
-    const int i = fok[r] ? rz.i * nxy + ry.i * nx + rx.i : 0;
+    fp[r] = brick_field(br, g, r, tid, i0, j0, k0);
 #pragma unroll
-    for (int m = 0; m < 3; m++) b0r[r][m] = b0p[m * N + i];
+    for (int m = 0; m < 3; m++) b0r[r][m] = b0p[m * N + fp[r].index];
   }
-  const int gi_t = i0 + tx, gj_t = j0 + ty, gk_t = k0 + tz;
-  const bool node = tid < nown && gi_t < nx && gj_t < ny && gk_t < nz;
-  const int own = node ? gk_t * nxy + gj_t * nx + gi_t : 0;
-  const bool face = node && fend[0] != 0;
-  T pk[NPKA][3], ps[NPS][3], vq[3];
-  double xq[3];
-#pragma unroll
-  for (int m = 0; m < 3; m++) {
-#pragma unroll
-    for (int j = 0; j < NPK; j++) pk[j][m] = static_cast<const T*>(a.k[LEAN ? (S == 3 ? 1 : 2 * j) : j])[m * N + own];
-    if constexpr (PS) ps[0][m] = static_cast<const T*>(S == 5 ? a.sum[0] : a.sum[1])[m * N + own];
-    if constexpr (PS && NPS == 2) ps[NPS - 1][m] = static_cast<const T*>(a.sum[2])[m * N + own];
-    if constexpr (CX) xq[m] = xn[m * N + own];
-    if constexpr (CV) vq[m] = wvec[m * N + own];
-  }
-
+  const bool node = fp[0].node();
+  const int own = fp[0].index;
+  const bool face = fp[0].face();
   // ---- stage input on the brick and its 2-node halo ------------------------------------------
 #pragma unroll
   for (int r = 0; r < NPW; r++) {
@@ -193,23 +110,36 @@ __global__ __launch_bounds__(BRICK_THREADS) __attribute__((amdgpu_waves_per_eu(N
       } else if constexpr (WV) {
         y = y + (double)wk[r][m];
       }
-      v[m] = y + (double)(((ww[r] >> (2 * m)) & 3) - 1) * g.period[m];
+      v[m] = y + wp[r].wrap(m) * g.period[m];
     }
-    if (e < nwin) {
+    if (e < br.nwin) {
 #pragma unroll
-      for (int m = 0; m < 3; m++) ys[m][e] = we[r] >= 0 ? v[m] : 0.0;
+      for (int m = 0; m < 3; m++) ys[m][e] = wp[r].on() ? v[m] : 0.0;
     }
   }
+  // The vectors read at the node, once the window's registers are free (4 waves a SIMD need 128); the
+  // octilateral walk needs them all, so there after it.
+  T pk[NPKA][3], ps[NPS][3], vq[3];
+  double xq[3];
+  auto load_node = [&]() {
+#pragma unroll
+    for (int m = 0; m < 3; m++) {
+#pragma unroll
+      for (int j = 0; j < NPK; j++) pk[j][m] = static_cast<const T*>(a.k[LEAN ? (S == 3 ? 1 : 2 * j) : j])[m * N + own];
+      if constexpr (PS) ps[0][m] = static_cast<const T*>(S == 5 ? a.sum[0] : a.sum[1])[m * N + own];
+      if constexpr (PS && NPS == 2) ps[NPS - 1][m] = static_cast<const T*>(a.sum[2])[m * N + own];
+      if constexpr (CX) xq[m] = xn[m * N + own];
+      if constexpr (CV) vq[m] = wvec[m * N + own];
+    }
+  };
+  if constexpr (!NNN) load_node();
   __syncthreads();
   if constexpr (!NNN) {
     // ghost nodes beyond line-tied faces (see stage.hip)
-    const bool faces = (bcx == BC_LINE_TIED && (i0 <= 1 || i0 + bx >= nx - 1)) ||
-                       (bcy == BC_LINE_TIED && (j0 <= 1 || j0 + by >= ny - 1)) ||
-                       (bcz == BC_LINE_TIED && (k0 <= 1 || k0 + bz >= nz - 1));
-    if (faces) {
+    if (br.at_face(g, i0, j0, k0)) {
 #pragma unroll
       for (int r = 0; r < NPW; r++) {
-        const int e = tid + r * BRICK_THREADS, s = wg[r];
+        const int e = tid + r * BRICK_THREADS, s = wp[r].ghost;
         if (s != 0) {
 #pragma unroll
           for (int m = 0; m < 3; m++) ys[m][e] = fma(3.0, ys[m][e + s] - ys[m][e + 2 * s], ys[m][e + 3 * s]);
@@ -226,8 +156,8 @@ __global__ __launch_bounds__(BRICK_THREADS) __attribute__((amdgpu_waves_per_eu(N
   int kap = 1;
 #pragma unroll
   for (int r = 0; r < NPF; r++) {
-    if (r == 0 || fo[r] >= 0) {
-      const int o = fw[r];
+    if (r == 0 || fp[r].slot >= 0) {
+      const int o = fp[r].window;
       double F[3][3];
       if constexpr (NNN) {
         // the one-sided rows themselves (see stage.hip)
@@ -238,9 +168,9 @@ __global__ __launch_bounds__(BRICK_THREADS) __attribute__((amdgpu_waves_per_eu(N
         };
 #pragma unroll
         for (int m = 0; m < 3; m++) {
-          F[m][0] = row(ys[m], 1, fend[r] & 3);
-          F[m][1] = row(ys[m], sx, (fend[r] >> 2) & 3);
-          F[m][2] = row(ys[m], sxy, (fend[r] >> 4) & 3);
+          F[m][0] = row(ys[m], 1, fp[r].ends & 3);
+          F[m][1] = row(ys[m], sx, (fp[r].ends >> 2) & 3);
+          F[m][2] = row(ys[m], sxy, (fp[r].ends >> 4) & 3);
         }
       } else {
 #pragma unroll
@@ -251,7 +181,7 @@ __global__ __launch_bounds__(BRICK_THREADS) __attribute__((amdgpu_waves_per_eu(N
         }
       }
       const double D = (NNN || MIXED) ? det3(F) : det3_fused(F);
-      const double rD = fok[r] ? rcp_nr(D) : 0.0;
+      const double rD = fp[r].on() ? rcp_nr(D) : 0.0;
       T q0 = b0r[r][0], q1 = b0r[r][1], q2 = b0r[r][2];
       if constexpr (DIAG) {
         q0 *= a.b0_mul[0];
@@ -271,9 +201,9 @@ __global__ __launch_bounds__(BRICK_THREADS) __attribute__((amdgpu_waves_per_eu(N
         Dq = D * g.inv8h3;
         if (STAGE1 && node) {
           double zeta = 1.0;
-          if (fend[0] & 3) zeta *= 0.5;
-          if (fend[0] & 12) zeta *= 0.5;
-          if (fend[0] & 48) zeta *= 0.5;
+          if (fp[0].ends & 3) zeta *= 0.5;
+          if (fp[0].ends & 12) zeta *= 0.5;
+          if (fp[0].ends & 48) zeta *= 0.5;
           double Bd[3];
 #pragma unroll
           for (int m = 0; m < 3; m++)
@@ -292,16 +222,16 @@ __global__ __launch_bounds__(BRICK_THREADS) __attribute__((amdgpu_waves_per_eu(N
               ez[0][m] = ys[m][o - sxy] - c0;
               ez[1][m] = ys[m][o + sxy] - c0;
             }
-            const bool convex = is_convex(ex, ey, ez, !(fend[0] & 1), !(fend[0] & 2), !(fend[0] & 4), !(fend[0] & 8),
-                                          !(fend[0] & 16), !(fend[0] & 32));
+            const bool convex = is_convex(ex, ey, ez, !(fp[0].ends & 1), !(fp[0].ends & 2), !(fp[0].ends & 4), !(fp[0].ends & 8),
+                                          !(fp[0].ends & 16), !(fp[0].ends & 32));
             acc.concave += convex ? 0.0 : 1.0;
             kap = convex ? 1 : -1;
           }
         }
       }
-      if (fo[r] >= 0) {
+      if (fp[r].slot >= 0) {
 #pragma unroll
-        for (int m = 0; m < 3; m++) bs[m][fo[r]] = B[m];
+        for (int m = 0; m < 3; m++) bs[m][fp[r].slot] = B[m];
       }
     }
   }
@@ -310,7 +240,7 @@ __global__ __launch_bounds__(BRICK_THREADS) __attribute__((amdgpu_waves_per_eu(N
   // ---- current, force, velocity and the stage's outputs at the own node --------------------------
   if (node) {
     StageOut<S, MIXED, NNN, DIAG, REC> so;
-    const int oy = fw[0], o = fo[0];
+    const int oy = fp[0].window, o = fp[0].slot;
     T u[3] = {T(0), T(0), T(0)};
     if constexpr (DIAG) {
 #pragma unroll
@@ -374,6 +304,7 @@ __global__ __launch_bounds__(BRICK_THREADS) __attribute__((amdgpu_waves_per_eu(N
       }
     } else {
       double err[3];
+      if constexpr (NNN) load_node();
       advance<S, MIXED, NNN, REC>(u, xq, vq, pk, ps, dt, so, err);
       if constexpr (S == 2) {
         put(static_cast<T*>(a.k[1]), so.k);

@@ -154,10 +154,8 @@ int choose_tz(const relax_config* c, int tiles_xy) {
 // 237, 64 x 64 x 192 205 / 207, 128^3 359 / 653; FP32-mixed 142 / 47, 156 / 54, 159 / 85, 171 / 108,
 // 181 / 178, 197 / 210, 169 / 183, 294 / 492.  The octilateral current, whose march holds one plane
 // more and two barriers: 400 / 72 at 16^3, 499 / 190 at 65^3, 503 / 413 at 96^3, 774 / 1017 at 128^3.
-bool choose_brick(const relax_config* c, int brick[3]) {
-  if (std::getenv("RELAX_TZ")) return false;  // a chosen chunk length is a choice of the march
-  const long long N = (long long)c->n[0] * c->n[1] * c->n[2];
-  if (N > (c->curl == RELAX_CURL_NNN ? 1000000 : 600000)) return false;
+// The brick of a grid for sweeps with at most `window` window points and `slots` resident workgroups.
+static void choose_brick(const relax_config* c, int window, int slots, int brick[3]) {
   // edges that split an axis evenly (every ceil(n / k) up to 64), shortest first
   int edge[3][64], ne[3];
   for (int a = 0; a < 3; a++) {
@@ -175,13 +173,13 @@ bool choose_brick(const relax_config* c, int brick[3]) {
         if (bx * by * bz > BRICK_THREADS) break;
         const int win = (bx + 4) * (by + 4) * (bz + 4), fld = (bx + 2) * (by + 2) * (bz + 2);
         const int shell = fld - bx * by * bz;
-        if (win > BRICK_WINDOW || fld > BRICK_FIELD || shell > BRICK_SHELL) break;
+        if (win > window || fld > BRICK_FIELD || shell > BRICK_SHELL) break;
         const long long blocks = (long long)((c->n[0] + bx - 1) / bx) * ((c->n[1] + by - 1) / by) * ((c->n[2] + bz - 1) / bz);
-        // rounds of the 512 resident workgroups x the passes of a workgroup over its points (4: its
+        // rounds of the resident workgroups x the passes of a workgroup over its points (4: its
         // fixed part); on a tie the fewer points loaded
         const int t = BRICK_THREADS;
         const double passes = 4.0 + (win + t - 1) / t + 1.5 * (1 + (shell + t - 1) / t);
-        const double cost = (double)((blocks + 511) / 512) * passes + 1e-9 * (double)(blocks * win);
+        const double cost = (double)((blocks + slots - 1) / slots) * passes + 1e-9 * (double)(blocks * win);
         if (best < 0.0 || cost < best) {
           best = cost;
           brick[0] = bx;
@@ -189,7 +187,6 @@ bool choose_brick(const relax_config* c, int brick[3]) {
           brick[2] = bz;
         }
       }
-  return best >= 0.0;
 }
 
 Geometry make_tiles(const relax_config* c) {
@@ -215,14 +212,20 @@ Geometry make_tiles(const relax_config* c) {
   return g;
 }
 
-Geometry make_geometry(const relax_config* c) {
+static Geometry with_bricks(const relax_config* c, long long max_nodes, int window, int slots) {
   Geometry g = make_tiles(c);
-  if (choose_brick(c, g.brick)) {
-    for (int a = 0; a < 3; a++) g.tiles[a] = (c->n[a] + g.brick[a] - 1) / g.brick[a];
-    g.nblocks = g.tiles[0] * g.tiles[1] * g.tiles[2];
-  }
+  if (g.N > max_nodes || std::getenv("RELAX_TZ")) return g;  // a chosen chunk length: the march
+  choose_brick(c, window, slots, g.brick);
+  for (int a = 0; a < 3; a++) g.tiles[a] = (c->n[a] + g.brick[a] - 1) / g.brick[a];
+  g.nblocks = g.tiles[0] * g.tiles[1] * g.tiles[2];
   return g;
 }
+
+Geometry make_geometry(const relax_config* c) {
+  return with_bricks(c, c->curl == RELAX_CURL_NNN ? 1000000 : 600000, BRICK_WINDOW, 512);
+}
+
+Geometry make_adj_geometry(const relax_config* c) { return with_bricks(c, 600000, ADJ_WINDOW, 256); }
 
 }  // namespace relax
 
@@ -622,7 +625,7 @@ int relax_backward(void* ctx, double seed_EM, double seed_R2, double* d_grad_x0,
   hipStream_t st = c->stream;
 
   AdjArgs a{};
-  a.g = make_tiles(&c->cfg);
+  a.g = make_adj_geometry(&c->cfg);
   a.B0 = c->d_B0_64;
   a.Fbar = c->d_Fbar;
   a.B0bar = c->d_B0bar;

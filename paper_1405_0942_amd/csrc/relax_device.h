@@ -33,6 +33,7 @@ constexpr int BRICK_THREADS = 512;
 constexpr int BRICK_WINDOW = 2048;
 constexpr int BRICK_FIELD = 1152;
 constexpr int BRICK_SHELL = 1024;
+constexpr int ADJ_WINDOW = 1920;  // the same limit for the reverse sweeps (adjoint.hip)
 
 enum { BC_LINE_TIED = 0, BC_PERIODIC = 1 };
 enum { CURL_NN = 0, CURL_NNN = 1 };  // the values of RELAX_CURL_NN / RELAX_CURL_NNN
@@ -149,9 +150,9 @@ struct CK {
 // ------------------------------------------------------------------------------------------
 bool valid_config(const relax_config* c);          // every field in range
 int choose_tz(const relax_config* c, int tiles_xy);  // z-chunk length
-bool choose_brick(const relax_config* c, int brick[3]);  // whether, and which, bricks
 Geometry make_tiles(const relax_config* c);        // scale factors, z-marching tiles and chunks
 Geometry make_geometry(const relax_config* c);     // the same with bricks where they are used
+Geometry make_adj_geometry(const relax_config* c);  // the geometry of the reverse field sweeps
 
 // ------------------------------------------------------------------------------------------
 // Launchers implemented in the kernel translation units

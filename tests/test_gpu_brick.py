@@ -56,3 +56,28 @@ def test_bricks_match_the_march(n, bc, kw, monkeypatch):
     assert np.abs(dx - dxm).max() <= (2e-6 if kw is MIXED else 1e-12) * np.abs(dxm).max() + 2 * ulp
     for f in ("E_M", "xi", "R2", "min_det"):
         assert rel(d[f], dm[f]) < 1e-12
+
+
+GRAD_CASES = [((4, 4, 4), (0, 0, 0)), ((5, 6, 7), (1, 1, 1)), ((17, 17, 17), (0, 0, 0)), ((70, 11, 9), (0, 1, 0)),
+              ((7, 66, 13), (1, 0, 1)), ((41, 43, 47), (0, 0, 1))]
+
+
+@pytest.mark.parametrize("n,bc", GRAD_CASES, ids=[f"{c[0]}-{c[1]}" for c in GRAD_CASES])
+def test_gradient_bricks_match_the_march(n, bc, monkeypatch):
+    """Both orders of the same sums: 1e-12 normwise, as against the oracle's complex step (1e-10)."""
+    banner(f"gradient bricks {n} {bc}")
+    g = W.make_grid(n, [(0.0, 0.1 * v) for v in n], bc)
+    x0 = W.distorted_grid(g, 0.02 * min(g.h), seed=21)
+    B0 = W.smooth_random_field(g, 0.6, seed=22) + np.array([0.2, -0.1, 1.0])[:, None, None, None]
+    outs = []
+    for tz in (None, "9"):
+        if tz is None:
+            monkeypatch.delenv("RELAX_TZ", raising=False)
+        else:
+            monkeypatch.setenv("RELAX_TZ", tz)
+        with context(g, x0, B0, K_record=3, dt0=0.02 * min(g.h) ** 2, adaptive=False, record=True,
+                     checkpoint_every=2) as r:
+            r.step(3, diag=False)
+            outs.append([host(t) for t in r.backward(1.0, 0.3)])
+    for a, b in zip(*outs):
+        assert nrel(a, b) < 1e-12

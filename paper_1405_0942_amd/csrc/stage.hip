@@ -80,9 +80,11 @@ namespace relax {
 namespace {
 
 // S: stage 1..6.  MIXED: the k_j, the partial sums and B0 in FP32, and the stencil past F' in
-// FP32.  NNN: the octilateral current.  DIAG (stage 1, FP64): the diagnostics sweep of x[diag_buf]: no step gating and no k_1; writes u (optionally scaled by
-// det F), B, J, alpha* and the convexity where the caller asked for them.  REC (FP64 stages
-// 4 and 6): also store the stage input at the node, for the reverse sweeps.
+// FP32.  NNN: the octilateral current.  DIAG (stage 1, FP64): the diagnostics sweep of x[diag_buf]:
+// no step gating and no k_1; with REC it writes u (optionally scaled by det F), B, J, alpha* and the
+// convexity where the caller asked for them, without REC only the sums (a store instruction takes its
+// time even when every lane is masked off: 128^3 60 -> 53 us).  REC in FP64 stages 4 and 6: also
+// store the stage input at the node, for the reverse sweeps.
 template <int S, bool MIXED, bool NNN, bool DIAG = false, bool REC = false>
 __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) void stage_kernel(SweepArgs a) {
   using T = typename std::conditional<MIXED, float, double>::type;
@@ -107,8 +109,9 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
   constexpr int NP2 = (RY2 * RX2 + NTHREADS - 1) / NTHREADS;  // stage-input points per thread
   constexpr int NP1 = (RY1 * RX1 + NTHREADS - 1) / NTHREADS;  // field points per thread
   static_assert(!DIAG || (S == 1 && !MIXED), "the diagnostics sweep is the FP64 stage-1 sweep");
-  static_assert(!REC || (!MIXED && (S == 4 || S == 6)), "REC: FP64 stages 4 and 6");
-  static_assert(!NNN || (!MIXED && !REC), "the octilateral current is an FP64 forward operator");
+  static_assert(!REC || DIAG || (!MIXED && (S == 4 || S == 6)), "REC: FP64 stages 4 and 6");
+  static_assert(!NNN || (!MIXED && (DIAG || !REC)), "the octilateral current is an FP64 forward operator");
+  constexpr bool YREC = REC && !DIAG;
 
   Control* ctl = a.ctl;
   constexpr bool diag_only = DIAG;
@@ -451,7 +454,9 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
   auto store_plane = [&](const Outputs& so, int qz, bool on, int kap = 1) {
     const long long zo = (long long)zload(qz) * nxy;
     const unsigned eo = on ? out_e : IE;
-    if constexpr (DIAG) {
+    if constexpr (DIAG && !REC) {
+      (void)eo;
+    } else if constexpr (DIAG) {
       // each output goes to the caller's array, or (masked) to x[diag_buf], never written
       double* fb = const_cast<double*>(a.x[cur]);
       double* du = a.u_out ? a.u_out : fb;
@@ -512,7 +517,7 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
 #pragma unroll
       for (int m = 0; m < 3; m++) bstore<double>(plane_rsrc(xo + m * N + zo, nxy), eo, so.y[m]);
     }
-    if constexpr (REC) {
+    if constexpr (YREC) {
       double* dy = a.yrec[S == 4 ? 0 : 1];
 #pragma unroll
       for (int m = 0; m < 3; m++) bstore<double>(plane_rsrc(dy + m * N + zo, nxy), eo, so.yc[m]);
@@ -693,7 +698,7 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
     Outputs so;
     if (qout) {
       const int oy = (ty + 2) * RX2 + tx + 2;  // the tile node in the window
-      if constexpr (REC) {
+      if constexpr (YREC) {
 #pragma unroll
         for (int m = 0; m < 3; m++) so.yc[m] = ys[yslot(q)][m][oy];
       }
@@ -827,10 +832,18 @@ hipError_t launch_stage_rec(int s, const SweepArgs& a, hipStream_t st) {
 hipError_t launch_diagnostics(const SweepArgs& a, hipStream_t st) {
   if (a.g.brick[0]) return launch_brick_diagnostics(a, st);
   const dim3 grid(a.g.nblocks), block(NTHREADS);
-  if (a.g.curl == CURL_NNN)
-    hipLaunchKernelGGL((stage_kernel<1, false, true, true>), grid, block, 0, st, a);
-  else
-    hipLaunchKernelGGL((stage_kernel<1, false, false, true>), grid, block, 0, st, a);
+  const bool fields = a.u_out || a.B_out || a.J_out || a.alpha_out || a.kappa_out;
+  if (a.g.curl == CURL_NNN) {
+    if (fields)
+      hipLaunchKernelGGL((stage_kernel<1, false, true, true, true>), grid, block, 0, st, a);
+    else
+      hipLaunchKernelGGL((stage_kernel<1, false, true, true>), grid, block, 0, st, a);
+  } else {
+    if (fields)
+      hipLaunchKernelGGL((stage_kernel<1, false, false, true, true>), grid, block, 0, st, a);
+    else
+      hipLaunchKernelGGL((stage_kernel<1, false, false, true>), grid, block, 0, st, a);
+  }
   return hipGetLastError();
 }
 

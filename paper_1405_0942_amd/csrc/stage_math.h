@@ -11,24 +11,35 @@
 
 namespace relax {
 
+__device__ __forceinline__ double max_nan(double a, double b) { return (b > a || b != b) ? b : a; }
+__device__ __forceinline__ double min_nan(double a, double b) { return (b < a || b != b) ? b : a; }
+
+// Reductions over a wave by DPP (four row shifts, then two row broadcasts): the result is in lane 63.
+// idle: what a lane without a partner takes in.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp(double v, double idle) {
+  typedef int i2 __attribute__((ext_vector_type(2)));
+  const i2 a = __builtin_bit_cast(i2, v), z = __builtin_bit_cast(i2, idle);
+  i2 r;
+  r.x = __builtin_amdgcn_update_dpp(z.x, a.x, CTRL, ROWS, 0xf, false);
+  r.y = __builtin_amdgcn_update_dpp(z.y, a.y, CTRL, ROWS, 0xf, false);
+  return __builtin_bit_cast(double, r);
+}
+template <typename Op>
+__device__ __forceinline__ double wave_reduce(double v, double idle, Op op) {
+  v = op(v, dpp<0x111, 0xf>(v, idle));
+  v = op(v, dpp<0x112, 0xf>(v, idle));
+  v = op(v, dpp<0x114, 0xf>(v, idle));
+  v = op(v, dpp<0x118, 0xf>(v, idle));
+  v = op(v, dpp<0x142, 0xa>(v, idle));
+  v = op(v, dpp<0x143, 0xc>(v, idle));
+  return v;
+}
 __device__ __forceinline__ double wave_sum(double v) {
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-  return v;
+  return wave_reduce(v, 0.0, [](double a, double b) { return a + b; });
 }
-__device__ __forceinline__ double wave_max(double v) {
-  for (int o = 32; o > 0; o >>= 1) {
-    double w = __shfl_xor(v, o, 64);
-    v = (w > v || w != w) ? w : v;
-  }
-  return v;
-}
-__device__ __forceinline__ double wave_min(double v) {
-  for (int o = 32; o > 0; o >>= 1) {
-    double w = __shfl_xor(v, o, 64);
-    v = (w < v || w != w) ? w : v;
-  }
-  return v;
-}
+__device__ __forceinline__ double wave_max(double v) { return wave_reduce(v, 0.0, max_nan); }  // v >= 0 or NaN
+__device__ __forceinline__ double wave_min(double v) { return wave_reduce(v, INFINITY, min_nan); }
 
 // What a stage reads and stores (S: stage 1..6; the variants are described at stage_kernel).
 template <int S, bool MIXED, bool NNN>
@@ -61,7 +72,7 @@ struct StageOut {
   double y[3];                                         // x_n copy (stage 1), y_3 (stage 2), y_5 (stage 4), x_{n+1}
   T s[Stage<S, MIXED, NNN>::SUMS_OUT ? 3 : 1][3];      // stage 3: d_4; stage 4: P6, X, E; stage 5: P6, -, E
   double p[DIAG ? 3 : 1][3];                           // DIAG: B, J, alpha*
-  double yc[REC ? 3 : 1];                              // REC: the stage input at the node
+  double yc[REC && !DIAG ? 3 : 1];                              // REC: the stage input at the node
 };
 
 // the octilateral loops of Sec. 2.3 through the eight ring neighbours of each grid
@@ -283,14 +294,13 @@ struct Sums {
   __device__ __forceinline__ void error(double err) { lam = (err > lam || err != err) ? err : lam; }
 };
 
-// workgroup reductions of NT threads into the partial record of stage 1 / of stage 6, in a fixed order
+// Workgroup reductions of NT threads, in a fixed order, into the partial record of stage 1 ...
 template <int NT>
 __device__ __forceinline__ void store_sums(const Sums& c, double red[NT / 64][NPART], double* pp) {
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-  const double acc_xi = sqrt(c.xi_F2) / c.xi_B2;
-  const double e = wave_sum(c.E), r2 = wave_sum(c.R2), xi = wave_max(acc_xi), mn = wave_min(c.min_det),
-               nl = wave_sum(c.nulls), cc = wave_sum(c.concave);
-  if (lane == 0) {
+  const double e = wave_sum(c.E), r2 = wave_sum(c.R2), xi = wave_max(sqrt(c.xi_F2) / c.xi_B2),
+               mn = wave_min(c.min_det), nl = wave_sum(c.nulls), cc = wave_sum(c.concave);
+  if (lane == 63) {
     red[wave][0] = e;
     red[wave][1] = r2;
     red[wave][2] = xi;
@@ -299,34 +309,30 @@ __device__ __forceinline__ void store_sums(const Sums& c, double red[NT / 64][NP
     red[wave][5] = cc;
   }
   __syncthreads();
-  if (tid == 0) {
-    double E = 0, R = 0, X = 0, M = INFINITY, Z = 0, Cc = 0;
+  if (tid < 6) {  // a thread per quantity
+    double sum = 0, X = 0, M = INFINITY;
+#pragma unroll
     for (int w = 0; w < NT / 64; w++) {
-      E += red[w][0];
-      R += red[w][1];
-      X = (red[w][2] > X || red[w][2] != red[w][2]) ? red[w][2] : X;
-      M = (red[w][3] < M || red[w][3] != red[w][3]) ? red[w][3] : M;
-      Z += red[w][4];
-      Cc += red[w][5];
+      const double v = red[w][tid];
+      sum += v;
+      X = max_nan(X, v);
+      M = min_nan(M, v);
     }
-    pp[0] = E;
-    pp[1] = R;
-    pp[2] = X;
-    pp[3] = M;
-    pp[4] = Z;
-    pp[5] = Cc;
+    pp[tid] = tid == 2 ? X : (tid == 3 ? M : sum);
   }
 }
 
+// ... and into the Lambda partial of stage 6
 template <int NT>
 __device__ __forceinline__ void store_lambda(const Sums& c, double red[NT / 64][NPART], double* pl) {
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  const int tid = threadIdx.x;
   const double l = wave_max(c.lam);
-  if (lane == 0) red[wave][5] = l;
+  if ((tid & 63) == 63) red[tid >> 6][6] = l;
   __syncthreads();
   if (tid == 0) {
     double L = 0;
-    for (int w = 0; w < NT / 64; w++) L = (red[w][5] > L || red[w][5] != red[w][5]) ? red[w][5] : L;
+#pragma unroll
+    for (int w = 0; w < NT / 64; w++) L = max_nan(L, red[w][6]);
     *pl = L;
   }
 }

@@ -66,8 +66,13 @@ struct Ctx {
   double* d_ybar = nullptr;
   double* d_B0bar = nullptr;
   double* d_useed = nullptr;
-  Control* h_ctl = nullptr;  // pinned mirror of the control block
+  // Pinned mirror of the control block.  Every call waits for the work it enqueued, so between calls
+  // the mirror is current and no call reads the block back before it starts; ctl_current is false from
+  // the launch of an attempt until the read-back after it (also when a HIP call failed in between).
+  Control* h_ctl = nullptr;
+  bool ctl_current = false;
   double* h_ring = nullptr;  // pinned copy of the diagnostics ring
+  double* h_out = nullptr;   // pinned: the final sums of a diagnostics sweep, written by the device
   int status = RELAX_OK;
   int cur = 0;  // host mirror of ctl->cur, valid between calls
   std::string err;
@@ -283,16 +288,23 @@ Layout make_layout(const relax_config* c, const Geometry& g, int K_record) {
   return L;
 }
 
-int sync_ctl(Ctx* c) {
+// wait for the stream and read the control block back, with the first ring_entries of the ring
+int sync_ctl(Ctx* c, int ring_entries = 0) {
   HIP_TRY(c, hipMemcpyAsync(c->h_ctl, c->d_ctl, sizeof(Control), hipMemcpyDeviceToHost, c->stream));
+  if (ring_entries > 0)
+    HIP_TRY(c, hipMemcpyAsync(c->h_ring, c->d_ring, (size_t)ring_entries * 8 * sizeof(double), hipMemcpyDeviceToHost,
+                              c->stream));
   HIP_TRY(c, hipStreamSynchronize(c->stream));
   c->cur = c->h_ctl->cur;
+  c->ctl_current = true;
   return RELAX_OK;
 }
 
+int need_ctl(Ctx* c) { return c->ctl_current ? RELAX_OK : sync_ctl(c); }
+
+// write the mirror to the device; the caller waits for the stream before it changes the mirror again
 int push_ctl(Ctx* c) {
   HIP_TRY(c, hipMemcpyAsync(c->d_ctl, c->h_ctl, sizeof(Control), hipMemcpyHostToDevice, c->stream));
-  HIP_TRY(c, hipStreamSynchronize(c->stream));
   return RELAX_OK;
 }
 
@@ -322,7 +334,7 @@ SweepArgs sweep_args(Ctx* c) {
   return a;
 }
 
-// FP64 diagnostics sweep of x[buf] into d_out[0..5] = {E, R2, xi, min det, nulls, concave}; host copy.
+// FP64 diagnostics sweep of x[buf]; out = {E, R2, xi, min det, nulls, concave}.
 // Non-null u_out, B_out, J_out, alpha_out, kappa_out also receive u, B, J, alpha* and the
 // convexity of x[buf].
 int diagnostics_sweep(Ctx* c, int buf, double out[6], double* u_out = nullptr, double u_det_scale = 0.0,
@@ -338,10 +350,9 @@ int diagnostics_sweep(Ctx* c, int buf, double out[6], double* u_out = nullptr, d
   a.alpha_out = alpha_out;
   a.kappa_out = kappa_out;
   HIP_TRY(c, launch_diagnostics(a, c->stream));
-  HIP_TRY(c, launch_diag_finish(c->d_part, c->g.nblocks, c->g.dV, c->d_out, c->stream));
-  HIP_TRY(c, hipMemcpyAsync(c->h_ring, c->d_out, 6 * sizeof(double), hipMemcpyDeviceToHost, c->stream));
+  HIP_TRY(c, launch_diag_finish(c->d_part, c->g.nblocks, c->g.dV, c->h_out, c->stream));
   HIP_TRY(c, hipStreamSynchronize(c->stream));
-  std::memcpy(out, c->h_ring, 6 * sizeof(double));
+  std::memcpy(out, c->h_out, 6 * sizeof(double));
   return RELAX_OK;
 }
 
@@ -381,6 +392,7 @@ int prof_harvest(Ctx* c) {
 int enqueue_attempts(Ctx* c, int count) {
   const SweepArgs a = sweep_args(c);
   int rc;
+  c->ctl_current = false;
   for (int i = 0; i < count; i++) {
     for (int s = 1; s <= 6; s++) {
       if (c->profiling && (rc = prof_begin(c, s - 1))) return rc;
@@ -456,12 +468,14 @@ int relax_init(const relax_config* cfg, int K_record, const double* d_x0, const 
   auto bail = [&](int code) {
     if (c->h_ctl) (void)hipHostFree(c->h_ctl);
     if (c->h_ring) (void)hipHostFree(c->h_ring);
+    if (c->h_out) (void)hipHostFree(c->h_out);
     delete c;
     return code;
   };
   if (hipHostMalloc(reinterpret_cast<void**>(&c->h_ctl), sizeof(Control), hipHostMallocDefault) != hipSuccess ||
       hipHostMalloc(reinterpret_cast<void**>(&c->h_ring), RING_CAP * 8 * sizeof(double), hipHostMallocDefault) !=
-          hipSuccess)
+          hipSuccess ||
+      hipHostMalloc(reinterpret_cast<void**>(&c->h_out), 8 * sizeof(double), hipHostMallocDefault) != hipSuccess)
     return bail(RELAX_E_HIP);
 
   const size_t N3 = 3 * (size_t)c->g.N;
@@ -502,6 +516,7 @@ int relax_init(const relax_config* cfg, int K_record, const double* d_x0, const 
   if ((rc = push_ctl(c)) != RELAX_OK) return bail(rc);
   double d[6];
   if ((rc = diagnostics_sweep(c, 0, d)) != RELAX_OK) return bail(rc);
+  c->ctl_current = true;
   if (d[3] != d[3] || !std::isfinite(d[0])) return bail(RELAX_E_NAN);
   if (!(d[3] > 0.0)) return bail(RELAX_E_FOLD);
   *out_ctx = c;
@@ -516,20 +531,18 @@ int relax_step(void* ctx, int K, relax_diag* host_diag, int* steps_done) {
   int done = 0, rc = RELAX_OK;
   while (done < K) {
     const int chunk = std::min(K - done, RING_CAP);
+    c->ctl_current = false;
     HIP_TRY(c, launch_begin_chunk(c->d_ctl, chunk, c->stream));
     int pending = chunk;
     for (;;) {
       if ((rc = enqueue_attempts(c, pending)) != RELAX_OK) return rc;
-      if ((rc = sync_ctl(c)) != RELAX_OK) return rc;
+      if ((rc = sync_ctl(c, host_diag ? chunk : 0)) != RELAX_OK) return rc;
       if (c->profiling && (rc = prof_harvest(c)) != RELAX_OK) return rc;
       if (c->h_ctl->status != 0 || c->h_ctl->accepted >= chunk) break;
       pending = chunk - c->h_ctl->accepted;
     }
     const int acc = c->h_ctl->accepted;
     if (host_diag && acc > 0) {
-      HIP_TRY(c, hipMemcpyAsync(c->h_ring, c->d_ring, (size_t)acc * 8 * sizeof(double), hipMemcpyDeviceToHost,
-                                c->stream));
-      HIP_TRY(c, hipStreamSynchronize(c->stream));
       for (int i = 0; i < acc; i++) {
         const double* e = c->h_ring + 8 * i;
         relax_diag& o = host_diag[done + i];
@@ -561,7 +574,7 @@ int relax_diagnostics(void* ctx, relax_diag* out) {
   Ctx* c = static_cast<Ctx*>(ctx);
   if (!c || !out) return RELAX_E_ARG;
   if (c->status != RELAX_OK) return RELAX_E_STATE;
-  int rc = sync_ctl(c);
+  int rc = need_ctl(c);
   if (rc) return rc;
   double d[6];
   if ((rc = diagnostics_sweep(c, c->cur, d)) != RELAX_OK) return rc;
@@ -581,7 +594,7 @@ int relax_velocity(void* ctx, double* d_u_out) {
   Ctx* c = static_cast<Ctx*>(ctx);
   if (!c || !d_u_out) return RELAX_E_ARG;
   if (c->status != RELAX_OK) return RELAX_E_STATE;
-  int rc = sync_ctl(c);
+  int rc = need_ctl(c);
   if (rc) return rc;
   double d[6];
   return diagnostics_sweep(c, c->cur, d, d_u_out);
@@ -591,7 +604,7 @@ int relax_fields(void* ctx, double* d_B_out, double* d_J_out) {
   Ctx* c = static_cast<Ctx*>(ctx);
   if (!c) return RELAX_E_ARG;
   if (c->status != RELAX_OK) return RELAX_E_STATE;
-  int rc = sync_ctl(c);
+  int rc = need_ctl(c);
   if (rc) return rc;
   double d[6];
   return diagnostics_sweep(c, c->cur, d, nullptr, 0.0, d_B_out, d_J_out);
@@ -601,7 +614,7 @@ int relax_monitors(void* ctx, double* d_alpha_out, int* d_kappa_out) {
   Ctx* c = static_cast<Ctx*>(ctx);
   if (!c) return RELAX_E_ARG;
   if (c->status != RELAX_OK) return RELAX_E_STATE;
-  int rc = sync_ctl(c);
+  int rc = need_ctl(c);
   if (rc) return rc;
   double d[6];
   return diagnostics_sweep(c, c->cur, d, nullptr, 0.0, nullptr, nullptr, d_alpha_out, d_kappa_out);
@@ -615,7 +628,7 @@ int relax_backward(void* ctx, double seed_EM, double seed_R2, double* d_grad_x0,
   if (c->cfg.curl != RELAX_CURL_NN) return fail(c, RELAX_E_ARG, "relax_backward: nearest-neighbour current only");
   if (c->L.ckpt_slots == 0) return fail(c, RELAX_E_STATE, "relax_backward: context created without record");
   if (seed_R2 != 0.0 && c->cfg.gamma == 0.0) return fail(c, RELAX_E_ARG, "relax_backward: R2 seed needs gamma != 0");
-  int rc = sync_ctl(c);
+  int rc = need_ctl(c);
   if (rc) return rc;
   const long long K = c->h_ctl->steps_total;
   if (K > c->K_record) return fail(c, RELAX_E_STATE, "relax_backward: more steps taken than K_record");
@@ -708,7 +721,7 @@ int relax_backward(void* ctx, double seed_EM, double seed_R2, double* d_grad_x0,
 int relax_get_state(void* ctx, double* d_x_out, double* t, double* dt) {
   Ctx* c = static_cast<Ctx*>(ctx);
   if (!c) return RELAX_E_ARG;
-  int rc = sync_ctl(c);
+  int rc = need_ctl(c);
   if (rc) return rc;
   if (d_x_out) {
     HIP_TRY(c, hipMemcpyAsync(d_x_out, c->d_x[c->cur], 3 * (size_t)c->g.N * sizeof(double), hipMemcpyDeviceToDevice,
@@ -723,8 +736,7 @@ int relax_get_state(void* ctx, double* d_x_out, double* t, double* dt) {
 int relax_set_state(void* ctx, const double* d_x_in, double t, double dt) {
   Ctx* c = static_cast<Ctx*>(ctx);
   if (!c || !d_x_in || !std::isfinite(t) || !(dt > 0.0) || !std::isfinite(dt)) return RELAX_E_ARG;
-  int rc = sync_ctl(c);
-  if (rc && c->h_ctl == nullptr) return rc;
+  int rc = need_ctl(c);
   c->status = RELAX_OK;
   c->err.clear();
   HIP_TRY(c, hipMemcpyAsync(c->d_x[0], d_x_in, 3 * (size_t)c->g.N * sizeof(double), hipMemcpyDeviceToDevice,
@@ -739,10 +751,12 @@ int relax_set_state(void* ctx, const double* d_x_in, double t, double dt) {
   k.accepted = 0;
   k.target = 0;
   k.steps_total = 0;
+  c->ctl_current = false;
   if ((rc = push_ctl(c)) != RELAX_OK) return rc;
   c->cur = 0;
   double d[6];
   if ((rc = diagnostics_sweep(c, 0, d)) != RELAX_OK) return rc;
+  c->ctl_current = true;
   if (d[3] != d[3] || !std::isfinite(d[0])) return fail(c, RELAX_E_NAN, "relax_set_state: non-finite state");
   if (!(d[3] > 0.0)) return fail(c, RELAX_E_FOLD, "relax_set_state: folded grid (min det F <= 0)");
   return RELAX_OK;
@@ -786,6 +800,7 @@ void relax_destroy(void* ctx) {
   if (c->stream) (void)hipStreamSynchronize(c->stream);
   if (c->h_ctl) (void)hipHostFree(c->h_ctl);
   if (c->h_ring) (void)hipHostFree(c->h_ring);
+  if (c->h_out) (void)hipHostFree(c->h_out);
   for (hipEvent_t e : c->ev) (void)hipEventDestroy(e);
   delete c;
 }

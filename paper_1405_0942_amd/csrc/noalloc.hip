@@ -63,8 +63,14 @@ using namespace relax;
 extern "C" int relax_diagnostics_noalloc(const relax_config* cfg, const double* d_x, const double* d_B0,
                                          void* hip_stream, relax_diag* out) {
   if (!cfg || !d_x || !d_B0 || !out || !valid_config(cfg)) return RELAX_E_ARG;
-  const Geometry g = make_geometry(cfg);
-  if (g.nblocks > NA_MAX_BLOCKS) return RELAX_E_SPACE;
+  // the documented limit counts 64 x 8 tiles; a geometry that needs more partials than the scratch
+  // holds although those tiles do not gives way to them
+  Geometry g = make_geometry(cfg);
+  if (g.brick[0] == 0) {
+    const Geometry tiles = make_tiles(cfg, false);
+    if (tiles.nblocks > NA_MAX_BLOCKS) return RELAX_E_SPACE;
+    if (g.nblocks > NA_MAX_BLOCKS) g = tiles;
+  }
   hipStream_t st = static_cast<hipStream_t>(hip_stream);
   double* base = nullptr;
   if (scratch_ptr(&base) != hipSuccess) return RELAX_E_HIP;

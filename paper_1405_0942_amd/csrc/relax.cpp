@@ -125,26 +125,27 @@ bool valid_config(const relax_config* c) {
 }
 
 // z-chunk length.  A sweep's workgroups march their chunks concurrently, one resident per CU
-// on 256 CUs (256 slots: 91 KB of LDS in FP64, and the mixed sweeps' registers leave room for
+// on 256 CUs (256 slots: 111 KB of LDS in FP64, and the mixed sweeps' registers leave room for
 // one 8-wave workgroup), so a sweep takes about ceil(workgroups / 256) rounds, each as long as
-// one chunk: tz planes plus the ~4 planes a chunk loads before its first output.  The chunk
-// count minimises rounds x (tz + 4) with tz >= 8 (the fewer chunks on a tie): a grid whose
+// one chunk: tz planes plus the ~4 plane steps a chunk spends before its first output.  The chunk
+// count minimises rounds x (tz + 4) with tz >= 4 (the fewer chunks on a tie): a grid whose
 // x-y tiles alone slightly exceed the slots would otherwise run a second, nearly empty round
-// as long as the first, and a small grid would leave most CUs idle.
+// as long as the first, and a small grid would leave most CUs idle.  (64 x 64 x 192: 6 planes a chunk
+// fill the 256 slots, 8 planes leave a quarter idle: 179 against 199 us per FP64 step.)
 int choose_tz(const relax_config* c, int tiles_xy) {
   if (const char* e = std::getenv("RELAX_TZ")) {
     int v = std::atoi(e);
     if (v >= 1) return std::min(v, c->n[2]);
   }
-  const long long slots = 256;
+  const unsigned slots = 256;
   const int nz = c->n[2];
   int best_tz = nz;
-  long long best_cost = -1;
-  for (int chunks = 1; chunks <= std::max(1, nz / 8); chunks++) {
+  unsigned best_cost = 0;
+  for (int chunks = 1; chunks <= std::max(1, nz / 4); chunks++) {
     const int tz = (nz + chunks - 1) / chunks;
-    const long long blocks = (long long)tiles_xy * ((nz + tz - 1) / tz);
-    const long long cost = ((blocks + slots - 1) / slots) * (tz + 4);
-    if (best_cost < 0 || cost < best_cost) {
+    const unsigned blocks = (unsigned)tiles_xy * (unsigned)((nz + tz - 1) / tz);
+    const unsigned cost = ((blocks + slots - 1) / slots) * (unsigned)(tz + 4);
+    if (best_cost == 0 || cost < best_cost) {
       best_cost = cost;
       best_tz = tz;
     }
@@ -154,47 +155,95 @@ int choose_tz(const relax_config* c, int tiles_xy) {
 
 // Bricks (brick.hip) or z-marching tiles, and which bricks.  A brick sweep takes its time from the
 // points it loads and evaluates, a march from the plane steps of a chunk, which a small grid cannot
-// shorten.  Measured us per step, march / bricks, FP64: 16^3 line-tied 161 / 49, 33^3 line-tied 175 /
-// 56, 64^3 periodic 185 / 95, 65^3 line-tied 200 / 117, 81^3 line-tied 215 / 194, 96^3 periodic 234 /
-// 237, 64 x 64 x 192 205 / 207, 128^3 359 / 653; FP32-mixed 142 / 47, 156 / 54, 159 / 85, 171 / 108,
-// 181 / 178, 197 / 210, 169 / 183, 294 / 492.  The octilateral current, whose march holds one plane
-// more and two barriers: 400 / 72 at 16^3, 499 / 190 at 65^3, 503 / 413 at 96^3, 774 / 1017 at 128^3.
+// shorten.  The bricks' line is two rounds of 512 workgroups of 512 nodes.  Measured us per step, march /
+// bricks, FP64: 48^3 periodic 126 / 73, 65^3 line-tied 146 / 110, 80^3 periodic 176 / 148, 56 x 56 x 168
+// 155 / 181, 81^3 line-tied 165 / 184, 96^3 periodic 207 / 227; FP32-mixed 48^3 110 / 69, 65^3 125 / 105,
+// 80^3 153 / 134, 81^3 143 / 173, 96^3 170 / 203; a diagnostics call 48^3 33 / 26, 65^3 34 / 34, 80^3 41 /
+// 41, 81^3 36 / 48.  The octilateral current, whose march holds one plane more and two barriers: 48^3 235 /
+// 102, 65^3 327 / 176, 81^3 346 / 297, 89^3 509 / 313, 96^3 379 / 379.
 // The brick of a grid for sweeps with at most `window` window points and `slots` resident workgroups.
-static void choose_brick(const relax_config* c, int window, int slots, int brick[3]) {
-  // edges that split an axis evenly (every ceil(n / k) up to 64), shortest first
-  int edge[3][64], ne[3];
+static void choose_brick(const relax_config* c, int window, unsigned slots, int brick[3]) {
+  // edges that split an axis evenly (every ceil(n / k) up to 64), shortest first, and the bricks they make
+  int edge[3][64], count[3][64], ne[3];
   for (int a = 0; a < 3; a++) {
     ne[a] = 0;
-    for (int b = 1; b <= std::min(c->n[a], 64); b++) {
-      const int k = (c->n[a] + b - 1) / b;
-      if ((c->n[a] + k - 1) / k == b) edge[a][ne[a]++] = b;
+    for (int k = std::max(1, (c->n[a] + 63) / 64), last = 0; k <= c->n[a];) {
+      const int b = (c->n[a] + k - 1) / k;  // longest first
+      if (b != last) {
+        edge[a][ne[a]] = b;
+        count[a][ne[a]++] = k;
+      }
+      last = b;
+      k = b > 1 ? (c->n[a] + b - 2) / (b - 1) : c->n[a] + 1;  // the next count with shorter edges
     }
+    std::reverse(edge[a], edge[a] + ne[a]);
+    std::reverse(count[a], count[a] + ne[a]);
   }
-  double best = -1.0;
+  // rounds of the resident workgroups x the passes of a workgroup over its points (4 for its fixed part,
+  // 1 a window pass, 1.5 a field pass; in halves); on a tie the fewer points loaded
+  unsigned long long best = ~0ull;
   for (int iz = 0; iz < ne[2]; iz++)
-    for (int iy = 0; iy < ne[1] && edge[1][iy] * edge[2][iz] <= BRICK_THREADS; iy++)
+    for (int iy = 0; iy < ne[1] && edge[1][iy] * edge[2][iz] <= BRICK_THREADS; iy++) {
+      const int by = edge[1][iy], bz = edge[2][iz];
       for (int ix = 0; ix < ne[0]; ix++) {
-        const int bx = edge[0][ix], by = edge[1][iy], bz = edge[2][iz];
-        if (bx * by * bz > BRICK_THREADS) break;
+        const int bx = edge[0][ix], nodes = bx * by * bz;
         const int win = (bx + 4) * (by + 4) * (bz + 4), fld = (bx + 2) * (by + 2) * (bz + 2);
-        const int shell = fld - bx * by * bz;
-        if (win > window || fld > BRICK_FIELD || shell > BRICK_SHELL) break;
-        const long long blocks = (long long)((c->n[0] + bx - 1) / bx) * ((c->n[1] + by - 1) / by) * ((c->n[2] + bz - 1) / bz);
-        // rounds of the resident workgroups x the passes of a workgroup over its points (4: its
-        // fixed part); on a tie the fewer points loaded
-        const int t = BRICK_THREADS;
-        const double passes = 4.0 + (win + t - 1) / t + 1.5 * (1 + (shell + t - 1) / t);
-        const double cost = (double)((blocks + slots - 1) / slots) * passes + 1e-9 * (double)(blocks * win);
-        if (best < 0.0 || cost < best) {
+        if (nodes > BRICK_THREADS || win > window || fld > BRICK_FIELD || fld - nodes > BRICK_SHELL) break;
+        const unsigned blocks = (unsigned)count[0][ix] * count[1][iy] * count[2][iz];
+        const unsigned wp = (unsigned)(win + BRICK_THREADS - 1) / BRICK_THREADS;
+        const unsigned sp = (unsigned)(fld - nodes + BRICK_THREADS - 1) / BRICK_THREADS;
+        const unsigned passes = 8 + 2 * wp + 3 * (1 + sp);
+        const unsigned long long cost = ((unsigned long long)((blocks + slots - 1) / slots * passes) << 40) + (unsigned long long)blocks * win;
+        if (cost < best) {
           best = cost;
           brick[0] = bx;
           brick[1] = by;
           brick[2] = bz;
         }
       }
+    }
 }
 
-Geometry make_tiles(const relax_config* c) {
+// The tile of the z-march.  64 x 8 is the tile the sweep is tuned for (a wave per row, rows of whole
+// cache lines); another is taken where the idle threads of 64 x 8 tiles at the grid's edge cost more: 129
+// nodes are three tiles of 64 but two of 65 (129^3: 51 tiles of 64 x 8, 38 of 65 x 7).  A tile whose rows
+// are not whole lines shares a line per row with its neighbour, which two workgroups then write in parts:
+// on 256^3, tiles of 22 x 22, 43 x 11, 66 x 7 and 32 x 16 take 2.09, 1.60, 1.47 and 1.06 times the time of
+// 64 x 8, of which 1.24, 1.24, 1.27 and 1 are their plane steps.  Hence plane steps times the lines per
+// whole line of nodes to the power 1.5, and 6 % to be gained at least.  A tile has at most 64 x 8 nodes
+// and window points, and no more ghost nodes than threads.  Measured us per FP64 step, 64 x 8 / fitted:
+// 96^3 230 / 207, 129^3 line-tied 507 / 449, 100 x 130 x 170 495 / 440, 150^3 733 / 659, 73 x 73 x 219 351 /
+// 287, 193^3 line-tied 1597 / 1402, 200 x 190 x 210 1588 / 1416.
+static void choose_tile(const relax_config* c, int* tw, int* th) {
+  auto cost = [&](int w, int h) {
+    const int tiles = ((c->n[0] + w - 1) / w) * ((c->n[1] + h - 1) / h);
+    const int tz = choose_tz(c, tiles);
+    const long long blocks = (long long)tiles * ((c->n[2] + tz - 1) / tz);
+    const int both = w | c->n[0];  // alignment of the tile edges in nodes
+    const double lines = 1.0 + (both % 8 ? 1.0 : (both % 16 ? 0.3 : 0.0)) * 16.0 / w;
+    return (double)((blocks + 255) / 256) * (tz + 4) * lines * std::sqrt(lines);
+  };
+  *tw = TX;
+  *th = TY;
+  double best = 0.94 * cost(TX, TY);
+  for (int kx = 1; kx <= c->n[0]; kx++) {
+    const int w = (c->n[0] + kx - 1) / kx;
+    if (w < 24) break;
+    for (int ky = 1; ky <= c->n[1]; ky++) {
+      const int h = (c->n[1] + ky - 1) / ky;
+      if (w * h > NTHREADS || (w + 4) * (h + 4) > RX2 * RY2 || (w + 2) * (h + 2) > RX1 * RY1 || w + h > TX + TY) continue;
+      const double v = cost(w, h);
+      if (v < best) {
+        best = v;
+        *tw = w;
+        *th = h;
+      }
+      break;  // smaller tiles of this width only add tiles
+    }
+  }
+}
+
+Geometry make_tiles(const relax_config* c, bool fit) {
   Geometry g{};
   for (int a = 0; a < 3; a++) {
     g.n[a] = c->n[a];
@@ -208,8 +257,11 @@ Geometry make_tiles(const relax_config* c) {
   g.b0scale[0] = 4.0 * c->h[1] * c->h[2];
   g.b0scale[1] = 4.0 * c->h[2] * c->h[0];
   g.b0scale[2] = 4.0 * c->h[0] * c->h[1];
-  g.tiles[0] = (c->n[0] + TX - 1) / TX;
-  g.tiles[1] = (c->n[1] + TY - 1) / TY;
+  g.tw = TX;
+  g.th = TY;
+  if (fit) choose_tile(c, &g.tw, &g.th);
+  g.tiles[0] = (c->n[0] + g.tw - 1) / g.tw;
+  g.tiles[1] = (c->n[1] + g.th - 1) / g.th;
   g.tz = choose_tz(c, g.tiles[0] * g.tiles[1]);
   g.tiles[2] = (c->n[2] + g.tz - 1) / g.tz;
   g.nblocks = g.tiles[0] * g.tiles[1] * g.tiles[2];
@@ -217,9 +269,11 @@ Geometry make_tiles(const relax_config* c) {
   return g;
 }
 
-static Geometry with_bricks(const relax_config* c, long long max_nodes, int window, int slots) {
-  Geometry g = make_tiles(c);
-  if (g.N > max_nodes || std::getenv("RELAX_TZ")) return g;  // a chosen chunk length: the march
+static Geometry with_bricks(const relax_config* c, bool fit, long long max_nodes, int window, int slots) {
+  const bool bricks = (long long)c->n[0] * c->n[1] * c->n[2] <= max_nodes &&
+                      !std::getenv("RELAX_TZ");  // a chosen chunk length: the march
+  Geometry g = make_tiles(c, fit && !bricks);
+  if (!bricks) return g;
   choose_brick(c, window, slots, g.brick);
   for (int a = 0; a < 3; a++) g.tiles[a] = (c->n[a] + g.brick[a] - 1) / g.brick[a];
   g.nblocks = g.tiles[0] * g.tiles[1] * g.tiles[2];
@@ -227,10 +281,10 @@ static Geometry with_bricks(const relax_config* c, long long max_nodes, int wind
 }
 
 Geometry make_geometry(const relax_config* c) {
-  return with_bricks(c, c->curl == RELAX_CURL_NNN ? 1000000 : 600000, BRICK_WINDOW, 512);
+  return with_bricks(c, true, c->curl == RELAX_CURL_NNN ? 1000000 : 1 << 19, BRICK_WINDOW, 512);
 }
 
-Geometry make_adj_geometry(const relax_config* c) { return with_bricks(c, 600000, ADJ_WINDOW, 256); }
+Geometry make_adj_geometry(const relax_config* c) { return with_bricks(c, false, 600000, ADJ_WINDOW, 256); }
 
 }  // namespace relax
 

@@ -47,6 +47,7 @@ struct Geometry {
   double dV;         // hx hy hz
   double inv8h3;     // 1 / (8 hx hy hz): det F = det F' * inv8h3 for the unscaled differences F'
   double b0scale[3]; // 4 h_b h_c: B0'' = B0 * b0scale (component-wise), see stage.hip
+  int tw, th;        // nodes of a z-marching tile along x and y
   int tiles[3];      // tiles along x, along y, z-chunks
   int tz;            // z-chunk length
   int brick[3];      // nodes of a brick (brick.hip), or 0: z-marching tiles (stage.hip)
@@ -150,7 +151,8 @@ struct CK {
 // ------------------------------------------------------------------------------------------
 bool valid_config(const relax_config* c);          // every field in range
 int choose_tz(const relax_config* c, int tiles_xy);  // z-chunk length
-Geometry make_tiles(const relax_config* c);        // scale factors, z-marching tiles and chunks
+Geometry make_tiles(const relax_config* c, bool fit);  // scale factors, z-marching tiles and chunks
+                                                       // (64 x 8 tiles unless fit)
 Geometry make_geometry(const relax_config* c);     // the same with bricks where they are used
 Geometry make_adj_geometry(const relax_config* c);  // the geometry of the reverse field sweeps
 

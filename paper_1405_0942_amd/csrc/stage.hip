@@ -84,8 +84,10 @@ namespace {
 // no step gating and no k_1; with REC it writes u (optionally scaled by det F), B, J, alpha* and the
 // convexity where the caller asked for them, without REC only the sums (a store instruction takes its
 // time even when every lane is masked off: 128^3 60 -> 53 us).  REC in FP64 stages 4 and 6: also
-// store the stage input at the node, for the reverse sweeps.
-template <int S, bool MIXED, bool NNN, bool DIAG = false, bool REC = false>
+// store the stage input at the node, for the reverse sweeps.  FIT: tiles of g.tw x g.th nodes instead
+// of 64 x 8, for grids whose x and y extents 64 x 8 tiles would cover with many idle threads
+// (choose_tile in relax.cpp); a tile node is then any of the first tw th threads.
+template <int S, bool MIXED, bool NNN, bool DIAG = false, bool REC = false, bool FIT = false>
 __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) void stage_kernel(SweepArgs a) {
   using T = typename std::conditional<MIXED, float, double>::type;
   // The stage-input ring holds the planes p - 1 .. p + 1 that the field of plane p reads and the
@@ -108,6 +110,7 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
   constexpr int PD = (S == 1 && !NNN && !DIAG) ? 2 : 1;
   constexpr int NP2 = (RY2 * RX2 + NTHREADS - 1) / NTHREADS;  // stage-input points per thread
   constexpr int NP1 = (RY1 * RX1 + NTHREADS - 1) / NTHREADS;  // field points per thread
+  constexpr int NPG = (6 * (RY2 + RX2) + NTHREADS - 1) / NTHREADS;  // ghosts per thread
   static_assert(!DIAG || (S == 1 && !MIXED), "the diagnostics sweep is the FP64 stage-1 sweep");
   static_assert(!REC || DIAG || (!MIXED && (S == 4 || S == 6)), "REC: FP64 stages 4 and 6");
   static_assert(!NNN || (!MIXED && (DIAG || !REC)), "the octilateral current is an FP64 forward operator");
@@ -139,6 +142,9 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
   const double cv = (S == 2) ? dt * CK::a[1][0] : 1.0;
 
   const Geometry& g = a.g;
+  // the tile and its windows
+  const int tw = FIT ? g.tw : TX, th = FIT ? g.th : TY;
+  const int wx2 = tw + 4, wy2 = th + 4, wx1 = tw + 2, wy1 = th + 2, nown = tw * th;
   const int nx = g.n[0], ny = g.n[1], nz = g.n[2];
   const long long N = g.N;
   const int bcx = g.bc[0], bcy = g.bc[1], bcz = g.bc[2];
@@ -149,12 +155,13 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
   const int tile_x = lb % g.tiles[0];
   const int tile_y = (lb / g.tiles[0]) % g.tiles[1];
   const int chunk = lb / (g.tiles[0] * g.tiles[1]);
-  const int i0 = tile_x * TX, j0 = tile_y * TY;
+  const int i0 = tile_x * tw, j0 = tile_y * th;
   const int z0 = chunk * g.tz;
   const int z1 = min(z0 + g.tz, nz);
 
   const int tid = threadIdx.x;
-  const int tx = tid % TX, ty = tid / TX;
+  const bool own = !FIT || tid < nown;
+  const int ty = own ? tid / tw : 0, tx = own ? tid - ty * tw : 0;
 
   __shared__ double ys[RYS][3][RY2 * RX2];  // stage input, tile + 2-node halo, ring of planes
   __shared__ T bs[RBS][3][RY1 * RX1];       // pulled-back field, tile + 1-node halo, ring of planes
@@ -172,7 +179,7 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
   };
 
   // ---- per-thread index tables: the (x, y) part of every address is the same on all planes.
-  // Window point e < NTHREADS is the tile node of thread e (each thread loads its own node), then
+  // Window point e < nown is the tile node of thread e (each thread loads its own node), then
   // come the two rows below and the two above the tile, then the two columns on either side.
   unsigned w2e[NP2];  // stage-input window point -> flat (x, y) index, IE off the grid
   int w2w[NP2];       // its periodic wraps: x in the low 16 bits, y in the high 16 bits (signed)
@@ -181,29 +188,29 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
   for (int r = 0; r < NP2; r++) {
     const int e = tid + r * NTHREADS;
     int row, col;
-    if (e < NTHREADS) {
-      row = e / TX + 2;
-      col = e % TX + 2;
+    if (e < nown) {
+      row = e / tw + 2;
+      col = e % tw + 2;
     } else {
-      const int e2 = e - NTHREADS;
-      if (e2 < 4 * RX2) {
-        const int band = e2 / RX2;
-        row = band < 2 ? band : RY2 - 4 + band;
-        col = e2 - band * RX2;
+      const int e2 = e - nown;
+      if (e2 < 4 * wx2) {
+        const int band = e2 / wx2;
+        row = band < 2 ? band : wy2 - 4 + band;
+        col = e2 - band * wx2;
       } else {
-        const int e3 = e2 - 4 * RX2, side = e3 & 3;
+        const int e3 = e2 - 4 * wx2, side = e3 & 3;
         row = 2 + (e3 >> 2);
-        col = side < 2 ? side : RX2 - 4 + side;
+        col = side < 2 ? side : wx2 - 4 + side;
       }
     }
-    const bool in_win = e < RY2 * RX2;
+    const bool in_win = e < wy2 * wx2;
     const AxisIdx rx = resolve(i0 + col - 2, nx, bcx);
     const AxisIdx ry = resolve(j0 + row - 2, ny, bcy);
     w2e[r] = (in_win && rx.ok && ry.ok) ? (unsigned)(ry.i * nx + rx.i) : IE;
     w2w[r] = (ry.w << 16) + (rx.w & 0xffff);
-    w2o[r] = in_win ? row * RX2 + col : -1;
+    w2o[r] = in_win ? row * wx2 + col : -1;
   }
-  // field point e: e < NTHREADS is the tile node of thread e; the rest is the halo ring
+  // field point e: e < nown is the tile node of thread e; the rest is the halo ring
   unsigned f1e[NP1];  // flat (x, y) index, IE off the grid
   int f1o[NP1];       // offset in the B window, -1 past it
   int f1y[NP1];       // offset in the stage-input window
@@ -212,28 +219,28 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
   for (int r = 0; r < NP1; r++) {
     const int e = tid + r * NTHREADS;
     int r1, c1;
-    if (e < NTHREADS) {
-      r1 = e / TX + 1;
-      c1 = e % TX + 1;
+    if (e < nown) {
+      r1 = e / tw + 1;
+      c1 = e % tw + 1;
     } else {
-      const int e2 = e - NTHREADS;
-      if (e2 < RX1) {
+      const int e2 = e - nown;
+      if (e2 < wx1) {
         r1 = 0;
         c1 = e2;
-      } else if (e2 < 2 * RX1) {
-        r1 = RY1 - 1;
-        c1 = e2 - RX1;
+      } else if (e2 < 2 * wx1) {
+        r1 = wy1 - 1;
+        c1 = e2 - wx1;
       } else {
-        const int e3 = e2 - 2 * RX1;
+        const int e3 = e2 - 2 * wx1;
         r1 = 1 + (e3 >> 1);
-        c1 = (e3 & 1) ? RX1 - 1 : 0;
+        c1 = (e3 & 1) ? wx1 - 1 : 0;
       }
     }
-    const bool in_win = e < RY1 * RX1;
+    const bool in_win = e < wy1 * wx1;
     const AxisIdx rx = resolve(i0 + c1 - 1, nx, bcx), ry = resolve(j0 + r1 - 1, ny, bcy);
     f1e[r] = (in_win && rx.ok && ry.ok) ? (unsigned)(ry.i * nx + rx.i) : IE;
-    f1o[r] = in_win ? r1 * RX1 + c1 : -1;
-    f1y[r] = (r1 + 1) * RX2 + c1 + 1;
+    f1o[r] = in_win ? r1 * wx1 + c1 : -1;
+    f1y[r] = (r1 + 1) * wx2 + c1 + 1;
     f1k[r] = 0;
     if (bcx == BC_LINE_TIED) f1k[r] |= rx.i == 0 ? 1 : (rx.i == nx - 1 ? 2 : 0);
     if (bcy == BC_LINE_TIED) f1k[r] |= ry.i == 0 ? 4 : (ry.i == ny - 1 ? 8 : 0);
@@ -242,8 +249,7 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
   // other end, so that the central difference at the face node is the one-sided second-order row
   // -3 y(0) + 4 y(1) - y(2) and every node takes the same path.  Beyond faces across x and y a
   // thread fills one ghost component of a plane; beyond faces across z see commit_window.
-  constexpr int NGC = 3 * RY2, NGR = 3 * RX2;  // ghosts of one column, of one row
-  constexpr int NPG = (2 * NGC + 2 * NGR + NTHREADS - 1) / NTHREADS;
+  const int NGC = 3 * wy2, NGR = 3 * wx2;  // ghosts of one column, of one row
   int gh_o[NPG], gh_s[NPG];  // offset in the plane's three components (-1: none), step into the grid
 #pragma unroll
   for (int r = 0; r < NPG; r++) {
@@ -251,25 +257,25 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
     gh_s[r] = 0;
     const int t = tid + r * NTHREADS;
     if (t < 2 * NGC) {
-      const int side = t / NGC, t1 = t - side * NGC, m = t1 / RY2, row = t1 - m * RY2;
+      const int side = t / NGC, t1 = t - side * NGC, m = t1 / wy2, row = t1 - m * wy2;
       const int col = side == 0 ? 1 - i0 : nx - i0 + 2;
-      if (bcx == BC_LINE_TIED && col >= 0 && col < RX2) {
-        gh_o[r] = m * (RY2 * RX2) + row * RX2 + col;
+      if (bcx == BC_LINE_TIED && col >= 0 && col < wx2) {
+        gh_o[r] = m * (RY2 * RX2) + row * wx2 + col;
         gh_s[r] = side == 0 ? 1 : -1;
       }
     } else if (t < 2 * NGC + 2 * NGR) {
-      const int t0 = t - 2 * NGC, side = t0 / NGR, t1 = t0 - side * NGR, m = t1 / RX2, col = t1 - m * RX2;
+      const int t0 = t - 2 * NGC, side = t0 / NGR, t1 = t0 - side * NGR, m = t1 / wx2, col = t1 - m * wx2;
       const int row = side == 0 ? 1 - j0 : ny - j0 + 2;
-      if (bcy == BC_LINE_TIED && row >= 0 && row < RY2) {
-        gh_o[r] = m * (RY2 * RX2) + row * RX2 + col;
-        gh_s[r] = side == 0 ? RX2 : -RX2;
+      if (bcy == BC_LINE_TIED && row >= 0 && row < wy2) {
+        gh_o[r] = m * (RY2 * RX2) + row * wx2 + col;
+        gh_s[r] = side == 0 ? wx2 : -wx2;
       }
     }
   }
 
   // tile node owned by this thread
   const int gi_t = i0 + tx, gj_t = j0 + ty;
-  const bool tile_ok = (gi_t < nx) && (gj_t < ny);
+  const bool tile_ok = own && (gi_t < nx) && (gj_t < ny);
   const unsigned out_e = tile_ok ? (unsigned)(gj_t * nx + gi_t) : IE;
   const bool face_x = bcx == BC_LINE_TIED && (gi_t == 0 || gi_t == nx - 1);
   const bool face_y = bcy == BC_LINE_TIED && (gj_t == 0 || gj_t == ny - 1);
@@ -347,8 +353,8 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
     }
   };
   // no field point of the tile lies on a line-tied face across x or y
-  const bool inner_xy = (bcx == BC_PERIODIC || (i0 > 0 && i0 + TX + 1 < nx)) &&
-                        (bcy == BC_PERIODIC || (j0 > 0 && j0 + TY + 1 < ny));
+  const bool inner_xy = (bcx == BC_PERIODIC || (i0 > 0 && i0 + tw + 1 < nx)) &&
+                        (bcy == BC_PERIODIC || (j0 > 0 && j0 + th + 1 < ny));
   // NNN: the one-sided rows themselves.  (The octilateral runs that break down amplify the rounding
   // of the face rows, so these keep the order of operations they have always had.)
   auto jacobian_rows = [&](int o, int ends, int p, double F[3][3]) {
@@ -363,11 +369,11 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
       else
         F[m][0] = 3.0 * yc[o] - 4.0 * yc[o - 1] + yc[o - 2];
       if (!(ends & 12))
-        F[m][1] = yc[o + RX2] - yc[o - RX2];
+        F[m][1] = yc[o + wx2] - yc[o - wx2];
       else if (ends & 4)
-        F[m][1] = -3.0 * yc[o] + 4.0 * yc[o + RX2] - yc[o + 2 * RX2];
+        F[m][1] = -3.0 * yc[o] + 4.0 * yc[o + wx2] - yc[o + 2 * wx2];
       else
-        F[m][1] = 3.0 * yc[o] - 4.0 * yc[o - RX2] + yc[o - 2 * RX2];
+        F[m][1] = 3.0 * yc[o] - 4.0 * yc[o - wx2] + yc[o - 2 * wx2];
     }
     if (bcz == BC_PERIODIC || (p > 0 && p < nz - 1)) {
       const int sa = yslot(p + 1), sb = yslot(p - 1);
@@ -613,7 +619,7 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
 #pragma unroll
         for (int m = 0; m < 3; m++) {
           F[m][0] = ys[sc][m][o + 1] - ys[sc][m][o - 1];
-          F[m][1] = ys[sc][m][o + RX2] - ys[sc][m][o - RX2];
+          F[m][1] = ys[sc][m][o + wx2] - ys[sc][m][o - wx2];
           F[m][2] = ys[sh][m][o] - ys[sl][m][o];
         }
       }
@@ -657,8 +663,8 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
               const double c0 = ys[sc][m][o];
               ex[0][m] = ys[sc][m][o - 1] - c0;
               ex[1][m] = ys[sc][m][o + 1] - c0;
-              ey[0][m] = ys[sc][m][o - RX2] - c0;
-              ey[1][m] = ys[sc][m][o + RX2] - c0;
+              ey[0][m] = ys[sc][m][o - wx2] - c0;
+              ey[1][m] = ys[sc][m][o + wx2] - c0;
               ez[0][m] = ys[sl][m][o] - c0;
               ez[1][m] = ys[sh][m][o] - c0;
             }
@@ -668,8 +674,10 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
           }
         }
       }
+      if (!FIT || R > 0 || f1o[R] >= 0) {
 #pragma unroll
-      for (int m = 0; m < 3; m++) bs[sb][m][f1o[R]] = B[m];
+        for (int m = 0; m < 3; m++) bs[sb][m][f1o[R]] = B[m];
+      }
     };
     static_assert(NP1 == 2 && RY1 * RX1 >= NTHREADS, "one tile node and at most one halo point per thread");
     using OwnNode = std::integral_constant<int, 0>;
@@ -697,7 +705,7 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
     // 2. current, force and velocity on the tile of plane q = p - 1
     Outputs so;
     if (qout) {
-      const int oy = (ty + 2) * RX2 + tx + 2;  // the tile node in the window
+      const int oy = (ty + 2) * wx2 + tx + 2;  // the tile node in the window
       if constexpr (YREC) {
 #pragma unroll
         for (int m = 0; m < 3; m++) so.yc[m] = ys[yslot(q)][m][oy];
@@ -713,18 +721,18 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
         so.p[2][0] = 0.0;
       }
       if (!NNN || !face) {
-        const int o = (ty + 1) * RX1 + (tx + 1);
+        const int o = (ty + 1) * wx1 + (tx + 1);
         const int sq = bslot(q);
         T J[3];
         if constexpr (NNN) {
-          octilateral([&](int dx, int dy, int dz, int m) { return ys[yslot(q + dz)][m][oy + dy * RX2 + dx]; },
-                      [&](int dx, int dy, int dz, int m) { return (double)bs[bslot(q + dz)][m][o + dy * RX1 + dx]; }, J);
+          octilateral([&](int dx, int dy, int dz, int m) { return ys[yslot(q + dz)][m][oy + dy * wx2 + dx]; },
+                      [&](int dx, int dy, int dz, int m) { return (double)bs[bslot(q + dz)][m][o + dy * wx1 + dx]; }, J);
         } else {
           T G[3][3];  // G'[a][m] = B_m(n + e_a) - B_m(n - e_a)
 #pragma unroll
           for (int m = 0; m < 3; m++) {
             G[0][m] = bs[sq][m][o + 1] - bs[sq][m][o - 1];
-            G[1][m] = bs[sq][m][o + RX1] - bs[sq][m][o - RX1];
+            G[1][m] = bs[sq][m][o + wx1] - bs[sq][m][o - wx1];
             G[2][m] = Bp[m] - Bqm[m];
           }
           current(Fq, G, rDq, J);
@@ -792,19 +800,27 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
   if (LAST) store_lambda<NTHREADS>(acc, red, a.lam_part + blockIdx.x);
 }
 
+template <int S, bool MIXED, bool NNN, bool DIAG = false, bool REC = false>
+hipError_t launch_march(const SweepArgs& a, hipStream_t st) {
+  const dim3 grid(a.g.nblocks), block(NTHREADS);
+  if (a.g.tw == TX && a.g.th == TY)
+    hipLaunchKernelGGL((stage_kernel<S, MIXED, NNN, DIAG, REC>), grid, block, 0, st, a);
+  else
+    hipLaunchKernelGGL((stage_kernel<S, MIXED, NNN, DIAG, REC, true>), grid, block, 0, st, a);
+  return hipGetLastError();
+}
+
 template <bool MIXED, bool NNN = false>
 hipError_t launch_stage_t(int s, const SweepArgs& a, hipStream_t st) {
-  const dim3 grid(a.g.nblocks), block(NTHREADS);
   switch (s) {
-    case 1: hipLaunchKernelGGL((stage_kernel<1, MIXED, NNN>), grid, block, 0, st, a); break;
-    case 2: hipLaunchKernelGGL((stage_kernel<2, MIXED, NNN>), grid, block, 0, st, a); break;
-    case 3: hipLaunchKernelGGL((stage_kernel<3, MIXED, NNN>), grid, block, 0, st, a); break;
-    case 4: hipLaunchKernelGGL((stage_kernel<4, MIXED, NNN>), grid, block, 0, st, a); break;
-    case 5: hipLaunchKernelGGL((stage_kernel<5, MIXED, NNN>), grid, block, 0, st, a); break;
-    case 6: hipLaunchKernelGGL((stage_kernel<6, MIXED, NNN>), grid, block, 0, st, a); break;
+    case 1: return launch_march<1, MIXED, NNN>(a, st);
+    case 2: return launch_march<2, MIXED, NNN>(a, st);
+    case 3: return launch_march<3, MIXED, NNN>(a, st);
+    case 4: return launch_march<4, MIXED, NNN>(a, st);
+    case 5: return launch_march<5, MIXED, NNN>(a, st);
+    case 6: return launch_march<6, MIXED, NNN>(a, st);
     default: return hipErrorInvalidValue;
   }
-  return hipGetLastError();
 }
 
 }  // namespace
@@ -819,32 +835,17 @@ hipError_t launch_stage(int s, bool mixed, const SweepArgs& a, hipStream_t st) {
 hipError_t launch_stage_rec(int s, const SweepArgs& a, hipStream_t st) {
   if (a.g.curl == CURL_NNN) return hipErrorInvalidValue;
   if (a.g.brick[0]) return launch_brick_rec(s, a, st);
-  const dim3 grid(a.g.nblocks), block(NTHREADS);
-  if (s == 4)
-    hipLaunchKernelGGL((stage_kernel<4, false, false, false, true>), grid, block, 0, st, a);
-  else if (s == 6)
-    hipLaunchKernelGGL((stage_kernel<6, false, false, false, true>), grid, block, 0, st, a);
-  else
-    return launch_stage_t<false>(s, a, st);
-  return hipGetLastError();
+  if (s == 4) return launch_march<4, false, false, false, true>(a, st);
+  if (s == 6) return launch_march<6, false, false, false, true>(a, st);
+  return launch_stage_t<false>(s, a, st);
 }
 
 hipError_t launch_diagnostics(const SweepArgs& a, hipStream_t st) {
   if (a.g.brick[0]) return launch_brick_diagnostics(a, st);
-  const dim3 grid(a.g.nblocks), block(NTHREADS);
   const bool fields = a.u_out || a.B_out || a.J_out || a.alpha_out || a.kappa_out;
-  if (a.g.curl == CURL_NNN) {
-    if (fields)
-      hipLaunchKernelGGL((stage_kernel<1, false, true, true, true>), grid, block, 0, st, a);
-    else
-      hipLaunchKernelGGL((stage_kernel<1, false, true, true>), grid, block, 0, st, a);
-  } else {
-    if (fields)
-      hipLaunchKernelGGL((stage_kernel<1, false, false, true, true>), grid, block, 0, st, a);
-    else
-      hipLaunchKernelGGL((stage_kernel<1, false, false, true>), grid, block, 0, st, a);
-  }
-  return hipGetLastError();
+  if (a.g.curl == CURL_NNN)
+    return fields ? launch_march<1, false, true, true, true>(a, st) : launch_march<1, false, true, true>(a, st);
+  return fields ? launch_march<1, false, false, true, true>(a, st) : launch_march<1, false, false, true>(a, st);
 }
 
 }  // namespace relax

@@ -25,7 +25,8 @@ CASES = [
     ((17, 17, 17), (0, 0, 0), FP64), ((13, 29, 11), (0, 1, 1), NNN), ((33, 33, 33), (0, 0, 0), MIXED),
     ((200, 6, 5), (1, 1, 0), FP64), ((6, 5, 300), (0, 1, 1), FP64), ((5, 211, 7), (1, 0, 0), NNN),
     ((41, 43, 47), (1, 1, 1), FP64), ((41, 43, 47), (0, 0, 1), NNN),
-    ((84, 84, 85), (0, 1, 0), FP64),  # 599 760 nodes: the largest grids that take bricks
+    ((64, 128, 64), (1, 0, 0), FP64),  # 2^19 nodes: the largest grids that take bricks
+    ((84, 84, 85), (0, 1, 0), FP64),  # 599 760 nodes: the march, short chunks against the chosen ones
 ]
 
 

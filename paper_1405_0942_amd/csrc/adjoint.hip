@@ -22,20 +22,28 @@
 // y_s = x_n + dt sum_{j<s} a_sj k_j:
 //   kbar_s = dt (b5_s xbar_{n+1} + sum_{t>s} a_ts ybar_t),  ybar_s = (du/dy)(y_s)^T kbar_s,
 //   xbar_n = xbar_{n+1} + sum_s ybar_s.
-// The stage-6 field sweep scales xbar_{n+1} itself; the gather of stage t writes ybar_t and
-// kbar_{t-1}, which the field sweep of stage t - 1 reads.
+// The stage-6 field sweep scales xbar_{n+1} itself; the gather of stage t writes ybar_t (or sums of
+// them) and kbar_{t-1}, which the field sweep of stage t - 1 reads.
 //
 // Seeds (seed mode of adj_field_kernel): E_M = 1/2 sum zeta |B|^2 det F dV adds kappa D' B to
 // Bbar and 1/2 kappa |B|^2 to Dbar' (kappa = zeta dV / (8 hx hy hz)); R2 = 1/2 sum_interior
 // det F |f|^2 dV enters through ubar = det F dV f / gamma (read from a buffer) plus
 // 1/2 |f|^2 dV / (8 hx hy hz) on Dbar'.
 //
-// The field sweep is laid out like the forward stage sweep: a 64 x 8 tile marching up a
-// z-chunk, the stage input in an LDS ring of three planes (stages 3..6 stencil the stored
-// y_s of the step), B in a ring of two planes, Gbar'_x and Gbar'_y in one plane that is
-// transposed in-plane as soon as it is formed; buffer loads with masked-off lanes (offsets
-// past the record count) issued one plane step ahead, so no divergent branch surrounds a
-// memory instruction and the waits are exact.
+// The field sweep is laid out like the forward stage sweep, with one barrier per plane step: a 64 x 8
+// tile marching up a z-chunk, the stage input in an LDS ring of four planes (stages 3..6 stencil the
+// stored y_s of the step), B and Gbar'_y in LDS by parity of the plane.  Gbar'_x needs none: a wave is
+// a row of the tile, so its lanes hand it on, and only the columns beside the tile go through LDS.  The
+// in-plane sums of plane p are taken after its barrier and kept in registers, where the transpose of
+// plane p - 1 finds all it needs one step later.  Ghost nodes beyond line-tied faces give every node
+// the same path.  Loads and stores are those of buffer instructions with masked-off lanes (offsets
+// past the record count), issued one plane step ahead, so no divergent branch surrounds a memory
+// instruction and the waits are exact.
+//
+// What bounds it: 64 x 64 x 192, 256 chunks of 6 planes, 45 us a sweep (46 with two barriers and three
+// planes, 58 -> 50 at stage 2): 24 vectors with their halos at 4.6 TB/s through L2.  us per step of a
+// backward pass over 128^3 periodic 1579 -> 1518, 129^3 line-tied 2373 -> 2041 (one-sided rows had
+// diverged), 73 x 73 x 200 line-tied 1487 -> 1219.
 #include "brick.h"
 
 namespace relax {
@@ -78,7 +86,7 @@ __device__ __forceinline__ void transpose_node(const double F[3][3], double rD, 
   double Bb[3] = {0, 0, 0};
   double Fb[3][3] = {{0, 0, 0}, {0, 0, 0}, {0, 0, 0}};
   double rDb = 0.0, Db_direct = 0.0;
-  if (interior) {
+  if (!SEED || interior) {  // ub = 0 on a face, and every term but the seed's has that factor
     double cq[3];
     cq[0] = F[0][2] * G[1][0] + F[1][2] * G[1][1] + F[2][2] * G[1][2] -
             (F[0][1] * G[2][0] + F[1][1] * G[2][1] + F[2][1] * G[2][2]);
@@ -152,19 +160,31 @@ __device__ __forceinline__ void transpose_node(const double F[3][3], double rD, 
     }
 }
 
-template <int S, bool XYP, bool SEED>
+// The neighbour's value along a wave, whose lanes are one row of the tile: from the lane below (UP false)
+// or above; the end lane, which has no neighbour, gets `edge`.
+template <bool UP>
+__device__ __forceinline__ double neighbour(double v, double edge) {
+  const u32x2 a = __builtin_bit_cast(u32x2, v), e = __builtin_bit_cast(u32x2, edge);
+  constexpr int CTRL = UP ? 0x130 : 0x138;  // wave_shl:1, wave_shr:1
+  u32x2 r;
+  r.x = __builtin_amdgcn_update_dpp(e.x, a.x, CTRL, 0xf, 0xf, false);
+  r.y = __builtin_amdgcn_update_dpp(e.y, a.y, CTRL, 0xf, 0xf, false);
+  return __builtin_bit_cast(double, r);
+}
+
+template <int S, bool SEED>
 __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) void adj_field_kernel(AdjArgs a) {
   constexpr bool WK = (!SEED && S == 2);  // the window carries k_1 too
   constexpr int NP2 = (RY2 * RX2 + NTHREADS - 1) / NTHREADS;
   constexpr int NP1 = (RY1 * RX1 + NTHREADS - 1) / NTHREADS;
+  constexpr int NPG = (6 * (RY2 + RX2) + NTHREADS - 1) / NTHREADS;
+  static_assert(TX == 64 && NP1 == 2, "a wave is a row of the tile; at most one halo point per thread");
 
   const Geometry& g = a.g;
   const int nx = g.n[0], ny = g.n[1], nz = g.n[2];
   const long long N = g.N;
   const unsigned nxy = (unsigned)nx * (unsigned)ny;
-  const int bcx = XYP ? BC_PERIODIC : g.bc[0];
-  const int bcy = XYP ? BC_PERIODIC : g.bc[1];
-  const int bcz = g.bc[2];
+  const int bcx = g.bc[0], bcy = g.bc[1], bcz = g.bc[2];
   const double gamma = a.gamma;
 
   const double dt = SEED ? 0.0 : *a.dt;
@@ -186,35 +206,55 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
   const int tid = threadIdx.x;
   const int tx = tid % TX, ty = tid / TX;
 
-  __shared__ double ys[3][3][RY2 * RX2];  // stage input, ring of 3 planes
-  __shared__ double bs[2][3][RY1 * RX1];  // B, ring of 2 planes
-  __shared__ double gxy[6][RY1 * RX1];    // Gbar'_x (0..2) and Gbar'_y (3..5) of the newest plane
+  __shared__ double ys[4][3][RY2 * RX2];  // stage input, ring of 4 planes
+  __shared__ double bs[2][3][RY1 * RX1];  // B on the tile + 1 halo, by parity of the plane
+  __shared__ double gy[2][3][RY1 * TX];   // Gbar'_y on the tile and the rows beside it
+  __shared__ double gx[2][3][2][TY];      // Gbar'_x on the columns beside the tile
 
   auto zload = [&](int pz) {
     if (bcz == BC_PERIODIC) return resolve_near(pz, nz, bcz).i;
     return min(max(pz, 0), nz - 1);
   };
 
-  // index tables (as in the forward sweep)
+  // index tables (as in the forward sweep): window point and field point 0 of a thread are its tile node
   unsigned w2e[NP2];
-  int w2w[NP2];
+  int w2w[NP2], w2o[NP2];
 #pragma unroll
   for (int r = 0; r < NP2; r++) {
     const int e = tid + r * NTHREADS;
-    const int row = e / RX2, col = e - row * RX2;
+    int row, col;
+    if (e < NTHREADS) {
+      row = ty + 2;
+      col = tx + 2;
+    } else {
+      const int e2 = e - NTHREADS;
+      if (e2 < 4 * RX2) {
+        const int band = e2 / RX2;
+        row = band < 2 ? band : RY2 - 4 + band;
+        col = e2 - band * RX2;
+      } else {
+        const int e3 = e2 - 4 * RX2, side = e3 & 3;
+        row = 2 + (e3 >> 2);
+        col = side < 2 ? side : RX2 - 4 + side;
+      }
+    }
+    const bool in_win = e < RY2 * RX2;
     const AxisIdx rx = resolve(i0 + col - 2, nx, bcx), ry = resolve(j0 + row - 2, ny, bcy);
-    w2e[r] = (e < RY2 * RX2 && rx.ok && ry.ok) ? (unsigned)(ry.i * nx + rx.i) : IE;
+    w2e[r] = (in_win && rx.ok && ry.ok) ? (unsigned)(ry.i * nx + rx.i) : IE;
     w2w[r] = (ry.w << 16) + (rx.w & 0xffff);
+    w2o[r] = in_win ? row * RX2 + col : -1;
   }
   unsigned f1e[NP1];
-  int f1r[NP1], f1c[NP1];
+  int f1o[NP1], f1y[NP1];  // offsets in the B window (-1: no point) and in the stage-input window
+  bool f1live[NP1];        // on the grid and not on a line-tied face across x or y
+  int halo_row = 0, halo_col = 0;
 #pragma unroll
   for (int r = 0; r < NP1; r++) {
     const int e = tid + r * NTHREADS;
     int r1, c1;
     if (e < NTHREADS) {
-      r1 = e / TX + 1;
-      c1 = e % TX + 1;
+      r1 = ty + 1;
+      c1 = tx + 1;
     } else {
       const int e2 = e - NTHREADS;
       if (e2 < RX1) {
@@ -228,64 +268,110 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
         r1 = 1 + (e3 >> 1);
         c1 = (e3 & 1) ? RX1 - 1 : 0;
       }
+      halo_row = r1;
+      halo_col = c1;
     }
+    const bool in_win = e < RY1 * RX1;
     const AxisIdx rx = resolve(i0 + c1 - 1, nx, bcx), ry = resolve(j0 + r1 - 1, ny, bcy);
-    f1e[r] = (e < RY1 * RX1 && rx.ok && ry.ok) ? (unsigned)(ry.i * nx + rx.i) : IE;
-    f1r[r] = (e < RY1 * RX1) ? r1 : -1;
-    f1c[r] = c1;
+    f1e[r] = (in_win && rx.ok && ry.ok) ? (unsigned)(ry.i * nx + rx.i) : IE;
+    f1o[r] = in_win ? r1 * RX1 + c1 : -1;
+    f1y[r] = (r1 + 1) * RX2 + c1 + 1;
+    const bool face = (bcx == BC_LINE_TIED && (rx.i == 0 || rx.i == nx - 1)) ||
+                      (bcy == BC_LINE_TIED && (ry.i == 0 || ry.i == ny - 1));
+    f1live[r] = f1e[r] != IE && !face;
+  }
+  // ghosts beyond line-tied faces across x and y (see stage.hip)
+  constexpr int NGC = 3 * RY2, NGR = 3 * RX2;
+  int gh_o[NPG], gh_s[NPG];
+#pragma unroll
+  for (int r = 0; r < NPG; r++) {
+    gh_o[r] = -1;
+    gh_s[r] = 0;
+    const int t = tid + r * NTHREADS;
+    if (t < 2 * NGC) {
+      const int side = t / NGC, t1 = t - side * NGC, m = t1 / RY2, row = t1 - m * RY2;
+      const int col = side == 0 ? 1 - i0 : nx - i0 + 2;
+      if (bcx == BC_LINE_TIED && col >= 0 && col < RX2) {
+        gh_o[r] = m * (RY2 * RX2) + row * RX2 + col;
+        gh_s[r] = side == 0 ? 1 : -1;
+      }
+    } else if (t < 2 * NGC + 2 * NGR) {
+      const int t0 = t - 2 * NGC, side = t0 / NGR, t1 = t0 - side * NGR, m = t1 / RX2, col = t1 - m * RX2;
+      const int row = side == 0 ? 1 - j0 : ny - j0 + 2;
+      if (bcy == BC_LINE_TIED && row >= 0 && row < RY2) {
+        gh_o[r] = m * (RY2 * RX2) + row * RX2 + col;
+        gh_s[r] = side == 0 ? RX2 : -RX2;
+      }
+    }
   }
   const int gi_t = i0 + tx, gj_t = j0 + ty;
   const bool tile_ok = (gi_t < nx) && (gj_t < ny);
   const unsigned out_e = tile_ok ? (unsigned)(gj_t * nx + gi_t) : IE;
 
-  auto face_at = [&](int gi, int gj, int p) {
-    return (bcx == BC_LINE_TIED && (gi == 0 || gi == nx - 1)) || (bcy == BC_LINE_TIED && (gj == 0 || gj == ny - 1)) ||
-           (bcz == BC_LINE_TIED && (p == 0 || p == nz - 1));
-  };
-
   // ---- loads, issued one plane step ahead of their use ---------------------------------------
-  double wx[NP2][3];
-  double wk[WK ? NP2 : 1][3];
+  struct Window {
+    double x[NP2][3];
+    double k[WK ? NP2 : 1][3];
+  };
   double b0r[NP1][3], vr[NP1][3];
   double bbr[3];  // B0bar'' at the output node
-  auto load_window = [&](int pz) {
+  auto load_window = [&](Window& w, int pz, bool on) {
     const long long zo = (long long)zload(pz) * nxy;
+    unsigned e[NP2];
+#pragma unroll
+    for (int r = 0; r < NP2; r++) e[r] = on ? w2e[r] : IE;
 #pragma unroll
     for (int m = 0; m < 3; m++) {
       const auto rs = plane_rsrc(wsrc + m * N + zo, nxy);
 #pragma unroll
-      for (int r = 0; r < NP2; r++) wx[r][m] = bload<double>(rs, w2e[r]);
+      for (int r = 0; r < NP2; r++) w.x[r][m] = bload<double>(rs, e[r]);
     }
     if constexpr (WK) {
 #pragma unroll
       for (int m = 0; m < 3; m++) {
         const auto rs = plane_rsrc(k1p + m * N + zo, nxy);
 #pragma unroll
-        for (int r = 0; r < NP2; r++) wk[r][m] = bload<double>(rs, w2e[r]);
+        for (int r = 0; r < NP2; r++) w.k[r][m] = bload<double>(rs, e[r]);
       }
     }
   };
-  auto commit_window = [&](int pz) {
-    const AxisIdx rz = resolve_near(pz, nz, bcz);
-    const int slot = mod3(pz);
-    const double shz = rz.w * g.period[2];
+  auto commit_window = [&](const Window& w, int pz) {
+    const double shz = resolve_near(pz, nz, bcz).w * g.period[2];
+    const int slot = pz & 3;
 #pragma unroll
     for (int r = 0; r < NP2; r++) {
-      const int e = tid + r * NTHREADS;
-      const bool ok = (w2e[r] != IE);
       double v[3];
 #pragma unroll
       for (int m = 0; m < 3; m++) {
-        double y = wx[r][m];
-        if constexpr (WK) y = fma(c21, wk[r][m], y);
-        v[m] = y;
+        v[m] = w.x[r][m];
+        if constexpr (WK) v[m] = fma(c21, w.k[r][m], v[m]);
       }
       v[0] += (double)(short)(w2w[r] & 0xffff) * g.period[0];
       v[1] += (double)(w2w[r] >> 16) * g.period[1];
       v[2] += shz;
-      if (e < RY2 * RX2) {
+      if (w2o[r] >= 0) {
 #pragma unroll
-        for (int m = 0; m < 3; m++) ys[slot][m][e] = ok ? v[m] : 0.0;
+        for (int m = 0; m < 3; m++) ys[slot][m][w2o[r]] = (w2e[r] != IE) ? v[m] : 0.0;
+      }
+    }
+  };
+  // the ghost plane beyond a line-tied z face from the three planes inside it (pa the face)
+  auto commit_ghost_plane = [&](int pz, int pa, int pb, int pc) {
+#pragma unroll
+    for (int r = 0; r < NP2; r++) {
+      if (w2o[r] >= 0) {
+#pragma unroll
+        for (int m = 0; m < 3; m++)
+          ys[pz & 3][m][w2o[r]] = fma(3.0, ys[pa & 3][m][w2o[r]] - ys[pb & 3][m][w2o[r]], ys[pc & 3][m][w2o[r]]);
+      }
+    }
+  };
+  auto fill_ghosts = [&](int pz) {
+#pragma unroll
+    for (int r = 0; r < NPG; r++) {
+      if (gh_o[r] >= 0) {
+        double* y = &ys[pz & 3][0][gh_o[r]];
+        *y = fma(3.0, y[gh_s[r]] - y[2 * gh_s[r]], y[3 * gh_s[r]]);
       }
     }
   };
@@ -308,204 +394,161 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
 #pragma unroll
     for (int m = 0; m < 3; m++) bbr[m] = bload<double, CPOL_STREAM>(plane_rsrc(a.B0bar + m * N + zo, nxy), on ? out_e : IE);
   };
-  double so_F[9], so_B[3];
-#pragma unroll
-  for (int i = 0; i < 9; i++) so_F[i] = 0.0;
-#pragma unroll
-  for (int m = 0; m < 3; m++) so_B[m] = 0.0;
-  auto store_point = [&](int qz, bool on) {
+  auto store_point = [&](const double Fb[9], const double B0b[3], int qz, bool on) {
     const long long zo = (long long)zload(qz) * nxy;
     const unsigned eo = on ? out_e : IE;
 #pragma unroll
-    for (int i = 0; i < 9; i++) bstore(plane_rsrc(a.Fbar + i * N + zo, nxy), eo, so_F[i]);
+    for (int i = 0; i < 9; i++) bstore(plane_rsrc(a.Fbar + i * N + zo, nxy), eo, Fb[i]);
 #pragma unroll
-    for (int m = 0; m < 3; m++) bstore(plane_rsrc(a.B0bar + m * N + zo, nxy), eo, so_B[m]);
-  };
-
-  auto jac_xy = [&](int r, int c, int p, int gi, int gj, double F[3][3]) {
-    const int o = r * RX2 + c;
-    const int sp = mod3(p);
-#pragma unroll
-    for (int m = 0; m < 3; m++) {
-      const double* yc = ys[sp][m];
-      if (XYP || bcx == BC_PERIODIC || (gi > 0 && gi < nx - 1))
-        F[m][0] = yc[o + 1] - yc[o - 1];
-      else if (gi == 0)
-        F[m][0] = -3.0 * yc[o] + 4.0 * yc[o + 1] - yc[o + 2];
-      else
-        F[m][0] = 3.0 * yc[o] - 4.0 * yc[o - 1] + yc[o - 2];
-      if (XYP || bcy == BC_PERIODIC || (gj > 0 && gj < ny - 1))
-        F[m][1] = yc[o + RX2] - yc[o - RX2];
-      else if (gj == 0)
-        F[m][1] = -3.0 * yc[o] + 4.0 * yc[o + RX2] - yc[o + 2 * RX2];
-      else
-        F[m][1] = 3.0 * yc[o] - 4.0 * yc[o - RX2] + yc[o - 2 * RX2];
-    }
-  };
-  auto jacobian = [&](int r, int c, int p, int gi, int gj, double F[3][3]) {
-    jac_xy(r, c, p, gi, gj, F);
-    const int o = r * RX2 + c;
-    if (bcz == BC_PERIODIC || (p > 0 && p < nz - 1)) {
-      const int sa = mod3(p + 1), sb = mod3(p - 1);
-#pragma unroll
-      for (int m = 0; m < 3; m++) F[m][2] = ys[sa][m][o] - ys[sb][m][o];
-    } else if (p == 0) {
-#pragma unroll
-      for (int m = 0; m < 3; m++) F[m][2] = -3.0 * ys[0][m][o] + 4.0 * ys[1][m][o] - ys[2][m][o];
-    } else {
-      const int s0 = mod3(p), s1 = mod3(p - 1), s2 = mod3(p - 2);
-#pragma unroll
-      for (int m = 0; m < 3; m++) F[m][2] = 3.0 * ys[s0][m][o] - 4.0 * ys[s1][m][o] + ys[s2][m][o];
-    }
+    for (int m = 0; m < 3; m++) bstore(plane_rsrc(a.B0bar + m * N + zo, nxy), eo, B0b[m]);
   };
 
   const bool perz = (bcz == BC_PERIODIC);
   const int pb0 = perz ? z0 - 1 : max(z0 - 1, 0);
   const int pb1 = perz ? z1 : min(z1, nz - 1);
-  auto need_hi = [&](int p) { return perz ? p + 1 : (p == 0 ? 2 : (p == nz - 1 ? p : p + 1)); };
-  auto need_lo = [&](int p) { return perz ? p - 1 : (p == 0 ? 0 : (p == nz - 1 ? p - 2 : p - 1)); };
 
-  // prologue: the first stage-input window, then the loads and (dropped) stores a plane step
-  // leaves in flight, in the same order
-  int hi = need_hi(pb0);
-  for (int pz = need_lo(pb0); pz <= hi; pz++) {
-    load_window(pz);
-    commit_window(pz);
+  // ---- prologue: the stage input on the planes pb0 - 1 .. pb0 + 1, loaded together
+  Window win;
+  {
+    const bool low = !perz && pb0 == 0;  // the plane below is a ghost plane
+    const int lo = low ? 0 : pb0 - 1;
+    Window w0, w1, w2;
+    load_window(w0, lo, true);
+    load_window(w1, lo + 1, true);
+    load_window(w2, lo + 2, true);
+    commit_window(w0, lo);
+    commit_window(w1, lo + 1);
+    commit_window(w2, lo + 2);
+    if (low) commit_ghost_plane(-1, 0, 1, 2);  // plane 2 is committed again by the first plane step
   }
   __syncthreads();
+  fill_ghosts(pb0);
+  // leave the same loads and (dropped) stores in flight, in the same order, as a plane step
+  load_window(win, pb0 + 2, pb0 + 2 <= pb1 + 1);
   load_field(pb0);
-  load_window(hi + 1);
   load_point(pb0 - 1);
-  store_point(pb0 - 1, false);
+  {
+    const double zero[9] = {};
+    store_point(zero, zero, pb0 - 1, false);
+  }
+  __builtin_amdgcn_sched_barrier(0);
+  __syncthreads();
 
-  // own-node values carried between plane steps (q = p - 1 is the output plane)
-  double Fzq[3] = {0, 0, 0};  // z column of F' at q (the x and y columns are re-read from the ring)
-  double rDq = 0.0;
-  double ubq[3] = {0, 0, 0}, Bq[3] = {0, 0, 0}, Bqm[3] = {0, 0, 0}, b0q[3] = {0, 0, 0};
-  double gzqm[3] = {0, 0, 0}, gzq[3] = {0, 0, 0};  // Gbar'_z at q - 1 and q
-  double Bbxyq[3] = {0, 0, 0};                     // in-plane transpose of Gbar' at q
+  // own-node values carried between plane steps; q = p - 1 is the output plane
+  double Fq[3][3] = {}, rDq = 0.0, ubq[3] = {}, b0q[3] = {};
+  double Bq[3] = {}, Bqm[3] = {};    // B at q, q - 1
+  double gzq[3] = {}, gzqm[3] = {};  // Gbar'_z at q, q - 1
+  double Gq[2][3] = {};              // x and y differences of B at q
+  double Btq[3] = {};                // in-plane transpose of Gbar' at q
   const int ot = (ty + 1) * RX1 + (tx + 1);
 
   for (int p = pb0; p <= z1; p++) {
     const int q = p - 1;
     const bool qout = (q >= z0 && q < z1);
-    // 1. B, Gbar'_x, Gbar'_y on the tile + 1-node halo of plane p; own-node values
-    double Fzp[3] = {0, 0, 0};
-    double rDp = 0.0, ubp[3] = {0, 0, 0}, Bp[3] = {0, 0, 0}, b0p[3] = {0, 0, 0}, gzp[3] = {0, 0, 0};
-    if (p <= pb1) {
-      const int sb = p & 1;
+    fill_ghosts(p + 1);
+    // 1. commit the plane the next field needs, load the one after it
+    commit_window(win, p + 2);  // past the chunk's last plane: zeros that nothing reads
+    if (!perz && p + 2 == nz) commit_ghost_plane(nz, nz - 1, nz - 2, nz - 3);
+    load_window(win, p + 3, p + 3 <= pb1 + 1);
+
+    // 2. B and Gbar' of the field points of plane p, 0 off the grid
+    const bool on_p = p <= pb1, live_p = on_p && (perz || (p > 0 && p < nz - 1));
+    double F[3][3], rD, ub[3], B[3], Gx[3], Gy[3], Gz[3];
+    auto field = [&](auto point) {
+      constexpr int R = decltype(point)::value;
+      const int o = f1y[R];
+      const int sc = p & 3, sl = (p - 1) & 3, sh = (p + 1) & 3;
 #pragma unroll
-      for (int r = 0; r < NP1; r++) {
-        __builtin_amdgcn_sched_barrier(0);
-        if (f1r[r] >= 0) {
-          const int r1 = f1r[r], c1 = f1c[r];
-          const int gi = i0 + c1 - 1, gj = j0 + r1 - 1;
-          double B[3] = {0, 0, 0}, Gx[3] = {0, 0, 0}, Gy[3] = {0, 0, 0}, Gz[3] = {0, 0, 0}, ub[3] = {0, 0, 0};
-          if (f1e[r] != IE) {
-            double F[3][3];
-            jacobian(r1 + 1, c1 + 1, p, gi, gj, F);
-            const double rD = rcp_nr(det3(F));
-            const bool live = !face_at(gi, gj, p);
+      for (int m = 0; m < 3; m++) {
+        F[m][0] = ys[sc][m][o + 1] - ys[sc][m][o - 1];
+        F[m][1] = ys[sc][m][o + RX2] - ys[sc][m][o - RX2];
+        F[m][2] = ys[sh][m][o] - ys[sl][m][o];
+      }
+      const double r = rcp_nr(det3(F));
+      rD = (on_p && f1e[R] != IE) ? r : 0.0;
 #pragma unroll
-            for (int m = 0; m < 3; m++) ub[m] = live ? cv * vr[r][m] : 0.0;
-            transpose_field(F, rD, b0r[r], ub, gamma, B, Gx, Gy, Gz);
-            if (r == 0) {
+      for (int m = 0; m < 3; m++) ub[m] = (live_p && f1live[R]) ? cv * vr[R][m] : 0.0;
+      transpose_field(F, rD, b0r[R], ub, gamma, B, Gx, Gy, Gz);
 #pragma unroll
-              for (int m = 0; m < 3; m++) {
-                Fzp[m] = F[m][2];
-                ubp[m] = ub[m];
-                Bp[m] = B[m];
-                b0p[m] = b0r[r][m];
-                gzp[m] = Gz[m];
-              }
-              rDp = rD;
-            }
-          }
-          const int o = r1 * RX1 + c1;
+      for (int m = 0; m < 3; m++) bs[p & 1][m][f1o[R]] = B[m];
+    };
+    if (f1o[1] >= 0) {
+      field(std::integral_constant<int, 1>{});
+      if (halo_row == 0 || halo_row == RY1 - 1) {
+        if (halo_col >= 1 && halo_col <= TX) {
 #pragma unroll
-          for (int m = 0; m < 3; m++) {
-            bs[sb][m][o] = B[m];
-            gxy[m][o] = Gx[m];
-            gxy[3 + m][o] = Gy[m];
-          }
+          for (int m = 0; m < 3; m++) gy[p & 1][m][halo_row * TX + halo_col - 1] = Gy[m];
         }
+      } else {
+#pragma unroll
+        for (int m = 0; m < 3; m++) gx[p & 1][m][halo_col != 0][halo_row - 1] = Gx[m];
       }
     }
-    load_field(p + 1 <= pb1 ? p + 1 : pb1);
-    // x and y columns of F' at the own node of plane q, read before the barrier: the commit
-    // below reuses plane q's ring slot
-    double F[3][3];
+    field(std::integral_constant<int, 0>{});
+#pragma unroll
+    for (int m = 0; m < 3; m++) gy[p & 1][m][(ty + 1) * TX + tx] = Gy[m];
+    double b0p[3];
+#pragma unroll
+    for (int m = 0; m < 3; m++) b0p[m] = b0r[0][m];
+    load_field(min(p + 1, pb1));
+
+    // 3. the transpose at the own node of plane q, from registers
+    double Fb[9] = {}, B0b[3] = {};
     if (qout) {
-      jac_xy(ty + 2, tx + 2, q, gi_t, gj_t, F);
+      const bool face_q = !perz && (q == 0 || q == nz - 1);
+      const bool interior = f1live[0] && !face_q;
+      double G[3][3], Bt[3];  // Bt: sum_a Gbar'_a(m - e_a) - Gbar'_a(m + e_a)
 #pragma unroll
-      for (int m = 0; m < 3; m++) F[m][2] = Fzq[m];
-    }
-    __syncthreads();
-
-    // 2. commit the stage-input plane field(p + 1) needs; issue the next one
-    if (p + 1 <= pb1 && need_hi(p + 1) > hi) {
-      hi++;
-      commit_window(hi);
-    }
-    load_window(hi + 1);
-
-    // 3. in-plane transpose of Gbar' at the own node of plane p (used by the next step)
-    double Bbxyp[3];
-#pragma unroll
-    for (int m = 0; m < 3; m++)
-      Bbxyp[m] = (gxy[m][ot - 1] - gxy[m][ot + 1]) + (gxy[3 + m][ot - RX1] - gxy[3 + m][ot + RX1]);
-
-    // 4. the transpose at the own node of plane q
-    if (qout) {
-      const bool interior = !face_at(gi_t, gj_t, q);
-      double G[3][3] = {};  // G[a][m]
-      if (interior) {
-        const int sq = q & 1;
-#pragma unroll
-        for (int m = 0; m < 3; m++) {
-          G[0][m] = bs[sq][m][ot + 1] - bs[sq][m][ot - 1];
-          G[1][m] = bs[sq][m][ot + RX1] - bs[sq][m][ot - RX1];
-          G[2][m] = Bp[m] - Bqm[m];
-        }
+      for (int m = 0; m < 3; m++) {
+        G[0][m] = Gq[0][m];
+        G[1][m] = Gq[1][m];
+        G[2][m] = B[m] - Bqm[m];
+        Bt[m] = Btq[m] + (gzqm[m] - Gz[m]);
       }
-      double Bt[3];  // transpose of G': sum_a Gbar'_a(m - e_a) - Gbar'_a(m + e_a)
-#pragma unroll
-      for (int m = 0; m < 3; m++) Bt[m] = Bbxyq[m] + (gzqm[m] - gzp[m]);
       double zeta = 1.0;
       if constexpr (SEED) {
         if (bcx == BC_LINE_TIED && (gi_t == 0 || gi_t == nx - 1)) zeta *= 0.5;
         if (bcy == BC_LINE_TIED && (gj_t == 0 || gj_t == ny - 1)) zeta *= 0.5;
-        if (bcz == BC_LINE_TIED && (q == 0 || q == nz - 1)) zeta *= 0.5;
+        if (face_q) zeta *= 0.5;
       }
       double dB[3];
-      transpose_node<SEED>(F, rDq, Bq, ubq, b0q, G, Bt, interior, zeta, a, so_F, dB);
+      transpose_node<SEED>(Fq, rDq, Bq, ubq, b0q, G, Bt, interior, zeta, a, Fb, dB);
 #pragma unroll
-      for (int m = 0; m < 3; m++) so_B[m] = bbr[m] + dB[m];
+      for (int m = 0; m < 3; m++) B0b[m] = bbr[m] + dB[m];
     }
     load_point(p);  // B0bar'' at the output node of the next plane step
-    store_point(q, qout);
+    store_point(Fb, B0b, q, qout);
     __syncthreads();
 
+    // 4. the in-plane part of the transpose at the own node of plane p, for the next step
 #pragma unroll
     for (int m = 0; m < 3; m++) {
-      Fzq[m] = Fzp[m];
-      ubq[m] = ubp[m];
+      const double* b = bs[p & 1][m];
+      const double* y = &gy[p & 1][m][(ty + 1) * TX + tx];
+      Gq[0][m] = b[ot + 1] - b[ot - 1];
+      Gq[1][m] = b[ot + RX1] - b[ot - RX1];
+      const double below = neighbour<false>(Gx[m], gx[p & 1][m][0][ty]);
+      const double above = neighbour<true>(Gx[m], gx[p & 1][m][1][ty]);
+      Btq[m] = (below - above) + (y[-TX] - y[TX]);
       Bqm[m] = Bq[m];
-      Bq[m] = Bp[m];
-      b0q[m] = b0p[m];
+      Bq[m] = B[m];
       gzqm[m] = gzq[m];
-      gzq[m] = gzp[m];
-      Bbxyq[m] = Bbxyp[m];
+      gzq[m] = Gz[m];
+      ubq[m] = ub[m];
+      b0q[m] = b0p[m];
+#pragma unroll
+      for (int c = 0; c < 3; c++) Fq[m][c] = F[m][c];
     }
-    rDq = rDp;
+    rDq = rD;
   }
 }
 
 // The same for small grids, a brick of nodes per workgroup (see brick.hip): the stage input with its
 // 2-node halo, B and the three Gbar' on the brick and its 1-node halo, all planes at once, two or three
 // barriers.  LDS: up to 157 KB (Gbar' takes 72 bytes a field point), one workgroup per CU.  Up to
-// 600 000 nodes (make_adj_geometry): us per step of a backward pass, march / bricks: 16^3 714 / 145,
-// 33^3 846 / 173, 64^3 606 / 322, 81^3 line-tied 1034 / 703, 64 x 64 x 192 731 / 797, 128^3 1580 / 2187.
+// 2^19 nodes (make_adj_geometry): us per step of a backward pass, march / bricks: 48^3 periodic 291 / 199,
+// 49^3 line-tied 330 / 221, 65^3 line-tied 471 / 413, 80^3 periodic 568 / 548, 81^3 line-tied 658 / 647,
+// 56 x 56 x 168 538 / 590, 88^3 periodic 710 / 753, 64 x 64 x 192 652 / 758.
 constexpr int NPW = (ADJ_WINDOW + BRICK_THREADS - 1) / BRICK_THREADS;
 constexpr int NPF = 1 + (BRICK_SHELL + BRICK_THREADS - 1) / BRICK_THREADS;
 
@@ -657,12 +700,16 @@ __global__ __launch_bounds__(BRICK_THREADS) __attribute__((amdgpu_waves_per_eu(2
 
 // ybar = D^T Fbar': each column a of Fbar' is pulled back along axis a with the transposed
 // difference rows (central: +1 at n+e_a, -1 at n-e_a; one-sided ends: (-3, 4, -1) and (3, -4, 1)).
-// MODE 0 (stage STAGE >= 2): ybar_t = D^T Fbar' -> ybar_out, and the cotangent of k_{t-1},
-//   dt (b5_{t-1} xbar + sum_{t' >= t} a_{t',t-1} ybar_{t'}) -> ubar_out;
-// MODE 1 (stage 1): xbar += D^T Fbar' + sum_{t=2..6} ybar_t;  MODE 2 (seed): xbar = D^T Fbar'.
-// Bound by its 190 to 290 bytes a node: one thread a node, rows of 64 along x so that every access is
-// coalesced and no index needs a 64-bit division (64 x 64 x 192: 29 us; 16^3: 8 -> 4 us against a
-// grid-stride loop with 64-bit divisions).
+// MODE 0 (stage STAGE >= 2): the cotangent of k_{t-1},
+//   dt (b5_{t-1} xbar + sum_{t' >= t} a_{t',t-1} ybar_{t'}) -> ubar_out.
+// MODE 1 (stage 1): xbar + D^T Fbar' + sum_{t=2..6} ybar_t -> xbar.  MODE 2 (seed): xbar = D^T Fbar'.
+// Stages 6 and 5 store ybar_t.  Stage 4 stores, in place of ybar_6, ybar_5 and its own, what is still
+// wanted of the three and of xbar: sum[0] = P2 = a62 ybar_6 + a52 ybar_5 + a42 ybar_4 for k_2 (b5_2 = 0),
+// sum[1] = P1, likewise with b5_1 xbar, for k_1, and sum[2] = xbar + ybar_6 + ybar_5 + ybar_4.  That is
+// 1008 instead of 1200 bytes a node and step for the six gathers, which bound them (64 x 64 x 192: 4.6 to
+// 5.8 TB/s, 161 -> 153 us the six).
+// One thread a node, rows of 64 along x so that every access is coalesced and no index needs a 64-bit
+// division (16^3: 8 -> 4 us against a grid-stride loop with 64-bit divisions).
 template <int MODE, int STAGE>
 __global__ __launch_bounds__(256) void adj_gather_kernel(AdjArgs a, int bxs, int bys) {
   const Geometry& g = a.g;
@@ -700,20 +747,37 @@ __global__ __launch_bounds__(256) void adj_gather_kernel(AdjArgs a, int bxs, int
   }
 #pragma unroll
   for (int r = 0; r < 3; r++) {
+    const long long o = p + r * N;
     if constexpr (MODE == 0) {
       constexpr int s = STAGE - 1;  // the stage whose k's cotangent is assembled
-      a.ybar_out[p + r * N] = yb[r];
-      double v = CK::b5[s - 1] * a.xbar[p + r * N] + CK::a[STAGE - 1][s - 1] * yb[r];
-#pragma unroll
-      for (int t = STAGE + 1; t <= 6; t++) v += CK::a[t - 1][s - 1] * a.ybar[t][p + r * N];
-      a.ubar_out[p + r * N] = dt * v;
+      const double y = yb[r];
+      double v = CK::a[STAGE - 1][s - 1] * y;
+      if constexpr (STAGE >= 4) {
+        const double y5 = STAGE == 4 ? a.ybar[5][o] : 0.0;
+        const double y6 = STAGE <= 5 ? a.ybar[6][o] : 0.0;
+        const double x = STAGE <= 5 ? a.xbar[o] : 0.0;
+        if constexpr (STAGE == 4) {
+          v = CK::a[5][2] * y6 + CK::a[4][2] * y5 + v;
+          a.sum[0][o] = CK::a[5][1] * y6 + CK::a[4][1] * y5 + CK::a[3][1] * y;
+          a.sum[1][o] = CK::b5[0] * x + CK::a[5][0] * y6 + CK::a[4][0] * y5 + CK::a[3][0] * y;
+          a.sum[2][o] = x + y6 + y5 + y;
+        } else {
+          if constexpr (STAGE == 5) v = CK::a[5][3] * y6 + v;
+          a.ybar[STAGE][o] = y;
+        }
+        if constexpr (STAGE <= 5) v = CK::b5[s - 1] * x + v;  // b5_5 = 0
+      } else if constexpr (STAGE == 3) {
+        v = a.sum[0][o] + v;
+        a.ybar[3][o] = y;
+      } else {
+        v = a.sum[1][o] + CK::a[2][0] * a.ybar[3][o] + v;
+        a.ybar[2][o] = y;
+      }
+      a.ubar_out[o] = dt * v;
     } else if constexpr (MODE == 1) {
-      double s = a.xbar_out[p + r * N] + yb[r];
-#pragma unroll
-      for (int t = 2; t <= 6; t++) s += a.ybar[t][p + r * N];
-      a.xbar_out[p + r * N] = s;
+      a.xbar_out[o] = a.sum[2][o] + a.ybar[3][o] + a.ybar[2][o] + yb[r];
     } else {
-      a.xbar_out[p + r * N] = yb[r];
+      a.xbar_out[o] = yb[r];
     }
   }
 }
@@ -736,24 +800,10 @@ __global__ void seg_step_kernel(Control* c2, const double* __restrict__ dt_recor
   }
 }
 
-template <int S, bool XYP, bool SEED>
+template <int S, bool SEED>
 hipError_t launch_field_t(const AdjArgs& a, hipStream_t st) {
-  hipLaunchKernelGGL((adj_field_kernel<S, XYP, SEED>), dim3(a.g.nblocks), dim3(NTHREADS), 0, st, a);
+  hipLaunchKernelGGL((adj_field_kernel<S, SEED>), dim3(a.g.nblocks), dim3(NTHREADS), 0, st, a);
   return hipGetLastError();
-}
-
-template <bool XYP>
-hipError_t launch_field_x(int s, bool seed, const AdjArgs& a, hipStream_t st) {
-  if (seed) return launch_field_t<1, XYP, true>(a, st);
-  switch (s) {
-    case 1: return launch_field_t<1, XYP, false>(a, st);
-    case 2: return launch_field_t<2, XYP, false>(a, st);
-    case 3: return launch_field_t<3, XYP, false>(a, st);
-    case 4: return launch_field_t<4, XYP, false>(a, st);
-    case 5: return launch_field_t<5, XYP, false>(a, st);
-    case 6: return launch_field_t<6, XYP, false>(a, st);
-    default: return hipErrorInvalidValue;
-  }
 }
 
 unsigned grid_for(long long n) {
@@ -780,8 +830,16 @@ hipError_t launch_adj_field(int s, bool seed, const AdjArgs& a, hipStream_t st) 
     }
     return hipGetLastError();
   }
-  const bool xyp = (a.g.bc[0] == BC_PERIODIC && a.g.bc[1] == BC_PERIODIC);
-  return xyp ? launch_field_x<true>(s, seed, a, st) : launch_field_x<false>(s, seed, a, st);
+  if (seed) return launch_field_t<1, true>(a, st);
+  switch (s) {
+    case 1: return launch_field_t<1, false>(a, st);
+    case 2: return launch_field_t<2, false>(a, st);
+    case 3: return launch_field_t<3, false>(a, st);
+    case 4: return launch_field_t<4, false>(a, st);
+    case 5: return launch_field_t<5, false>(a, st);
+    case 6: return launch_field_t<6, false>(a, st);
+    default: return hipErrorInvalidValue;
+  }
 }
 
 hipError_t launch_adj_gather(const AdjArgs& a, int mode, int stage, hipStream_t st) {

@@ -284,7 +284,7 @@ Geometry make_geometry(const relax_config* c) {
   return with_bricks(c, true, c->curl == RELAX_CURL_NNN ? 1000000 : 1 << 19, BRICK_WINDOW, 512);
 }
 
-Geometry make_adj_geometry(const relax_config* c) { return with_bricks(c, false, 600000, ADJ_WINDOW, 256); }
+Geometry make_adj_geometry(const relax_config* c) { return with_bricks(c, false, 1 << 19, ADJ_WINDOW, 256); }
 
 }  // namespace relax
 
@@ -701,6 +701,7 @@ int relax_backward(void* ctx, double seed_EM, double seed_R2, double* d_grad_x0,
   a.seed_R2 = seed_R2;
   a.xbar = c->d_xbar;
   for (int t = 2; t <= 6; t++) a.ybar[t] = c->d_ybar + (size_t)(t - 2) * N3;
+  for (int i = 0; i < 3; i++) a.sum[i] = a.ybar[4 + i];
   a.ubar = c->d_ubar;
   a.ubar_out = c->d_ubar;
   HIP_TRY(c, launch_fill(c->d_B0bar, (long long)N3, 0.0, st));
@@ -756,7 +757,6 @@ int relax_backward(void* ctx, double seed_EM, double seed_R2, double* d_grad_x0,
       for (int s = 6; s >= 1; s--) {
         HIP_TRY(c, launch_adj_field(s, false, a, st));
         if (s >= 2) {
-          a.ybar_out = c->d_ybar + (size_t)(s - 2) * N3;
           HIP_TRY(c, launch_adj_gather(a, 0, s, st));
         } else {
           a.xbar_out = c->d_xbar;

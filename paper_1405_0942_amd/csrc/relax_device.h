@@ -117,12 +117,12 @@ struct AdjArgs {
   const double* dt;       // device pointer to the step's dt
   const double* B0;       // B0'' (prescaled, FP64)
   const double* xbar;     // cotangent of x_{n+1}
-  const double* ybar[7];  // ybar_t for t = 2..6 (index t)
+  double* ybar[7];        // ybar_t for t = 2, 3, 5, 6 (index t)
+  double* sum[3];         // sums over stages 4 to 6 (see adj_gather_kernel); [1] and [2] take the place of ybar_5, ybar_6
   const double* ubar;     // cotangent of k_s for the field sweep of stage s < 6 (gather output)
   const double* useed;    // seed sweep: cotangent of u (may be null)
   double* Fbar;           // [9][N] cotangent of F' (row-major 3x3 per node, component-major)
   double* B0bar;          // [3][N] accumulated cotangent of B0''
-  double* ybar_out;       // gather mode 0 output: ybar_t
   double* ubar_out;       // gather mode 0 output: cotangent of k_{t-1}
   double* xbar_out;       // gather modes 1, 2 output
   double gamma, seed_EM, seed_R2;

@@ -544,7 +544,7 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
 }
 
 // The same for small grids, a brick of nodes per workgroup (see brick.hip): the stage input with its
-// 2-node halo, B and the three Gbar' on the brick and its 1-node halo, all planes at once, two or three
+// 2-node halo, B and the three Gbar' on the brick and its 1-node halo, all planes at once, two
 // barriers.  LDS: up to 157 KB (Gbar' takes 72 bytes a field point), one workgroup per CU.  Up to
 // 2^19 nodes (make_adj_geometry): us per step of a backward pass, march / bricks: 48^3 periodic 291 / 199,
 // 49^3 line-tied 330 / 221, 65^3 line-tied 471 / 413, 80^3 periodic 568 / 548, 81^3 line-tied 658 / 647,
@@ -558,10 +558,7 @@ __global__ __launch_bounds__(BRICK_THREADS) __attribute__((amdgpu_waves_per_eu(2
   const Geometry& g = a.g;
   const long long N = g.N;
   const Brick br(g);
-  const int lb = logical_block(blockIdx.x, g.nblocks);
-  const int i0 = (lb % g.tiles[0]) * br.bx;
-  const int j0 = ((lb / g.tiles[0]) % g.tiles[1]) * br.by;
-  const int k0 = (lb / (g.tiles[0] * g.tiles[1])) * br.bz;
+  const BrickOrigin at0(br, g);
   const int tid = threadIdx.x;
   const double dt = SEED ? 0.0 : *a.dt;
   const double c21 = dt * CK::a[1][0];
@@ -574,36 +571,44 @@ __global__ __launch_bounds__(BRICK_THREADS) __attribute__((amdgpu_waves_per_eu(2
   __shared__ double bs[3][BRICK_FIELD];
   __shared__ double gs[9][BRICK_FIELD];
 
-  // ---- all loads first
+  // ---- all loads first; a wave skips the points past the brick's
   double wx[NPW][3], wk[WK ? NPW : 1][3];
   BrickPoint wp[NPW];
 #pragma unroll
   for (int r = 0; r < NPW; r++) {
-    wp[r] = brick_window(br, g, tid + r * BRICK_THREADS, i0, j0, k0);
-    const int i = wp[r].index;
+    const int e = tid + r * BRICK_THREADS;
+    if (e < br.nwin) {
+      wp[r] = brick_window(br, g, e, at0);
+      const unsigned i = wp[r].index;
 #pragma unroll
-    for (int m = 0; m < 3; m++) wx[r][m] = wsrc[m * N + i];
-    if constexpr (WK) {
+      for (int m = 0; m < 3; m++) wx[r][m] = at(wsrc + m * N, i);
+      if constexpr (WK) {
 #pragma unroll
-      for (int m = 0; m < 3; m++) wk[r][m] = a.k[0][m * N + i];
+        for (int m = 0; m < 3; m++) wk[r][m] = at(a.k[0] + m * N, i);
+      }
     }
   }
   double b0r[NPF][3], vr[NPF][3];
   BrickField fp[NPF];
 #pragma unroll
   for (int r = 0; r < NPF; r++) {
-    fp[r] = brick_field(br, g, r, tid, i0, j0, k0);
+    fp[r].slot = -1;
+    if (r == 0 || tid + (r - 1) * BRICK_THREADS < br.nshell) {
+      fp[r] = brick_field(br, g, r, tid, at0);
+      const unsigned i = fp[r].index;
 #pragma unroll
-    for (int m = 0; m < 3; m++) {
-      b0r[r][m] = a.B0[m * N + fp[r].index];
-      vr[r][m] = vsrc[m * N + fp[r].index];
+      for (int m = 0; m < 3; m++) {
+        b0r[r][m] = at(a.B0 + m * N, i);
+        vr[r][m] = at(vsrc + m * N, i);
+      }
     }
   }
   const bool node = fp[0].node();
   const int own = fp[0].index;
   double bbr[3];
 #pragma unroll
-  for (int m = 0; m < 3; m++) bbr[m] = a.B0bar[m * N + own];
+  for (int m = 0; m < 3; m++) bbr[m] = at(a.B0bar + m * N, (unsigned)own);
+  const bool at_face = br.at_face(g, at0.i0, at0.j0, at0.k0);
 
   // ---- stage input
 #pragma unroll
@@ -619,17 +624,6 @@ __global__ __launch_bounds__(BRICK_THREADS) __attribute__((amdgpu_waves_per_eu(2
     }
   }
   __syncthreads();
-  if (br.at_face(g, i0, j0, k0)) {
-#pragma unroll
-    for (int r = 0; r < NPW; r++) {
-      const int e = tid + r * BRICK_THREADS, s = wp[r].ghost;
-      if (s != 0) {
-#pragma unroll
-        for (int m = 0; m < 3; m++) ys[m][e] = fma(3.0, ys[m][e + s] - ys[m][e + 2 * s], ys[m][e + 3 * s]);
-      }
-    }
-    __syncthreads();
-  }
 
   // ---- B and Gbar' on the brick and its 1-node halo
   double Fq[3][3], Bq[3], ubq[3], rDq;
@@ -638,12 +632,7 @@ __global__ __launch_bounds__(BRICK_THREADS) __attribute__((amdgpu_waves_per_eu(2
     if (r == 0 || fp[r].slot >= 0) {
       const int o = fp[r].window;
       double F[3][3], B[3], Gx[3], Gy[3], Gz[3], ub[3];
-#pragma unroll
-      for (int m = 0; m < 3; m++) {
-        F[m][0] = ys[m][o + 1] - ys[m][o - 1];
-        F[m][1] = ys[m][o + br.sx] - ys[m][o - br.sx];
-        F[m][2] = ys[m][o + br.sxy] - ys[m][o - br.sxy];
-      }
+      face_differences(br, fp[r].ends, at_face, ys, o, F);
       const double rD = fp[r].on() ? rcp_nr(det3(F)) : 0.0;
       const bool live = fp[r].on() && !fp[r].face();
 #pragma unroll

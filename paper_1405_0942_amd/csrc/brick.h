@@ -7,20 +7,27 @@
 
 namespace relax {
 
-// e / d for 0 <= e < 4096, 1 <= d < 4096: (e + 1/2) / d is at least 1 / (2 d) away from an integer,
-// far more than the rounding of the reciprocal
+// e / d for 0 <= e < 2^21, 1 <= d: (e + 1/2) / d is at least 1 / (2 d) away from an integer, more than
+// the 1.8e-7 (e + 1/2) / d that the reciprocal and the product round
 __device__ __forceinline__ int small_div(int e, int d) {
   return (int)(((float)e + 0.5f) * __builtin_amdgcn_rcpf((float)d));
+}
+
+// The value at element i of a component, i < 2^28: base in scalar registers, byte offset in one register
+template <typename V>
+__device__ __forceinline__ V at(const V* __restrict__ base, unsigned i) {
+  return *reinterpret_cast<const V*>(reinterpret_cast<const char*>(base) + i * (unsigned)sizeof(V));
 }
 
 struct Brick {
   int bx, by, bz;    // nodes
   int sx, sy, sxy;   // strides of the stage-input window (2-node halo)
   int fx, fxy;       // strides of the field window (1-node halo)
-  int nwin, nown;    // points of the window, nodes
+  int nwin, nown, nshell;  // points of the window, nodes, field points around them
   __device__ __forceinline__ explicit Brick(const Geometry& g)
       : bx(g.brick[0]), by(g.brick[1]), bz(g.brick[2]), sx(bx + 4), sy(by + 4), sxy(sx * sy), fx(bx + 2),
-        fxy(fx * (by + 2)), nwin(sxy * (bz + 4)), nown(bx * by * bz) {}
+        fxy(fx * (by + 2)), nwin(sxy * (bz + 4)), nown(bx * by * bz),
+        nshell(fxy * (bz + 2) - nown) {}
   // whether the window of the brick at (i0, j0, k0) reaches beyond a line-tied face
   __device__ __forceinline__ bool at_face(const Geometry& g, int i0, int j0, int k0) const {
     return (g.bc[0] == BC_LINE_TIED && (i0 <= 1 || i0 + bx >= g.n[0] - 1)) ||
@@ -29,32 +36,36 @@ struct Brick {
   }
 };
 
+// Where the brick of this workgroup begins
+struct BrickOrigin {
+  int i0, j0, k0;
+  __device__ __forceinline__ BrickOrigin(const Brick& b, const Geometry& g) {
+    const int lb = logical_block(blockIdx.x, g.nblocks);
+    const int row = __builtin_amdgcn_readfirstlane(small_div(lb, g.tiles[0]));
+    const int plane = __builtin_amdgcn_readfirstlane(small_div(row, g.tiles[1]));
+    i0 = (lb - row * g.tiles[0]) * b.bx;
+    j0 = (row - plane * g.tiles[1]) * b.by;
+    k0 = plane * b.bz;
+  }
+};
+
 struct BrickPoint {
   int index;  // grid index (0 off the grid)
-  int ghost;  // step into the grid of a ghost point just beyond a line-tied face (0: none)
   int wraps;  // periodic wraps of x, y, z, each + 1, in bits 0-1, 2-3, 4-5; bit 6: on the grid
   __device__ __forceinline__ bool on() const { return wraps & 64; }
   __device__ __forceinline__ double wrap(int m) const { return (double)(((wraps >> (2 * m)) & 3) - 1); }
 };
 
-// window point e (past the window: off the grid, no ghost)
-__device__ __forceinline__ BrickPoint brick_window(const Brick& b, const Geometry& g, int e, int i0, int j0, int k0) {
+// window point e < nwin
+__device__ __forceinline__ BrickPoint brick_window(const Brick& b, const Geometry& g, int e, const BrickOrigin& at) {
   const int nx = g.n[0], ny = g.n[1], nz = g.n[2];
-  const int lz = small_div(e, b.sxy), e2 = e - lz * b.sxy, ly = small_div(e2, b.sx), lx = e2 - ly * b.sx;
-  const int gi = i0 + lx - 2, gj = j0 + ly - 2, gk = k0 + lz - 2;
-  const AxisIdx rx = resolve_near(gi, nx, g.bc[0]), ry = resolve_near(gj, ny, g.bc[1]);
-  const AxisIdx rz = resolve_near(gk, nz, g.bc[2]);
-  const bool in = e < b.nwin;
+  const int lz = small_div(e, b.sxy), e2 = e - __mul24(lz, b.sxy), ly = small_div(e2, b.sx), lx = e2 - __mul24(ly, b.sx);
+  const AxisIdx rx = axis_index(at.i0 + lx - 2, nx, g.bc[0]), ry = axis_index(at.j0 + ly - 2, ny, g.bc[1]);
+  const AxisIdx rz = axis_index(at.k0 + lz - 2, nz, g.bc[2]);
   BrickPoint p;
-  const bool on = in && rx.ok && ry.ok && rz.ok;
-  p.index = on ? (rz.i * ny + ry.i) * nx + rx.i : 0;
+  const bool on = rx.ok && ry.ok && rz.ok;
+  p.index = on ? __mul24(__mul24(rz.i, ny) + ry.i, nx) + rx.i : 0;
   p.wraps = (rx.w + 1) | (ry.w + 1) << 2 | (rz.w + 1) << 4 | (on ? 64 : 0);
-  p.ghost = 0;
-  if (in) {
-    if (ry.ok && rz.ok && !rx.ok) p.ghost = gi == -1 ? 1 : (gi == nx ? -1 : 0);
-    if (rx.ok && rz.ok && !ry.ok) p.ghost = gj == -1 ? b.sx : (gj == ny ? -b.sx : 0);
-    if (rx.ok && ry.ok && !rz.ok) p.ghost = gk == -1 ? b.sxy : (gk == nz ? -b.sxy : 0);
-  }
   return p;
 }
 
@@ -71,28 +82,27 @@ struct BrickField {
 
 // field point r of thread tid: r = 0 is the own node; then the shell: the planes below and above the
 // brick, then a ring around each of its planes
-__device__ __forceinline__ BrickField brick_field(const Brick& b, const Geometry& g, int r, int tid, int i0, int j0,
-                                                  int k0) {
+__device__ __forceinline__ BrickField brick_field(const Brick& b, const Geometry& g, int r, int tid, const BrickOrigin& at) {
   const int nx = g.n[0], ny = g.n[1], nz = g.n[2];
   int cx, cy, cz;  // field window coordinates
   bool in;
   if (r == 0) {
     in = tid < b.nown;
-    const int e = in ? tid : 0;
-    const int tz = small_div(e, b.bx * b.by), ty = small_div(e - tz * b.bx * b.by, b.bx);
-    cx = e - (tz * b.by + ty) * b.bx + 1;
+    const int e = in ? tid : 0, bxy = __mul24(b.bx, b.by);
+    const int tz = small_div(e, bxy), e2 = e - __mul24(tz, bxy), ty = small_div(e2, b.bx);
+    cx = e2 - __mul24(ty, b.bx) + 1;
     cy = ty + 1;
     cz = tz + 1;
   } else {
     const int e = tid + (r - 1) * BRICK_THREADS, ring = 2 * (b.fx + b.by);
     if (e < 2 * b.fxy) {
-      const int top = e >= b.fxy ? 1 : 0, e2 = e - top * b.fxy;
-      cz = top * (b.bz + 1);
+      const int top = e >= b.fxy ? 1 : 0, e2 = e - (top ? b.fxy : 0);
+      cz = top ? b.bz + 1 : 0;
       cy = small_div(e2, b.fx);
-      cx = e2 - cy * b.fx;
+      cx = e2 - __mul24(cy, b.fx);
       in = true;
     } else {
-      const int e2 = e - 2 * b.fxy, layer = small_div(e2, ring), e3 = e2 - layer * ring;
+      const int e2 = e - 2 * b.fxy, layer = small_div(e2, ring), e3 = e2 - __mul24(layer, ring);
       in = layer < b.bz;
       cz = in ? layer + 1 : 0;
       if (e3 < 2 * b.fx) {
@@ -104,19 +114,48 @@ __device__ __forceinline__ BrickField brick_field(const Brick& b, const Geometry
       }
     }
   }
-  const AxisIdx rx = resolve_near(i0 + cx - 1, nx, g.bc[0]), ry = resolve_near(j0 + cy - 1, ny, g.bc[1]);
-  const AxisIdx rz = resolve_near(k0 + cz - 1, nz, g.bc[2]);
+  const AxisIdx rx = axis_index(at.i0 + cx - 1, nx, g.bc[0]), ry = axis_index(at.j0 + cy - 1, ny, g.bc[1]);
+  const AxisIdx rz = axis_index(at.k0 + cz - 1, nz, g.bc[2]);
   BrickField p;
   const bool on = in && rx.ok && ry.ok && rz.ok;
-  p.slot = in ? cz * b.fxy + cy * b.fx + cx : -1;
-  p.window = (cz + 1) * b.sxy + (cy + 1) * b.sx + cx + 1;
+  p.slot = in ? __mul24(cz, b.fxy) + __mul24(cy, b.fx) + cx : -1;
+  p.window = __mul24(cz + 1, b.sxy) + __mul24(cy + 1, b.sx) + cx + 1;
   p.ends = on ? 64 : 0;
-  if (r == 0 && in && i0 + cx - 1 < nx && j0 + cy - 1 < ny && k0 + cz - 1 < nz) p.ends |= 128;
+  if (r == 0 && in && at.i0 + cx - 1 < nx && at.j0 + cy - 1 < ny && at.k0 + cz - 1 < nz) p.ends |= 128;
   if (g.bc[0] == BC_LINE_TIED) p.ends |= rx.i == 0 ? 1 : (rx.i == nx - 1 ? 2 : 0);
   if (g.bc[1] == BC_LINE_TIED) p.ends |= ry.i == 0 ? 4 : (ry.i == ny - 1 ? 8 : 0);
   if (g.bc[2] == BC_LINE_TIED) p.ends |= rz.i == 0 ? 16 : (rz.i == nz - 1 ? 32 : 0);
-  p.index = on ? (rz.i * ny + ry.i) * nx + rx.i : 0;
+  p.index = on ? __mul24(__mul24(rz.i, ny) + ry.i, nx) + rx.i : 0;
   return p;
+}
+
+// F' at the field point with offset o in the window, by central differences.  Beyond a line-tied face the
+// neighbour is the ghost 3 (y(0) - y(1)) + y(2) (see stage.hip), formed here by the few points that need
+// it: a pass that wrote the ghosts to LDS took a barrier more (us per step, 33^3 49.9 -> 45.6, 65^3 107 -> 97).
+template <typename Y>
+__device__ __forceinline__ void face_differences(const Brick& b, int ends, bool at_face, const Y& ys, int o, double F[3][3]) {
+#pragma unroll
+  for (int c = 0; c < 3; c++) {
+    const int s = c == 0 ? 1 : (c == 1 ? b.sx : b.sxy);
+    double lo[3], hi[3];
+#pragma unroll
+    for (int m = 0; m < 3; m++) {
+      lo[m] = ys[m][o - s];
+      hi[m] = ys[m][o + s];
+    }
+    if (at_face) {
+      const int end = (ends >> (2 * c)) & 3;  // 1: low end, 2: high end
+      if (end == 1) {
+#pragma unroll
+        for (int m = 0; m < 3; m++) lo[m] = fma(3.0, ys[m][o] - hi[m], ys[m][o + 2 * s]);
+      } else if (end == 2) {
+#pragma unroll
+        for (int m = 0; m < 3; m++) hi[m] = fma(3.0, ys[m][o] - lo[m], ys[m][o - 2 * s]);
+      }
+    }
+#pragma unroll
+    for (int m = 0; m < 3; m++) F[m][c] = hi[m] - lo[m];
+  }
 }
 
 }  // namespace relax

@@ -4,8 +4,7 @@
 // and LDS work each, with at least 12 steps per chunk, on a grid that has too few tiles to fill the
 // CUs.  Here a workgroup of 512 threads loads the stage input of a whole brick with its 2-node halo
 // into LDS at once, forms F', det F' and B on the brick and its 1-node halo (the own node first, then
-// the shell), and the current, force and update of one node per thread: two barriers in all (three at
-// line-tied faces), so that a sweep takes one round of global latency instead of a dozen.  The price is
+// the shell), and the current, force and update of one node per thread: two barriers in all, so that a sweep takes one round of global latency instead of a dozen.  The price is
 // the halo: a brick of 8 x 8 x 8 loads 3.4 window points and evaluates 2 fields per node where the
 // march of a tall chunk takes 1.6 and 1.3, so that bricks are used only where latency decides
 // (choose_brick in relax.cpp).  The arithmetic of a node is that of stage.hip (stage_math.h).
@@ -27,94 +26,103 @@ __global__ __launch_bounds__(BRICK_THREADS) __attribute__((amdgpu_waves_per_eu(4
   constexpr int NPK = St::NPK, NPKA = St::NPKA, NPS = St::NPS;
   static_assert(!DIAG || (S == 1 && !MIXED), "the diagnostics sweep is the FP64 stage-1 sweep");
 
-  Control* ctl = a.ctl;
-  int cur;
+  // Scalars first, in one go: each that is fetched behind a branch on another costs its latency again
+  // (six such fetches stood before the first load; with the index arithmetic cut to a third, us per step
+  // 16^3 46.8 -> 38.5, 32^3 periodic 65.6 -> 47.4, 80^3 periodic 149 -> 135).
+  const Control* ctl = a.ctl;
+  int status = 0, need_k1 = 1, cur = a.diag_buf, record = 0;
+  long long accepted = 0, target = 1, steps_total = 0;
   double dt = 0.0;
-  bool record_ck = false;
-  long long ck_slot = 0;
   if (!DIAG) {
-    if (ctl->status != 0 || ctl->accepted >= ctl->target) return;
-    if (STAGE1 && ctl->need_k1 == 0) return;
+    status = ctl->status;
     cur = ctl->cur;
+    accepted = ctl->accepted;
+    target = ctl->target;
     dt = ctl->dt;
-    if (STAGE1 && ctl->record) {
-      const long long st = ctl->steps_total;
-      if (st % ctl->ck_every == 0 && st / ctl->ck_every < a.ckpt_slots) {
-        record_ck = true;
-        ck_slot = st / ctl->ck_every;
-      }
+    if constexpr (STAGE1) {
+      need_k1 = ctl->need_k1;
+      record = ctl->record;
+      steps_total = ctl->steps_total;
     }
-  } else {
-    cur = a.diag_buf;
   }
   const double gamma = ctl->gamma;
   const double tau_B2 = ctl->tau_B2;
-  const double cv = (S == 2) ? dt * CK::a[1][0] : 1.0;
 
   const Geometry& g = a.g;
   const long long N = g.N;
   const Brick br(g);
   const int sx = br.sx, sxy = br.sxy, fx = br.fx, fxy = br.fxy;
-
-  const int lb = logical_block(blockIdx.x, g.nblocks);
-  const int i0 = (lb % g.tiles[0]) * br.bx;
-  const int j0 = ((lb / g.tiles[0]) % g.tiles[1]) * br.by;
-  const int k0 = (lb / (g.tiles[0] * g.tiles[1])) * br.bz;
+  const BrickOrigin at0(br, g);
   const int tid = threadIdx.x;
 
   __shared__ double ys[3][BRICK_WINDOW];
   __shared__ T bs[3][BRICK_FIELD];
   __shared__ double red[BRICK_THREADS / 64][NPART];
 
-  const double* __restrict__ xn = a.x[cur];
-  const double* __restrict__ wbase = (S == 3) ? a.y3 : ((S == 5) ? a.y5 : xn);
-  const T* __restrict__ wvec = static_cast<const T*>(S == 2 ? a.k[0] : (S == 4 ? a.d4 : a.sum[0]));
-  const T* __restrict__ b0p = static_cast<const T*>(a.B0);
-
-  // ---- the window and B0 first ---------------------------------------------------------------------
+  // ---- the window and B0 first; a wave skips the points past the brick's
   double wx[NPW][3];
   T wk[WV ? NPW : 1][3];
   BrickPoint wp[NPW];
+  wp[0] = brick_window(br, g, min(tid, br.nwin - 1), at0);
+  const double* __restrict__ xn = cur ? a.x[1] : a.x[0];
+  const double* __restrict__ wbase = (S == 3) ? a.y3 : ((S == 5) ? a.y5 : xn);
+  const T* __restrict__ wvec = static_cast<const T*>(S == 2 ? a.k[0] : (S == 4 ? a.d4 : a.sum[0]));
+  const T* __restrict__ b0p = static_cast<const T*>(a.B0);
+  if (!DIAG && (status != 0 || accepted >= target)) return;
+  if (!DIAG && STAGE1 && need_k1 == 0) return;
 #pragma unroll
   for (int r = 0; r < NPW; r++) {
-    wp[r] = brick_window(br, g, tid + r * BRICK_THREADS, i0, j0, k0);
-    const int i = wp[r].index;
+    const int e = tid + r * BRICK_THREADS;
+    if (r == 0 || e < br.nwin) {
+      if (r > 0) wp[r] = brick_window(br, g, e, at0);
+      const unsigned i = wp[r].index;
 #pragma unroll
-    for (int m = 0; m < 3; m++) wx[r][m] = wbase[m * N + i];
-    if constexpr (WV) {
+      for (int m = 0; m < 3; m++) wx[r][m] = at(wbase + m * N, i);
+      if constexpr (WV) {
 #pragma unroll
-      for (int m = 0; m < 3; m++) wk[r][m] = wvec[m * N + i];
+        for (int m = 0; m < 3; m++) wk[r][m] = at(wvec + m * N, i);
+      }
     }
   }
   T b0r[NPF][3];
   BrickField fp[NPF];
 #pragma unroll
   for (int r = 0; r < NPF; r++) {
-    fp[r] = brick_field(br, g, r, tid, i0, j0, k0);
+    fp[r].slot = -1;
+    if (r == 0 || tid + (r - 1) * BRICK_THREADS < br.nshell) {
+      fp[r] = brick_field(br, g, r, tid, at0);
 #pragma unroll
-    for (int m = 0; m < 3; m++) b0r[r][m] = b0p[m * N + fp[r].index];
+      for (int m = 0; m < 3; m++) b0r[r][m] = at(b0p + m * N, (unsigned)fp[r].index);
+    }
   }
   const bool node = fp[0].node();
   const int own = fp[0].index;
   const bool face = fp[0].face();
+  const double cv = (S == 2) ? dt * CK::a[1][0] : 1.0;
+  bool record_ck = false;
+  long long ck_slot = 0;
+  if (!DIAG && STAGE1 && record) {
+    const long long every = ctl->ck_every;
+    if (steps_total % every == 0 && steps_total / every < a.ckpt_slots) {
+      record_ck = true;
+      ck_slot = steps_total / every;
+    }
+  }
   // ---- stage input on the brick and its 2-node halo ------------------------------------------
 #pragma unroll
   for (int r = 0; r < NPW; r++) {
     const int e = tid + r * BRICK_THREADS;
-    double v[3];
-#pragma unroll
-    for (int m = 0; m < 3; m++) {
-      double y = wx[r][m];
-      if constexpr (S == 2) {
-        y = y + cv * (double)wk[r][m];
-      } else if constexpr (WV) {
-        y = y + (double)wk[r][m];
-      }
-      v[m] = y + wp[r].wrap(m) * g.period[m];
-    }
     if (e < br.nwin) {
 #pragma unroll
-      for (int m = 0; m < 3; m++) ys[m][e] = wp[r].on() ? v[m] : 0.0;
+      for (int m = 0; m < 3; m++) {
+        double y = wx[r][m];
+        if constexpr (S == 2) {
+          y = y + cv * (double)wk[r][m];
+        } else if constexpr (WV) {
+          y = y + (double)wk[r][m];
+        }
+        ys[m][e] = wp[r].on() ? y + wp[r].wrap(m) * g.period[m] : 0.0;
+      }
     }
   }
   // The vectors read at the node, once the window's registers are free (4 waves a SIMD need 128); the
@@ -125,30 +133,16 @@ __global__ __launch_bounds__(BRICK_THREADS) __attribute__((amdgpu_waves_per_eu(4
 #pragma unroll
     for (int m = 0; m < 3; m++) {
 #pragma unroll
-      for (int j = 0; j < NPK; j++) pk[j][m] = static_cast<const T*>(a.k[LEAN ? (S == 3 ? 1 : 2 * j) : j])[m * N + own];
-      if constexpr (PS) ps[0][m] = static_cast<const T*>(S == 5 ? a.sum[0] : a.sum[1])[m * N + own];
-      if constexpr (PS && NPS == 2) ps[NPS - 1][m] = static_cast<const T*>(a.sum[2])[m * N + own];
-      if constexpr (CX) xq[m] = xn[m * N + own];
-      if constexpr (CV) vq[m] = wvec[m * N + own];
+      for (int j = 0; j < NPK; j++) pk[j][m] = at(static_cast<const T*>(a.k[LEAN ? (S == 3 ? 1 : 2 * j) : j]) + m * N, own);
+      if constexpr (PS) ps[0][m] = at(static_cast<const T*>(S == 5 ? a.sum[0] : a.sum[1]) + m * N, own);
+      if constexpr (PS && NPS == 2) ps[NPS - 1][m] = at(static_cast<const T*>(a.sum[2]) + m * N, own);
+      if constexpr (CX) xq[m] = at(xn + m * N, own);
+      if constexpr (CV) vq[m] = at(wvec + m * N, own);
     }
   };
   if constexpr (!NNN) load_node();
   __syncthreads();
-  if constexpr (!NNN) {
-    // ghost nodes beyond line-tied faces (see stage.hip)
-    if (br.at_face(g, i0, j0, k0)) {
-#pragma unroll
-      for (int r = 0; r < NPW; r++) {
-        const int e = tid + r * BRICK_THREADS, s = wp[r].ghost;
-        if (s != 0) {
-#pragma unroll
-          for (int m = 0; m < 3; m++) ys[m][e] = fma(3.0, ys[m][e + s] - ys[m][e + 2 * s], ys[m][e + 3 * s]);
-        }
-      }
-      __syncthreads();
-    }
-  }
-
+  const bool at_face = br.at_face(g, at0.i0, at0.j0, at0.k0);
   // ---- F', det F' and B on the brick and its 1-node halo ---------------------------------------
   Sums acc;
   T Fq[3][3], Bq[3], rDq;
@@ -173,12 +167,7 @@ __global__ __launch_bounds__(BRICK_THREADS) __attribute__((amdgpu_waves_per_eu(4
           F[m][2] = row(ys[m], sxy, (fp[r].ends >> 4) & 3);
         }
       } else {
-#pragma unroll
-        for (int m = 0; m < 3; m++) {
-          F[m][0] = ys[m][o + 1] - ys[m][o - 1];
-          F[m][1] = ys[m][o + sx] - ys[m][o - sx];
-          F[m][2] = ys[m][o + sxy] - ys[m][o - sxy];
-        }
+        face_differences(br, fp[r].ends, at_face, ys, o, F);
       }
       const double D = (NNN || MIXED) ? det3(F) : det3_fused(F);
       const double rD = fp[r].on() ? rcp_nr(D) : 0.0;
@@ -286,7 +275,8 @@ __global__ __launch_bounds__(BRICK_THREADS) __attribute__((amdgpu_waves_per_eu(4
     }
     auto put = [&](auto* to, const auto (&v)[3]) {
 #pragma unroll
-      for (int m = 0; m < 3; m++) to[m * N + own] = v[m];
+      for (int m = 0; m < 3; m++)
+        *reinterpret_cast<decltype(to)>(reinterpret_cast<char*>(to + m * N) + (unsigned)own * (unsigned)sizeof(*to)) = v[m];
     };
     if constexpr (DIAG) {
       const double sc = a.u_det_scale != 0.0 ? Dq * a.u_det_scale : 1.0;
@@ -330,7 +320,7 @@ __global__ __launch_bounds__(BRICK_THREADS) __attribute__((amdgpu_waves_per_eu(4
       put(a.yrec[S == 4 ? 0 : 1], yo);
     }
   }
-  if (STAGE1) store_sums<BRICK_THREADS>(acc, red, a.part + (long long)blockIdx.x * NPART);
+  if (STAGE1) store_sums<BRICK_THREADS, DIAG>(acc, red, a.part + (long long)blockIdx.x * NPART);
   if (LAST) store_lambda<BRICK_THREADS>(acc, red, a.lam_part + blockIdx.x);
 }
 

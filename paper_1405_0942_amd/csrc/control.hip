@@ -9,83 +9,80 @@
 //     otherwise                -> accept, keep dt
 // (Lambda == 0 grows the step 5x.)  On acceptance it records the step's diagnostics in
 // the device ring and swaps the position buffers.
-#include "relax_device.h"
+#include "sweep_common.h"
 
 namespace relax {
 namespace {
 
-constexpr int CT = 256;  // control workgroup size
-
-__device__ __forceinline__ double max_nan(double a, double b) { return (b > a || b != b) ? b : a; }
-__device__ __forceinline__ double min_nan(double a, double b) { return (b < a || b != b) ? b : a; }
+constexpr int CT = 256;  // workgroup size of the set-up reductions
 
 // status codes (the values of include/relax.h)
 constexpr int E_FOLD = -3, E_DT = -4, E_NAN = -5;
 
-__global__ __launch_bounds__(CT) void control_kernel(Control* ctl, const double* __restrict__ part,
-                                                      const double* __restrict__ lam_part, int nblocks,
-                                                      double* __restrict__ ring, double* __restrict__ dt_record) {
-  if (ctl->status != 0 || ctl->accepted >= ctl->target) return;
-  const int tid = threadIdx.x;
-  const bool fresh = (ctl->need_k1 != 0);
-  __shared__ double sE[CT], sR[CT], sX[CT], sM[CT], sZ[CT], sL[CT];
-  double E = 0, R = 0, X = 0, M = INFINITY, Z = 0, L = 0;
-  for (int b = tid; b < nblocks; b += CT) {
-    if (fresh) {
-      const double* p = part + (long long)b * NPART;
-      E += p[0];
-      R += p[1];
-      X = max_nan(X, p[2]);
-      M = min_nan(M, p[3]);
-      Z += p[4];
-    }
-    L = max_nan(L, lam_part[b]);
+// The reduction of the workgroups' records: two waves per quantity, each lane a share of the records in a
+// fixed order, then the lanes by DPP.  Quantity 5 of a record is `sixth` with stride `stride6`: Lambda of
+// stage 6, or the concave count of a diagnostics sweep.  The loads of all quantities go out together and
+// wait for nothing else, which is what the time of these kernels is made of: 64 records 4.4 -> 3.0 us, 256
+// records 6.3 -> 5.0, against LDS trees of six arrays after the control block's fields one by one.
+constexpr int RT = 768;
+template <bool LAMBDA>
+__device__ __forceinline__ void reduce_records(const double* __restrict__ part, const double* __restrict__ sixth,
+                                               int stride6, int nblocks, double s[12]) {
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, q = wave % 6, half = wave / 6;
+  const double* p = q == 5 ? sixth : part + q;
+  const int stride = q == 5 ? stride6 : NPART;
+  double sum = 0.0, X = 0.0, M = INFINITY;
+#pragma unroll 4
+  for (int b = half * 64 + lane; b < nblocks; b += 128) {
+    const double v = p[(long long)b * stride];
+    sum += v;
+    X = max_nan(X, v);
+    M = min_nan(M, v);
   }
-  sE[tid] = E;
-  sR[tid] = R;
-  sX[tid] = X;
-  sM[tid] = M;
-  sZ[tid] = Z;
-  sL[tid] = L;
-  __syncthreads();
-  for (int s = CT / 2; s > 0; s >>= 1) {
-    if (tid < s) {
-      sE[tid] += sE[tid + s];
-      sR[tid] += sR[tid + s];
-      sX[tid] = max_nan(sX[tid], sX[tid + s]);
-      sM[tid] = min_nan(sM[tid], sM[tid + s]);
-      sZ[tid] += sZ[tid + s];
-      sL[tid] = max_nan(sL[tid], sL[tid + s]);
-    }
-    __syncthreads();
-  }
-  if (tid != 0) return;
+  double v;
+  if (q == 2 || (LAMBDA && q == 5))
+    v = wave_max(X);
+  else if (q == 3)
+    v = wave_min(M);
+  else
+    v = wave_sum(sum);
+  if (lane == 63) s[wave] = v;
+}
 
-  Control& c = *ctl;
-  if (fresh) {
-    c.E = 0.5 * sE[0] * c.dV;
-    c.R2 = 0.5 * sR[0] * c.dV;
-    c.xi = sX[0];
-    c.min_det = sM[0];
-    c.nulls = sZ[0];
-    c.need_k1 = 0;
+__global__ __launch_bounds__(RT) void control_kernel(Control* ctl, const double* __restrict__ part,
+                                                     const double* __restrict__ lam_part, int nblocks,
+                                                     double* __restrict__ ring, double* __restrict__ dt_record) {
+  Control c = *ctl;
+  __shared__ double s[12];
+  reduce_records<true>(part, lam_part, 1, nblocks, s);
+  if (c.status != 0 || c.accepted >= c.target) return;
+  __syncthreads();
+  if (threadIdx.x != 0) return;
+
+  if (c.need_k1 != 0) {  // x_n is new: stage 1 has left its diagnostics
+    ctl->E = c.E = 0.5 * (s[0] + s[6]) * c.dV;
+    ctl->R2 = c.R2 = 0.5 * (s[1] + s[7]) * c.dV;
+    ctl->xi = c.xi = max_nan(s[2], s[8]);
+    ctl->min_det = c.min_det = min_nan(s[3], s[9]);
+    ctl->nulls = s[4] + s[10];
+    ctl->need_k1 = 0;
     if (c.min_det != c.min_det) {
-      c.status = E_NAN;
+      ctl->status = E_NAN;
       return;
     }
     if (!(c.min_det > 0.0)) {
-      c.status = E_FOLD;
+      ctl->status = E_FOLD;
       return;
     }
     if (!isfinite(c.E) || !isfinite(c.R2)) {
-      c.status = E_NAN;
+      ctl->status = E_NAN;
       return;
     }
   }
-  const double lam = sL[0];
-  c.lambda = lam;
+  const double lam = max_nan(s[5], s[11]);
+  ctl->lambda = lam;
   if (lam != lam || isinf(lam)) {
-    c.status = E_NAN;
+    ctl->status = E_NAN;
     return;
   }
   const double dt = c.dt;
@@ -101,9 +98,9 @@ __global__ __launch_bounds__(CT) void control_kernel(Control* ctl, const double*
     }
   }
   if (!accept) {
-    c.rejects += 1;
-    c.dt = dt_next;
-    if (dt_next < c.dt_min) c.status = E_DT;
+    ctl->rejects = c.rejects + 1;
+    ctl->dt = dt_next;
+    if (dt_next < c.dt_min) ctl->status = E_DT;
     return;
   }
   double* e = ring + (long long)c.accepted * 8;
@@ -116,55 +113,25 @@ __global__ __launch_bounds__(CT) void control_kernel(Control* ctl, const double*
   e[6] = c.min_det;
   e[7] = (double)c.rejects;
   if (c.record && dt_record && c.steps_total < c.record_cap) dt_record[c.steps_total] = dt;
-  c.t += dt;
-  c.dt = dt_next;
-  c.cur = 1 - c.cur;
-  c.accepted += 1;
-  c.steps_total += 1;
-  c.rejects = 0;
-  c.need_k1 = 1;
+  ctl->t = c.t + dt;
+  ctl->dt = dt_next;
+  ctl->cur = 1 - c.cur;
+  ctl->accepted = c.accepted + 1;
+  ctl->steps_total = c.steps_total + 1;
+  ctl->rejects = 0;
+  ctl->need_k1 = 1;
 }
 
-// final reduction of a diagnostics sweep: out = {sum E, sum R2, max xi, min det, nulls}
-__global__ __launch_bounds__(CT) void diag_finish_kernel(const double* __restrict__ part, int nblocks, double dV,
-                                                          double* __restrict__ out) {
-  const int tid = threadIdx.x;
-  __shared__ double sE[CT], sR[CT], sX[CT], sM[CT], sZ[CT], sC[CT];
-  double E = 0, R = 0, X = 0, M = INFINITY, Z = 0, Cc = 0;
-  for (int b = tid; b < nblocks; b += CT) {
-    const double* p = part + (long long)b * NPART;
-    E += p[0];
-    R += p[1];
-    X = max_nan(X, p[2]);
-    M = min_nan(M, p[3]);
-    Z += p[4];
-    Cc += p[5];
-  }
-  sE[tid] = E;
-  sR[tid] = R;
-  sX[tid] = X;
-  sM[tid] = M;
-  sZ[tid] = Z;
-  sC[tid] = Cc;
+// final reduction of a diagnostics sweep: out = {sum E, sum R2, max xi, min det, nulls, concave cells}
+__global__ __launch_bounds__(RT) void diag_finish_kernel(const double* __restrict__ part, int nblocks, double dV,
+                                                         double* __restrict__ out) {
+  __shared__ double s[12];
+  reduce_records<false>(part, part + 5, NPART, nblocks, s);
   __syncthreads();
-  for (int s = CT / 2; s > 0; s >>= 1) {
-    if (tid < s) {
-      sE[tid] += sE[tid + s];
-      sR[tid] += sR[tid + s];
-      sX[tid] = max_nan(sX[tid], sX[tid + s]);
-      sM[tid] = min_nan(sM[tid], sM[tid + s]);
-      sZ[tid] += sZ[tid + s];
-      sC[tid] += sC[tid + s];
-    }
-    __syncthreads();
-  }
-  if (tid == 0) {
-    out[0] = 0.5 * sE[0] * dV;
-    out[1] = 0.5 * sR[0] * dV;
-    out[2] = sX[0];
-    out[3] = sM[0];
-    out[4] = sZ[0];
-    out[5] = sC[0];
+  const int q = threadIdx.x;
+  if (q < 6) {
+    const double v = q == 2 ? max_nan(s[2], s[8]) : (q == 3 ? min_nan(s[3], s[9]) : s[q] + s[q + 6]);
+    out[q] = q < 2 ? 0.5 * v * dV : v;
   }
 }
 
@@ -209,8 +176,10 @@ __global__ __launch_bounds__(CT) void max_norm2_part_kernel(const double* __rest
   if (threadIdx.x == 0) part[blockIdx.x] = s[0];
 }
 
+// ... and, with a control block, what the diagnostics sweep of a call without a context reads from it
 __global__ __launch_bounds__(CT) void max_reduce_kernel(const double* __restrict__ part, int n,
-                                                        double* __restrict__ out) {
+                                                        double* __restrict__ out, Control* ctl, double gamma,
+                                                        double xi_null_tau) {
   __shared__ double s[CT];
   double m = 0.0;
   for (int i = threadIdx.x; i < n; i += CT) m = max_nan(m, part[i]);
@@ -220,19 +189,25 @@ __global__ __launch_bounds__(CT) void max_reduce_kernel(const double* __restrict
     if (threadIdx.x < k) s[threadIdx.x] = max_nan(s[threadIdx.x], s[threadIdx.x + k]);
     __syncthreads();
   }
-  if (threadIdx.x == 0) *out = s[0];
+  if (threadIdx.x == 0) {
+    *out = s[0];
+    if (ctl) {
+      ctl->gamma = gamma;
+      ctl->tau_B2 = xi_null_tau * s[0];
+    }
+  }
 }
 
 }  // namespace
 
 hipError_t launch_control(Control* ctl, const double* part, const double* lam_part, int nblocks, double* ring,
                           double* dt_record, hipStream_t st) {
-  hipLaunchKernelGGL(control_kernel, dim3(1), dim3(CT), 0, st, ctl, part, lam_part, nblocks, ring, dt_record);
+  hipLaunchKernelGGL(control_kernel, dim3(1), dim3(RT), 0, st, ctl, part, lam_part, nblocks, ring, dt_record);
   return hipGetLastError();
 }
 
 hipError_t launch_diag_finish(const double* part, int nblocks, double dV, double* out6, hipStream_t st) {
-  hipLaunchKernelGGL(diag_finish_kernel, dim3(1), dim3(CT), 0, st, part, nblocks, dV, out6);
+  hipLaunchKernelGGL(diag_finish_kernel, dim3(1), dim3(RT), 0, st, part, nblocks, dV, out6);
   return hipGetLastError();
 }
 
@@ -258,13 +233,14 @@ hipError_t launch_prescale(double* B0, long long N, const double scale[3], hipSt
 }
 
 hipError_t launch_max_norm2(const double* v, long long N, double* out, double* scratch, int nscratch,
-                            hipStream_t st) {
+                            hipStream_t st, Control* ctl, double gamma, double xi_null_tau) {
   long long blocks = (N + CT - 1) / CT;
   if (blocks > nscratch) blocks = nscratch;
   if (blocks > 2048) blocks = 2048;
   if (blocks < 1) blocks = 1;
   hipLaunchKernelGGL(max_norm2_part_kernel, dim3((unsigned)blocks), dim3(CT), 0, st, v, N, scratch);
-  hipLaunchKernelGGL(max_reduce_kernel, dim3(1), dim3(CT), 0, st, scratch, (int)blocks, out);
+  hipLaunchKernelGGL(max_reduce_kernel, dim3(1), dim3(CT), 0, st, scratch, (int)blocks, out, ctl, gamma,
+                     xi_null_tau);
   return hipGetLastError();
 }
 

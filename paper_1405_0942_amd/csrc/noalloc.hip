@@ -47,14 +47,6 @@ hipError_t scratch_ptr(double** out) {
   return hipSuccess;
 }
 
-// the two control fields the diagnostics sweep reads
-__global__ void na_setup_kernel(Control* ctl, double gamma, double xi_null_tau, const double* maxB2) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) {
-    ctl->gamma = gamma;
-    ctl->tau_B2 = xi_null_tau * (*maxB2);
-  }
-}
-
 }  // namespace
 }  // namespace relax
 
@@ -90,9 +82,9 @@ extern "C" int relax_diagnostics_noalloc(const relax_config* cfg, const double* 
 
   // max |B0|^2 of the caller's field (the xi null guard), the two control fields, the FP64
   // diagnostics sweep and its fixed-order final reduction
-  if (launch_max_norm2(d_B0, g.N, d_maxB2, d_part, NA_MAX_BLOCKS * NPART, st) != hipSuccess) return RELAX_E_HIP;
-  hipLaunchKernelGGL(na_setup_kernel, dim3(1), dim3(64), 0, st, ctl, cfg->gamma, cfg->xi_null_tau, d_maxB2);
-  if (hipGetLastError() != hipSuccess) return RELAX_E_HIP;
+  if (launch_max_norm2(d_B0, g.N, d_maxB2, d_part, NA_MAX_BLOCKS * NPART, st, ctl, cfg->gamma, cfg->xi_null_tau) !=
+      hipSuccess)
+    return RELAX_E_HIP;
   if (launch_diagnostics(a, st) != hipSuccess) return RELAX_E_HIP;
   if (launch_diag_finish(d_part, g.nblocks, g.dV, d_out, st) != hipSuccess) return RELAX_E_HIP;
   double d[6];

@@ -182,6 +182,6 @@ hipError_t launch_fill(double* v, long long n, double val, hipStream_t st);
 hipError_t launch_seg_step(Control* c2, const double* dt_record, long long n, hipStream_t st);
 // out = max over nodes of |v|^2; scratch holds nscratch >= 1 doubles of per-workgroup maxima
 hipError_t launch_max_norm2(const double* v, long long N, double* out, double* scratch, int nscratch,
-                            hipStream_t st);
+                            hipStream_t st, Control* ctl = nullptr, double gamma = 0.0, double xi_null_tau = 0.0);
 
 }  // namespace relax

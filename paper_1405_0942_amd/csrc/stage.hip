@@ -796,7 +796,7 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
   }
 
   // ---- workgroup reductions -> partial records -----------------------------------------
-  if (STAGE1) store_sums<NTHREADS>(acc, red, a.part + (long long)blockIdx.x * NPART);
+  if (STAGE1) store_sums<NTHREADS, DIAG>(acc, red, a.part + (long long)blockIdx.x * NPART);
   if (LAST) store_lambda<NTHREADS>(acc, red, a.lam_part + blockIdx.x);
 }
 

@@ -11,36 +11,6 @@
 
 namespace relax {
 
-__device__ __forceinline__ double max_nan(double a, double b) { return (b > a || b != b) ? b : a; }
-__device__ __forceinline__ double min_nan(double a, double b) { return (b < a || b != b) ? b : a; }
-
-// Reductions over a wave by DPP (four row shifts, then two row broadcasts): the result is in lane 63.
-// idle: what a lane without a partner takes in.
-template <int CTRL, int ROWS>
-__device__ __forceinline__ double dpp(double v, double idle) {
-  typedef int i2 __attribute__((ext_vector_type(2)));
-  const i2 a = __builtin_bit_cast(i2, v), z = __builtin_bit_cast(i2, idle);
-  i2 r;
-  r.x = __builtin_amdgcn_update_dpp(z.x, a.x, CTRL, ROWS, 0xf, false);
-  r.y = __builtin_amdgcn_update_dpp(z.y, a.y, CTRL, ROWS, 0xf, false);
-  return __builtin_bit_cast(double, r);
-}
-template <typename Op>
-__device__ __forceinline__ double wave_reduce(double v, double idle, Op op) {
-  v = op(v, dpp<0x111, 0xf>(v, idle));
-  v = op(v, dpp<0x112, 0xf>(v, idle));
-  v = op(v, dpp<0x114, 0xf>(v, idle));
-  v = op(v, dpp<0x118, 0xf>(v, idle));
-  v = op(v, dpp<0x142, 0xa>(v, idle));
-  v = op(v, dpp<0x143, 0xc>(v, idle));
-  return v;
-}
-__device__ __forceinline__ double wave_sum(double v) {
-  return wave_reduce(v, 0.0, [](double a, double b) { return a + b; });
-}
-__device__ __forceinline__ double wave_max(double v) { return wave_reduce(v, 0.0, max_nan); }  // v >= 0 or NaN
-__device__ __forceinline__ double wave_min(double v) { return wave_reduce(v, INFINITY, min_nan); }
-
 // What a stage reads and stores (S: stage 1..6; the variants are described at stage_kernel).
 template <int S, bool MIXED, bool NNN>
 struct Stage {
@@ -295,11 +265,11 @@ struct Sums {
 };
 
 // Workgroup reductions of NT threads, in a fixed order, into the partial record of stage 1 ...
-template <int NT>
+template <int NT, bool DIAG>
 __device__ __forceinline__ void store_sums(const Sums& c, double red[NT / 64][NPART], double* pp) {
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const double e = wave_sum(c.E), r2 = wave_sum(c.R2), xi = wave_max(sqrt(c.xi_F2) / c.xi_B2),
-               mn = wave_min(c.min_det), nl = wave_sum(c.nulls), cc = wave_sum(c.concave);
+               mn = wave_min(c.min_det), nl = wave_sum(c.nulls), cc = DIAG ? wave_sum(c.concave) : 0.0;
   if (lane == 63) {
     red[wave][0] = e;
     red[wave][1] = r2;

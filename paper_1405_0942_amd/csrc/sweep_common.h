@@ -1,7 +1,7 @@
 // sweep_common.h -- device helpers shared by the forward stage sweeps (stage.hip) and the
 // reverse sweeps (adjoint.hip): index resolution on line-tied and periodic axes, raw buffer
-// accesses with masked-off lanes, the XCD-aware tile order, the 3x3 determinant and a
-// Newton-refined reciprocal.  Internal to the library.
+// accesses with masked-off lanes, the XCD-aware tile order, the 3x3 determinant, a
+// Newton-refined reciprocal and reductions over a wave (also control.hip's).  Internal to the library.
 #pragma once
 
 #include "relax_device.h"
@@ -42,6 +42,14 @@ __device__ __forceinline__ AxisIdx resolve_near(int v, int n, int bc) {
     return AxisIdx{min(max(v - w * n, 0), n - 1), w, true};
   }
   return resolve(v, n, bc);
+}
+
+// The same for a window's points, without a branch: at most one period away, others are off the grid.
+// w is the wrap of a periodic axis, and 0 on a line-tied one.
+__device__ __forceinline__ AxisIdx axis_index(int v, int n, int bc) {
+  const int pn = bc == BC_PERIODIC ? n : 0, pw = bc == BC_PERIODIC ? 1 : 0;
+  const int i = v + (v < 0 ? pn : (v >= n ? -pn : 0)), w = v < 0 ? -pw : (v >= n ? pw : 0);
+  return AxisIdx{i, w, (unsigned)i < (unsigned)n};
 }
 
 // ---- buffer access --------------------------------------------------------------------------
@@ -107,5 +115,35 @@ __device__ __forceinline__ double rcp_nr(double d) {
   e = fma(-d, r, 1.0);
   return fma(r, e, r);
 }
+
+__device__ __forceinline__ double max_nan(double a, double b) { return (b > a || b != b) ? b : a; }
+__device__ __forceinline__ double min_nan(double a, double b) { return (b < a || b != b) ? b : a; }
+
+// Reductions over a wave by DPP (four row shifts, then two row broadcasts): the result is in lane 63.
+// idle: what a lane without a partner takes in.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp(double v, double idle) {
+  typedef int i2 __attribute__((ext_vector_type(2)));
+  const i2 a = __builtin_bit_cast(i2, v), z = __builtin_bit_cast(i2, idle);
+  i2 r;
+  r.x = __builtin_amdgcn_update_dpp(z.x, a.x, CTRL, ROWS, 0xf, false);
+  r.y = __builtin_amdgcn_update_dpp(z.y, a.y, CTRL, ROWS, 0xf, false);
+  return __builtin_bit_cast(double, r);
+}
+template <typename Op>
+__device__ __forceinline__ double wave_reduce(double v, double idle, Op op) {
+  v = op(v, dpp<0x111, 0xf>(v, idle));
+  v = op(v, dpp<0x112, 0xf>(v, idle));
+  v = op(v, dpp<0x114, 0xf>(v, idle));
+  v = op(v, dpp<0x118, 0xf>(v, idle));
+  v = op(v, dpp<0x142, 0xa>(v, idle));
+  v = op(v, dpp<0x143, 0xc>(v, idle));
+  return v;
+}
+__device__ __forceinline__ double wave_sum(double v) {
+  return wave_reduce(v, 0.0, [](double a, double b) { return a + b; });
+}
+__device__ __forceinline__ double wave_max(double v) { return wave_reduce(v, 0.0, max_nan); }  // v >= 0 or NaN
+__device__ __forceinline__ double wave_min(double v) { return wave_reduce(v, INFINITY, min_nan); }
 
 }  // namespace relax

@@ -239,11 +239,50 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
       }
     }
     const bool in_win = e < RY2 * RX2;
-    const AxisIdx rx = resolve(i0 + col - 2, nx, bcx), ry = resolve(j0 + row - 2, ny, bcy);
+    const AxisIdx rx = axis_index(i0 + col - 2, nx, bcx), ry = axis_index(j0 + row - 2, ny, bcy);
     w2e[r] = (in_win && rx.ok && ry.ok) ? (unsigned)(ry.i * nx + rx.i) : IE;
     w2w[r] = (ry.w << 16) + (rx.w & 0xffff);
     w2o[r] = in_win ? row * RX2 + col : -1;
   }
+  // ---- loads, issued one plane step ahead of their use ---------------------------------------
+  struct Window {
+    double x[NP2][3];
+    double k[WK ? NP2 : 1][3];
+  };
+  auto load_window = [&](Window& w, int pz, bool on) {
+    const long long zo = (long long)zload(pz) * nxy;
+    unsigned e[NP2];
+#pragma unroll
+    for (int r = 0; r < NP2; r++) e[r] = on ? w2e[r] : IE;
+#pragma unroll
+    for (int m = 0; m < 3; m++) {
+      const auto rs = plane_rsrc(wsrc + m * N + zo, nxy);
+#pragma unroll
+      for (int r = 0; r < NP2; r++) w.x[r][m] = bload<double>(rs, e[r]);
+    }
+    if constexpr (WK) {
+#pragma unroll
+      for (int m = 0; m < 3; m++) {
+        const auto rs = plane_rsrc(k1p + m * N + zo, nxy);
+#pragma unroll
+        for (int r = 0; r < NP2; r++) w.k[r][m] = bload<double>(rs, e[r]);
+      }
+    }
+  };
+  const bool perz = (bcz == BC_PERIODIC);
+  const int pb0 = perz ? z0 - 1 : max(z0 - 1, 0);
+  const int pb1 = perz ? z1 : min(z1, nz - 1);
+
+  // the first three planes, so that the rest of the tables is built while they are under way (64 x 64 x 192:
+  // 654 -> 634 us per step of a backward pass)
+  const bool low = !perz && pb0 == 0;  // the plane below is a ghost plane
+  const int lo = low ? 0 : pb0 - 1;
+  Window w0, w1, w2;
+  load_window(w0, lo, true);
+  load_window(w1, lo + 1, true);
+  load_window(w2, lo + 2, true);
+  __builtin_amdgcn_sched_barrier(0);
+
   unsigned f1e[NP1];
   int f1o[NP1], f1y[NP1];  // offsets in the B window (-1: no point) and in the stage-input window
   bool f1live[NP1];        // on the grid and not on a line-tied face across x or y
@@ -272,7 +311,7 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
       halo_col = c1;
     }
     const bool in_win = e < RY1 * RX1;
-    const AxisIdx rx = resolve(i0 + c1 - 1, nx, bcx), ry = resolve(j0 + r1 - 1, ny, bcy);
+    const AxisIdx rx = axis_index(i0 + c1 - 1, nx, bcx), ry = axis_index(j0 + r1 - 1, ny, bcy);
     f1e[r] = (in_win && rx.ok && ry.ok) ? (unsigned)(ry.i * nx + rx.i) : IE;
     f1o[r] = in_win ? r1 * RX1 + c1 : -1;
     f1y[r] = (r1 + 1) * RX2 + c1 + 1;
@@ -308,33 +347,8 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
   const bool tile_ok = (gi_t < nx) && (gj_t < ny);
   const unsigned out_e = tile_ok ? (unsigned)(gj_t * nx + gi_t) : IE;
 
-  // ---- loads, issued one plane step ahead of their use ---------------------------------------
-  struct Window {
-    double x[NP2][3];
-    double k[WK ? NP2 : 1][3];
-  };
   double b0r[NP1][3], vr[NP1][3];
   double bbr[3];  // B0bar'' at the output node
-  auto load_window = [&](Window& w, int pz, bool on) {
-    const long long zo = (long long)zload(pz) * nxy;
-    unsigned e[NP2];
-#pragma unroll
-    for (int r = 0; r < NP2; r++) e[r] = on ? w2e[r] : IE;
-#pragma unroll
-    for (int m = 0; m < 3; m++) {
-      const auto rs = plane_rsrc(wsrc + m * N + zo, nxy);
-#pragma unroll
-      for (int r = 0; r < NP2; r++) w.x[r][m] = bload<double>(rs, e[r]);
-    }
-    if constexpr (WK) {
-#pragma unroll
-      for (int m = 0; m < 3; m++) {
-        const auto rs = plane_rsrc(k1p + m * N + zo, nxy);
-#pragma unroll
-        for (int r = 0; r < NP2; r++) w.k[r][m] = bload<double>(rs, e[r]);
-      }
-    }
-  };
   auto commit_window = [&](const Window& w, int pz) {
     const double shz = resolve_near(pz, nz, bcz).w * g.period[2];
     const int slot = pz & 3;
@@ -403,19 +417,9 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
     for (int m = 0; m < 3; m++) bstore(plane_rsrc(a.B0bar + m * N + zo, nxy), eo, B0b[m]);
   };
 
-  const bool perz = (bcz == BC_PERIODIC);
-  const int pb0 = perz ? z0 - 1 : max(z0 - 1, 0);
-  const int pb1 = perz ? z1 : min(z1, nz - 1);
-
-  // ---- prologue: the stage input on the planes pb0 - 1 .. pb0 + 1, loaded together
+  // ---- prologue: the stage input on the planes pb0 - 1 .. pb0 + 1
   Window win;
   {
-    const bool low = !perz && pb0 == 0;  // the plane below is a ghost plane
-    const int lo = low ? 0 : pb0 - 1;
-    Window w0, w1, w2;
-    load_window(w0, lo, true);
-    load_window(w1, lo + 1, true);
-    load_window(w2, lo + 2, true);
     commit_window(w0, lo);
     commit_window(w1, lo + 1);
     commit_window(w2, lo + 2);
@@ -546,9 +550,9 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
 // The same for small grids, a brick of nodes per workgroup (see brick.hip): the stage input with its
 // 2-node halo, B and the three Gbar' on the brick and its 1-node halo, all planes at once, two
 // barriers.  LDS: up to 157 KB (Gbar' takes 72 bytes a field point), one workgroup per CU.  Up to
-// 2^19 nodes (make_adj_geometry): us per step of a backward pass, march / bricks: 48^3 periodic 291 / 199,
-// 49^3 line-tied 330 / 221, 65^3 line-tied 471 / 413, 80^3 periodic 568 / 548, 81^3 line-tied 658 / 647,
-// 56 x 56 x 168 538 / 590, 88^3 periodic 710 / 753, 64 x 64 x 192 652 / 758.
+// 2^19 nodes (make_adj_geometry): us per step of a backward pass, march / bricks (its forward replay too):
+// 65^3 line-tied 491 / 377, 73^3 line-tied 585 / 485, 80^3 periodic 581 / 512, 81^3 line-tied 652 / 621,
+// 56 x 56 x 168 521 / 562, 90^3 periodic 772 / 748, 64 x 64 x 192 632 / 734.
 constexpr int NPW = (ADJ_WINDOW + BRICK_THREADS - 1) / BRICK_THREADS;
 constexpr int NPF = 1 + (BRICK_SHELL + BRICK_THREADS - 1) / BRICK_THREADS;
 

@@ -7,12 +7,6 @@
 
 namespace relax {
 
-// e / d for 0 <= e < 2^21, 1 <= d: (e + 1/2) / d is at least 1 / (2 d) away from an integer, more than
-// the 1.8e-7 (e + 1/2) / d that the reciprocal and the product round
-__device__ __forceinline__ int small_div(int e, int d) {
-  return (int)(((float)e + 0.5f) * __builtin_amdgcn_rcpf((float)d));
-}
-
 // The value at element i of a component, i < 2^28: base in scalar registers, byte offset in one register
 template <typename V>
 __device__ __forceinline__ V at(const V* __restrict__ base, unsigned i) {

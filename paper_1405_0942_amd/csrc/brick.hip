@@ -31,7 +31,8 @@ __global__ __launch_bounds__(BRICK_THREADS) __attribute__((amdgpu_waves_per_eu(4
   // 16^3 46.8 -> 38.5, 32^3 periodic 65.6 -> 47.4, 80^3 periodic 149 -> 135).
   const Control* ctl = a.ctl;
   int status = 0, need_k1 = 1, cur = a.diag_buf, record = 0;
-  long long accepted = 0, target = 1, steps_total = 0;
+  int accepted = 0, target = 1;
+  long long steps_total = 0;
   double dt = 0.0;
   if (!DIAG) {
     status = ctl->status;

@@ -156,11 +156,11 @@ int choose_tz(const relax_config* c, int tiles_xy) {
 // Bricks (brick.hip) or z-marching tiles, and which bricks.  A brick sweep takes its time from the
 // points it loads and evaluates, a march from the plane steps of a chunk, which a small grid cannot
 // shorten.  The bricks' line is two rounds of 512 workgroups of 512 nodes.  Measured us per step, march /
-// bricks, FP64: 48^3 periodic 126 / 73, 65^3 line-tied 146 / 110, 80^3 periodic 176 / 148, 56 x 56 x 168
-// 155 / 181, 81^3 line-tied 165 / 184, 96^3 periodic 207 / 227; FP32-mixed 48^3 110 / 69, 65^3 125 / 105,
-// 80^3 153 / 134, 81^3 143 / 173, 96^3 170 / 203; a diagnostics call 48^3 33 / 26, 65^3 34 / 34, 80^3 41 /
-// 41, 81^3 36 / 48.  The octilateral current, whose march holds one plane more and two barriers: 48^3 235 /
-// 102, 65^3 327 / 176, 81^3 346 / 297, 89^3 509 / 313, 96^3 379 / 379.
+// bricks, FP64: 48^3 periodic 116 / 62, 65^3 line-tied 139 / 96, 80^3 periodic 167 / 131, 56 x 56 x 168
+// 145 / 156, 81^3 line-tied 157 / 162, 90^3 periodic 209 / 181, 96^3 periodic 197 / 201; FP32-mixed 48^3
+// 102 / 59, 65^3 118 / 93, 80^3 144 / 120, 81^3 135 / 155, 96^3 161 / 182; a diagnostics call 48^3 31 / 25,
+// 65^3 34 / 33, 80^3 39 / 38, 81^3 35 / 46, 90^3 45 / 49.  The octilateral current, whose march holds one
+// plane more and two barriers: 48^3 227 / 90, 65^3 322 / 164, 81^3 338 / 279, 89^3 504 / 296, 96^3 371 / 340.
 // The brick of a grid for sweeps with at most `window` window points and `slots` resident workgroups.
 static void choose_brick(const relax_config* c, int window, unsigned slots, int brick[3]) {
   // edges that split an axis evenly (every ceil(n / k) up to 64), shortest first, and the bricks they make

@@ -116,26 +116,22 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
   static_assert(!NNN || (!MIXED && (DIAG || !REC)), "the octilateral current is an FP64 forward operator");
   constexpr bool YREC = REC && !DIAG;
 
-  Control* ctl = a.ctl;
+  // Scalars first, in one go: each that is fetched behind a branch on another costs its latency again
+  const Control* ctl = a.ctl;
   constexpr bool diag_only = DIAG;
-  int cur;
+  int status = 0, need_k1 = 1, cur = a.diag_buf, record = 0;
+  int accepted = 0, target = 1;
   double dt = 0.0;
-  bool record_ck = false;
-  long long ck_slot = 0;
   if (!diag_only) {
-    if (ctl->status != 0 || ctl->accepted >= ctl->target) return;
-    if (STAGE1 && ctl->need_k1 == 0) return;
+    status = ctl->status;
     cur = ctl->cur;
+    accepted = ctl->accepted;
+    target = ctl->target;
     dt = ctl->dt;
-    if (STAGE1 && ctl->record) {
-      const long long st = ctl->steps_total;
-      if (st % ctl->ck_every == 0 && st / ctl->ck_every < a.ckpt_slots) {
-        record_ck = true;
-        ck_slot = st / ctl->ck_every;
-      }
+    if constexpr (STAGE1) {
+      need_k1 = ctl->need_k1;
+      record = ctl->record;
     }
-  } else {
-    cur = a.diag_buf;
   }
   const double gamma = ctl->gamma;
   const double tau_B2 = ctl->tau_B2;
@@ -161,13 +157,14 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
 
   const int tid = threadIdx.x;
   const bool own = !FIT || tid < nown;
-  const int ty = own ? tid / tw : 0, tx = own ? tid - ty * tw : 0;
+  auto div = [](int e, int d) { return FIT ? small_div(e, d) : e / d; };
+  const int ty = own ? div(tid, tw) : 0, tx = own ? tid - ty * tw : 0;
 
   __shared__ double ys[RYS][3][RY2 * RX2];  // stage input, tile + 2-node halo, ring of planes
   __shared__ T bs[RBS][3][RY1 * RX1];       // pulled-back field, tile + 1-node halo, ring of planes
   __shared__ double red[NTHREADS / 64][NPART];
 
-  const double* __restrict__ xn = a.x[cur];
+  const double* __restrict__ xn = cur ? a.x[1] : a.x[0];
   const double* __restrict__ wbase = (S == 3) ? a.y3 : ((S == 5) ? a.y5 : xn);  // the window base
   const T* __restrict__ wvec = static_cast<const T*>(S == 2 ? a.k[0] : (S == 4 ? a.d4 : a.sum[0]));
   const T* __restrict__ b0p = static_cast<const T*>(a.B0);
@@ -189,12 +186,12 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
     const int e = tid + r * NTHREADS;
     int row, col;
     if (e < nown) {
-      row = e / tw + 2;
-      col = e % tw + 2;
+      row = div(e, tw) + 2;
+      col = e - (row - 2) * tw + 2;
     } else {
       const int e2 = e - nown;
       if (e2 < 4 * wx2) {
-        const int band = e2 / wx2;
+        const int band = div(e2, wx2);
         row = band < 2 ? band : wy2 - 4 + band;
         col = e2 - band * wx2;
       } else {
@@ -204,82 +201,12 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
       }
     }
     const bool in_win = e < wy2 * wx2;
-    const AxisIdx rx = resolve(i0 + col - 2, nx, bcx);
-    const AxisIdx ry = resolve(j0 + row - 2, ny, bcy);
+    const AxisIdx rx = axis_index(i0 + col - 2, nx, bcx);
+    const AxisIdx ry = axis_index(j0 + row - 2, ny, bcy);
     w2e[r] = (in_win && rx.ok && ry.ok) ? (unsigned)(ry.i * nx + rx.i) : IE;
     w2w[r] = (ry.w << 16) + (rx.w & 0xffff);
     w2o[r] = in_win ? row * wx2 + col : -1;
   }
-  // field point e: e < nown is the tile node of thread e; the rest is the halo ring
-  unsigned f1e[NP1];  // flat (x, y) index, IE off the grid
-  int f1o[NP1];       // offset in the B window, -1 past it
-  int f1y[NP1];       // offset in the stage-input window
-  int f1k[NP1];       // NNN: line-tied ends it lies on: 1, 2 along x, 4, 8 along y
-#pragma unroll
-  for (int r = 0; r < NP1; r++) {
-    const int e = tid + r * NTHREADS;
-    int r1, c1;
-    if (e < nown) {
-      r1 = e / tw + 1;
-      c1 = e % tw + 1;
-    } else {
-      const int e2 = e - nown;
-      if (e2 < wx1) {
-        r1 = 0;
-        c1 = e2;
-      } else if (e2 < 2 * wx1) {
-        r1 = wy1 - 1;
-        c1 = e2 - wx1;
-      } else {
-        const int e3 = e2 - 2 * wx1;
-        r1 = 1 + (e3 >> 1);
-        c1 = (e3 & 1) ? wx1 - 1 : 0;
-      }
-    }
-    const bool in_win = e < wy1 * wx1;
-    const AxisIdx rx = resolve(i0 + c1 - 1, nx, bcx), ry = resolve(j0 + r1 - 1, ny, bcy);
-    f1e[r] = (in_win && rx.ok && ry.ok) ? (unsigned)(ry.i * nx + rx.i) : IE;
-    f1o[r] = in_win ? r1 * wx1 + c1 : -1;
-    f1y[r] = (r1 + 1) * wx2 + c1 + 1;
-    f1k[r] = 0;
-    if (bcx == BC_LINE_TIED) f1k[r] |= rx.i == 0 ? 1 : (rx.i == nx - 1 ? 2 : 0);
-    if (bcy == BC_LINE_TIED) f1k[r] |= ry.i == 0 ? 4 : (ry.i == ny - 1 ? 8 : 0);
-  }
-  // Ghost nodes just beyond a line-tied face: y(-1) = 3 (y(0) - y(1)) + y(2), and likewise at the
-  // other end, so that the central difference at the face node is the one-sided second-order row
-  // -3 y(0) + 4 y(1) - y(2) and every node takes the same path.  Beyond faces across x and y a
-  // thread fills one ghost component of a plane; beyond faces across z see commit_window.
-  const int NGC = 3 * wy2, NGR = 3 * wx2;  // ghosts of one column, of one row
-  int gh_o[NPG], gh_s[NPG];  // offset in the plane's three components (-1: none), step into the grid
-#pragma unroll
-  for (int r = 0; r < NPG; r++) {
-    gh_o[r] = -1;
-    gh_s[r] = 0;
-    const int t = tid + r * NTHREADS;
-    if (t < 2 * NGC) {
-      const int side = t / NGC, t1 = t - side * NGC, m = t1 / wy2, row = t1 - m * wy2;
-      const int col = side == 0 ? 1 - i0 : nx - i0 + 2;
-      if (bcx == BC_LINE_TIED && col >= 0 && col < wx2) {
-        gh_o[r] = m * (RY2 * RX2) + row * wx2 + col;
-        gh_s[r] = side == 0 ? 1 : -1;
-      }
-    } else if (t < 2 * NGC + 2 * NGR) {
-      const int t0 = t - 2 * NGC, side = t0 / NGR, t1 = t0 - side * NGR, m = t1 / wx2, col = t1 - m * wx2;
-      const int row = side == 0 ? 1 - j0 : ny - j0 + 2;
-      if (bcy == BC_LINE_TIED && row >= 0 && row < wy2) {
-        gh_o[r] = m * (RY2 * RX2) + row * wx2 + col;
-        gh_s[r] = side == 0 ? wx2 : -wx2;
-      }
-    }
-  }
-
-  // tile node owned by this thread
-  const int gi_t = i0 + tx, gj_t = j0 + ty;
-  const bool tile_ok = own && (gi_t < nx) && (gj_t < ny);
-  const unsigned out_e = tile_ok ? (unsigned)(gj_t * nx + gi_t) : IE;
-  const bool face_x = bcx == BC_LINE_TIED && (gi_t == 0 || gi_t == nx - 1);
-  const bool face_y = bcy == BC_LINE_TIED && (gj_t == 0 || gj_t == ny - 1);
-
   // ---- loads of one plane, issued one plane step ahead of their use -------------------------
   struct Nodes {
     T b0[NP1][3];   // B0'' at the field points
@@ -310,6 +237,103 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
       }
     }
   };
+  // planes of B this chunk needs
+  const bool perz = (bcz == BC_PERIODIC);
+  const int pb0 = perz ? z0 - 1 : max(z0 - 1, 0);
+  const int pb1 = perz ? z1 : min(z1, nz - 1);
+
+  // The first three planes go out here, so that the rest of the tables is built while they are under
+  // way; with the scalars above and tables without divisions, us per step: 64 x 64 x 192 176 -> 168,
+  // 96^3 206 -> 197, 129^3 450 -> 438, 256^3 2404 -> 2393.
+  if (!diag_only && (status != 0 || accepted >= target)) return;
+  if (!diag_only && STAGE1 && need_k1 == 0) return;
+  const bool low = !perz && pb0 == 0;  // the plane below is a ghost plane
+  const int lo = low ? 0 : pb0 - 1;
+  Window w0, w1, w2;
+  load_window(w0, lo, true);
+  load_window(w1, lo + 1, true);
+  load_window(w2, lo + 2, true);
+  __builtin_amdgcn_sched_barrier(0);
+
+  // field point e: e < nown is the tile node of thread e; the rest is the halo ring
+  unsigned f1e[NP1];  // flat (x, y) index, IE off the grid
+  int f1o[NP1];       // offset in the B window, -1 past it
+  int f1y[NP1];       // offset in the stage-input window
+  int f1k[NP1];       // NNN: line-tied ends it lies on: 1, 2 along x, 4, 8 along y
+#pragma unroll
+  for (int r = 0; r < NP1; r++) {
+    const int e = tid + r * NTHREADS;
+    int r1, c1;
+    if (e < nown) {
+      r1 = div(e, tw) + 1;
+      c1 = e - (r1 - 1) * tw + 1;
+    } else {
+      const int e2 = e - nown;
+      if (e2 < wx1) {
+        r1 = 0;
+        c1 = e2;
+      } else if (e2 < 2 * wx1) {
+        r1 = wy1 - 1;
+        c1 = e2 - wx1;
+      } else {
+        const int e3 = e2 - 2 * wx1;
+        r1 = 1 + (e3 >> 1);
+        c1 = (e3 & 1) ? wx1 - 1 : 0;
+      }
+    }
+    const bool in_win = e < wy1 * wx1;
+    const AxisIdx rx = axis_index(i0 + c1 - 1, nx, bcx), ry = axis_index(j0 + r1 - 1, ny, bcy);
+    f1e[r] = (in_win && rx.ok && ry.ok) ? (unsigned)(ry.i * nx + rx.i) : IE;
+    f1o[r] = in_win ? r1 * wx1 + c1 : -1;
+    f1y[r] = (r1 + 1) * wx2 + c1 + 1;
+    f1k[r] = 0;
+    if (bcx == BC_LINE_TIED) f1k[r] |= rx.i == 0 ? 1 : (rx.i == nx - 1 ? 2 : 0);
+    if (bcy == BC_LINE_TIED) f1k[r] |= ry.i == 0 ? 4 : (ry.i == ny - 1 ? 8 : 0);
+  }
+  // Ghost nodes just beyond a line-tied face: y(-1) = 3 (y(0) - y(1)) + y(2), and likewise at the
+  // other end, so that the central difference at the face node is the one-sided second-order row
+  // -3 y(0) + 4 y(1) - y(2) and every node takes the same path.  Beyond faces across x and y a
+  // thread fills one ghost component of a plane; beyond faces across z see commit_window.
+  const int NGC = 3 * wy2, NGR = 3 * wx2;  // ghosts of one column, of one row
+  int gh_o[NPG], gh_s[NPG];  // offset in the plane's three components (-1: none), step into the grid
+#pragma unroll
+  for (int r = 0; r < NPG; r++) {
+    gh_o[r] = -1;
+    gh_s[r] = 0;
+    const int t = tid + r * NTHREADS;
+    if (t < 2 * NGC) {
+      const int side = t >= NGC, t1 = t - side * NGC, m = div(t1, wy2), row = t1 - m * wy2;
+      const int col = side == 0 ? 1 - i0 : nx - i0 + 2;
+      if (bcx == BC_LINE_TIED && col >= 0 && col < wx2) {
+        gh_o[r] = m * (RY2 * RX2) + row * wx2 + col;
+        gh_s[r] = side == 0 ? 1 : -1;
+      }
+    } else if (t < 2 * NGC + 2 * NGR) {
+      const int t0 = t - 2 * NGC, side = t0 >= NGR, t1 = t0 - side * NGR, m = div(t1, wx2), col = t1 - m * wx2;
+      const int row = side == 0 ? 1 - j0 : ny - j0 + 2;
+      if (bcy == BC_LINE_TIED && row >= 0 && row < wy2) {
+        gh_o[r] = m * (RY2 * RX2) + row * wx2 + col;
+        gh_s[r] = side == 0 ? wx2 : -wx2;
+      }
+    }
+  }
+
+  // tile node owned by this thread
+  const int gi_t = i0 + tx, gj_t = j0 + ty;
+  const bool tile_ok = own && (gi_t < nx) && (gj_t < ny);
+  const unsigned out_e = tile_ok ? (unsigned)(gj_t * nx + gi_t) : IE;
+  const bool face_x = bcx == BC_LINE_TIED && (gi_t == 0 || gi_t == nx - 1);
+  const bool face_y = bcy == BC_LINE_TIED && (gj_t == 0 || gj_t == ny - 1);
+
+  bool record_ck = false;
+  long long ck_slot = 0;
+  if (!diag_only && STAGE1 && record) {
+    const long long st = ctl->steps_total, every = ctl->ck_every;
+    if (st % every == 0 && st / every < a.ckpt_slots) {
+      record_ck = true;
+      ck_slot = st / every;
+    }
+  }
   // y = base + cv v, rounded once, plus the periodic shift of a wrapped neighbour
   auto window_value = [&](const Window& w, int r, double shz, double v[3]) {
 #pragma unroll
@@ -448,11 +472,6 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
     }
   };
 
-  // planes of B this chunk needs
-  const bool perz = (bcz == BC_PERIODIC);
-  const int pb0 = perz ? z0 - 1 : max(z0 - 1, 0);
-  const int pb1 = perz ? z1 : min(z1, nz - 1);
-
   Sums acc;
 
   // ---- stores of one output plane (every lane issues them; masked-off lanes are dropped) ----
@@ -538,14 +557,8 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
     carry(win);
   };
 
-  // ---- prologue: the stage input on the planes pb0 - 1 .. pb0 + 1, loaded together
+  // ---- prologue: the stage input on the planes pb0 - 1 .. pb0 + 1
   {
-    const bool low = !perz && pb0 == 0;  // the plane below is a ghost plane
-    const int lo = low ? 0 : pb0 - 1;
-    Window w0, w1, w2;
-    load_window(w0, lo, true);
-    load_window(w1, lo + 1, true);
-    load_window(w2, lo + 2, true);
     commit_window(w0, lo);
     commit_window(w1, lo + 1);
     commit_window(w2, lo + 2);

@@ -12,6 +12,12 @@ __device__ __forceinline__ int floordiv(int a, int n) { return a >= 0 ? a / n : 
 // p mod 3 in [0, 3) for p >= -3072 (plane indices reach at most three planes below 0)
 __device__ __forceinline__ int mod3(int p) { return (int)((unsigned)(p + 3072) % 3u); }
 
+// e / d for 0 <= e < 2^21, 1 <= d: (e + 1/2) / d is at least 1 / (2 d) away from an integer, more than
+// the 1.8e-7 (e + 1/2) / d that the reciprocal and the product round
+__device__ __forceinline__ int small_div(int e, int d) {
+  return (int)(((float)e + 0.5f) * __builtin_amdgcn_rcpf((float)d));
+}
+
 // One axis of a neighbour index: the in-range index, the number of periods wrapped (periodic
 // axes), and whether the node exists (line-tied axes end at the boundary nodes).
 struct AxisIdx {

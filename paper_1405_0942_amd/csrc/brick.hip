@@ -4,10 +4,12 @@
 // and LDS work each, with at least 12 steps per chunk, on a grid that has too few tiles to fill the
 // CUs.  Here a workgroup of 512 threads loads the stage input of a whole brick with its 2-node halo
 // into LDS at once, forms F', det F' and B on the brick and its 1-node halo (the own node first, then
-// the shell), and the current, force and update of one node per thread: two barriers in all, so that a sweep takes one round of global latency instead of a dozen.  The price is
-// the halo: a brick of 8 x 8 x 8 loads 3.4 window points and evaluates 2 fields per node where the
-// march of a tall chunk takes 1.6 and 1.3, so that bricks are used only where latency decides
-// (choose_brick in relax.cpp).  The arithmetic of a node is that of stage.hip (stage_math.h).
+// the shell), and the current, force and update of one node per thread: two barriers in all, so that a
+// sweep takes one round of global latency instead of a dozen (16^3: 5.0 to 6.4 us a sweep, where
+// the march took 42 to 57).  The price is the halo: a brick of 8 x 8 x 8 loads 3.4 window points and
+// evaluates 2 fields per node where the march of a tall chunk takes 1.6 and 1.3, so that bricks are used
+// only where latency decides (choose_brick in relax.cpp).  The arithmetic of a node is that of stage.hip
+// (stage_math.h).
 #include "brick.h"
 #include "stage_math.h"
 

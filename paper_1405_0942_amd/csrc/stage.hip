@@ -73,7 +73,7 @@
 // What bounds it: at 256^3 a stage moves its bytes at 5.5 to 6.0 TB/s, against 6.1 of a streaming
 // kernel with the same accesses; without any global access in the march the same sweep takes a
 // third of the time (0.15 of 0.44 ms, stage 3).  Small grids are bound by latency: about 1.2 us of
-// dependent FP64 and LDS work per plane step, 5 us before the first plane.
+// dependent FP64 and LDS work per plane step, and the first planes' way from HBM before it.
 #include "stage_math.h"
 
 namespace relax {

@@ -105,9 +105,11 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
   constexpr bool LEAN = St::LEAN, WV = St::WV, CX = St::CX, CV = St::CV, PS = St::PS;
   constexpr int NPK = St::NPK, NPKA = St::NPKA, NPS = St::NPS;
   // Plane steps between a load and its use.  Stage 1 has the registers for two sets: 256^3 270 -> 260
-  // us (FP64), 250 -> 236 us (mixed).  The other stages gain at most 1 % from a second set at 256^3 and
-  // lose 2 to 5 % on grids with short chunks (an extra step and a longer prologue).
-  constexpr int PD = (S == 1 && !NNN && !DIAG) ? 2 : 1;
+  // us (FP64), 250 -> 236 us (mixed), a diagnostics call on raw arrays of 256^3 387 -> 374 us, of 128^3
+  // 84.4 -> 81.9 us, of 56 x 56 x 168 (chunks of 4 planes) 53.0 -> 53.5.  The other stages gain at most 1 %
+  // from a second set at 256^3 and lose 2 to 5 % on grids with short chunks (an extra step and a longer
+  // prologue).
+  constexpr int PD = (S == 1 && !NNN) ? 2 : 1;
   constexpr int NP2 = (RY2 * RX2 + NTHREADS - 1) / NTHREADS;  // stage-input points per thread
   constexpr int NP1 = (RY1 * RX1 + NTHREADS - 1) / NTHREADS;  // field points per thread
   constexpr int NPG = (6 * (RY2 + RX2) + NTHREADS - 1) / NTHREADS;  // ghosts per thread

@@ -75,6 +75,7 @@
 // third of the time (0.15 of 0.44 ms, stage 3).  Small grids are bound by latency: about 1.2 us of
 // dependent FP64 and LDS work per plane step, and the first planes' way from HBM before it.
 #include "stage_math.h"
+#include "tile.h"
 
 namespace relax {
 namespace {
@@ -186,22 +187,7 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
 #pragma unroll
   for (int r = 0; r < NP2; r++) {
     const int e = tid + r * NTHREADS;
-    int row, col;
-    if (e < nown) {
-      row = div(e, tw) + 2;
-      col = e - (row - 2) * tw + 2;
-    } else {
-      const int e2 = e - nown;
-      if (e2 < 4 * wx2) {
-        const int band = div(e2, wx2);
-        row = band < 2 ? band : wy2 - 4 + band;
-        col = e2 - band * wx2;
-      } else {
-        const int e3 = e2 - 4 * wx2, side = e3 & 3;
-        row = 2 + (e3 >> 2);
-        col = side < 2 ? side : wx2 - 4 + side;
-      }
-    }
+    const auto [row, col] = window_point(e, tw, th, div);
     const bool in_win = e < wy2 * wx2;
     const AxisIdx rx = axis_index(i0 + col - 2, nx, bcx);
     const AxisIdx ry = axis_index(j0 + row - 2, ny, bcy);
@@ -265,29 +251,13 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
 #pragma unroll
   for (int r = 0; r < NP1; r++) {
     const int e = tid + r * NTHREADS;
-    int r1, c1;
-    if (e < nown) {
-      r1 = div(e, tw) + 1;
-      c1 = e - (r1 - 1) * tw + 1;
-    } else {
-      const int e2 = e - nown;
-      if (e2 < wx1) {
-        r1 = 0;
-        c1 = e2;
-      } else if (e2 < 2 * wx1) {
-        r1 = wy1 - 1;
-        c1 = e2 - wx1;
-      } else {
-        const int e3 = e2 - 2 * wx1;
-        r1 = 1 + (e3 >> 1);
-        c1 = (e3 & 1) ? wx1 - 1 : 0;
-      }
-    }
+    const TilePoint pt = field_point(e, tw, th, div);
+    const int r1 = pt.row, c1 = pt.col;
     const bool in_win = e < wy1 * wx1;
     const AxisIdx rx = axis_index(i0 + c1 - 1, nx, bcx), ry = axis_index(j0 + r1 - 1, ny, bcy);
     f1e[r] = (in_win && rx.ok && ry.ok) ? (unsigned)(ry.i * nx + rx.i) : IE;
     f1o[r] = in_win ? r1 * wx1 + c1 : -1;
-    f1y[r] = (r1 + 1) * wx2 + c1 + 1;
+    f1y[r] = field_offset(pt, in_win, tw);
     f1k[r] = 0;
     if (bcx == BC_LINE_TIED) f1k[r] |= rx.i == 0 ? 1 : (rx.i == nx - 1 ? 2 : 0);
     if (bcy == BC_LINE_TIED) f1k[r] |= ry.i == 0 ? 4 : (ry.i == ny - 1 ? 8 : 0);

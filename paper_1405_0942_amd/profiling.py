@@ -24,7 +24,7 @@ import re
 import sys
 
 HERE = os.path.dirname(os.path.abspath(__file__))
-KERNEL_SOURCES = ("csrc/stage.hip", "csrc/stage_math.h", "csrc/sweep_common.h", "csrc/relax_device.h",
+KERNEL_SOURCES = ("csrc/stage.hip", "csrc/stage_math.h", "csrc/tile.h", "csrc/sweep_common.h", "csrc/relax_device.h",
                   "csrc/relax.cpp")
 COPY_BYTES = 1 << 30
 

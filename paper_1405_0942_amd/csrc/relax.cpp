@@ -140,11 +140,11 @@ int choose_tz(const relax_config* c, int tiles_xy) {
   const unsigned slots = 256;
   const int nz = c->n[2];
   int best_tz = nz;
-  unsigned best_cost = 0;
+  unsigned long long best_cost = 0;  // up to 2^40 nodes are a valid configuration: 2^33 workgroups and more
   for (int chunks = 1; chunks <= std::max(1, nz / 4); chunks++) {
     const int tz = (nz + chunks - 1) / chunks;
-    const unsigned blocks = (unsigned)tiles_xy * (unsigned)((nz + tz - 1) / tz);
-    const unsigned cost = ((blocks + slots - 1) / slots) * (unsigned)(tz + 4);
+    const unsigned long long blocks = (unsigned long long)tiles_xy * (unsigned)((nz + tz - 1) / tz);
+    const unsigned long long cost = (blocks + slots - 1) / slots * (unsigned)(tz + 4);
     if (best_cost == 0 || cost < best_cost) {
       best_cost = cost;
       best_tz = tz;

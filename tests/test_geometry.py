@@ -1,0 +1,19 @@
+"""The choice of tiles and chunks (relax.cpp) as relax_workspace_bytes shows it, on the CPU."""
+import types
+
+import pytest
+
+import paper_1405_0942_amd as R
+
+
+def _config(n, **kw):
+    g = types.SimpleNamespace(n=n, h=(0.1, 0.1, 0.1), bc=(R.RELAX_PERIODIC,) * 3)
+    return R.make_config(g, dt0=1e-3, **kw)
+
+
+@pytest.mark.parametrize("n", [(4, 2 ** 26 - 1, 4096), (4, 2 ** 25, 4096), (4, 2 ** 24, 2 ** 14), (8, 2 ** 25 - 1, 2048)])
+def test_workspace_of_the_widest_grids_holds_the_partial_records(n):
+    """Twelve FP64 vectors, and for each 64 x 8 tile of the x-y plane at least one record of eight doubles
+    and one Lambda: also where tiles times chunks pass 2^32."""
+    tiles = -(-n[0] // 64) * -(-n[1] // 8)
+    assert R.relax_workspace_bytes(_config(n)) >= 12 * 24 * n[0] * n[1] * n[2] + tiles * 72

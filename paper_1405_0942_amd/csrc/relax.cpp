@@ -132,25 +132,29 @@ bool valid_config(const relax_config* c) {
 // x-y tiles alone slightly exceed the slots would otherwise run a second, nearly empty round
 // as long as the first, and a small grid would leave most CUs idle.  (64 x 64 x 192: 6 planes a chunk
 // fill the 256 slots, 8 planes leave a quarter idle: 179 against 199 us per FP64 step.)
-int choose_tz(const relax_config* c, int tiles_xy) {
-  if (const char* e = std::getenv("RELAX_TZ")) {
-    int v = std::atoi(e);
-    if (v >= 1) return std::min(v, c->n[2]);
-  }
+// Every chunk length is tried once, at its least chunk count, about 2 sqrt(nz) of them.  `fixed`: the length
+// asked for in the environment, 0 if none.
+static int choose_tz(int nz, int tiles_xy, int fixed) {
+  if (fixed > 0) return std::min(fixed, nz);
   const unsigned slots = 256;
-  const int nz = c->n[2];
   int best_tz = nz;
   unsigned long long best_cost = 0;  // up to 2^40 nodes are a valid configuration: 2^33 workgroups and more
-  for (int chunks = 1; chunks <= std::max(1, nz / 4); chunks++) {
-    const int tz = (nz + chunks - 1) / chunks;
-    const unsigned long long blocks = (unsigned long long)tiles_xy * (unsigned)((nz + tz - 1) / tz);
+  for (int chunks = 1; chunks <= std::max(1, nz / 4);) {
+    const int tz = (nz - 1) / chunks + 1;
+    const unsigned long long blocks = (unsigned long long)tiles_xy * (unsigned)((nz - 1) / tz + 1);
     const unsigned long long cost = (blocks + slots - 1) / slots * (unsigned)(tz + 4);
     if (best_cost == 0 || cost < best_cost) {
       best_cost = cost;
       best_tz = tz;
     }
+    chunks = (nz - 1) / (tz - 1) + 1;  // the least count with shorter chunks; tz >= 4 here
   }
   return best_tz;
+}
+
+static int fixed_tz() {
+  const char* e = std::getenv("RELAX_TZ");
+  return e ? std::max(0, std::atoi(e)) : 0;
 }
 
 // Bricks (brick.hip) or z-marching tiles, and which bricks.  A brick sweep takes its time from the
@@ -214,32 +218,35 @@ static void choose_brick(const relax_config* c, int window, unsigned slots, int 
 // and window points, and no more ghost nodes than threads.  Measured us per FP64 step, 64 x 8 / fitted:
 // 96^3 230 / 207, 129^3 line-tied 507 / 449, 100 x 130 x 170 495 / 440, 150^3 733 / 659, 73 x 73 x 219 351 /
 // 287, 193^3 line-tied 1597 / 1402, 200 x 190 x 210 1588 / 1416.
-static void choose_tile(const relax_config* c, int* tw, int* th) {
+// Every width is tried once, with the tallest tile that it allows (shorter ones only add tiles).
+static void choose_tile(const relax_config* c, int fixed, int* tw, int* th) {
+  const int nx = c->n[0], ny = c->n[1];
   auto cost = [&](int w, int h) {
-    const int tiles = ((c->n[0] + w - 1) / w) * ((c->n[1] + h - 1) / h);
-    const int tz = choose_tz(c, tiles);
+    const int tiles = ((nx + w - 1) / w) * ((ny + h - 1) / h);
+    const int tz = choose_tz(c->n[2], tiles, fixed);
     const long long blocks = (long long)tiles * ((c->n[2] + tz - 1) / tz);
-    const int both = w | c->n[0];  // alignment of the tile edges in nodes
+    const int both = w | nx;  // alignment of the tile edges in nodes
     const double lines = 1.0 + (both % 8 ? 1.0 : (both % 16 ? 0.3 : 0.0)) * 16.0 / w;
     return (double)((blocks + 255) / 256) * (tz + 4) * lines * std::sqrt(lines);
   };
   *tw = TX;
   *th = TY;
   double best = 0.94 * cost(TX, TY);
-  for (int kx = 1; kx <= c->n[0]; kx++) {
-    const int w = (c->n[0] + kx - 1) / kx;
+  for (int kx = (nx + TX + TY - 2) / (TX + TY - 1);;) {
+    const int w = (nx + kx - 1) / kx;
     if (w < 24) break;
-    for (int ky = 1; ky <= c->n[1]; ky++) {
-      const int h = (c->n[1] + ky - 1) / ky;
-      if (w * h > NTHREADS || (w + 4) * (h + 4) > RX2 * RY2 || (w + 2) * (h + 2) > RX1 * RY1 || w + h > TX + TY) continue;
+    const int tallest = std::min(std::min(NTHREADS / w, RX2 * RY2 / (w + 4) - 4),
+                                 std::min(RX1 * RY1 / (w + 2) - 2, TX + TY - w));
+    if (tallest > 0) {
+      const int ky = (ny + tallest - 1) / tallest, h = (ny + ky - 1) / ky;
       const double v = cost(w, h);
       if (v < best) {
         best = v;
         *tw = w;
         *th = h;
       }
-      break;  // smaller tiles of this width only add tiles
     }
+    kx = (nx + w - 2) / (w - 1);  // the least count of narrower tiles
   }
 }
 
@@ -259,10 +266,11 @@ Geometry make_tiles(const relax_config* c, bool fit) {
   g.b0scale[2] = 4.0 * c->h[0] * c->h[1];
   g.tw = TX;
   g.th = TY;
-  if (fit) choose_tile(c, &g.tw, &g.th);
+  const int fixed = fixed_tz();
+  if (fit) choose_tile(c, fixed, &g.tw, &g.th);
   g.tiles[0] = (c->n[0] + g.tw - 1) / g.tw;
   g.tiles[1] = (c->n[1] + g.th - 1) / g.th;
-  g.tz = choose_tz(c, g.tiles[0] * g.tiles[1]);
+  g.tz = choose_tz(c->n[2], g.tiles[0] * g.tiles[1], fixed);
   g.tiles[2] = (c->n[2] + g.tz - 1) / g.tz;
   g.nblocks = g.tiles[0] * g.tiles[1] * g.tiles[2];
   g.curl = c->curl;

@@ -150,7 +150,6 @@ struct CK {
 // Host helpers implemented in relax.cpp
 // ------------------------------------------------------------------------------------------
 bool valid_config(const relax_config* c);          // every field in range
-int choose_tz(const relax_config* c, int tiles_xy);  // z-chunk length
 Geometry make_tiles(const relax_config* c, bool fit);  // scale factors, z-marching tiles and chunks
                                                        // (64 x 8 tiles unless fit)
 Geometry make_geometry(const relax_config* c);     // the same with bricks where they are used

@@ -1,4 +1,6 @@
 """The choice of tiles and chunks (relax.cpp) as relax_workspace_bytes shows it, on the CPU."""
+import math
+import time
 import types
 
 import pytest
@@ -17,3 +19,15 @@ def test_workspace_of_the_widest_grids_holds_the_partial_records(n):
     and one Lambda: also where tiles times chunks pass 2^32."""
     tiles = -(-n[0] // 64) * -(-n[1] // 8)
     assert R.relax_workspace_bytes(_config(n)) >= 12 * 24 * n[0] * n[1] * n[2] + tiles * 72
+
+
+@pytest.mark.parametrize("n", [(16384, 16383, 4), (4, 4, 2 ** 22)])
+def test_choosing_the_geometry_of_wide_and_long_grids_takes_little_time(n):
+    """Every call without a context chooses its geometry: some 60 tile widths and 2 sqrt(nz) chunk lengths
+    are a few ten microseconds, a walk over all tile heights or chunk counts took 10 ms."""
+    cfg, best = _config(n), math.inf
+    for _ in range(7):
+        t = time.perf_counter()
+        assert R.relax_workspace_bytes(cfg) > 0
+        best = min(best, time.perf_counter() - t)
+    assert best < 2e-3

@@ -37,8 +37,8 @@ def _compile(src: str, verbose: bool, tile_y: int) -> str:
     lang = ["-x", "hip"] if src.endswith(".hip") else []
     # the 64 x 4 build's octilateral sweeps hold 94 KB of LDS, one 4-wave workgroup per CU, so
     # they cannot reach the two waves per SIMD their attribute asks for; the 64 x 8 build can
-    quiet = ["-Wno-pass-failed"] if tile_y != 8 else []
-    cmd = [HIPCC, *FLAGS, *quiet, f"-DRELAX_TILE_Y={tile_y}", *lang, "-c", path, "-o", obj]
+    extra = ["-Wno-pass-failed", "-DRELAX_GATHER_BLOCKS=64"] if tile_y != 8 else []
+    cmd = [HIPCC, *FLAGS, *extra, f"-DRELAX_TILE_Y={tile_y}", *lang, "-c", path, "-o", obj]
     if verbose:
         print(" ".join(cmd), flush=True)
     r = subprocess.run(cmd, capture_output=True, text=True)
@@ -49,9 +49,9 @@ def _compile(src: str, verbose: bool, tile_y: int) -> str:
     return obj
 
 
-# The same library with 64 x 4 workgroup tiles instead of 64 x 8: built only so that a test
-# can check that per-node results do not depend on the tile shape (an LDS race or a halo
-# mistake would show there).
+# The same library with 64 x 4 workgroup tiles instead of 64 x 8 and gathers of 64 workgroups a
+# launch: built only so that a test can check that per-node results do not depend on the tile shape
+# (an LDS race or a halo mistake would show there) nor on the pieces of a gather.
 LIB_TY4 = os.path.join(HERE, "librelax_ty4.so")
 
 

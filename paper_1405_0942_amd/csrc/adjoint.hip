@@ -46,6 +46,8 @@
 // diverged), 73 x 73 x 200 line-tied 1487 -> 1219.
 #include "brick.h"
 
+#include <algorithm>
+
 namespace relax {
 namespace {
 
@@ -702,13 +704,14 @@ __global__ __launch_bounds__(BRICK_THREADS) __attribute__((amdgpu_waves_per_eu(2
 // 1008 instead of 1200 bytes a node and step for the six gathers, which bound them (64 x 64 x 192: 4.6 to
 // 5.8 TB/s, 161 -> 153 us the six).
 // One thread a node, rows of 64 along x so that every access is coalesced and no index needs a 64-bit
-// division (16^3: 8 -> 4 us against a grid-stride loop with 64-bit divisions).
+// division (16^3: 8 -> 4 us against a grid-stride loop with 64-bit divisions).  A launch takes the workgroups
+// first, first + 1, ... of the pass: fewer than 2^32 work-items, which long thin grids pass (4 x 5 x 2^23).
 template <int MODE, int STAGE>
-__global__ __launch_bounds__(256) void adj_gather_kernel(AdjArgs a, int bxs, int bys) {
+__global__ __launch_bounds__(256) void adj_gather_kernel(AdjArgs a, int bxs, int bys, unsigned first) {
   const Geometry& g = a.g;
   const long long N = g.N;
   const int nx = g.n[0], ny = g.n[1];
-  const int lb = logical_block(blockIdx.x, gridDim.x);
+  const int lb = (int)first + logical_block(blockIdx.x, gridDim.x);
   const int k = lb / (bxs * bys), rem = lb - k * bxs * bys, jb = rem / bxs;
   const int i = (rem - jb * bxs) * 64 + (threadIdx.x & 63), j = jb * 4 + (threadIdx.x >> 6);
   if (i >= nx || j >= ny) return;
@@ -839,18 +842,21 @@ hipError_t launch_adj_gather(const AdjArgs& a, int mode, int stage, hipStream_t 
   const int bxs = (a.g.n[0] + 63) / 64, bys = (a.g.n[1] + 3) / 4;
   const long long blocks = (long long)bxs * bys * a.g.n[2];
   if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
-  const dim3 grid((unsigned)blocks), block(256);
-  switch (mode == 0 ? stage : 10 + mode) {
-    case 2: hipLaunchKernelGGL((adj_gather_kernel<0, 2>), grid, block, 0, st, a, bxs, bys); break;
-    case 3: hipLaunchKernelGGL((adj_gather_kernel<0, 3>), grid, block, 0, st, a, bxs, bys); break;
-    case 4: hipLaunchKernelGGL((adj_gather_kernel<0, 4>), grid, block, 0, st, a, bxs, bys); break;
-    case 5: hipLaunchKernelGGL((adj_gather_kernel<0, 5>), grid, block, 0, st, a, bxs, bys); break;
-    case 6: hipLaunchKernelGGL((adj_gather_kernel<0, 6>), grid, block, 0, st, a, bxs, bys); break;
-    case 11: hipLaunchKernelGGL((adj_gather_kernel<1, 1>), grid, block, 0, st, a, bxs, bys); break;
-    case 12: hipLaunchKernelGGL((adj_gather_kernel<2, 1>), grid, block, 0, st, a, bxs, bys); break;
-    default: return hipErrorInvalidValue;
+  for (unsigned first = 0; first < (unsigned)blocks; first += GATHER_BLOCKS) {
+    const dim3 grid(std::min<unsigned>(GATHER_BLOCKS, (unsigned)blocks - first)), block(256);
+    switch (mode == 0 ? stage : 10 + mode) {
+      case 2: hipLaunchKernelGGL((adj_gather_kernel<0, 2>), grid, block, 0, st, a, bxs, bys, first); break;
+      case 3: hipLaunchKernelGGL((adj_gather_kernel<0, 3>), grid, block, 0, st, a, bxs, bys, first); break;
+      case 4: hipLaunchKernelGGL((adj_gather_kernel<0, 4>), grid, block, 0, st, a, bxs, bys, first); break;
+      case 5: hipLaunchKernelGGL((adj_gather_kernel<0, 5>), grid, block, 0, st, a, bxs, bys, first); break;
+      case 6: hipLaunchKernelGGL((adj_gather_kernel<0, 6>), grid, block, 0, st, a, bxs, bys, first); break;
+      case 11: hipLaunchKernelGGL((adj_gather_kernel<1, 1>), grid, block, 0, st, a, bxs, bys, first); break;
+      case 12: hipLaunchKernelGGL((adj_gather_kernel<2, 1>), grid, block, 0, st, a, bxs, bys, first); break;
+      default: return hipErrorInvalidValue;
+    }
+    if (const hipError_t e = hipGetLastError(); e != hipSuccess) return e;
   }
-  return hipGetLastError();
+  return hipSuccess;
 }
 
 hipError_t launch_fill(double* v, long long n, double val, hipStream_t st) {

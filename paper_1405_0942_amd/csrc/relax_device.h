@@ -35,6 +35,11 @@ constexpr int BRICK_FIELD = 1152;
 constexpr int BRICK_SHELL = 1024;
 constexpr int ADJ_WINDOW = 1920;  // the same limit for the reverse sweeps (adjoint.hip)
 
+#ifndef RELAX_GATHER_BLOCKS
+#define RELAX_GATHER_BLOCKS (1 << 23)  // fewer are built only to check that the pieces make one pass
+#endif
+constexpr unsigned GATHER_BLOCKS = RELAX_GATHER_BLOCKS;  // workgroups of 256 in one launch of a gather (adjoint.hip)
+
 enum { BC_LINE_TIED = 0, BC_PERIODIC = 1 };
 enum { CURL_NN = 0, CURL_NNN = 1 };  // the values of RELAX_CURL_NN / RELAX_CURL_NNN
 

@@ -19,11 +19,11 @@ def run(source, tmp_path, *args):
     src, exe = tmp_path / "check.cpp", tmp_path / "check"
     src.write_text(source)
     libdir = os.path.dirname(R.LIB_PATH)
-    cmd = ["g++", "-std=c++17", "-O1", "-w", "-D__HIP_PLATFORM_AMD__", f"-I{ROCM}/include", f"-I{B.CSRC}",
+    cmd = ["g++", "-std=c++17", "-O1", "-w", "-rdynamic", "-D__HIP_PLATFORM_AMD__", f"-I{ROCM}/include", f"-I{B.CSRC}",
            f"-I{os.path.join(B.ROOT, 'include')}", str(src), "-o", str(exe), f"-L{libdir}", "-l:librelax.so",
            f"-L{ROCM}/lib", "-lamdhip64", f"-Wl,-rpath,{libdir}:{ROCM}/lib"]
     r = subprocess.run(cmd, capture_output=True, text=True)
     assert r.returncode == 0, r.stderr[-3000:]
     r = subprocess.run([str(exe), *map(str, args)], capture_output=True, text=True, timeout=300)
-    assert r.returncode == 0, (r.stdout + r.stderr)[-3000:]
+    assert r.returncode == 0, f"exit {r.returncode}\n{r.stdout}{r.stderr}"[-3000:]
     return r.stdout

@@ -262,6 +262,22 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
     if (bcx == BC_LINE_TIED) f1k[r] |= rx.i == 0 ? 1 : (rx.i == nx - 1 ? 2 : 0);
     if (bcy == BC_LINE_TIED) f1k[r] |= ry.i == 0 ? 4 : (ry.i == ny - 1 ? 8 : 0);
   }
+  // NNN: points off the grid take no field (B stays 0 there, and no node off a face reads it), nor does a
+  // wave without a node: narrow line-tied grids are mostly such points (us per step, 4 x 4 x 65536 11173 ->
+  // 9837, 1024 x 4 x 1024 2887 -> 2782, 66 x 66 x 500 1110 -> 1078, 160^3 as before)
+  int pb1_own = pb1;
+  if constexpr (NNN) {
+#pragma unroll
+    for (int r = 0; r < NP1; r++) {
+      if (f1e[r] == IE && f1o[r] >= 0) {
+#pragma unroll
+        for (int i = 0; i < RBS; i++)
+#pragma unroll
+          for (int m = 0; m < 3; m++) bs[i][m][f1o[r]] = T(0);
+      }
+    }
+    if (!__any(f1e[0] != IE)) pb1_own = -2;
+  }
   // Ghost nodes just beyond a line-tied face: y(-1) = 3 (y(0) - y(1)) + y(2), and likewise at the
   // other end, so that the central difference at the face node is the one-sided second-order row
   // -3 y(0) + 4 y(1) - y(2) and every node takes the same path.  Beyond faces across x and y a
@@ -336,7 +352,8 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
     }
   };
   // the ghost plane beyond a line-tied z face from the three planes pa, pb, pc inside it (pa the
-  // face): each thread reads back the points it committed itself
+  // face): each thread reads back the points it committed itself.  NNN: the rows read no ghost, only
+  // the diagnostics' edge vectors, whose trihedra there are not formed
   auto commit_ghost_plane = [&](int pz, int pa, int pb, int pc) {
     const int slot = yslot(pz), sa = yslot(pa), sb = yslot(pb), sc = yslot(pc);
 #pragma unroll
@@ -525,7 +542,7 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
   Nodes nodes[PD];
   auto commit_next = [&](const Window& win, int p) {
     commit_window(win, p + 2);  // past the chunk's last plane: zeros that nothing reads
-    if (!perz && p + 2 == nz) commit_ghost_plane(nz, nz - 1, nz - 2, nz - 3);
+    if ((!NNN || DIAG) && !perz && p + 2 == nz) commit_ghost_plane(nz, nz - 1, nz - 2, nz - 3);
     carry(win);
   };
 
@@ -535,7 +552,7 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
     commit_window(w1, lo + 1);
     commit_window(w2, lo + 2);
     if (low) {  // plane 2 stays in the ring and is committed again by the first plane step
-      commit_ghost_plane(-1, 0, 1, 2);
+      if constexpr (!NNN || DIAG) commit_ghost_plane(-1, 0, 1, 2);
       carry(w0);
       carry(w0);
       carry(w1);
@@ -668,11 +685,9 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
     using OwnNode = std::integral_constant<int, 0>;
     using HaloPoint = std::integral_constant<int, 1>;
     if constexpr (NNN) {
-      if (p <= pb1) {
-        field(OwnNode{});
-        __builtin_amdgcn_sched_barrier(0);  // one field point at a time: bounds live temporaries
-        if (f1o[1] >= 0) field(HaloPoint{});
-      }
+      if (p <= pb1_own) field(OwnNode{});
+      __builtin_amdgcn_sched_barrier(0);  // one field point at a time: bounds live temporaries
+      if (p <= pb1 && f1e[1] != IE) field(HaloPoint{});
     } else {
       // the halo points first (three of the eight waves); past the chunk's last plane the field is
       // computed too and not read

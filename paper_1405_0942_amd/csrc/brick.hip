@@ -120,7 +120,7 @@ __global__ __launch_bounds__(BRICK_THREADS) __attribute__((amdgpu_waves_per_eu(4
       for (int m = 0; m < 3; m++) {
         double y = wx[r][m];
         if constexpr (S == 2) {
-          y = y + cv * (double)wk[r][m];
+          y = fma(cv, (double)wk[r][m], y);
         } else if constexpr (WV) {
           y = y + (double)wk[r][m];
         }

@@ -328,7 +328,7 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
     for (int m = 0; m < 3; m++) {
       double y = w.x[r][m];
       if constexpr (S == 2) {
-        y = y + cv * (double)w.v[r][m];
+        y = fma(cv, (double)w.v[r][m], y);
       } else if constexpr (WV) {
         y = y + (double)w.v[r][m];
       }

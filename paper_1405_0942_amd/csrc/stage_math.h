@@ -1,8 +1,10 @@
 // stage_math.h -- the node-wise arithmetic of a Runge-Kutta stage, shared by the sweeps of stage.hip
 // (z-marching tiles) and brick.hip (small grids): the current from F' and the differences of B or from
-// the octilateral loops, the stage updates, the convexity test and the workgroup reductions.  The
-// order of operations is the same in both, so a node's result does not depend on the sweep.  The
-// method and the stored vectors are described at the top of stage.hip.  Internal to the library.
+// the octilateral loops, the stage updates, the convexity test and the workgroup reductions.  In FP64 with
+// the nearest-neighbour current a node's result does not depend on the sweep, bit for bit: the products
+// are fused by hand, below.  FP32-mixed and the octilateral current leave that to the compiler, and may
+// part by a rounding.  The method and the stored vectors are described at the top of stage.hip.  Internal
+// to the library.
 #pragma once
 
 #include <type_traits>

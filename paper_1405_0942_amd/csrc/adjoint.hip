@@ -196,7 +196,7 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
   const double* __restrict__ vsrc = SEED ? (a.useed ? a.useed : a.B0) : (S == 6 ? a.xbar : a.ubar);
   const double cv = (!SEED && S == 6) ? dt * CK::b5[5] : 1.0;
   const double* __restrict__ wsrc = (SEED || S <= 2) ? a.x : a.y[S > 2 ? S - 3 : 0];
-  const double* __restrict__ k1p = a.k[0];
+  const double* __restrict__ k1p = a.k1;
 
   const int lb = logical_block(blockIdx.x, g.nblocks);
   const int tile_x = lb % g.tiles[0];
@@ -590,7 +590,7 @@ __global__ __launch_bounds__(BRICK_THREADS) __attribute__((amdgpu_waves_per_eu(2
       for (int m = 0; m < 3; m++) wx[r][m] = at(wsrc + m * N, i);
       if constexpr (WK) {
 #pragma unroll
-        for (int m = 0; m < 3; m++) wk[r][m] = at(a.k[0] + m * N, i);
+        for (int m = 0; m < 3; m++) wk[r][m] = at(a.k1 + m * N, i);
       }
     }
   }

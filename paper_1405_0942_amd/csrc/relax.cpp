@@ -337,7 +337,7 @@ Layout make_layout(const relax_config* c, const Geometry& g, int K_record) {
     L.ckpt = take((size_t)L.ckpt_slots * N3 * sizeof(double));
     L.ctl2 = take(sizeof(Control));
     L.seg_x = take((cpe + 1) * N3 * sizeof(double));
-    L.seg_k = take(cpe * 3 * N3 * sizeof(double));
+    L.seg_k = take(cpe * N3 * sizeof(double));
     L.seg_y = take(cpe * 4 * N3 * sizeof(double));
     L.Fbar = take(3 * N3 * sizeof(double));
     L.xbar = take(N3 * sizeof(double));
@@ -741,14 +741,15 @@ int relax_backward(void* ctx, double seed_EM, double seed_R2, double* d_grad_x0,
     const int len = (int)(s1 - s0);
     HIP_TRY(c, hipMemcpyAsync(c->d_seg_x, c->d_ckpt + (size_t)seg * N3, N3 * sizeof(double),
                               hipMemcpyDeviceToDevice, st));
-    // forward recompute, keeping x_n, k_1..k_3 and y_3..y_6 of every step
+    // forward recompute, keeping x_n, k_1 and y_3..y_6 of every step; C4 and k_3 are read within the step
+    // alone and go where the forward steps have them, which an attempt writes before it reads
     for (int j = 0; j < len; j++) {
       HIP_TRY(c, launch_seg_step(c->d_ctl2, c->d_dtrec, s0 + j, st));
       fw.x[0] = c->d_seg_x + (size_t)j * N3;
       fw.x[1] = c->d_seg_x + (size_t)(j + 1) * N3;
       fw.xout[0] = c->d_seg_x + (size_t)j * N3;
       fw.xout[1] = c->d_seg_x + (size_t)(j + 1) * N3;
-      for (int s = 0; s < 3; s++) fw.k[s] = c->d_seg_k + ((size_t)j * 3 + s) * N3;
+      fw.k[0] = c->d_seg_k + (size_t)j * N3;
       // y_3 .. y_6 of step j: stages 2 and 4 write y_3 and y_5 there; stages 4 and 6 add y_4, y_6
       double* ys = c->d_seg_y + (size_t)j * 4 * N3;
       fw.y3 = ys;
@@ -759,7 +760,7 @@ int relax_backward(void* ctx, double seed_EM, double seed_R2, double* d_grad_x0,
     }
     for (int j = len - 1; j >= 0; j--) {
       a.x = c->d_seg_x + (size_t)j * N3;
-      for (int s = 0; s < 3; s++) a.k[s] = c->d_seg_k + ((size_t)j * 3 + s) * N3;
+      a.k1 = c->d_seg_k + (size_t)j * N3;
       for (int t = 0; t < 4; t++) a.y[t] = c->d_seg_y + ((size_t)j * 4 + t) * N3;
       a.dt = c->d_dtrec + s0 + j;
       for (int s = 6; s >= 1; s--) {

@@ -117,7 +117,7 @@ struct SweepArgs {
 struct AdjArgs {
   Geometry g;
   const double* x;        // x_n of the step (or x_K for the seed sweep)
-  const double* k[5];     // k_1..k_3 of the step (k_1 is part of the stage-2 window)
+  const double* k1;       // k_1 of the step (part of the stage-2 window)
   const double* y[4];     // stage inputs y_3..y_6 of the step
   const double* dt;       // device pointer to the step's dt
   const double* B0;       // B0'' (prescaled, FP64)

@@ -31,3 +31,11 @@ def test_choosing_the_geometry_of_wide_and_long_grids_takes_little_time(n):
         assert R.relax_workspace_bytes(cfg) > 0
         best = min(best, time.perf_counter() - t)
     assert best < 2e-3
+
+
+def test_a_recorded_step_keeps_what_the_reverse_sweeps_read():
+    """A longer checkpoint segment holds, for each step more, x_n, k_1 and y_3 to y_6: six FP64 vectors (and
+    no other checkpoint, with one slot for K_record = 4 steps either way)."""
+    n = (32, 32, 32)
+    a, b = (R.relax_workspace_bytes(_config(n, record=True, checkpoint_every=c), 4) for c in (5, 9))
+    assert b - a == 4 * 6 * 24 * n[0] * n[1] * n[2]

@@ -8,7 +8,6 @@
 
 namespace relax {
 
-__device__ __forceinline__ int floordiv(int a, int n) { return a >= 0 ? a / n : -((-a + n - 1) / n); }
 // p mod 3 in [0, 3) for p >= -3072 (plane indices reach at most three planes below 0)
 __device__ __forceinline__ int mod3(int p) { return (int)((unsigned)(p + 3072) % 3u); }
 
@@ -26,28 +25,14 @@ struct AxisIdx {
   bool ok;
 };
 
-__device__ __forceinline__ AxisIdx resolve(int v, int n, int bc) {
-  AxisIdx r;
-  if (bc == BC_PERIODIC) {
-    r.w = floordiv(v, n);
-    r.i = v - r.w * n;
-    r.ok = true;
-  } else {
-    r.w = 0;
-    r.i = v;
-    r.ok = (v >= 0 && v < n);
-  }
-  return r;
-}
-
-// resolve() without divisions, exact for v in [-n, 2n): the plane indices of a z march lie
-// within three planes of [0, n) and n >= 4.  Other v give a wrong but in-range index.
+// Exact for v in [-n, 2n): the plane indices of a z march lie within three planes of [0, n) and
+// n >= 4.  Other v give a wrong but in-range index on a periodic axis.
 __device__ __forceinline__ AxisIdx resolve_near(int v, int n, int bc) {
   if (bc == BC_PERIODIC) {
     const int w = v < 0 ? -1 : (v >= n ? 1 : 0);
     return AxisIdx{min(max(v - w * n, 0), n - 1), w, true};
   }
-  return resolve(v, n, bc);
+  return AxisIdx{v, 0, v >= 0 && v < n};
 }
 
 // The same for a window's points, without a branch: at most one period away, others are off the grid.

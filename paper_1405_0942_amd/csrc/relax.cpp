@@ -159,11 +159,14 @@ static int fixed_tz() {
 
 // Bricks (brick.hip) or z-marching tiles, and which bricks.  A brick sweep takes its time from the
 // points it loads and evaluates, a march from the plane steps of a chunk, which a small grid cannot
-// shorten.  The bricks' line is two rounds of 512 workgroups of 512 nodes.  Measured us per step, march /
-// bricks, FP64: 48^3 periodic 116 / 62, 65^3 line-tied 139 / 96, 80^3 periodic 167 / 131, 56 x 56 x 168
-// 145 / 156, 81^3 line-tied 157 / 162, 90^3 periodic 209 / 181, 96^3 periodic 197 / 201; FP32-mixed 48^3
-// 102 / 59, 65^3 118 / 93, 80^3 144 / 120, 81^3 135 / 155, 96^3 161 / 182; a diagnostics call 48^3 31 / 25,
-// 65^3 34 / 33, 80^3 39 / 38, 81^3 35 / 46, 90^3 45 / 49.  The octilateral current, whose march holds one
+// shorten.  The bricks' line is two rounds of 512 workgroups of 512 nodes.  One count for every shape and
+// kind of sweep is a compromise: FP64 steps of 90^3, above it, would be 12 % faster over bricks, where 56 x
+// 56 x 168 and 96^3, on either side of 90^3, and the other sweeps are faster over the march.  Measured us
+// per step, march / bricks, FP64: 48^3 periodic 116 / 62, 65^3 line-tied 139 / 96, 80^3 periodic 167 / 131,
+// 56 x 56 x 168 145 / 158, 81^3 line-tied 156 / 164, 90^3 periodic 208 / 185, 96^3 periodic 198 / 206;
+// FP32-mixed 48^3 102 / 59, 65^3 118 / 93, 80^3 144 / 120, 56 x 56 x 168 123 / 147, 81^3 134 / 157, 90^3 174 /
+// 172, 96^3 161 / 186; a diagnostics call 48^3 31 / 25, 65^3 34 / 33, 80^3 39 / 38, 56 x 56 x 168 38 / 47,
+// 81^3 39 / 49, 90^3 46 / 50.  The octilateral current, whose march holds one
 // plane more and two barriers: 48^3 227 / 90, 65^3 322 / 164, 81^3 338 / 279, 89^3 504 / 296, 96^3 371 / 340.
 // The brick of a grid for sweeps with at most `window` window points and `slots` resident workgroups.
 static void choose_brick(const relax_config* c, int window, unsigned slots, int brick[3]) {

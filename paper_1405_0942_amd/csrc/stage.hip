@@ -43,11 +43,13 @@
 //                                             Lambda = max |E + mu d_6 + dt e_6 k_6|
 // k_2, k_4, k_5 and k_6 are never stored: 768 HBM bytes per node and attempt, where storing k_2
 // and adding e_5 k_5 to E in stage 5 took 864 (256^3: 2.83 -> 2.52 ms per attempt).  Against
-// 80-bit arithmetic the error of Lambda is the same (1e-17 to 5e-15 of dt |k|, from the k_j
-// themselves).  FP32-mixed keeps k_2 and accumulates E in stage 5, since there mu d_6 would add its
-// FP32 rounding to E: Lambda off by 1.1e-8 instead of 5e-9 of dt |k| in the worst case measured.
-// So does the octilateral current, whose runs that break down amplify every rounding.  Their
-// stages 2..6:
+// 80-bit arithmetic the sums themselves round more, E + mu d_6 at 2.7e-17 of dt |k| rms instead of
+// 2.8e-18 and d_5 at 2.1e-16 instead of 1.6e-16 (nearly equal k_j), but the rounding of the k_j
+// outweighs both: the estimate as a whole is off by 3e-17 to 1.8e-16 of dt |k| rms on five grids of 16^3
+// to 33^3 nodes and every kind of face, the same within 1 % for either set.  FP32-mixed keeps k_2 and
+// accumulates E in stage 5, since there mu d_6 would add its FP32 rounding to E: Lambda off by 1.1e-8
+// instead of 5e-9 of dt |k| in the worst case measured.  So does the octilateral current, whose runs
+// that break down amplify every rounding.  Their stages 2..6:
 //   stage 2: as above                      -> k_2, y_3
 //   stage 3: window y_3; k_1, k_2          -> k_3, d_4
 //   stage 4: window x_n + d_4; k_1..k_3    -> y_5, P6, X, E = dt sum e_j k_j

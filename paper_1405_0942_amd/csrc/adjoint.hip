@@ -35,7 +35,7 @@
 // stored y_s of the step), B and Gbar'_y in LDS by parity of the plane.  Gbar'_x needs none: a wave is
 // a row of the tile, so its lanes hand it on, and only the columns beside the tile go through LDS.  The
 // in-plane sums of plane p are taken after its barrier and kept in registers, where the transpose of
-// plane p - 1 finds all it needs one step later.  Ghost nodes beyond line-tied faces give every node
+// plane p - 1 finds all it needs one step later.  The sums of the one-sided rows beyond line-tied faces (see stage.hip) give every node
 // the same path.  Loads and stores are those of buffer instructions with masked-off lanes (offsets
 // past the record count), issued one plane step ahead, so no divergent branch surrounds a memory
 // instruction and the waits are exact.
@@ -45,6 +45,7 @@
 // backward pass over 128^3 periodic 1579 -> 1518, 129^3 line-tied 2373 -> 2041 (one-sided rows had
 // diverged), 73 x 73 x 200 line-tied 1487 -> 1219.
 #include "brick.h"
+#include "tile.h"
 
 #include <algorithm>
 
@@ -174,7 +175,7 @@ __device__ __forceinline__ double neighbour(double v, double edge) {
   return __builtin_bit_cast(double, r);
 }
 
-template <int S, bool SEED>
+template <int S, bool SEED, bool FACES>
 __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) void adj_field_kernel(AdjArgs a) {
   constexpr bool WK = (!SEED && S == 2);  // the window carries k_1 too
   constexpr int NP2 = (RY2 * RX2 + NTHREADS - 1) / NTHREADS;
@@ -251,8 +252,9 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
     double x[NP2][3];
     double k[WK ? NP2 : 1][3];
   };
+  // (plane nz + 1 of a line-tied axis: nz - 3 once more, see stage.hip)
   auto load_window = [&](Window& w, int pz, bool on) {
-    const long long zo = (long long)zload(pz) * nxy;
+    const long long zo = (long long)(bcz != BC_PERIODIC && pz > nz ? nz - 3 : zload(pz)) * nxy;
     unsigned e[NP2];
 #pragma unroll
     for (int r = 0; r < NP2; r++) e[r] = on ? w2e[r] : IE;
@@ -274,10 +276,11 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
   const bool perz = (bcz == BC_PERIODIC);
   const int pb0 = perz ? z0 - 1 : max(z0 - 1, 0);
   const int pb1 = perz ? z1 : min(z1, nz - 1);
+  const int pw1 = !perz && pb1 == nz - 1 ? nz + 1 : pb1 + 1;  // last plane of the stage input
 
   // the first three planes, so that the rest of the tables is built while they are under way (64 x 64 x 192:
   // 654 -> 634 us per step of a backward pass)
-  const bool low = !perz && pb0 == 0;  // the plane below is a ghost plane
+  const bool low = !perz && pb0 == 0;  // the plane below holds the sums of the face
   const int lo = low ? 0 : pb0 - 1;
   Window w0, w1, w2;
   load_window(w0, lo, true);
@@ -286,7 +289,9 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
   __builtin_amdgcn_sched_barrier(0);
 
   unsigned f1e[NP1];
-  int f1o[NP1], f1y[NP1];  // offsets in the B window (-1: no point) and in the stage-input window
+  int f1o[NP1];            // offset in the B window (-1: no point)
+  int f1y[NP1];            // offset in the stage-input window
+  int f1dx[NP1], f1dy[NP1];  // offsets of the two points whose difference is F' along x, along y: plus | minus << 16
   bool f1live[NP1];        // on the grid and not on a line-tied face across x or y
   int halo_row = 0, halo_col = 0;
 #pragma unroll
@@ -316,12 +321,15 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
     const AxisIdx rx = axis_index(i0 + c1 - 1, nx, bcx), ry = axis_index(j0 + r1 - 1, ny, bcy);
     f1e[r] = (in_win && rx.ok && ry.ok) ? (unsigned)(ry.i * nx + rx.i) : IE;
     f1o[r] = in_win ? r1 * RX1 + c1 : -1;
+    int ends = 0;  // 1, 2: low, high end along x; 4, 8: along y
+    if (bcx == BC_LINE_TIED) ends |= rx.i == 0 ? 1 : (rx.i == nx - 1 ? 2 : 0);
+    if (bcy == BC_LINE_TIED) ends |= ry.i == 0 ? 4 : (ry.i == ny - 1 ? 8 : 0);
     f1y[r] = (r1 + 1) * RX2 + c1 + 1;
-    const bool face = (bcx == BC_LINE_TIED && (rx.i == 0 || rx.i == nx - 1)) ||
-                      (bcy == BC_LINE_TIED && (ry.i == 0 || ry.i == ny - 1));
-    f1live[r] = f1e[r] != IE && !face;
+    f1dx[r] = difference_points(f1y[r], 1, ends & 3);
+    f1dy[r] = difference_points(f1y[r], RX2, ends >> 2);
+    f1live[r] = f1e[r] != IE && ends == 0;
   }
-  // ghosts beyond line-tied faces across x and y (see stage.hip)
+  // the sums of the rows of line-tied faces across x and y, just beyond them (see stage.hip)
   constexpr int NGC = 3 * RY2, NGR = 3 * RX2;
   int gh_o[NPG], gh_s[NPG];
 #pragma unroll
@@ -371,23 +379,23 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
       }
     }
   };
-  // the ghost plane beyond a line-tied z face from the three planes inside it (pa the face)
-  auto commit_ghost_plane = [&](int pz, int pa, int pb, int pc) {
+  // the sums of a line-tied z face, in the plane beyond it, from the face's plane pa and the next, pb
+  auto commit_sum_plane = [&](int pz, int pa, int pb) {
 #pragma unroll
     for (int r = 0; r < NP2; r++) {
       if (w2o[r] >= 0) {
 #pragma unroll
-        for (int m = 0; m < 3; m++)
-          ys[pz & 3][m][w2o[r]] = fma(3.0, ys[pa & 3][m][w2o[r]] - ys[pb & 3][m][w2o[r]], ys[pc & 3][m][w2o[r]]);
+        for (int m = 0; m < 3; m++) ys[pz & 3][m][w2o[r]] = face_sum(ys[pa & 3][m][w2o[r]], ys[pb & 3][m][w2o[r]]);
       }
     }
   };
-  auto fill_ghosts = [&](int pz) {
+  auto fill_sums = [&](int pz) {
+    if constexpr (!FACES) return;
 #pragma unroll
     for (int r = 0; r < NPG; r++) {
       if (gh_o[r] >= 0) {
         double* y = &ys[pz & 3][0][gh_o[r]];
-        *y = fma(3.0, y[gh_s[r]] - y[2 * gh_s[r]], y[3 * gh_s[r]]);
+        *y = face_sum(y[gh_s[r]], y[2 * gh_s[r]]);
       }
     }
   };
@@ -425,12 +433,12 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
     commit_window(w0, lo);
     commit_window(w1, lo + 1);
     commit_window(w2, lo + 2);
-    if (low) commit_ghost_plane(-1, 0, 1, 2);  // plane 2 is committed again by the first plane step
+    if (low) commit_sum_plane(-1, 0, 1);  // plane 2 is committed again by the first plane step
   }
   __syncthreads();
-  fill_ghosts(pb0);
+  fill_sums(pb0);
   // leave the same loads and (dropped) stores in flight, in the same order, as a plane step
-  load_window(win, pb0 + 2, pb0 + 2 <= pb1 + 1);
+  load_window(win, pb0 + 2, pb0 + 2 <= pw1);
   load_field(pb0);
   load_point(pb0 - 1);
   {
@@ -451,24 +459,38 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
   for (int p = pb0; p <= z1; p++) {
     const int q = p - 1;
     const bool qout = (q >= z0 && q < z1);
-    fill_ghosts(p + 1);
+    fill_sums(p + 1);
     // 1. commit the plane the next field needs, load the one after it
     commit_window(win, p + 2);  // past the chunk's last plane: zeros that nothing reads
-    if (!perz && p + 2 == nz) commit_ghost_plane(nz, nz - 1, nz - 2, nz - 3);
-    load_window(win, p + 3, p + 3 <= pb1 + 1);
+    if (!perz && p + 2 == nz) commit_sum_plane(nz, nz - 1, nz - 2);
+    load_window(win, p + 3, p + 3 <= pw1);
 
     // 2. B and Gbar' of the field points of plane p, 0 off the grid
     const bool on_p = p <= pb1, live_p = on_p && (perz || (p > 0 && p < nz - 1));
     double F[3][3], rD, ub[3], B[3], Gx[3], Gy[3], Gz[3];
+    // the planes whose difference is F' along z (line-tied faces: the sum and plane 2 or nz - 3)
+    const bool low_face = !perz && p == 0, high_face = !perz && p == nz - 1;
+    const int sp = (low_face ? -1 : (high_face ? p - 2 : p + 1)) & 3;
+    const int sm = (low_face ? 2 : (high_face ? p + 1 : p - 1)) & 3;
     auto field = [&](auto point) {
       constexpr int R = decltype(point)::value;
       const int o = f1y[R];
-      const int sc = p & 3, sl = (p - 1) & 3, sh = (p + 1) & 3;
+      int dx = f1dx[R], dy = f1dy[R];
+      if constexpr (FACES) {  // taken apart here, not kept apart over the march: registers
+        pin(dx);
+        pin(dy);
+      }
+      const int sc = p & 3;
 #pragma unroll
       for (int m = 0; m < 3; m++) {
-        F[m][0] = ys[sc][m][o + 1] - ys[sc][m][o - 1];
-        F[m][1] = ys[sc][m][o + RX2] - ys[sc][m][o - RX2];
-        F[m][2] = ys[sh][m][o] - ys[sl][m][o];
+        if constexpr (FACES) {
+          F[m][0] = ys[sc][m][dx & 0xffff] - ys[sc][m][dx >> 16];
+          F[m][1] = ys[sc][m][dy & 0xffff] - ys[sc][m][dy >> 16];
+        } else {
+          F[m][0] = ys[sc][m][o + 1] - ys[sc][m][o - 1];
+          F[m][1] = ys[sc][m][o + RX2] - ys[sc][m][o - RX2];
+        }
+        F[m][2] = ys[sp][m][o] - ys[sm][m][o];
       }
       const double r = rcp_nr(det3(F));
       rD = (on_p && f1e[R] != IE) ? r : 0.0;
@@ -798,7 +820,10 @@ __global__ void seg_step_kernel(Control* c2, const double* __restrict__ dt_recor
 
 template <int S, bool SEED>
 hipError_t launch_field_t(const AdjArgs& a, hipStream_t st) {
-  hipLaunchKernelGGL((adj_field_kernel<S, SEED>), dim3(a.g.nblocks), dim3(NTHREADS), 0, st, a);
+  if (a.g.bc[0] == BC_LINE_TIED || a.g.bc[1] == BC_LINE_TIED)
+    hipLaunchKernelGGL((adj_field_kernel<S, SEED, true>), dim3(a.g.nblocks), dim3(NTHREADS), 0, st, a);
+  else
+    hipLaunchKernelGGL((adj_field_kernel<S, SEED, false>), dim3(a.g.nblocks), dim3(NTHREADS), 0, st, a);
   return hipGetLastError();
 }
 

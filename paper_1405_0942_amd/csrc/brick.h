@@ -1,5 +1,5 @@
 // brick.h -- the points of a brick (small-grid sweeps: brick.hip and the reverse sweeps of
-// adjoint.hip): strides of its windows, and which grid node, wrap or ghost a window point or a field
+// adjoint.hip): strides of its windows, and which grid node and wrap a window point or a field
 // point is.  Internal to the library.
 #pragma once
 
@@ -123,9 +123,9 @@ __device__ __forceinline__ BrickField brick_field(const Brick& b, const Geometry
   return p;
 }
 
-// F' at the field point with offset o in the window, by central differences.  Beyond a line-tied face the
-// neighbour is the ghost 3 (y(0) - y(1)) + y(2) (see stage.hip), formed here by the few points that need
-// it: a pass that wrote the ghosts to LDS took a barrier more (us per step, 33^3 49.9 -> 45.6, 65^3 107 -> 97).
+// F' at the field point with offset o in the window: central differences, on line-tied faces the one-sided
+// rows, formed here by the few points that need them: a pass that wrote them to LDS took a barrier more (us per
+// step, 33^3 49.9 -> 45.6, 65^3 107 -> 97).
 template <typename Y>
 __device__ __forceinline__ void face_differences(const Brick& b, int ends, bool at_face, const Y& ys, int o, double F[3][3]) {
 #pragma unroll
@@ -141,10 +141,16 @@ __device__ __forceinline__ void face_differences(const Brick& b, int ends, bool 
       const int end = (ends >> (2 * c)) & 3;  // 1: low end, 2: high end
       if (end == 1) {
 #pragma unroll
-        for (int m = 0; m < 3; m++) lo[m] = fma(3.0, ys[m][o] - hi[m], ys[m][o + 2 * s]);
+        for (int m = 0; m < 3; m++) {
+          hi[m] = face_sum(ys[m][o], hi[m]);
+          lo[m] = ys[m][o + 2 * s];
+        }
       } else if (end == 2) {
 #pragma unroll
-        for (int m = 0; m < 3; m++) hi[m] = fma(3.0, ys[m][o] - lo[m], ys[m][o - 2 * s]);
+        for (int m = 0; m < 3; m++) {
+          lo[m] = face_sum(ys[m][o], lo[m]);
+          hi[m] = ys[m][o - 2 * s];
+        }
       }
     }
 #pragma unroll

@@ -89,13 +89,16 @@ namespace {
 // time even when every lane is masked off: 128^3 60 -> 53 us).  REC in FP64 stages 4 and 6: also
 // store the stage input at the node, for the reverse sweeps.  FIT: tiles of g.tw x g.th nodes instead
 // of 64 x 8, for grids whose x and y extents 64 x 8 tiles would cover with many idle threads
-// (choose_tile in relax.cpp); a tile node is then any of the first tw th threads.
-template <int S, bool MIXED, bool NNN, bool DIAG = false, bool REC = false, bool FIT = false>
+// (choose_tile in relax.cpp); a tile node is then any of the first tw th threads.  FACES: x or y is line-tied,
+// and a field point has two points of its own for F' (us per step against the neighbours for all: 129^3 4537 ->
+// 4596, 200^3 of both kinds 1 to 2 %; on periodic grids that would be 2 % for nothing).
+template <int S, bool MIXED, bool NNN, bool DIAG, bool REC, bool FIT, bool FACES>
 __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) void stage_kernel(SweepArgs a) {
   using T = typename std::conditional<MIXED, float, double>::type;
   // The stage-input ring holds the planes p - 1 .. p + 1 that the field of plane p reads and the
   // plane p + 2 committed meanwhile; B is written on plane p while the current of plane p - 1
-  // reads its own, so one barrier per plane step is enough.  NNN: the octilateral loops (Sec. 2.3)
+  // reads its own, so one barrier per plane step is enough.  (On a line-tied z face the field reads plane 2
+  // or nz - 3 instead, which is that fourth plane: it is committed once more, with the same bits.)  NNN: the octilateral loops (Sec. 2.3)
   // of plane p - 1 read positions and B on the planes p - 2 .. p, B of plane p included: a barrier
   // before them, five planes of stage input and three of B.
   constexpr int RYS = NNN ? 5 : 4;
@@ -115,10 +118,10 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
   constexpr int PD = (S == 1 && !NNN) ? 2 : 1;
   constexpr int NP2 = (RY2 * RX2 + NTHREADS - 1) / NTHREADS;  // stage-input points per thread
   constexpr int NP1 = (RY1 * RX1 + NTHREADS - 1) / NTHREADS;  // field points per thread
-  constexpr int NPG = (6 * (RY2 + RX2) + NTHREADS - 1) / NTHREADS;  // ghosts per thread
+  constexpr int NPG = (6 * (RY2 + RX2) + NTHREADS - 1) / NTHREADS;  // sums beyond faces per thread
   static_assert(!DIAG || (S == 1 && !MIXED), "the diagnostics sweep is the FP64 stage-1 sweep");
   static_assert(!REC || DIAG || (!MIXED && (S == 4 || S == 6)), "REC: FP64 stages 4 and 6");
-  static_assert(!NNN || (!MIXED && (DIAG || !REC)), "the octilateral current is an FP64 forward operator");
+  static_assert(!NNN || (!MIXED && !FACES && (DIAG || !REC)), "the octilateral current is an FP64 forward operator");
   constexpr bool YREC = REC && !DIAG;
 
   // Scalars first, in one go: each that is fetched behind a branch on another costs its latency again
@@ -207,8 +210,9 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
     double x[NP2][3];      // window base (x_n, y_3 or y_5)
     T v[WV ? NP2 : 1][3];  // the window vector
   };
+  // (plane nz + 1 of a line-tied axis: nz - 3 once more, for the row of the face, whose place in the ring it takes)
   auto load_window = [&](Window& w, int pz, bool on) {
-    const long long zo = (long long)zload(pz) * nxy;
+    const long long zo = (long long)(bcz != BC_PERIODIC && pz > nz ? nz - 3 : zload(pz)) * nxy;
     unsigned e[NP2];
 #pragma unroll
     for (int r = 0; r < NP2; r++) e[r] = on ? w2e[r] : IE;
@@ -231,13 +235,14 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
   const bool perz = (bcz == BC_PERIODIC);
   const int pb0 = perz ? z0 - 1 : max(z0 - 1, 0);
   const int pb1 = perz ? z1 : min(z1, nz - 1);
+  const int pw1 = !perz && pb1 == nz - 1 ? nz + 1 : pb1 + 1;  // last plane of the stage input
 
   // The first three planes go out here, so that the rest of the tables is built while they are under
   // way; with the scalars above and tables without divisions, us per step: 64 x 64 x 192 176 -> 168,
   // 96^3 206 -> 197, 129^3 450 -> 438, 256^3 2404 -> 2393.
   if (!diag_only && (status != 0 || accepted >= target)) return;
   if (!diag_only && STAGE1 && need_k1 == 0) return;
-  const bool low = !perz && pb0 == 0;  // the plane below is a ghost plane
+  const bool low = !perz && pb0 == 0;  // the plane below holds the sums of the face
   const int lo = low ? 0 : pb0 - 1;
   Window w0, w1, w2;
   load_window(w0, lo, true);
@@ -249,7 +254,8 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
   unsigned f1e[NP1];  // flat (x, y) index, IE off the grid
   int f1o[NP1];       // offset in the B window, -1 past it
   int f1y[NP1];       // offset in the stage-input window
-  int f1k[NP1];       // NNN: line-tied ends it lies on: 1, 2 along x, 4, 8 along y
+  int f1k[NP1];       // line-tied ends it lies on: 1, 2 along x, 4, 8 along y
+  int f1dx[NP1], f1dy[NP1];  // offsets of the two points whose difference is F' along x, along y: plus | minus << 16
 #pragma unroll
   for (int r = 0; r < NP1; r++) {
     const int e = tid + r * NTHREADS;
@@ -263,6 +269,8 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
     f1k[r] = 0;
     if (bcx == BC_LINE_TIED) f1k[r] |= rx.i == 0 ? 1 : (rx.i == nx - 1 ? 2 : 0);
     if (bcy == BC_LINE_TIED) f1k[r] |= ry.i == 0 ? 4 : (ry.i == ny - 1 ? 8 : 0);
+    f1dx[r] = difference_points(f1y[r], 1, f1k[r] & 3);
+    f1dy[r] = difference_points(f1y[r], wx2, f1k[r] >> 2);
   }
   // NNN: points off the grid take no field (B stays 0 there, and no node off a face reads it), nor does a
   // wave without a node: narrow line-tied grids are mostly such points (us per step, 4 x 4 x 65536 11173 ->
@@ -280,11 +288,11 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
     }
     if (!__any(f1e[0] != IE)) pb1_own = -2;
   }
-  // Ghost nodes just beyond a line-tied face: y(-1) = 3 (y(0) - y(1)) + y(2), and likewise at the
-  // other end, so that the central difference at the face node is the one-sided second-order row
-  // -3 y(0) + 4 y(1) - y(2) and every node takes the same path.  Beyond faces across x and y a
-  // thread fills one ghost component of a plane; beyond faces across z see commit_window.
-  const int NGC = 3 * wy2, NGR = 3 * wx2;  // ghosts of one column, of one row
+  // Just beyond a line-tied face stands the sum 4 y(1) - 3 y(0) of the face node's one-sided row, which is its
+  // difference from y(2): a face node differs from the others by the two points it takes, not by its path.
+  // Beyond faces across x and y a thread fills one component of one row of a plane; beyond faces across z
+  // see commit_sum_plane.
+  const int NGC = 3 * wy2, NGR = 3 * wx2;  // sums of one column, of one row
   int gh_o[NPG], gh_s[NPG];  // offset in the plane's three components (-1: none), step into the grid
 #pragma unroll
   for (int r = 0; r < NPG; r++) {
@@ -353,17 +361,16 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
       }
     }
   };
-  // the ghost plane beyond a line-tied z face from the three planes pa, pb, pc inside it (pa the
-  // face): each thread reads back the points it committed itself.  NNN: the rows read no ghost, only
-  // the diagnostics' edge vectors, whose trihedra there are not formed
-  auto commit_ghost_plane = [&](int pz, int pa, int pb, int pc) {
-    const int slot = yslot(pz), sa = yslot(pa), sb = yslot(pb), sc = yslot(pc);
+  // the sums of a line-tied z face, in the plane beyond it, from the face's plane pa and the next, pb: each
+  // thread reads back the points it committed itself.  NNN: only the diagnostics' edge vectors read them,
+  // whose trihedra there are not formed
+  auto commit_sum_plane = [&](int pz, int pa, int pb) {
+    const int slot = yslot(pz), sa = yslot(pa), sb = yslot(pb);
 #pragma unroll
     for (int r = 0; r < NP2; r++) {
       if (w2o[r] >= 0) {
 #pragma unroll
-        for (int m = 0; m < 3; m++)
-          ys[slot][m][w2o[r]] = fma(3.0, ys[sa][m][w2o[r]] - ys[sb][m][w2o[r]], ys[sc][m][w2o[r]]);
+        for (int m = 0; m < 3; m++) ys[slot][m][w2o[r]] = face_sum(ys[sa][m][w2o[r]], ys[sb][m][w2o[r]]);
       }
     }
   };
@@ -403,13 +410,13 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
       for (int m = 0; m < 3; m++) F[m][2] = 3.0 * ys[s0][m][o] - 4.0 * ys[s1][m][o] + ys[s2][m][o];
     }
   };
-  auto fill_ghosts = [&](int pz) {
-    if constexpr (NNN) return;
+  auto fill_sums = [&](int pz) {
+    if constexpr (!FACES) return;
 #pragma unroll
     for (int r = 0; r < NPG; r++) {
       if (gh_o[r] >= 0) {
         double* y = &ys[yslot(pz)][0][gh_o[r]];
-        *y = fma(3.0, y[gh_s[r]] - y[2 * gh_s[r]], y[3 * gh_s[r]]);
+        *y = face_sum(y[gh_s[r]], y[2 * gh_s[r]]);
       }
     }
   };
@@ -544,7 +551,7 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
   Nodes nodes[PD];
   auto commit_next = [&](const Window& win, int p) {
     commit_window(win, p + 2);  // past the chunk's last plane: zeros that nothing reads
-    if ((!NNN || DIAG) && !perz && p + 2 == nz) commit_ghost_plane(nz, nz - 1, nz - 2, nz - 3);
+    if ((!NNN || DIAG) && !perz && p + 2 == nz) commit_sum_plane(nz, nz - 1, nz - 2);
     carry(win);
   };
 
@@ -553,8 +560,8 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
     commit_window(w0, lo);
     commit_window(w1, lo + 1);
     commit_window(w2, lo + 2);
-    if (low) {  // plane 2 stays in the ring and is committed again by the first plane step
-      if constexpr (!NNN || DIAG) commit_ghost_plane(-1, 0, 1, 2);
+    if (low) {  // plane 2 stays in the ring; the first plane step commits it again, with the same bits
+      if constexpr (!NNN || DIAG) commit_sum_plane(-1, 0, 1);
       carry(w0);
       carry(w0);
       carry(w1);
@@ -565,15 +572,15 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
     }
   }
   __syncthreads();
-  fill_ghosts(pb0);
+  fill_sums(pb0);
   // leave the same loads and (dropped) stores in flight, in the same order, as a plane step
 #pragma unroll
   for (int d = 0; d < PD; d++) {
-    if constexpr (!NNN) load_window(win[d], pb0 + d + 2, pb0 + d + 2 <= pb1 + 1);
+    if constexpr (!NNN) load_window(win[d], pb0 + d + 2, pb0 + d + 2 <= pw1);
     load_b0(nodes[d], min(pb0 + d, pb1));
     load_point(nodes[d], pb0 + d - 1);
     store_plane(Outputs{}, pb0 + d - 1, false);
-    if constexpr (NNN) load_window(win[d], pb0 + d + 2, pb0 + d + 2 <= pb1 + 1);
+    if constexpr (NNN) load_window(win[d], pb0 + d + 2, pb0 + d + 2 <= pw1);
     __builtin_amdgcn_sched_barrier(0);
   }
   __syncthreads();
@@ -588,7 +595,7 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
   auto step = [&](int p, Nodes& nd, Window& win) {
     const int q = p - 1;
     const bool qout = (q >= z0 && q < z1);
-    fill_ghosts(p + 1);
+    fill_sums(p + 1);
     // own-node values of plane q
     double xq[3] = {0.0, 0.0, 0.0};
     T vq[3] = {T(0), T(0), T(0)};
@@ -602,13 +609,17 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
     // step (256^3, stage 3: 375 -> 354 us, stage 5: 312 -> 285)
     if constexpr (!NNN) {
       commit_next(win, p);
-      load_window(win, p + PD + 2, p + PD + 2 <= pb1 + 1);
+      load_window(win, p + PD + 2, p + PD + 2 <= pw1);
     }
     // 1. F', det F' and B of field point R of plane p; off the grid B = 0
     T Bp[3], Fp[3][3], rDp;
     double Dp;
     int kap_p = 1;
     const bool central = inner_xy && (perz || (p > 0 && p < nz - 1));
+    // the planes whose difference is F' along z (line-tied faces: the sum and plane 2 or nz - 3)
+    const bool low_face = !perz && p == 0, high_face = !perz && p == nz - 1;
+    const int sp = yslot(low_face ? -1 : (high_face ? p - 2 : p + 1));
+    const int sm = yslot(low_face ? 2 : (high_face ? p + 1 : p - 1));
     auto field = [&](auto point) {
       constexpr int R = decltype(point)::value;
       const int sb = bslot(p);
@@ -622,9 +633,14 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
       } else {
 #pragma unroll
         for (int m = 0; m < 3; m++) {
-          F[m][0] = ys[sc][m][o + 1] - ys[sc][m][o - 1];
-          F[m][1] = ys[sc][m][o + wx2] - ys[sc][m][o - wx2];
-          F[m][2] = ys[sh][m][o] - ys[sl][m][o];
+          if constexpr (FACES) {
+            F[m][0] = ys[sc][m][f1dx[R] & 0xffff] - ys[sc][m][f1dx[R] >> 16];
+            F[m][1] = ys[sc][m][f1dy[R] & 0xffff] - ys[sc][m][f1dy[R] >> 16];
+          } else {
+            F[m][0] = ys[sc][m][o + 1] - ys[sc][m][o - 1];
+            F[m][1] = ys[sc][m][o + wx2] - ys[sc][m][o - wx2];
+          }
+          F[m][2] = ys[NNN ? sh : sp][m][o] - ys[NNN ? sl : sm][m][o];
         }
       }
       const double D = (NNN || MIXED) ? det3(F) : det3_fused(F);
@@ -777,7 +793,7 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
     load_point(nd, p + PD - 1);  // output node of the plane step that uses this set next
     store_plane(so, q, qout, kap_q);
 
-    if constexpr (NNN) load_window(win, p + PD + 2, p + PD + 2 <= pb1 + 1);
+    if constexpr (NNN) load_window(win, p + PD + 2, p + PD + 2 <= pw1);
     __syncthreads();
 
 #pragma unroll
@@ -802,14 +818,20 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
   if (LAST) store_lambda<NTHREADS>(acc, red, a.lam_part + blockIdx.x);
 }
 
-template <int S, bool MIXED, bool NNN, bool DIAG = false, bool REC = false>
-hipError_t launch_march(const SweepArgs& a, hipStream_t st) {
+template <int S, bool MIXED, bool NNN, bool DIAG, bool REC, bool FACES>
+hipError_t launch_tiles(const SweepArgs& a, hipStream_t st) {
   const dim3 grid(a.g.nblocks), block(NTHREADS);
   if (a.g.tw == TX && a.g.th == TY)
-    hipLaunchKernelGGL((stage_kernel<S, MIXED, NNN, DIAG, REC>), grid, block, 0, st, a);
+    hipLaunchKernelGGL((stage_kernel<S, MIXED, NNN, DIAG, REC, false, FACES>), grid, block, 0, st, a);
   else
-    hipLaunchKernelGGL((stage_kernel<S, MIXED, NNN, DIAG, REC, true>), grid, block, 0, st, a);
+    hipLaunchKernelGGL((stage_kernel<S, MIXED, NNN, DIAG, REC, true, FACES>), grid, block, 0, st, a);
   return hipGetLastError();
+}
+template <int S, bool MIXED, bool NNN, bool DIAG = false, bool REC = false>
+hipError_t launch_march(const SweepArgs& a, hipStream_t st) {
+  if constexpr (!NNN)
+    if (a.g.bc[0] == BC_LINE_TIED || a.g.bc[1] == BC_LINE_TIED) return launch_tiles<S, MIXED, NNN, DIAG, REC, true>(a, st);
+  return launch_tiles<S, MIXED, NNN, DIAG, REC, false>(a, st);
 }
 
 template <bool MIXED, bool NNN = false>

@@ -91,6 +91,13 @@ __device__ __forceinline__ int logical_block(int bid, int nb) {
   return xcd * q + (xcd < r ? xcd : r) + j;
 }
 
+// The one-sided second-order row at a line-tied face, y0 the face node and y1, y2 the nodes inside it:
+// (4 y1 - 3 y0) - y2 at the low end, y2 - (4 y1 - 3 y0) at the high end.  This is the sum in parentheses.  The
+// row has one rounding, that of the sum, which lies inside the grid.  (A central difference with the ghost
+// 3 (y0 - y1) + y2 would have that of the ghost, which lies outside: where a face is at a power of two, of
+// half the accuracy.  51^3 on a box of +-4, +-4, +-10: u off by 4.4e-14 rms instead of 2.9e-14.)
+__device__ __forceinline__ double face_sum(double y0, double y1) { return fma(-3.0, y0, 4.0 * y1); }
+
 template <typename T>
 __device__ __forceinline__ T det3(const T F[3][3]) {
   return F[0][0] * (F[1][1] * F[2][2] - F[1][2] * F[2][1]) - F[0][1] * (F[1][0] * F[2][2] - F[1][2] * F[2][0]) +

@@ -69,4 +69,13 @@ __host__ __device__ __forceinline__ int field_offset(TilePoint p, bool in_window
   return in_window ? (p.row + 1) * wx2 + p.col + 1 : 2 * wx2 + 2;
 }
 
+// The two points (plus | minus << 16) whose difference is F' along an axis at offset o of the stage-input window,
+// s a step along it: its neighbours; on a line-tied face (end 1: low, 2: high) the sum 4 y(1) - 3 y(0), which
+// stands beyond it, and y(2)
+__host__ __device__ __forceinline__ int difference_points(int o, int s, int end) {
+  const int plus = end == 1 ? o - s : (end == 2 ? o - 2 * s : o + s);
+  const int minus = end == 1 ? o + 2 * s : (end == 2 ? o + s : o - s);
+  return plus | minus << 16;
+}
+
 }  // namespace relax

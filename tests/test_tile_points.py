@@ -32,6 +32,16 @@ static int check(int tw, int th) {
       for (int s : {1, wx2})
         if (o - s < 0 || o + s >= wx2 * wy2) return 4;
       if (in && o != (p.row + 1) * wx2 + p.col + 1) return 5;
+      // the points of F': a low face beyond column 0 is one of the columns 1 to tw, a high face likewise
+      for (int end = 0; end < 3; end++)
+        for (int axis = 0; axis < 2; axis++) {
+          const int at = axis ? p.row : p.col, last = axis ? th : tw, s = axis ? wx2 : 1;
+          if (in && end && (at < 1 || at > last)) continue;
+          const int d = difference_points(o, s, end), plus = d & 0xffff, minus = d >> 16;
+          if (plus >= wx2 * wy2 || minus < 0 || minus >= wx2 * wy2) return 7;
+          if (plus != (end == 1 ? o - s : end == 2 ? o - 2 * s : o + s)) return 8;
+          if (minus != (end == 1 ? o + 2 * s : end == 2 ? o + s : o - s)) return 8;
+        }
     }
   }
   return (int)win.size() == wx2 * wy2 && (int)fld.size() == wx1 * wy1 ? 0 : 6;

@@ -175,7 +175,7 @@ __device__ __forceinline__ double neighbour(double v, double edge) {
   return __builtin_bit_cast(double, r);
 }
 
-template <int S, bool SEED, bool FACES>
+template <int S, bool SEED, int FACES>
 __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) void adj_field_kernel(AdjArgs a) {
   constexpr bool WK = (!SEED && S == 2);  // the window carries k_1 too
   constexpr int NP2 = (RY2 * RX2 + NTHREADS - 1) / NTHREADS;
@@ -215,7 +215,7 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
   __shared__ double gx[2][3][2][TY];      // Gbar'_x on the columns beside the tile
 
   auto zload = [&](int pz) {
-    if (bcz == BC_PERIODIC) return resolve_near(pz, nz, bcz).i;
+    if (FACES == FACES_NONE || bcz == BC_PERIODIC) return resolve_near(pz, nz, BC_PERIODIC).i;
     return min(max(pz, 0), nz - 1);
   };
 
@@ -252,9 +252,8 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
     double x[NP2][3];
     double k[WK ? NP2 : 1][3];
   };
-  // (plane nz + 1 of a line-tied axis: nz - 3 once more, see stage.hip)
   auto load_window = [&](Window& w, int pz, bool on) {
-    const long long zo = (long long)(bcz != BC_PERIODIC && pz > nz ? nz - 3 : zload(pz)) * nxy;
+    const long long zo = (long long)zload(pz) * nxy;
     unsigned e[NP2];
 #pragma unroll
     for (int r = 0; r < NP2; r++) e[r] = on ? w2e[r] : IE;
@@ -273,10 +272,10 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
       }
     }
   };
-  const bool perz = (bcz == BC_PERIODIC);
+  const bool perz = FACES == FACES_NONE || bcz == BC_PERIODIC;
   const int pb0 = perz ? z0 - 1 : max(z0 - 1, 0);
   const int pb1 = perz ? z1 : min(z1, nz - 1);
-  const int pw1 = !perz && pb1 == nz - 1 ? nz + 1 : pb1 + 1;  // last plane of the stage input
+  const int pw1 = perz ? pb1 + 1 : min(pb1 + 1, nz - 1);  // last plane of the stage input
 
   // the first three planes, so that the rest of the tables is built while they are under way (64 x 64 x 192:
   // 654 -> 634 us per step of a backward pass)
@@ -390,7 +389,7 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
     }
   };
   auto fill_sums = [&](int pz) {
-    if constexpr (!FACES) return;
+    if constexpr (FACES != FACES_XY) return;
 #pragma unroll
     for (int r = 0; r < NPG; r++) {
       if (gh_o[r] >= 0) {
@@ -461,8 +460,10 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
     const bool qout = (q >= z0 && q < z1);
     fill_sums(p + 1);
     // 1. commit the plane the next field needs, load the one after it
-    commit_window(win, p + 2);  // past the chunk's last plane: zeros that nothing reads
-    if (!perz && p + 2 == nz) commit_sum_plane(nz, nz - 1, nz - 2);
+    if (perz || p + 2 < nz)  // past the chunk's last plane: zeros that nothing reads; beyond a face see stage.hip
+      commit_window(win, p + 2);
+    else if (p + 2 == nz)
+      commit_sum_plane(nz, nz - 1, nz - 2);
     load_window(win, p + 3, p + 3 <= pw1);
 
     // 2. B and Gbar' of the field points of plane p, 0 off the grid
@@ -476,14 +477,14 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
       constexpr int R = decltype(point)::value;
       const int o = f1y[R];
       int dx = f1dx[R], dy = f1dy[R];
-      if constexpr (FACES) {  // taken apart here, not kept apart over the march: registers
+      if constexpr (FACES == FACES_XY) {  // taken apart here, not kept apart over the march: registers
         pin(dx);
         pin(dy);
       }
       const int sc = p & 3;
 #pragma unroll
       for (int m = 0; m < 3; m++) {
-        if constexpr (FACES) {
+        if constexpr (FACES == FACES_XY) {
           F[m][0] = ys[sc][m][dx & 0xffff] - ys[sc][m][dx >> 16];
           F[m][1] = ys[sc][m][dy & 0xffff] - ys[sc][m][dy >> 16];
         } else {
@@ -820,10 +821,12 @@ __global__ void seg_step_kernel(Control* c2, const double* __restrict__ dt_recor
 
 template <int S, bool SEED>
 hipError_t launch_field_t(const AdjArgs& a, hipStream_t st) {
-  if (a.g.bc[0] == BC_LINE_TIED || a.g.bc[1] == BC_LINE_TIED)
-    hipLaunchKernelGGL((adj_field_kernel<S, SEED, true>), dim3(a.g.nblocks), dim3(NTHREADS), 0, st, a);
-  else
-    hipLaunchKernelGGL((adj_field_kernel<S, SEED, false>), dim3(a.g.nblocks), dim3(NTHREADS), 0, st, a);
+  const dim3 grid(a.g.nblocks), block(NTHREADS);
+  switch (faces_of(a.g)) {
+    case FACES_NONE: hipLaunchKernelGGL((adj_field_kernel<S, SEED, FACES_NONE>), grid, block, 0, st, a); break;
+    case FACES_Z: hipLaunchKernelGGL((adj_field_kernel<S, SEED, FACES_Z>), grid, block, 0, st, a); break;
+    default: hipLaunchKernelGGL((adj_field_kernel<S, SEED, FACES_XY>), grid, block, 0, st, a); break;
+  }
   return hipGetLastError();
 }
 

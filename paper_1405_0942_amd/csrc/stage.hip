@@ -89,16 +89,17 @@ namespace {
 // time even when every lane is masked off: 128^3 60 -> 53 us).  REC in FP64 stages 4 and 6: also
 // store the stage input at the node, for the reverse sweeps.  FIT: tiles of g.tw x g.th nodes instead
 // of 64 x 8, for grids whose x and y extents 64 x 8 tiles would cover with many idle threads
-// (choose_tile in relax.cpp); a tile node is then any of the first tw th threads.  FACES: x or y is line-tied,
-// and a field point has two points of its own for F' (us per step against the neighbours for all: 129^3 4537 ->
-// 4596, 200^3 of both kinds 1 to 2 %; on periodic grids that would be 2 % for nothing).
-template <int S, bool MIXED, bool NNN, bool DIAG, bool REC, bool FIT, bool FACES>
+// (choose_tile in relax.cpp); a tile node is then any of the first tw th threads.  FACES: which axes may be line-tied
+// (tile.h): with x or y a field point has two points of its own for F', with z two planes (129^3, us per step,
+// against the neighbours for all 4537 -> 4596; a periodic grid would pay 2 % for nothing).
+template <int S, bool MIXED, bool NNN, bool DIAG, bool REC, bool FIT, int FACES>
 __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) void stage_kernel(SweepArgs a) {
   using T = typename std::conditional<MIXED, float, double>::type;
   // The stage-input ring holds the planes p - 1 .. p + 1 that the field of plane p reads and the
   // plane p + 2 committed meanwhile; B is written on plane p while the current of plane p - 1
   // reads its own, so one barrier per plane step is enough.  (On a line-tied z face the field reads plane 2
-  // or nz - 3 instead, which is that fourth plane: it is committed once more, with the same bits.)  NNN: the octilateral loops (Sec. 2.3)
+  // or nz - 3 instead, which is that fourth plane: plane 2 is committed once more, with the same bits, and
+  // nothing is committed over nz - 3.)  NNN: the octilateral loops (Sec. 2.3)
   // of plane p - 1 read positions and B on the planes p - 2 .. p, B of plane p included: a barrier
   // before them, five planes of stage input and three of B.
   constexpr int RYS = NNN ? 5 : 4;
@@ -121,7 +122,7 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
   constexpr int NPG = (6 * (RY2 + RX2) + NTHREADS - 1) / NTHREADS;  // sums beyond faces per thread
   static_assert(!DIAG || (S == 1 && !MIXED), "the diagnostics sweep is the FP64 stage-1 sweep");
   static_assert(!REC || DIAG || (!MIXED && (S == 4 || S == 6)), "REC: FP64 stages 4 and 6");
-  static_assert(!NNN || (!MIXED && !FACES && (DIAG || !REC)), "the octilateral current is an FP64 forward operator");
+  static_assert(!NNN || (!MIXED && FACES == FACES_Z && (DIAG || !REC)), "the octilateral current is an FP64 forward operator");
   constexpr bool YREC = REC && !DIAG;
 
   // Scalars first, in one go: each that is fetched behind a branch on another costs its latency again
@@ -179,7 +180,7 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
 
   // plane index of a load (line-tied z: clamped; such planes are loaded but never used)
   auto zload = [&](int pz) {
-    if (bcz == BC_PERIODIC) return resolve_near(pz, nz, bcz).i;
+    if (FACES == FACES_NONE || bcz == BC_PERIODIC) return resolve_near(pz, nz, BC_PERIODIC).i;
     return min(max(pz, 0), nz - 1);
   };
 
@@ -210,9 +211,8 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
     double x[NP2][3];      // window base (x_n, y_3 or y_5)
     T v[WV ? NP2 : 1][3];  // the window vector
   };
-  // (plane nz + 1 of a line-tied axis: nz - 3 once more, for the row of the face, whose place in the ring it takes)
   auto load_window = [&](Window& w, int pz, bool on) {
-    const long long zo = (long long)(bcz != BC_PERIODIC && pz > nz ? nz - 3 : zload(pz)) * nxy;
+    const long long zo = (long long)zload(pz) * nxy;
     unsigned e[NP2];
 #pragma unroll
     for (int r = 0; r < NP2; r++) e[r] = on ? w2e[r] : IE;
@@ -232,10 +232,10 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
     }
   };
   // planes of B this chunk needs
-  const bool perz = (bcz == BC_PERIODIC);
+  const bool perz = FACES == FACES_NONE || bcz == BC_PERIODIC;
   const int pb0 = perz ? z0 - 1 : max(z0 - 1, 0);
   const int pb1 = perz ? z1 : min(z1, nz - 1);
-  const int pw1 = !perz && pb1 == nz - 1 ? nz + 1 : pb1 + 1;  // last plane of the stage input
+  const int pw1 = perz ? pb1 + 1 : min(pb1 + 1, nz - 1);  // last plane of the stage input
 
   // The first three planes go out here, so that the rest of the tables is built while they are under
   // way; with the scalars above and tables without divisions, us per step: 64 x 64 x 192 176 -> 168,
@@ -411,7 +411,7 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
     }
   };
   auto fill_sums = [&](int pz) {
-    if constexpr (!FACES) return;
+    if constexpr (FACES != FACES_XY) return;
 #pragma unroll
     for (int r = 0; r < NPG; r++) {
       if (gh_o[r] >= 0) {
@@ -550,8 +550,12 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
   Window win[PD];
   Nodes nodes[PD];
   auto commit_next = [&](const Window& win, int p) {
-    commit_window(win, p + 2);  // past the chunk's last plane: zeros that nothing reads
-    if ((!NNN || DIAG) && !perz && p + 2 == nz) commit_sum_plane(nz, nz - 1, nz - 2);
+    // past the chunk's last plane: zeros that nothing reads; beyond a face the sums, and then nothing, since
+    // plane nz - 3 is still wanted for the row
+    if (perz || p + 2 < nz)
+      commit_window(win, p + 2);
+    else if ((!NNN || DIAG) && p + 2 == nz)
+      commit_sum_plane(nz, nz - 1, nz - 2);
     carry(win);
   };
 
@@ -633,7 +637,7 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
       } else {
 #pragma unroll
         for (int m = 0; m < 3; m++) {
-          if constexpr (FACES) {
+          if constexpr (FACES == FACES_XY) {
             F[m][0] = ys[sc][m][f1dx[R] & 0xffff] - ys[sc][m][f1dx[R] >> 16];
             F[m][1] = ys[sc][m][f1dy[R] & 0xffff] - ys[sc][m][f1dy[R] >> 16];
           } else {
@@ -784,7 +788,14 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
         }
       } else {
         double err[3];
-        advance<S, MIXED, NNN, REC>(u, xq, vq, nd.pk, nd.ps, dt, so, err);
+        if constexpr (FACES == FACES_NONE && !MIXED && (S == 3 || S == 5)) {  // 256^3: 362 -> 352, 299 -> 283 us
+          double from[1][3];
+#pragma unroll
+          for (int m = 0; m < 3; m++) from[0][m] = taken(S == 3 ? nd.pk[0][m] : nd.ps[0][m]);
+          advance<S, MIXED, NNN, REC>(u, xq, vq, from, from, dt, so, err);
+        } else {
+          advance<S, MIXED, NNN, REC>(u, xq, vq, nd.pk, nd.ps, dt, so, err);
+        }
         if constexpr (LAST)
 #pragma unroll
           for (int m = 0; m < 3; m++) acc.error(tile_ok ? err[m] : 0.0);
@@ -818,7 +829,7 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) v
   if (LAST) store_lambda<NTHREADS>(acc, red, a.lam_part + blockIdx.x);
 }
 
-template <int S, bool MIXED, bool NNN, bool DIAG, bool REC, bool FACES>
+template <int S, bool MIXED, bool NNN, bool DIAG, bool REC, int FACES>
 hipError_t launch_tiles(const SweepArgs& a, hipStream_t st) {
   const dim3 grid(a.g.nblocks), block(NTHREADS);
   if (a.g.tw == TX && a.g.th == TY)
@@ -829,9 +840,11 @@ hipError_t launch_tiles(const SweepArgs& a, hipStream_t st) {
 }
 template <int S, bool MIXED, bool NNN, bool DIAG = false, bool REC = false>
 hipError_t launch_march(const SweepArgs& a, hipStream_t st) {
-  if constexpr (!NNN)
-    if (a.g.bc[0] == BC_LINE_TIED || a.g.bc[1] == BC_LINE_TIED) return launch_tiles<S, MIXED, NNN, DIAG, REC, true>(a, st);
-  return launch_tiles<S, MIXED, NNN, DIAG, REC, false>(a, st);
+  if constexpr (!NNN) {
+    if (faces_of(a.g) == FACES_NONE) return launch_tiles<S, MIXED, NNN, DIAG, REC, FACES_NONE>(a, st);
+    if (faces_of(a.g) == FACES_XY) return launch_tiles<S, MIXED, NNN, DIAG, REC, FACES_XY>(a, st);
+  }
+  return launch_tiles<S, MIXED, NNN, DIAG, REC, FACES_Z>(a, st);
 }
 
 template <bool MIXED, bool NNN = false>

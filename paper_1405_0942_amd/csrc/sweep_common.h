@@ -83,6 +83,14 @@ __device__ __forceinline__ void pin(V& v) {
   asm volatile("" : "+v"(v));
 }
 
+// v in other registers, which the result does not share even where v ends here: for a loaded value that a sum
+// starts from.  The sum would be formed in its place, and the next load of it go elsewhere, as above.
+__device__ __forceinline__ double taken(double v) {
+  double r;
+  asm volatile("v_mov_b64_e32 %0, %1" : "=&v"(r) : "v"(v));
+  return r;
+}
+
 // logical tile of this workgroup; consecutive logical tiles share an XCD (the hardware
 // hands workgroup b to XCD b mod 8), so neighbouring tiles reuse each other's halos in L2
 __device__ __forceinline__ int logical_block(int bid, int nb) {

@@ -7,6 +7,13 @@
 
 namespace relax {
 
+// Which axes of a grid may be line-tied in a marching kernel: none, z alone, any
+enum { FACES_NONE = 0, FACES_Z = 1, FACES_XY = 2 };
+inline int faces_of(const Geometry& g) {
+  if (g.bc[0] == BC_LINE_TIED || g.bc[1] == BC_LINE_TIED) return FACES_XY;
+  return g.bc[2] == BC_LINE_TIED ? FACES_Z : FACES_NONE;
+}
+
 struct TilePoint {
   int row, col;  // in its window
 };

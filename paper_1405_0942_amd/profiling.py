@@ -58,7 +58,7 @@ def read_counter(run_dir: str, counter: str):
 def _stage_of(name: str):
     # stage_kernel<S, MIXED, NNN, DIAG, REC, FIT, FACES>, brick_kernel<S, MIXED, NNN, DIAG, REC>, trailing ones
     # left out or not; the diagnostics variant (DIAG true) is not a stage
-    m = re.search(r"(?:stage|brick)_kernel<(\d), (false|true), (false|true)(?:, false(?:, (?:false|true)){0,3})?>", name)
+    m = re.search(r"(?:stage|brick)_kernel<(\d), (false|true), (false|true)(?:, false(?:, (?:false|true)){0,2}(?:, \d)?)?>", name)
     if not m:
         return None
     return int(m.group(1)), m.group(2) == "true"

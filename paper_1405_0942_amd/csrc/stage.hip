@@ -90,8 +90,9 @@ namespace {
 // store the stage input at the node, for the reverse sweeps.  FIT: tiles of g.tw x g.th nodes instead
 // of 64 x 8, for grids whose x and y extents 64 x 8 tiles would cover with many idle threads
 // (choose_tile in relax.cpp); a tile node is then any of the first tw th threads.  FACES: which axes may be line-tied
-// (tile.h): with x or y a field point has two points of its own for F', with z two planes (129^3, us per step,
-// against the neighbours for all 4537 -> 4596; a periodic grid would pay 2 % for nothing).
+// (tile.h): with x or y a field point has two points of its own for F', with z two planes.  Against the
+// neighbours for all, us per step 129^3 454 -> 460, 64 x 64 x 192 (z alone) 204 -> 204; a diagnostics call of 129^3,
+// which forms eight determinants a node and is bound by its vector instructions, 97 -> 102.
 template <int S, bool MIXED, bool NNN, bool DIAG, bool REC, bool FIT, int FACES>
 __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(2))) void stage_kernel(SweepArgs a) {
   using T = typename std::conditional<MIXED, float, double>::type;
